@@ -57,6 +57,7 @@ hipError_t ensure_device_init(DeviceInfo* info)
         (void)tuning();
         if ((e = init_ffn_kernels()) != hipSuccess) return e;
         if ((e = init_route_kernels()) != hipSuccess) return e;
+        if ((e = init_distill_kernels()) != hipSuccess) return e;
         int n_cu = 0;
         if ((e = hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev)) != hipSuccess) return e;
         void* sp = nullptr;
@@ -559,35 +560,50 @@ moe_status moe_build_united(const moe_config* cfg, const moe_ffn_weights* expert
 
     const FfnWeights fe = to_ffn(experts), fu = to_ffn(&united_ro), fs{nullptr, nullptr, nullptr};
     const TilePlan plan = make_tile_plan(n_calib);
-    int32_t* unit_cnt = at<int32_t>(workspace, W.unit_cnt);
-    int32_t* unit_off = at<int32_t>(workspace, W.unit_off);
-    float* ones = at<float>(workspace, W.ones);
     bf16_t* H = at<bf16_t>(workspace, W.H);
     bf16_t* Yu = at<bf16_t>(workspace, W.Y);
-    bf16_t* Yo = Yu + (size_t)n_calib * D.d;
+    const size_t nd = (size_t)n_calib * D.d;
+    float* partial = W.partial_bytes ? at<float>(workspace, W.partial) : nullptr;
+    int32_t* row_token = at<int32_t>(workspace, W.row_token);
     int32_t* tiles = at<int32_t>(workspace, W.tiles0);
     const bf16_t* xb = static_cast<const bf16_t*>(calib_x);
-    e = launch_zero_f32(loss_per_group, G, s);
-    if (e != hipSuccess) return hip_fail(e, "moe_build_united/zero");
-    auto run_unit = [&](int u, bf16_t* Y) -> hipError_t {
-        hipError_t err = launch_single_unit(unit_cnt, unit_off, D.U, u, n_calib, ones, s);
+    // The workspace holds the FFN rows of K+N_s units: the student's in the first slot, kept while the teachers go
+    // through the others in equal batches (one slot only: the teachers' outputs go to the second plane of Y).
+    const int cap = D.slots > 1 ? D.slots - 1 : 1;
+    const int sq_blocks = (int)std::min<size_t>({(nd / 8 + 255) / 256, (size_t)kSqdiffBlocks,
+                                                 align_up((size_t)n_calib * 4, 256) / 8});
+    double* sq_part = at<double>(workspace, W.ones);
+    if ((e = launch_repeat_tokens(row_token, n_calib, D.slots, s)) != hipSuccess) return hip_fail(e, "moe_build_united/rows");
+    auto run_units = [&](int u0, int n0, int u1, int n1, int first_slot, bf16_t* Y) -> hipError_t {
+        hipError_t err = launch_uniform_units(u0, n0, u1, n1, first_slot, n_calib, plan.bm, tiles, s);
         if (err != hipSuccess) return err;
-        return launch_ffn(D, u, u + 1, D.F, plan, xb, nullptr, unit_cnt, unit_off, fe, fu, fs, tiles, false, H, Y,
-                          W.partial_bytes ? at<float>(workspace, W.partial) : nullptr, s);
+        return launch_ffn(D, 0, n0 + n1, D.F, plan, xb, row_token, nullptr, nullptr, fe, fu, fs, tiles, true, H, Y, partial, s);
     };
     for (int g = 0; g < G; ++g) {
-        const int lo = g * way, hi = lo + way < m ? lo + way : m;
-        e = run_unit(m + g, Yu);
-        if (e != hipSuccess) return hip_fail(e, "moe_build_united/student");
-        for (int i = lo; i < hi; ++i) {
-            e = run_unit(i, Yo);
+        const int lo = g * way, hi = lo + way < m ? lo + way : m, k = hi - lo;
+        const int batches = ceil_div(k, cap);
+        if (D.slots == 1) {
+            e = run_units(m + g, 1, 0, 0, 0, Yu);
+            if (e != hipSuccess) return hip_fail(e, "moe_build_united/student");
+        }
+        for (int q = 0; q < batches; ++q) {
+            const int i0 = lo + (int)((int64_t)k * q / batches), i1 = lo + (int)((int64_t)k * (q + 1) / batches);
+            if (D.slots == 1) e = run_units(i0, i1 - i0, 0, 0, 0, Yu + nd);
+            else if (q == 0) e = run_units(m + g, 1, i0, i1 - i0, 0, Yu);
+            else e = run_units(i0, i1 - i0, 0, 0, 1, Yu);
             if (e != hipSuccess) return hip_fail(e, "moe_build_united/teacher");
-            e = launch_sqdiff_accumulate(Yu, Yo, (size_t)n_calib * D.d, 1.0f / ((float)(hi - lo) * (float)n_calib),
-                                         loss_per_group + g, s);
+            e = launch_sqdiff(Yu, Yu + nd, i1 - i0, nd, sq_blocks, q == 0, q == batches - 1, 1.0 / ((double)k * n_calib),
+                              sq_part, loss_per_group + g, s);
             if (e != hipSuccess) return hip_fail(e, "moe_build_united/loss");
         }
     }
     return MOE_OK;
+}
+
+// Groups with more than one member (all but a ragged last one, or none): the first ones.
+static int trained_groups(int m, int way)
+{
+    return way == 1 ? 0 : m / way + (m % way > 1 ? 1 : 0);
 }
 
 static moe_status check_distill(const moe_config* cfg, int32_t n_calib)
@@ -598,13 +614,18 @@ static moe_status check_distill(const moe_config* cfg, int32_t n_calib)
     return check_T(cfg, n_calib);
 }
 
+static size_t distill_bytes(const Dims& D, int n_calib)
+{
+    return distill_buffer_bytes(n_calib, D.d, D.F, distill_groups_at_once(n_calib, D.d, D.F, trained_groups(D.m, D.way)));
+}
+
 moe_status moe_distill_workspace_size(const moe_config* cfg, int32_t n_calib, size_t* bytes)
 {
     if (!bytes) return MOE_ERR_INVALID_ARG;
     moe_status st = check_distill(cfg, n_calib);
     if (st != MOE_OK) return st;
     const Dims D = make_dims(*cfg, n_calib);
-    *bytes = align_up(carve_workspace(D).total, 256) + distill_buffer_bytes(n_calib, D.d, D.F);
+    *bytes = align_up(carve_workspace(D).total, 256) + distill_bytes(D, n_calib);
     return MOE_OK;
 }
 
@@ -629,58 +650,53 @@ moe_status moe_distill_united(const moe_config* cfg, const moe_ffn_weights* expe
     D.ksplit = 1;
     const TilePlan plan = make_tile_plan(n_calib);
     const size_t fwd_bytes = align_up(W.total, 256);
-    if (!workspace || workspace_bytes < fwd_bytes + distill_buffer_bytes(n_calib, D.d, D.F)) return MOE_ERR_WORKSPACE;
+    if (!workspace || workspace_bytes < fwd_bytes + distill_bytes(D, n_calib)) return MOE_ERR_WORKSPACE;
     if (reinterpret_cast<uintptr_t>(workspace) & 255u) return MOE_ERR_ALIGNMENT;
     void* buf = static_cast<char*>(workspace) + fwd_bytes;
     const FfnWeights fe = to_ffn(experts), fu = to_ffn(&united_ro), fs{nullptr, nullptr, nullptr};
-    int32_t* unit_cnt = at<int32_t>(workspace, W.unit_cnt);
-    int32_t* unit_off = at<int32_t>(workspace, W.unit_off);
-    float* ones = at<float>(workspace, W.ones);
     bf16_t* H = at<bf16_t>(workspace, W.H);
     bf16_t* Yo = at<bf16_t>(workspace, W.Y);
     int32_t* tiles = at<int32_t>(workspace, W.tiles0);
+    int32_t* row_token = at<int32_t>(workspace, W.row_token);
+    float* partial = W.partial_bytes ? at<float>(workspace, W.partial) : nullptr;
     const bf16_t* xb = static_cast<const bf16_t*>(calib_x);
-    const size_t nd = (size_t)n_calib * D.d, dF = (size_t)D.d * D.F;
-    float* tbar = distill_tbar(buf, n_calib, D.d, D.F);
-    float* floor_ = distill_floor(buf, n_calib, D.d, D.F);
+    const size_t dF = (size_t)D.d * D.F;
+    bf16_t* wu[3] = {static_cast<bf16_t*>(united->w1), static_cast<bf16_t*>(united->w3), static_cast<bf16_t*>(united->w2)};
     hipError_t e;
-    auto teacher = [&](int i) -> hipError_t {
-        hipError_t err = launch_single_unit(unit_cnt, unit_off, D.U, i, n_calib, ones, s);
-        if (err != hipSuccess) return err;
-        return launch_ffn(D, i, i + 1, D.F, plan, xb, nullptr, unit_cnt, unit_off, fe, fu, fs, tiles, false, H, Yo,
-                          W.partial_bytes ? at<float>(workspace, W.partial) : nullptr, s);
-    };
-    for (int g = 0; g < G; ++g) {
-        const int lo = g * way, hi = lo + way < m ? lo + way : m, k = hi - lo;
-        bf16_t* wu[3] = {static_cast<bf16_t*>(united->w1) + (size_t)g * dF, static_cast<bf16_t*>(united->w3) + (size_t)g * dF,
-                         static_cast<bf16_t*>(united->w2) + (size_t)g * dF};
-        if (k == 1) {
-            // a lone member is its own best student: the minimiser (loss 0) is known, nothing to train
-            const void* we[3] = {experts->w1, experts->w3, experts->w2};
-            for (int q = 0; q < 3; ++q) {
-                e = hipMemcpyAsync(wu[q], static_cast<const bf16_t*>(we[q]) + (size_t)lo * dF, dF * 2,
-                                   hipMemcpyDeviceToDevice, s);
-                if (e != hipSuccess) return hip_fail(e, "moe_distill_united/copy");
+    const int trained = trained_groups(m, way);
+    const int at_once = distill_groups_at_once(n_calib, D.d, D.F, trained);
+    if (trained > 0 && (e = launch_repeat_tokens(row_token, n_calib, D.slots, s)) != hipSuccess)
+        return hip_fail(e, "moe_distill_united/rows");
+    for (int g0 = 0; g0 < trained; g0 += at_once) {
+        const int g1 = std::min(trained, g0 + at_once);
+        for (int g = g0; g < g1; ++g) {
+            // the teachers' outputs, as many at a time as the workspace holds FFN rows for, and their mean
+            const int lo = g * way, hi = lo + way < m ? lo + way : m, k = hi - lo;
+            const int batches = ceil_div(k, D.slots);
+            for (int q = 0; q < batches; ++q) {
+                const int i0 = lo + (int)((int64_t)k * q / batches), i1 = lo + (int)((int64_t)k * (q + 1) / batches);
+                if ((e = launch_uniform_units(i0, i1 - i0, 0, 0, 0, n_calib, plan.bm, tiles, s)) != hipSuccess ||
+                    (e = launch_ffn(D, 0, i1 - i0, D.F, plan, xb, row_token, nullptr, nullptr, fe, fu, fs, tiles, true, H, Yo,
+                                    partial, s)) != hipSuccess)
+                    return hip_fail(e, "moe_distill_united/teacher");
+                e = launch_teacher_stats(Yo, i1 - i0, q == 0, q == batches - 1, k, n_calib, D.d, D.F, g - g0, buf, s);
+                if (e != hipSuccess) return hip_fail(e, "moe_distill_united/mean");
             }
-            if (loss_history && (e = launch_fill_f32(loss_history + (size_t)g * (steps + 1), steps + 1, 0.0f, s)) != hipSuccess)
-                return hip_fail(e, "moe_distill_united/clear");
-            continue;
         }
-        if ((e = launch_fill_f32(tbar, nd, 0.0f, s)) != hipSuccess) return hip_fail(e, "moe_distill_united/clear");
-        if ((e = launch_fill_f32(floor_, 1, 0.0f, s)) != hipSuccess) return hip_fail(e, "moe_distill_united/clear");
-        for (int i = lo; i < hi; ++i) {
-            if ((e = teacher(i)) != hipSuccess) return hip_fail(e, "moe_distill_united/teacher");
-            if ((e = launch_teacher_mean(Yo, tbar, nd, 1.0f / (float)k, s)) != hipSuccess)
-                return hip_fail(e, "moe_distill_united/mean");
-        }
-        for (int i = lo; i < hi; ++i) {
-            if ((e = teacher(i)) != hipSuccess) return hip_fail(e, "moe_distill_united/teacher");
-            if ((e = launch_teacher_spread(Yo, tbar, nd, 1.0f / ((float)k * (float)n_calib), floor_, s)) != hipSuccess)
-                return hip_fail(e, "moe_distill_united/spread");
-        }
-        e = distill_group(xb, n_calib, D.d, D.F, wu[0], wu[1], wu[2], steps, lr,
-                          loss_history ? loss_history + (size_t)g * (steps + 1) : nullptr, buf, s);
+        e = distill_groups(xb, n_calib, D.d, D.F, g1 - g0, wu[0] + g0 * dF, wu[1] + g0 * dF, wu[2] + g0 * dF, steps, lr,
+                           loss_history ? loss_history + (size_t)g0 * (steps + 1) : nullptr, buf, s);
         if (e != hipSuccess) return hip_fail(e, "moe_distill_united/train");
+    }
+    for (int g = trained; g < G; ++g) {
+        // a lone member is its own best student: the minimiser (loss 0) is known, nothing to train
+        const void* we[3] = {experts->w1, experts->w3, experts->w2};
+        for (int q = 0; q < 3; ++q) {
+            e = hipMemcpyAsync(wu[q] + g * dF, static_cast<const bf16_t*>(we[q]) + (size_t)g * way * dF, dF * 2,
+                               hipMemcpyDeviceToDevice, s);
+            if (e != hipSuccess) return hip_fail(e, "moe_distill_united/copy");
+        }
+        if (loss_history && (e = launch_fill_f32(loss_history + (size_t)g * (steps + 1), steps + 1, 0.0f, s)) != hipSuccess)
+            return hip_fail(e, "moe_distill_united/clear");
     }
     return MOE_OK;
 }

@@ -1,17 +1,31 @@
-// United-expert distillation (the paper's section "United Expert Model"): the student FFN of one group is
+// United-expert distillation (the paper's section "United Expert Model"): the student FFN of a group is
 // fitted to the group's teacher FFNs on calibration tokens by minimising the section's MSE equation
 //   L = (1/k) sum_i || H_u - H_o^i ||^2   (summed over features, averaged over tokens)
 // with full-batch Adam.  The paper gives no optimiser, settings or data; this is the reading documented in
-// the header.  Off the serving path: plain GEMMs through the 64-row kernel (fp32 results), explicit
-// transposes for the contractions over tokens, element-wise kernels for SwiGLU and the update.
+// the header.
 //   forward   G = X W1^T, U = X W3^T, A = silu(G) U, Y = A W2^T
 //   backward  dY = Y - mean_i Y_i  (the factor 2/n goes into the update), dW2 = dY^T A, dA = dY W2,
 //             dG = dA U silu'(G), dU = dA silu(G), dW1 = dG^T X, dW3 = dU^T X
+// A step is four launches of one GEMM kernel with four epilogues, over several groups at a time (the groups are
+// independent and one of a small model does not fill the chip):
+//   kSwiglu  G, U, A and A^T            kResidual  dY, dY^T and the loss        (Y is not stored)
+//   kBackward  dG^T, dU^T (dA is not stored; the loss of the step is summed up on the way)
+//   kAdam  the three gradients stay in registers: masters, moments, the bf16 copies and W2^T are updated there
+// The contractions over tokens read K-contiguous operands that the earlier epilogues have written transposed.
+// Why: with each of these as a pass of its own (64-row GEMM tiles with fp32 results, transposes, SwiGLU, Adam, the loss
+// summed by one block) a pass over two groups of 8 and 4 teachers at n = d = 2048, F = 1408 with 8 steps took 56.9 ms,
+// 50 of them in the one-block sums and 3.4 in the GEMMs; now 3.58 ms.  Of those a step's four launches take 0.38 ms
+// (kSwiglu 78 us, kResidual 45, kBackward 59, kAdam 194 of which 484 MB of masters and moments are 107 us at the rate
+// of a large copy).
 #include "internal.h"
 
 #include <algorithm>
 
 namespace bmoe {
+
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 
 __device__ __forceinline__ float bf_to_f(unsigned short b) { return __uint_as_float(((unsigned)b) << 16); }
 __device__ __forceinline__ unsigned short f_to_bf(float f)
@@ -20,24 +34,23 @@ __device__ __forceinline__ unsigned short f_to_bf(float f)
     u += 0x7FFFu + ((u >> 16) & 1u);
     return (unsigned short)(u >> 16);
 }
+__device__ __forceinline__ uint2 pack4(const unsigned short (&v)[4])
+{
+    return make_uint2((unsigned)v[0] | ((unsigned)v[1] << 16), (unsigned)v[2] | ((unsigned)v[3] << 16));
+}
 
-// out[c][r] = in[r][c] (16-bit elements), R and C multiples of 64
-__global__ void __launch_bounds__(256) transpose16_kernel(const unsigned short* __restrict__ in,
-                                                          unsigned short* __restrict__ out, int R, int C)
+// out[c][r] = in[r][c] (16-bit elements), R and C multiples of 64; blockIdx.z: group
+__global__ void __launch_bounds__(256) transpose16_kernel(const unsigned short* __restrict__ in, size_t in_stride,
+                                                          unsigned short* __restrict__ out, size_t out_stride, int R, int C)
 {
     __shared__ unsigned short tile[64][66];
+    in += blockIdx.z * in_stride;
+    out += blockIdx.z * out_stride;
     const int r0 = blockIdx.y * 64, c0 = blockIdx.x * 64;
     const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
     for (int i = ty; i < 64; i += 4) tile[i][tx] = in[(size_t)(r0 + i) * C + c0 + tx];
     __syncthreads();
     for (int i = ty; i < 64; i += 4) out[(size_t)(c0 + i) * R + r0 + tx] = tile[tx][i];
-}
-
-__global__ void __launch_bounds__(256) bf16_to_f32_kernel(const unsigned short* __restrict__ in, float* __restrict__ out,
-                                                          size_t n)
-{
-    const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
-    if (i < n) out[i] = bf_to_f(in[i]);
 }
 
 __global__ void __launch_bounds__(256) fill_f32_kernel(float* __restrict__ p, size_t n, float v)
@@ -46,231 +59,491 @@ __global__ void __launch_bounds__(256) fill_f32_kernel(float* __restrict__ p, si
     if (i < n) p[i] = v;
 }
 
-// tbar += y / k  (y: FFN output rows in half precision)
-__global__ void __launch_bounds__(256) teacher_mean_kernel(const unsigned short* __restrict__ y, float* __restrict__ tbar,
-                                                           size_t n, float inv_k)
+// Sum of a double over the block (256 threads), fixed order; the result is valid in thread 0.
+__device__ __forceinline__ double block_sum(double s, double* red)
 {
-    const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
-    if (i < n) tbar[i] += (float)__builtin_bit_cast(_Float16, y[i]) * inv_k;
-}
-
-// A = silu(G) * U
-__global__ void __launch_bounds__(256) swiglu_fwd_kernel(const float* __restrict__ G, const float* __restrict__ U,
-                                                         unsigned short* __restrict__ A, size_t n)
-{
-    const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= n) return;
-    const float g = G[i];
-    A[i] = f_to_bf(g / (1.0f + __expf(-g)) * U[i]);
-}
-
-// dG = dA U sig(G) (1 + G (1 - sig(G))), dU = dA silu(G)
-__global__ void __launch_bounds__(256) swiglu_bwd_kernel(const float* __restrict__ G, const float* __restrict__ U,
-                                                         const float* __restrict__ dA, unsigned short* __restrict__ dG,
-                                                         unsigned short* __restrict__ dU, size_t n)
-{
-    const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= n) return;
-    const float g = G[i], u = U[i], da = dA[i];
-    const float sg = 1.0f / (1.0f + __expf(-g));
-    dG[i] = f_to_bf(da * u * sg * (1.0f + g * (1.0f - sg)));
-    dU[i] = f_to_bf(da * g * sg);
-}
-
-// dY = Y - tbar (bf16), and hist[0] = offset + scale * sum (Y - tbar)^2: one block, fixed summation order
-__global__ void __launch_bounds__(1024) diff_loss_kernel(const float* __restrict__ Y, const float* __restrict__ tbar,
-                                                         unsigned short* __restrict__ dY, size_t n, float scale,
-                                                         const float* __restrict__ offset, float* __restrict__ hist)
-{
-    __shared__ double red[16];
-    double s = 0.0;
-    for (size_t e = threadIdx.x; e < n; e += 1024) {
-        const float df = Y[e] - tbar[e];
-        if (dY) dY[e] = f_to_bf(df);
-        s += (double)df * (double)df;
-    }
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) s += __shfl_xor(s, off);
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
     __syncthreads();
-    if (threadIdx.x == 0 && hist) {
-        double t = 0.0;
-        for (int w = 0; w < 16; ++w) t += red[w];
-        hist[0] = (offset ? offset[0] : 0.0f) + (float)(t * (double)scale);
-    }
+    return red[0] + red[1] + red[2] + red[3];
 }
 
-// floor[0] += scale * sum (y - tbar)^2 for one teacher (y in half precision): one block
-__global__ void __launch_bounds__(1024) teacher_spread_kernel(const unsigned short* __restrict__ y,
-                                                              const float* __restrict__ tbar, size_t n, float scale,
-                                                              float* __restrict__ floor_)
+// One batch of b teachers (FFN output rows in half precision, y_stride elements apart): sum over the teachers so
+// far in tbar (the first batch starts it, the last one turns it into the mean of k), and per block
+// sum_i y_i^2 (last batch: - sum (sum_i y_i)^2 / k, which leaves sum_i |y_i - mean|^2) in fp64.
+__global__ void __launch_bounds__(256) teacher_stats_kernel(const unsigned short* __restrict__ y, size_t y_stride, int b,
+                                                            float* __restrict__ tbar, size_t n8, int first, int last, int k,
+                                                            double* __restrict__ part)
 {
-    __shared__ double red[16];
-    double s = 0.0;
-    for (size_t e = threadIdx.x; e < n; e += 1024) {
-        const float df = (float)__builtin_bit_cast(_Float16, y[e]) - tbar[e];
-        s += (double)df * (double)df;
-    }
+    __shared__ double red[4];
+    double q = 0.0;
+    for (size_t e = (size_t)blockIdx.x * 256 + threadIdx.x; e < n8; e += (size_t)gridDim.x * 256) {
+        float s[8];
+        if (first) {
 #pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) s += __shfl_xor(s, off);
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        double t = 0.0;
-        for (int w = 0; w < 16; ++w) t += red[w];
-        floor_[0] += (float)(t * (double)scale);
+            for (int c = 0; c < 8; ++c) s[c] = 0.0f;
+        } else {
+            const float4 a = reinterpret_cast<const float4*>(tbar)[2 * e], c4 = reinterpret_cast<const float4*>(tbar)[2 * e + 1];
+            s[0] = a.x; s[1] = a.y; s[2] = a.z; s[3] = a.w;
+            s[4] = c4.x; s[5] = c4.y; s[6] = c4.z; s[7] = c4.w;
+        }
+        for (int i = 0; i < b; ++i) {
+            const f16x8 v = *reinterpret_cast<const f16x8*>(y + i * y_stride + e * 8);
+#pragma unroll
+            for (int c = 0; c < 8; ++c) {
+                const float f = (float)v[c];
+                s[c] += f;
+                q += (double)(f * f);                      // the product of two halves is exact in fp32
+            }
+        }
+        if (last) {
+#pragma unroll
+            for (int c = 0; c < 8; ++c) {
+                q -= (double)s[c] * (double)s[c] / (double)k;
+                s[c] = s[c] / (float)k;
+            }
+        }
+        reinterpret_cast<float4*>(tbar)[2 * e] = make_float4(s[0], s[1], s[2], s[3]);
+        reinterpret_cast<float4*>(tbar)[2 * e + 1] = make_float4(s[4], s[5], s[6], s[7]);
     }
+    const double t = block_sum(q, red);
+    if (threadIdx.x == 0) part[blockIdx.x] = first ? t : part[blockIdx.x] + t;
 }
 
-// Adam with bias correction on fp32 master weights; writes the bf16 copy the GEMMs use.
-__global__ void __launch_bounds__(256) adam_kernel(float* __restrict__ w, float* __restrict__ m, float* __restrict__ v,
-                                                   const float* __restrict__ grad, unsigned short* __restrict__ w_bf16,
-                                                   size_t n, float gscale, float lr, float beta1, float beta2, float eps,
-                                                   float c1, float c2)
+// out[g] = (offset ? offset[g] : 0) + scale * sum part[g][0..n): one block per group (strides in bytes)
+__device__ __forceinline__ float sum_partials(const double* part, int n, float offset, double scale, double* red)
 {
-    const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= n) return;
-    const float g = grad[i] * gscale;
-    const float mi = beta1 * m[i] + (1.0f - beta1) * g;
-    const float vi = beta2 * v[i] + (1.0f - beta2) * g * g;
-    m[i] = mi;
-    v[i] = vi;
-    const float wi = w[i] - lr * (mi * c1) / (sqrtf(vi * c2) + eps);
-    w[i] = wi;
-    w_bf16[i] = f_to_bf(wi);
+    double s = 0.0;
+    for (int i = threadIdx.x; i < n; i += 256) s += part[i];
+    return offset + (float)fmax(block_sum(s, red) * scale, 0.0);   // sums of squares: not below zero by rounding
+}
+__global__ void __launch_bounds__(256) sum_partials_kernel(const char* part, size_t part_stride, int n, const char* offset,
+                                                           size_t offset_stride, double scale, float* out, size_t out_stride)
+{
+    __shared__ double red[4];
+    const int g = blockIdx.x;
+    const float off = offset ? *reinterpret_cast<const float*>(offset + g * offset_stride) : 0.0f;
+    const float v = sum_partials(reinterpret_cast<const double*>(part + g * part_stride), n, off, scale, red);
+    if (threadIdx.x == 0) out[g * out_stride] = v;
 }
 
-static inline int nblk(size_t n) { return (int)((n + 255) / 256); }
-
-struct DistillBufs {
-    float *W[3], *M[3], *V[3], *Gd[3];                    // masters, Adam moments, gradients of W1, W3, W2
-    bf16_t* w2t;                                          // W2^T
-    float *Gf, *Uf, *dAf;                                 // [n][F]
-    bf16_t *A, *dG, *dU, *At, *dGt, *dUt;                 // [n][F] and [F][n]
-    float *Y, *tbar;                                      // [n][d]
-    bf16_t *dY, *dYt, *xt;                                // [n][d], [d][n], [d][n]
-    float* floor_;
-    int32_t* table;
-    size_t total;
+// ------------------------------------------------------------------------------------------------
+// C = A . B^T (A [M][K], B [N][K], bf16, fp32 accumulators; M, N, K multiples of 64) with an epilogue.
+// ------------------------------------------------------------------------------------------------
+struct Ref {                                              // a buffer of every group, `stride` bytes apart
+    char* p; size_t stride;
+    template <typename T> __device__ __forceinline__ T* at(int g) const { return reinterpret_cast<T*>(p + g * stride); }
+};
+enum { kSwiglu, kResidual, kBackward, kAdam };
+struct DJob {
+    Ref A, B, B1;                                          // B1: kSwiglu only (B = W1, B1 = W3)
+    int M, N, K;
+    int mt, nt;                                            // tiles
+    Ref r[5];                                              // see the epilogues
+};
+struct DGemm {
+    DJob job[3];
+    int n_jobs, tiles;                                     // every job has the same number of tiles per group
+    int total;                                             // groups * jobs * tiles
+    float gscale, lr, c1, c2;                              // kAdam
+    int first;                                             // kAdam: no masters or moments yet
+    Ref part, floor_; int n_part; double lscale; float* hist; size_t hist_stride;   // kBackward: the loss of this step
 };
 
-static DistillBufs carve_distill(void* buf, int n, int d, int F)
+constexpr int kImgPitch = 272;                             // bytes per row of a 128 x 128 bf16 image in LDS
+constexpr int kDGemmLds = 2 * 128 * kImgPitch;             // two images; the two stages of the k loop need 64 KiB
+
+// 128 x 128 x 64 tiles, four waves (64 x 64 each, 16x16x32 MFMA), two LDS stages filled by direct global->LDS
+// loads, two blocks per CU: the second block's waves cover the barrier and the load latency of the first.
+// A wave's 64 x 64 tile is either inside the matrix or outside (M and N are multiples of 64).
+template <int EPI>
+__global__ void __launch_bounds__(256, 2) distill_gemm_kernel(DGemm p)
+{
+    constexpr int STAGE = 256 * 128;
+    constexpr int BNC = EPI == kSwiglu ? 64 : 128;         // output columns of a tile
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    __shared__ double red[4];
+    // block id mod 8 is the XCD: a contiguous range of tiles each, super-tiles of 8 M tiles x all N tiles inside
+    const int chunk = (p.total + 7) >> 3;
+    const int L = (blockIdx.x & 7) * chunk + (blockIdx.x >> 3);
+    if ((int)(blockIdx.x >> 3) >= chunk || L >= p.total) return;
+    const int gj = L / p.tiles, tile = L - gj * p.tiles;
+    const int g = gj / p.n_jobs;
+    const DJob& J = p.job[gj - g * p.n_jobs];
+    const int gspan = 8 * J.nt, gi = tile / gspan, rem = tile - gi * gspan;
+    const int gsz = min(8, J.mt - gi * 8);
+    const int nt = rem / gsz, mt = gi * 8 + (rem - nt * gsz);
+    const int m0 = mt * 128, n0 = nt * BNC;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int wm = wave >> 1, wn = wave & 1;
+    const int K = J.K;
+
+    // wave w moves the 8-row groups w, w+4, ... of a stage (A rows first, then B rows); 16-byte chunk c of row r
+    // sits in slot c ^ ((r/2)&7) (conflict-free ds_read_b128)
+    const bf16_t* src[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        const int row = (wave + i * 4) * 8 + (lane >> 3);
+        const bf16_t* base;
+        if (i < 4) {
+            base = J.A.at<const bf16_t>(g) + (size_t)min(m0 + row, J.M - 1) * K;
+        } else if (EPI == kSwiglu) {
+            // the wave tile's 16-column MFMA tiles alternate W1 / W3 of the same 16 columns
+            const int n = row - 128, w_n = n >> 6, j = (n >> 4) & 3;
+            const int col = n0 + w_n * 32 + (j >> 1) * 16 + (n & 15);
+            base = ((j & 1) ? J.B1 : J.B).at<const bf16_t>(g) + (size_t)min(col, J.N - 1) * K;
+        } else {
+            base = J.B.at<const bf16_t>(g) + (size_t)min(n0 + row - 128, J.N - 1) * K;
+        }
+        src[i] = base + (((lane & 7) ^ ((row >> 1) & 7)) << 3);
+    }
+    auto issue = [&](int kt) {
+        char* dst = smem + (kt & 1) * STAGE + wave * 1024;
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src[i] + kt * 64),
+                                             (__attribute__((address_space(3))) void*)(dst + i * 4096), 16, 0, 0);
+    };
+    f32x4 acc[4][4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const int a_off = (wm * 64 + (lane & 15)) * 128, b_off = (128 + wn * 64 + (lane & 15)) * 128;
+    const int swz = ((lane & 15) >> 1) & 7;
+    const int nk = K >> 6;
+    issue(0);
+    for (int kt = 0; kt < nk; ++kt) {
+        __builtin_amdgcn_s_waitcnt(0x0F70);               // vmcnt(0): this wave's part of tile kt has landed
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_barrier();                     // everyone's part has; nobody still reads the other stage
+        asm volatile("" ::: "memory");
+        if (kt + 1 < nk) issue(kt + 1);
+        const char* St = smem + (kt & 1) * STAGE;
+#pragma unroll
+        for (int kk = 0; kk < 2; ++kk) {
+            const int sw = ((kk * 4 + (lane >> 4)) ^ swz) << 4;
+            bf16x8 fa[4], fb[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) fa[i] = *reinterpret_cast<const bf16x8*>(St + a_off + i * 2048 + sw);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) fb[j] = *reinterpret_cast<const bf16x8*>(St + b_off + j * 2048 + sw);
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[j], fa[i], acc[i][j], 0, 0, 0);
+        }
+    }
+    __syncthreads();                                      // every wave has left the stages: images go there
+
+    // A lane holds, for row wm*64 + 16 i + (lane & 15) of the tile, the columns wn*64 + 16 j + 4 (lane >> 4) + 0..3.
+    const int r_l = wm * 64 + (lane & 15), c4 = 4 * (lane >> 4);
+    const bool w_in = m0 + wm * 64 < J.M && (EPI == kSwiglu || n0 + wn * 64 < J.N);
+    // bf16 results go through LDS: `rows` holds [tile row][tile column], `cols` [tile column][tile row]
+    auto put_row = [&](char* img, int r, int c, const unsigned short (&v)[4]) {
+        *reinterpret_cast<uint2*>(img + r * kImgPitch + c * 2) = pack4(v);
+    };
+    auto put_col = [&](char* img, int r, int c, const unsigned short (&v)[4]) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) *reinterpret_cast<unsigned short*>(img + (c + e) * kImgPitch + r * 2) = v[e];
+    };
+    // image of R rows x C columns -> out[(row0 + r) * ld + col0 + c], 16 bytes per thread, rows < row_end, columns < col_end
+    auto flush = [&](const char* img, int R, int C, unsigned short* out, int ld, int row0, int row_end, int col0, int col_end) {
+        const int cpr = C >> 3;
+        for (int i = tid; i < R * cpr; i += 256) {
+            const int r = i / cpr, c = (i - r * cpr) * 8;
+            if (row0 + r < row_end && col0 + c < col_end)
+                *reinterpret_cast<uint4*>(out + (size_t)(row0 + r) * ld + col0 + c) =
+                    *reinterpret_cast<const uint4*>(img + r * kImgPitch + c * 2);
+        }
+    };
+    char* rows = smem;
+    char* cols = smem + 128 * kImgPitch;
+
+    if constexpr (EPI == kSwiglu) {
+        // r: G, U (fp32 [n][F]), A [n][F], A^T [F][n]
+        float* G = J.r[0].at<float>(g);
+        float* U = J.r[1].at<float>(g);
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int jp = 0; jp < 2; ++jp) {
+                const f32x4 gv = acc[i][2 * jp], uv = acc[i][2 * jp + 1];
+                const int r = r_l + i * 16, c = wn * 32 + jp * 16 + c4;
+                unsigned short a[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) a[e] = f_to_bf(gv[e] / (1.0f + __expf(-gv[e])) * uv[e]);
+                put_row(rows, r, c, a);
+                put_col(cols, r, c, a);
+                if (w_in) {
+                    const size_t at = (size_t)(m0 + r) * J.N + n0 + c;
+                    *reinterpret_cast<f32x4*>(G + at) = gv;
+                    *reinterpret_cast<f32x4*>(U + at) = uv;
+                }
+            }
+        __syncthreads();
+        flush(rows, 128, 64, J.r[2].at<unsigned short>(g), J.N, m0, J.M, n0, J.N);
+        flush(cols, 64, 128, J.r[3].at<unsigned short>(g), J.M, n0, J.N, m0, J.M);
+    } else if constexpr (EPI == kResidual) {
+        // r: mean teacher output (fp32 [n][d]), dY [n][d], dY^T [d][n] (null: loss only), loss partials [tiles]
+        const float* tb = J.r[0].at<const float>(g);
+        const bool store = J.r[1].p != nullptr;
+        double s = 0.0;
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int r = r_l + i * 16, c = wn * 64 + j * 16 + c4;
+                f32x4 t = {0.f, 0.f, 0.f, 0.f};
+                if (w_in) t = *reinterpret_cast<const f32x4*>(tb + (size_t)(m0 + r) * J.N + n0 + c);
+                unsigned short v[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const float df = acc[i][j][e] - t[e];
+                    v[e] = f_to_bf(df);
+                    if (w_in) s += (double)df * (double)df;
+                }
+                if (store) {
+                    put_row(rows, r, c, v);
+                    put_col(cols, r, c, v);
+                }
+            }
+        const double t = block_sum(s, red);               // (its barrier also completes the images)
+        if (tid == 0) J.r[3].at<double>(g)[tile] = t;
+        if (store) {
+            flush(rows, 128, 128, J.r[1].at<unsigned short>(g), J.N, m0, J.M, n0, J.N);
+            flush(cols, 128, 128, J.r[2].at<unsigned short>(g), J.M, n0, J.N, m0, J.M);
+        }
+    } else if constexpr (EPI == kBackward) {
+        // r: G, U (fp32 [n][F]), dG^T, dU^T [F][n].  dG = dA U sig(G) (1 + G (1 - sig(G))), dU = dA silu(G)
+        const float* G = J.r[0].at<const float>(g);
+        const float* U = J.r[1].at<const float>(g);
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int r = r_l + i * 16, c = wn * 64 + j * 16 + c4;
+                f32x4 gv = {0.f, 0.f, 0.f, 0.f}, uv = gv;
+                if (w_in) {
+                    const size_t at = (size_t)(m0 + r) * J.N + n0 + c;
+                    gv = *reinterpret_cast<const f32x4*>(G + at);
+                    uv = *reinterpret_cast<const f32x4*>(U + at);
+                }
+                unsigned short dg[4], du[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const float da = acc[i][j][e], sg = 1.0f / (1.0f + __expf(-gv[e]));
+                    dg[e] = f_to_bf(da * uv[e] * sg * (1.0f + gv[e] * (1.0f - sg)));
+                    du[e] = f_to_bf(da * gv[e] * sg);
+                }
+                put_col(rows, r, c, dg);
+                put_col(cols, r, c, du);
+            }
+        __syncthreads();
+        flush(rows, 128, 128, J.r[2].at<unsigned short>(g), J.M, n0, J.N, m0, J.M);
+        flush(cols, 128, 128, J.r[3].at<unsigned short>(g), J.M, n0, J.N, m0, J.M);
+        if (tile == 0 && p.hist != nullptr) {
+            const float l = sum_partials(p.part.at<const double>(g), p.n_part, *p.floor_.at<const float>(g), p.lscale, red);
+            if (tid == 0) p.hist[g * p.hist_stride] = l;
+        }
+    } else {
+        // r: master, first and second moment (fp32 [M][N]), the bf16 copy [M][N], its transpose [N][M] or null.
+        // Adam with bias correction; the first step starts from the bf16 copy and zero moments.
+        float* W = J.r[0].at<float>(g);
+        float* Mo = J.r[1].at<float>(g);
+        float* V = J.r[2].at<float>(g);
+        unsigned short* wb = J.r[3].at<unsigned short>(g);
+        const float beta1 = 0.9f, beta2 = 0.999f, eps = 1e-8f;
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int r = r_l + i * 16, c = wn * 64 + j * 16 + c4;
+                const size_t at = (size_t)(m0 + r) * J.N + n0 + c;
+                unsigned short o[4] = {0, 0, 0, 0};
+                if (w_in) {
+                    f32x4 w, m, v;
+                    if (p.first) {
+                        const uint2 b = *reinterpret_cast<const uint2*>(wb + at);
+                        w = f32x4{bf_to_f(b.x & 0xFFFF), bf_to_f(b.x >> 16), bf_to_f(b.y & 0xFFFF), bf_to_f(b.y >> 16)};
+                        m = f32x4{0.f, 0.f, 0.f, 0.f};
+                        v = m;
+                    } else {
+                        w = *reinterpret_cast<const f32x4*>(W + at);
+                        m = *reinterpret_cast<const f32x4*>(Mo + at);
+                        v = *reinterpret_cast<const f32x4*>(V + at);
+                    }
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const float gr = acc[i][j][e] * p.gscale;
+                        m[e] = beta1 * m[e] + (1.0f - beta1) * gr;
+                        v[e] = beta2 * v[e] + (1.0f - beta2) * gr * gr;
+                        w[e] = w[e] - p.lr * (m[e] * p.c1) / (sqrtf(v[e] * p.c2) + eps);
+                        o[e] = f_to_bf(w[e]);
+                    }
+                    *reinterpret_cast<f32x4*>(W + at) = w;
+                    *reinterpret_cast<f32x4*>(Mo + at) = m;
+                    *reinterpret_cast<f32x4*>(V + at) = v;
+                }
+                put_row(rows, r, c, o);
+                if (J.r[4].p) put_col(cols, r, c, o);
+            }
+        __syncthreads();
+        flush(rows, 128, 128, wb, J.N, m0, J.M, n0, J.N);
+        if (J.r[4].p) flush(cols, 128, 128, J.r[4].at<unsigned short>(g), J.M, n0, J.N, m0, J.M);
+    }
+}
+
+template <int EPI>
+static hipError_t launch_dgemm(DGemm& p, int groups, hipStream_t s)
+{
+    for (int j = 0; j < p.n_jobs; ++j) {
+        p.job[j].mt = ceil_div(p.job[j].M, 128);
+        p.job[j].nt = ceil_div(p.job[j].N, EPI == kSwiglu ? 64 : 128);
+    }
+    p.tiles = p.job[0].mt * p.job[0].nt;
+    p.total = groups * p.n_jobs * p.tiles;
+    distill_gemm_kernel<EPI><<<ceil_div(p.total, 8) * 8, 256, kDGemmLds, s>>>(p);
+    return hipGetLastError();
+}
+
+hipError_t init_distill_kernels()
+{
+    const void* k[] = {reinterpret_cast<const void*>(distill_gemm_kernel<kSwiglu>),
+                       reinterpret_cast<const void*>(distill_gemm_kernel<kResidual>),
+                       reinterpret_cast<const void*>(distill_gemm_kernel<kBackward>),
+                       reinterpret_cast<const void*>(distill_gemm_kernel<kAdam>)};
+    for (const void* f : k) {
+        const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, kDGemmLds);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
+// Groups trained side by side: enough that the smallest of a step's GEMMs gives every CU two blocks, at most 8.
+int distill_groups_at_once(int n, int d, int F, int n_groups)
+{
+    const int64_t t = std::min((int64_t)ceil_div(n, 128) * ceil_div(F, 128), (int64_t)ceil_div(n, 128) * ceil_div(d, 128));
+    return (int)std::max<int64_t>(1, std::min<int64_t>({n_groups, (512 + t - 1) / t, 8}));
+}
+
+constexpr int kStatBlocks = 512;                          // most blocks of the teacher statistics
+
+// Buffers of one group (offsets from the group's base) and, behind those of all groups, X^T.
+struct DistillLayout {
+    size_t W[3], M[3], V[3], w2t, G, U, A, At, dGt, dUt, tbar, dY, dYt, floor_, part, group, xt, total;
+};
+
+static DistillLayout distill_layout(int n, int d, int F, int groups)
 {
     const size_t dF = (size_t)d * F, nF = (size_t)n * F, nd = (size_t)n * d;
-    char* base = static_cast<char*>(buf);
+    DistillLayout B;
     size_t o = 0;
-    auto take = [&](size_t bytes) { char* p = base + o; o = align_up(o + bytes, 256); return p; };
-    DistillBufs B;
-    for (int q = 0; q < 3; ++q) B.W[q] = reinterpret_cast<float*>(take(dF * 4));
-    for (int q = 0; q < 3; ++q) B.M[q] = reinterpret_cast<float*>(take(dF * 4));
-    for (int q = 0; q < 3; ++q) B.V[q] = reinterpret_cast<float*>(take(dF * 4));
-    for (int q = 0; q < 3; ++q) B.Gd[q] = reinterpret_cast<float*>(take(dF * 4));
-    B.w2t = reinterpret_cast<bf16_t*>(take(dF * 2));
-    B.Gf = reinterpret_cast<float*>(take(nF * 4));
-    B.Uf = reinterpret_cast<float*>(take(nF * 4));
-    B.dAf = reinterpret_cast<float*>(take(nF * 4));
-    B.A = reinterpret_cast<bf16_t*>(take(nF * 2));
-    B.dG = reinterpret_cast<bf16_t*>(take(nF * 2));
-    B.dU = reinterpret_cast<bf16_t*>(take(nF * 2));
-    B.At = reinterpret_cast<bf16_t*>(take(nF * 2));
-    B.dGt = reinterpret_cast<bf16_t*>(take(nF * 2));
-    B.dUt = reinterpret_cast<bf16_t*>(take(nF * 2));
-    B.Y = reinterpret_cast<float*>(take(nd * 4));
-    B.tbar = reinterpret_cast<float*>(take(nd * 4));
-    B.dY = reinterpret_cast<bf16_t*>(take(nd * 2));
-    B.dYt = reinterpret_cast<bf16_t*>(take(nd * 2));
-    B.xt = reinterpret_cast<bf16_t*>(take(nd * 2));
-    B.floor_ = reinterpret_cast<float*>(take(256));
-    B.table = reinterpret_cast<int32_t*>(take(16 + 16 * (size_t)(std::max(std::max(n, d), F) / 64 + 1)));
-    B.total = o;
+    auto take = [&](size_t bytes) { const size_t at = o; o = align_up(o + bytes, 256); return at; };
+    for (int q = 0; q < 3; ++q) B.W[q] = take(dF * 4);
+    for (int q = 0; q < 3; ++q) B.M[q] = take(dF * 4);
+    for (int q = 0; q < 3; ++q) B.V[q] = take(dF * 4);
+    B.w2t = take(dF * 2);
+    B.G = take(nF * 4);
+    B.U = take(nF * 4);
+    B.A = take(nF * 2);
+    B.At = take(nF * 2);
+    B.dGt = take(nF * 2);
+    B.dUt = take(nF * 2);
+    B.tbar = take(nd * 4);
+    B.dY = take(nd * 2);
+    B.dYt = take(nd * 2);
+    B.floor_ = take(4);
+    B.part = take(8 * (size_t)std::max(kStatBlocks, ceil_div(n, 128) * ceil_div(d, 128)));
+    B.group = o;
+    B.xt = o * groups;
+    B.total = B.xt + align_up(nd * 2, 256);
     return B;
 }
 
-size_t distill_buffer_bytes(int n, int d, int F) { return carve_distill(nullptr, n, d, F).total; }
-float* distill_tbar(void* buf, int n, int d, int F) { return carve_distill(buf, n, d, F).tbar; }
-float* distill_floor(void* buf, int n, int d, int F) { return carve_distill(buf, n, d, F).floor_; }
+size_t distill_buffer_bytes(int n, int d, int F, int groups) { return distill_layout(n, d, F, groups).total; }
 
-// Trains the student (w1u, w3u [F][d], w2u [d][F], bf16, updated in place) of ONE group.  The mean teacher
-// output (distill_tbar) and the loss at it (distill_floor) have been prepared by the caller in buf.
-hipError_t distill_group(const bf16_t* x, int n, int d, int F, bf16_t* w1u, bf16_t* w3u, bf16_t* w2u, int steps,
-                         float lr, float* hist, void* buf, hipStream_t s)
+hipError_t launch_teacher_stats(const bf16_t* y_half, int b, bool first, bool last, int k, int n, int d, int F, int g, void* buf,
+                                hipStream_t s)
 {
-    const size_t dF = (size_t)d * F, nF = (size_t)n * F, nd = (size_t)n * d;
-    const DistillBufs B = carve_distill(buf, n, d, F);
-    float* const* W = B.W; float* const* M = B.M; float* const* V = B.V; float* const* Gd = B.Gd;
-    bf16_t* w2t = B.w2t;
-    float *Gf = B.Gf, *Uf = B.Uf, *dAf = B.dAf;
-    bf16_t *A = B.A, *dG = B.dG, *dU = B.dU, *At = B.At, *dGt = B.dGt, *dUt = B.dUt;
-    float* Y = B.Y;
-    const float* tbar = B.tbar;
-    const float* floor_ = B.floor_;
-    bf16_t *dY = B.dY, *dYt = B.dYt, *xt = B.xt;
-    int32_t* table = B.table;
+    const DistillLayout B = distill_layout(n, d, F, 1);
+    char* base = static_cast<char*>(buf) + g * B.group;
+    const size_t n8 = (size_t)n * d / 8;
+    const int blocks = (int)std::min<size_t>((n8 + 255) / 256, kStatBlocks);
+    double* part = reinterpret_cast<double*>(base + B.part);
+    teacher_stats_kernel<<<blocks, 256, 0, s>>>(reinterpret_cast<const unsigned short*>(y_half), (size_t)n * d, b,
+                                                reinterpret_cast<float*>(base + B.tbar), n8, first, last, k, part);
+    if (last)
+        sum_partials_kernel<<<1, 256, 0, s>>>(base + B.part, 0, blocks, nullptr, 0, 1.0 / ((double)k * n),
+                                              reinterpret_cast<float*>(base + B.floor_), 0);
+    return hipGetLastError();
+}
 
-    auto us = [](bf16_t* p) { return reinterpret_cast<unsigned short*>(p); };
-    auto cus = [](const bf16_t* p) { return reinterpret_cast<const unsigned short*>(p); };
-    auto transpose = [&](const bf16_t* in, bf16_t* out, int R, int C) {
-        transpose16_kernel<<<dim3(C / 64, R / 64), 256, 0, s>>>(cus(in), us(out), R, C);
+// Trains the students of `groups` consecutive groups (w1u, w3u [g][F][d], w2u [g][d][F], bf16, updated in place).
+// Their teachers' statistics are in buf (launch_teacher_stats).  hist: [g][steps + 1] or null.
+hipError_t distill_groups(const bf16_t* x, int n, int d, int F, int groups, bf16_t* w1u, bf16_t* w3u, bf16_t* w2u, int steps,
+                          float lr, float* hist, void* buf, hipStream_t s)
+{
+    const DistillLayout B = distill_layout(n, d, F, groups);
+    char* base = static_cast<char*>(buf);
+    const size_t dF = (size_t)d * F;
+    auto ref = [&](size_t off) { return Ref{base + off, B.group}; };
+    auto weight = [&](const bf16_t* w) { return Ref{reinterpret_cast<char*>(const_cast<bf16_t*>(w)), dF * 2}; };
+    const Ref none{nullptr, 0}, X{reinterpret_cast<char*>(const_cast<bf16_t*>(x)), 0}, Xt{base + B.xt, 0};
+    auto us = [](const void* p) { return static_cast<const unsigned short*>(p); };
+    auto job = [&](Ref a, Ref b, Ref b1, int M, int N, int K, Ref r0, Ref r1, Ref r2, Ref r3, Ref r4) {
+        DJob j;
+        j.A = a; j.B = b; j.B1 = b1; j.M = M; j.N = N; j.K = K; j.mt = j.nt = 0;
+        j.r[0] = r0; j.r[1] = r1; j.r[2] = r2; j.r[3] = r3; j.r[4] = r4;
+        return j;
     };
-    bf16_t* wb[3] = {w1u, w3u, w2u};
-    for (int q = 0; q < 3; ++q) {
-        bf16_to_f32_kernel<<<nblk(dF), 256, 0, s>>>(cus(wb[q]), W[q], dF);
-        fill_f32_kernel<<<nblk(dF), 256, 0, s>>>(M[q], dF, 0.0f);
-        fill_f32_kernel<<<nblk(dF), 256, 0, s>>>(V[q], dF, 0.0f);
-    }
-    transpose(x, xt, n, d);                               // X^T [d][n]
-    const float beta1 = 0.9f, beta2 = 0.999f, eps = 1e-8f;
-    double b1t = 1.0, b2t = 1.0;
+    transpose16_kernel<<<dim3(d / 64, n / 64, 1), 256, 0, s>>>(us(x), 0, reinterpret_cast<unsigned short*>(base + B.xt), 0, n, d);
+    if (steps > 0)
+        transpose16_kernel<<<dim3(F / 64, d / 64, groups), 256, 0, s>>>(
+            us(w2u), dF, reinterpret_cast<unsigned short*>(base + B.w2t), B.group / 2, d, F);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
+    double b1t = 1.0, b2t = 1.0;
+    const int loss_tiles = ceil_div(n, 128) * ceil_div(d, 128);
     for (int t = 0; t <= steps; ++t) {
-        // forward
-        if ((e = launch_plain_gemm(x, w1u, n, F, d, Gf, table, s)) != hipSuccess) return e;
-        if ((e = launch_plain_gemm(x, w3u, n, F, d, Uf, table, s)) != hipSuccess) return e;
-        swiglu_fwd_kernel<<<nblk(nF), 256, 0, s>>>(Gf, Uf, us(A), nF);
-        if ((e = launch_plain_gemm(A, w2u, n, d, F, Y, table, s)) != hipSuccess) return e;
-        diff_loss_kernel<<<1, 1024, 0, s>>>(Y, tbar, t < steps ? us(dY) : nullptr, nd, 1.0f / (float)n, floor_,
-                                            hist ? hist + t : nullptr);
-        if (t == steps) break;
-        // backward
-        transpose(dY, dYt, n, d);                         // [d][n]
-        transpose(A, At, n, F);                           // [F][n]
-        if ((e = launch_plain_gemm(dYt, At, d, F, n, Gd[2], table, s)) != hipSuccess) return e;      // dW2 [d][F]
-        transpose(w2u, w2t, d, F);                        // W2^T [F][d]
-        if ((e = launch_plain_gemm(dY, w2t, n, F, d, dAf, table, s)) != hipSuccess) return e;        // dA [n][F]
-        swiglu_bwd_kernel<<<nblk(nF), 256, 0, s>>>(Gf, Uf, dAf, us(dG), us(dU), nF);
-        transpose(dG, dGt, n, F);
-        transpose(dU, dUt, n, F);
-        if ((e = launch_plain_gemm(dGt, xt, F, d, n, Gd[0], table, s)) != hipSuccess) return e;      // dW1 [F][d]
-        if ((e = launch_plain_gemm(dUt, xt, F, d, n, Gd[1], table, s)) != hipSuccess) return e;      // dW3 [F][d]
-        // update
-        b1t *= beta1;
-        b2t *= beta2;
-        const float c1 = (float)(1.0 / (1.0 - b1t)), c2 = (float)(1.0 / (1.0 - b2t));
-        for (int q = 0; q < 3; ++q)
-            adam_kernel<<<nblk(dF), 256, 0, s>>>(W[q], M[q], V[q], Gd[q], us(wb[q]), dF, 2.0f / (float)n, lr, beta1, beta2,
-                                                 eps, c1, c2);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
+        const bool train = t < steps;
+        if (!train && hist == nullptr) break;
+        DGemm p;
+        p.gscale = 2.0f / (float)n; p.lr = lr; p.c1 = p.c2 = 1.0f; p.first = t == 0 ? 1 : 0;
+        p.part = ref(B.part); p.floor_ = ref(B.floor_); p.n_part = loss_tiles; p.lscale = (double)(1.0f / (float)n);
+        p.hist = hist ? hist + t : nullptr; p.hist_stride = steps + 1;
+        p.n_jobs = 1;
+        p.job[0] = p.job[1] = p.job[2] =
+            job(X, weight(w1u), weight(w3u), n, F, d, ref(B.G), ref(B.U), ref(B.A), ref(B.At), none);
+        if ((e = launch_dgemm<kSwiglu>(p, groups, s)) != hipSuccess) return e;
+        p.job[0] = job(ref(B.A), weight(w2u), none, n, d, F, ref(B.tbar), train ? ref(B.dY) : none,
+                       train ? ref(B.dYt) : none, ref(B.part), none);
+        if ((e = launch_dgemm<kResidual>(p, groups, s)) != hipSuccess) return e;
+        if (!train) {
+            sum_partials_kernel<<<groups, 256, 0, s>>>(base + B.part, B.group, loss_tiles, base + B.floor_, B.group, p.lscale,
+                                                       p.hist, p.hist_stride);
+            return hipGetLastError();
+        }
+        p.job[0] = job(ref(B.dY), ref(B.w2t), none, n, F, d, ref(B.G), ref(B.U), ref(B.dGt), ref(B.dUt), none);
+        if ((e = launch_dgemm<kBackward>(p, groups, s)) != hipSuccess) return e;
+        b1t *= 0.9f;
+        b2t *= 0.999f;
+        p.c1 = (float)(1.0 / (1.0 - b1t));
+        p.c2 = (float)(1.0 / (1.0 - b2t));
+        p.n_jobs = 3;
+        p.job[0] = job(ref(B.dGt), Xt, none, F, d, n, ref(B.W[0]), ref(B.M[0]), ref(B.V[0]), weight(w1u), none);
+        p.job[1] = job(ref(B.dUt), Xt, none, F, d, n, ref(B.W[1]), ref(B.M[1]), ref(B.V[1]), weight(w3u), none);
+        p.job[2] = job(ref(B.dYt), ref(B.At), none, d, F, n, ref(B.W[2]), ref(B.M[2]), ref(B.V[2]), weight(w2u), ref(B.w2t));
+        if ((e = launch_dgemm<kAdam>(p, groups, s)) != hipSuccess) return e;
     }
-    return hipGetLastError();
-}
-
-hipError_t launch_teacher_mean(const bf16_t* y_half, float* tbar, size_t n, float inv_k, hipStream_t s)
-{
-    teacher_mean_kernel<<<nblk(n), 256, 0, s>>>(reinterpret_cast<const unsigned short*>(y_half), tbar, n, inv_k);
-    return hipGetLastError();
-}
-
-hipError_t launch_teacher_spread(const bf16_t* y_half, const float* tbar, size_t n, float scale, float* floor_,
-                                 hipStream_t s)
-{
-    teacher_spread_kernel<<<1, 1024, 0, s>>>(reinterpret_cast<const unsigned short*>(y_half), tbar, n, scale, floor_);
-    return hipGetLastError();
+    return hipSuccess;
 }
 
 hipError_t launch_fill_f32(float* p, size_t n, float v, hipStream_t s)
 {
-    fill_f32_kernel<<<nblk(n), 256, 0, s>>>(p, n, v);
+    fill_f32_kernel<<<(int)((n + 255) / 256), 256, 0, s>>>(p, n, v);
     return hipGetLastError();
 }
 

@@ -82,7 +82,6 @@ struct GemmArgs {
     int n_ntiles;
     int group_m;                                // M tiles per L2 super-tile
     int ksplit; long plane;                     // GEMM2 only: K split into ksplit slices, slice s writes out + s*plane
-    float* out32;                               // plain GEMM only (32- and 64-row kernel): fp32 output instead of out
     float* partial;                             // four-wave kernel, ksplit 1: scratch of the K-split tail (or null)
     int partial_cap;                            // fp32 tiles it holds
 };
@@ -171,64 +170,20 @@ __device__ __forceinline__ const bf16_t* b_row_ptr(const GemmArgs& p, const Tile
     return W + (size_t)col * p.K;
 }
 
-// Epilogue.  The MFMAs are issued as (weights x rows), so a lane holds, for output row lane&31, the four
-// consecutive columns 8*(v>>2) + 4*(lane>>5) + 0..3 of each 32x32 tile: SwiGLU in registers, 8-byte stores.
-template <int FM, int FN, int TM, int TN, bool SWIGLU>
-__device__ __forceinline__ void store_tile(const GemmArgs& p, const Tile& t, const f32x16 (&acc)[FM][FN], int wm,
-                                           int wn, int lane)
-{
-    unsigned short* out = reinterpret_cast<unsigned short*>(p.out) + (size_t)t.kslice * p.plane;
-#pragma unroll
-    for (int i = 0; i < FM; ++i) {
-        const int rl = wm * TM + i * 32 + (lane & 31);
-        if (rl >= t.nrows) continue;
-        unsigned short* orow = out + (long)(t.row0 + rl) * p.ldo;
-        if (SWIGLU) {
-#pragma unroll
-            for (int jp = 0; jp < FN / 2; ++jp) {
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const int col = t.n0 + (wn * (TN / 64) + jp) * 32 + 8 * q + 4 * (lane >> 5);
-                    float h[4];
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) h[e] = swiglu(acc[i][2 * jp][4 * q + e], acc[i][2 * jp + 1][4 * q + e]);
-                    if (col < p.N)
-                        *reinterpret_cast<uint2*>(orow + col) = make_uint2(pack_bf16(h[0], h[1]), pack_bf16(h[2], h[3]));
-                }
-            }
-        } else {
-#pragma unroll
-            for (int j = 0; j < FN; ++j) {
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const int col = t.n0 + wn * TN + j * 32 + 8 * q + 4 * (lane >> 5);
-                    if (col >= p.N) continue;
-                    if (p.out32)
-                        *reinterpret_cast<float4*>(p.out32 + (long)(t.row0 + rl) * p.ldo + col) =
-                            make_float4(acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]);
-                    else
-                        *reinterpret_cast<uint2*>(orow + col) =
-                            make_uint2(pack_f16(acc[i][j][4 * q], acc[i][j][4 * q + 1]),
-                                       pack_f16(acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]));
-                }
-            }
-        }
-    }
-}
-
-// The same tile written as whole row segments.  In the accumulator layout neighbouring lanes hold different
-// rows, so a store instruction of store_tile reaches memory as 64 separate 8-byte writes.  Here the wave tile
+// Epilogue of the small-batch kernels: the tile is written as whole row segments.  The MFMAs are issued as
+// (weights x rows), so a lane holds, for output row lane&31, the four consecutive columns 8*(v>>2) + 4*(lane>>5)
+// + 0..3 of each 32x32 tile: neighbouring lanes hold different rows, and stored straight from the accumulators a store
+// instruction reaches memory as 64 separate 8-byte writes.  Here the wave tile
 // (32 FM rows x 64 tile columns: 64 output columns of GEMM2 = one 128-byte line per row, 32 of GEMM1 = 64
 // bytes) goes through 4 KiB (2 KiB) per 32 rows of LDS private to the wave and comes back row-contiguous,
 // 16 bytes per lane.  `scratch`: 8 KiB of the stage buffers, which are free once every wave has left the k
 // loop (the caller's barrier).  8-byte slot s of row r lives at slot s ^ 2((r/2)&7) (rows of 64 bytes:
-// s ^ 2((r/4)&3)): writes and reads are free of bank conflicts.  fp32 output keeps the plain path.
+// s ^ 2((r/4)&3)): writes and reads are free of bank conflicts.
 template <int FM, int FN, int TM, int TN, bool SWIGLU>
 __device__ __forceinline__ void store_tile_lines(const GemmArgs& p, const Tile& t, const f32x16 (&acc)[FM][FN], int wm,
                                                  int wn, int lane, char* scratch)
 {
     static_assert(FN == 2 && FM <= 2, "wave tile of 64 tile columns, one scratch half per 32 rows");
-    if (p.out32) { store_tile<FM, FN, TM, TN, SWIGLU>(p, t, acc, wm, wn, lane); return; }
     unsigned short* out = reinterpret_cast<unsigned short*>(p.out) + (size_t)t.kslice * p.plane;
     const int r = lane & 31, hb = lane >> 5;
     constexpr int ROWB = SWIGLU ? 64 : 128;                     // bytes of a row in the scratch
@@ -1351,7 +1306,7 @@ hipError_t launch_ffn(const Dims& D, int u_lo, int u_hi, int Fdim, const TilePla
     g1.n_ntiles = 0;                            // set by the launcher from its tile width
     g1.group_m = tuning().group_m ? tuning().group_m : (plan.bm == 256 ? 8 : 4);
     g1.ksplit = 1; g1.plane = 0;
-    g1.out32 = nullptr; g1.partial = partial; g1.partial_cap = D.tail_blocks;
+    g1.partial = partial; g1.partial_cap = D.tail_blocks;
     g1.table = table;
     {
         ProfScope ps(MOE_STAGE_GEMM1, s);
@@ -1367,7 +1322,7 @@ hipError_t launch_ffn(const Dims& D, int u_lo, int u_hi, int Fdim, const TilePla
     g2.n_ntiles = 0;
     g2.group_m = g1.group_m;
     g2.ksplit = D.ksplit; g2.plane = D.y_plane;
-    g2.out32 = nullptr; g2.partial = partial; g2.partial_cap = D.tail_blocks;
+    g2.partial = partial; g2.partial_cap = D.tail_blocks;
     g2.table = table;
     {
         ProfScope ps(MOE_STAGE_GEMM2, s);
@@ -1375,32 +1330,6 @@ hipError_t launch_ffn(const Dims& D, int u_lo, int u_hi, int Fdim, const TilePla
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
-}
-
-// ------------------------------------------------------------------------------------------------
-// Plain GEMM for the distillation trainer: C[M][N] (fp32) = A[M][K] . B[N][K]^T, bf16 operands, through
-// the 64-row kernel with a one-unit tile table (table: 4 + 4 * ceil(M/64) ints of scratch).
-// ------------------------------------------------------------------------------------------------
-__global__ void __launch_bounds__(256) plain_table_kernel(int32_t* __restrict__ table, int M)
-{
-    const int n_mt = (M + 63) / 64;
-    const int i = blockIdx.x * 256 + threadIdx.x;
-    if (i == 0) { table[0] = n_mt; table[1] = 0; table[2] = 0; table[3] = 0; }
-    if (i < n_mt) reinterpret_cast<int4*>(table + 4)[i] = make_int4(0, i * 64, min(64, M - i * 64), 0);
-}
-
-hipError_t launch_plain_gemm(const bf16_t* A, const bf16_t* B, int M, int N, int K, float* C, int32_t* table,
-                             hipStream_t s)
-{
-    const int n_mt = ceil_div(M, 64);
-    plain_table_kernel<<<ceil_div(n_mt, 256), 256, 0, s>>>(table, M);
-    GemmArgs g;
-    g.A = A; g.lda = K; g.gather = nullptr; g.table = table;
-    g.wa0 = B; g.wa1 = g.wa2 = nullptr; g.wb0 = g.wb1 = g.wb2 = nullptr;
-    g.m = 1; g.G = 0; g.N = N; g.K = K;
-    g.out = nullptr; g.ldo = N; g.n_ntiles = 0; g.group_m = 4; g.ksplit = 1; g.plane = 0;
-    g.out32 = C; g.partial = nullptr; g.partial_cap = 0; 
-    return launch_small<64, 256, 1, 4, 64, 3, false>(g, n_mt, s);
 }
 
 hipError_t launch_combine(const Dims& D, const bf16_t* x, const bf16_t* Y, const int32_t* token_rows,

@@ -118,28 +118,29 @@ hipError_t launch_combine(const Dims& D, const bf16_t* x, const bf16_t* Y, const
                           const float* row_weight, bf16_t* out, hipStream_t s);
 
 // ---- united experts (united.hip) ----
-// C[M][N] fp32 = A[M][K] . B[N][K]^T (bf16 operands, K a multiple of 64, N a multiple of 64); table: scratch of
-// 4 + 4 * ceil(M/64) ints.
-hipError_t launch_plain_gemm(const bf16_t* A, const bf16_t* B, int M, int N, int K, float* C, int32_t* table,
-                             hipStream_t s);
 hipError_t launch_united_mean(const bf16_t* w, int m, int way, size_t n_elem, bf16_t* u, hipStream_t s);
-hipError_t launch_single_unit(int32_t* unit_cnt, int32_t* unit_off, int U, int u, int n, float* ones,
-                              hipStream_t s);
-hipError_t launch_zero_f32(float* p, int n, hipStream_t s);
-// loss[g] += scale * sum_{e<n} (a[e]-b[e])^2   (one block, deterministic)
-hipError_t launch_sqdiff_accumulate(const bf16_t* a, const bf16_t* b, size_t n, float scale, float* loss_g,
-                                    hipStream_t s);
+// Tile table of n_units0 units u0, u0+1, ... and n_units1 units u1, ..., each holding the n rows r*n .. r*n+n-1
+// (r: position in that list, + first_slot), and, if row_token is given, row_token[r*n + t] = t for `slots` such units.
+hipError_t launch_uniform_units(int u0, int n_units0, int u1, int n_units1, int first_slot, int n, int bm, int32_t* table,
+                                hipStream_t s);
+hipError_t launch_repeat_tokens(int32_t* row_token, int n, int slots, hipStream_t s);
+// part[0..blocks) (+)= per-block sums of (yu - yo_i)^2 over b teachers' rows of n elements each; if last,
+// *loss = scale * sum of part.  part: kSqdiffBlocks doubles at most.
+constexpr int kSqdiffBlocks = 512;
+hipError_t launch_sqdiff(const bf16_t* yu, const bf16_t* yo, int b, size_t n, int blocks, bool first, bool last, double scale,
+                         double* part, float* loss, hipStream_t s);
 
-// United-expert distillation (distill.hip).  buf: distill_buffer_bytes(n, d, F) bytes of device memory.
-size_t distill_buffer_bytes(int n, int d, int F);
-float* distill_tbar(void* buf, int n, int d, int F);      // [n][d] mean teacher output, filled by the caller
-float* distill_floor(void* buf, int n, int d, int F);     // [1] loss at the mean teacher output
+// United-expert distillation (distill.hip).  buf: distill_buffer_bytes of device memory for `groups` groups trained
+// side by side (distill_groups_at_once).
+hipError_t init_distill_kernels();
+int distill_groups_at_once(int n, int d, int F, int n_groups);
+size_t distill_buffer_bytes(int n, int d, int F, int groups);
 hipError_t launch_fill_f32(float* p, size_t n, float v, hipStream_t s);
-hipError_t launch_teacher_mean(const bf16_t* y_half, float* tbar, size_t n, float inv_k, hipStream_t s);
-hipError_t launch_teacher_spread(const bf16_t* y_half, const float* tbar, size_t n, float scale, float* floor_,
-                                 hipStream_t s);
-hipError_t distill_group(const bf16_t* x, int n, int d, int F, bf16_t* w1u, bf16_t* w3u, bf16_t* w2u, int steps,
-                         float lr, float* hist, void* buf, hipStream_t s);
+// FFN output rows (half) of b of the k teachers of group g, n*d elements apart; first / last: of the k
+hipError_t launch_teacher_stats(const bf16_t* y_half, int b, bool first, bool last, int k, int n, int d, int F, int g, void* buf,
+                                hipStream_t s);
+hipError_t distill_groups(const bf16_t* x, int n, int d, int F, int groups, bf16_t* w1u, bf16_t* w3u, bf16_t* w2u, int steps,
+                          float lr, float* hist, void* buf, hipStream_t s);
 
 // Probes (probe.hip): sustained rate of a pure MFMA loop on the caller's operand bits (operands: 64 KiB of
 // bf16, sink: 2 MiB), and of a read-only sweep over buf (sink: 4 bytes).  Both wait for the stream.
