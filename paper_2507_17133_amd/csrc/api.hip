@@ -14,7 +14,9 @@
 // that lives in the library's own device image.  In host code this name is only a handle for
 // hipGetSymbolAddress; the device address is looked up once per device in ensure_device_init.
 constexpr size_t kStaticScratchBytes = (size_t)8 << 20;
-static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
+// Behind it: room for the gate's logits (a larger batch goes through it in pieces).
+constexpr size_t kStaticLogitBytes = (size_t)2 << 20;
+static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes + kStaticLogitBytes];
 
 namespace bmoe {
 
@@ -410,7 +412,8 @@ moe_status moe_route(const moe_config* cfg, const void* x, int32_t T, const void
     none.n = 0; none.cap = 0;
     hipError_t e = launch_route(D, static_cast<const bf16_t*>(x), gate_w, gate_bias, threshold,
                                 use_full_brownout ? 1 : 0, R, at<bf16_t>(workspace, W.gate_split),
-                                at<int32_t>(workspace, W.seg_cnt), at<int32_t>(workspace, W.seg_off), none, s);
+                                at<int32_t>(workspace, W.seg_cnt), at<int32_t>(workspace, W.seg_off),
+                                at<void>(workspace, W.H), W.total - W.H, none, s);
     if (e != hipSuccess) return hip_fail(e, "moe_route");
     return MOE_OK;
 }
@@ -437,7 +440,8 @@ moe_status moe_route_static(const moe_config* cfg, const void* x, int32_t T, con
     // everything the kernels read from the scratch they write first in the same call (counters are cleared by
     // the first kernel), so what an earlier call left there does not matter
     e = launch_route(D, static_cast<const bf16_t*>(x), gate_w, gate_bias, threshold, use_full_brownout ? 1 : 0, R,
-                     at<bf16_t>(sp, W.gate_split), at<int32_t>(sp, W.seg_cnt), at<int32_t>(sp, W.seg_off), none, s);
+                     at<bf16_t>(sp, W.gate_split), at<int32_t>(sp, W.seg_cnt), at<int32_t>(sp, W.seg_off),
+                     at<void>(sp, kStaticScratchBytes), kStaticLogitBytes, none, s);
     if (e != hipSuccess) return hip_fail(e, "moe_route_static");
     return MOE_OK;
 }
@@ -501,7 +505,7 @@ moe_status moe_forward(const moe_config* cfg, const void* x, int32_t T, const vo
     if (!route) {
         e = launch_route(D, xb, gate_w, gate_bias, threshold, use_full_brownout ? 1 : 0, R,
                          at<bf16_t>(workspace, W.gate_split), at<int32_t>(workspace, W.seg_cnt),
-                         at<int32_t>(workspace, W.seg_off), jobs, s);
+                         at<int32_t>(workspace, W.seg_off), at<void>(workspace, W.H), W.total - W.H, jobs, s);
         if (e != hipSuccess) return hip_fail(e, "moe_forward/route");
     }
     const bool built = route == nullptr;

@@ -96,11 +96,12 @@ struct ProfScope {
 // ---- routing (route.hip) ----
 struct TileJobs;
 // gate: fp32 [m][d] (D.gate_format MOE_GATE_FP32; split into gate_split on the way) or the packed pieces
-// (MOE_GATE_PACKED; gate_split unused).  jobs: GEMM tile tables to build once the unit counts are known
-// (jobs.n == 0: none).
+// (MOE_GATE_PACKED; gate_split unused).  logits: scratch of the many-expert gate, at least 64 bytes per expert
+// (m_pad).  jobs: GEMM tile tables to build once the unit counts are known (jobs.n == 0: none).
 hipError_t launch_route(const Dims& D, const bf16_t* x, const void* gate, const float* gate_bias,
                         double threshold, int full_brownout, const RouteBufs& R, bf16_t* gate_split,
-                        int32_t* seg_cnt, int32_t* seg_off, const TileJobs& jobs, hipStream_t s);
+                        int32_t* seg_cnt, int32_t* seg_off, void* logits, size_t logit_bytes, const TileJobs& jobs,
+                        hipStream_t s);
 hipError_t launch_pack_gate(const float* gate_w, int m, int m_pad, int d, bf16_t* packed, hipStream_t s);
 
 // ---- FFN (ffn.hip) ----

@@ -63,10 +63,13 @@ __global__ void __launch_bounds__(256) prep_kernel(const float* __restrict__ gat
 // ------------------------------------------------------------------------------------------------
 struct GateArgs {
     const bf16_t* x; const unsigned short* split; const float* bias;
-    int T, d, m, m_pad, K, score_fn, n_stage;
+    int T, d, m, m_pad, K, score_fn;
     int32_t* topk_idx; float* topk_w; uint8_t* near_tie;
     int32_t* expert_cnt;   // the launch's expert counts, cleared beforehand (atomics); null for small batches,
                            // whose routing block counts the experts itself
+    int n_slice;           // 17 experts and more: slices of K, each leaving fp64 partial logits
+    void* logits;          // one slice: [T][m_pad] fp32, bias added; else [n_slice][T][m_pad] fp64
+    int32_t* clear_cnt;    // expert counters the logit kernel clears for the TopK launch behind it (or null)
 };
 
 // TopK(.,K) of one token by one wavefront: lane holds experts lane, lane+64, ...; K (+1 for the best
@@ -92,18 +95,14 @@ __device__ __forceinline__ void better_of_two(float& bv, int& bi, float ov, int 
     if (take) { bv = ov; bi = oi; }
 }
 
-__device__ __forceinline__ void topk_token(const GateArgs& p, const float* logit_row, int t, int lane, int* hist)
+__device__ __forceinline__ void topk_token(const GateArgs& p, const float (&v)[4], int t, int lane, int* hist)
 {
     const int K = p.K;
     const int n_pick = K < p.m ? K + 1 : K;    // one extra pick: the best loser, for the near-tie flag
-    float v[4];
     unsigned taken = 0;
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
-        const int e = lane + 64 * c;
-        v[c] = e < p.m ? logit_row[e] : 0.0f;
-        if (e >= p.m) taken |= 1u << c;
-    }
+    for (int c = 0; c < 4; ++c)
+        if (lane + 64 * c >= p.m) taken |= 1u << c;
     float my_v = 0.0f;
     int my_i = 0;
     for (int j = 0; j < n_pick; ++j) {
@@ -149,7 +148,7 @@ __device__ __forceinline__ void topk_token(const GateArgs& p, const float* logit
     if (lane < K) {
         p.topk_idx[(size_t)t * K + lane] = my_i;
         p.topk_w[(size_t)t * K + lane] = num / den;
-        atomicAdd(&hist[my_i], 1);
+        if (hist != nullptr) atomicAdd(&hist[my_i], 1);
     }
     if (lane == 0 && p.near_tie != nullptr) p.near_tie[t] = any_close != 0ull ? 1 : 0;
 }
@@ -160,20 +159,13 @@ __device__ __forceinline__ void topk_token(const GateArgs& p, const float* logit
 // have been picked hold -infinity (logits are finite, and a row always has an expert left to pick), so a round
 // is a branch-free maximum over NC registers (first of equal values: the lower id) and four rotations.
 // Needs K + 1 <= 16 (lane j of the row keeps the j-th winner).
-// tl: this row's token inside the block's logit array, t: its global index, valid: whether it exists.
+// v[c]: the logit of expert r + 16 c (-infinity: no such expert), t: the row's token, valid: whether it exists.
 template <int NC>
-__device__ __forceinline__ void topk_rows(const GateArgs& p, const float* logit, int tl, int t, bool valid, int lane, int* hist)
+__device__ __forceinline__ void topk_rows(const GateArgs& p, float (&v)[NC], int t, bool valid, int lane, int* hist)
 {
     const int K = p.K, r = lane & 15;
     const int n_pick = K < p.m ? K + 1 : K;
-    const float* logit_row = logit + tl * p.m_pad;
     const float none = -__builtin_inff();
-    float v[NC];
-#pragma unroll
-    for (int c = 0; c < NC; ++c) {
-        const int e = r + 16 * c;
-        v[c] = e < p.m ? logit_row[e] : none;
-    }
     float my_v = 0.0f;
     int my_i = 0;
     for (int j = 0; j < n_pick; ++j) {
@@ -208,7 +200,7 @@ __device__ __forceinline__ void topk_rows(const GateArgs& p, const float* logit,
         if (r < K) {
             p.topk_idx[(size_t)t * K + r] = my_i;
             p.topk_w[(size_t)t * K + r] = num / den;
-            atomicAdd(&hist[my_i], 1);
+            if (hist != nullptr) atomicAdd(&hist[my_i], 1);
         }
         if (r == 0 && p.near_tie != nullptr) p.near_tie[t] = ((any_close >> (lane & 48)) & 0xFFFFull) != 0ull ? 1 : 0;
     }
@@ -302,7 +294,8 @@ __global__ void __launch_bounds__(512) gate_few_kernel(GateArgs p)
     if (wave < 4) {                                       // four tokens per wavefront (K + 1 <= m_pad = 16 picks)
         const int tl = wave * 4 + (lane >> 4);
         const bool valid = t0 + tl < p.T;
-        topk_rows<1>(p, logit, valid ? tl : wave * 4, t0 + tl, valid && t0 + wave * 4 < p.T, lane, hist);
+        float v[1] = {(lane & 15) < p.m ? logit[tl * 16 + (lane & 15)] : -__builtin_inff()};
+        topk_rows<1>(p, v, t0 + tl, valid, lane, hist);
     }
     __syncthreads();
     if (p.expert_cnt != nullptr && tid < p.m && hist[tid] > 0) atomicAdd(&p.expert_cnt[tid], hist[tid]);
@@ -387,7 +380,10 @@ __global__ void __launch_bounds__(256) gate_small_kernel(GateArgs p, const float
         }
     }
     __syncthreads();
-    if (wave < TPB && t0 + wave < p.T) topk_token(p, logit[wave], t0 + wave, lane, hist);
+    if (wave < TPB && t0 + wave < p.T) {
+        const float v[4] = {lane < p.m ? logit[wave][lane & 15] : 0.0f, 0.0f, 0.0f, 0.0f};
+        topk_token(p, v, t0 + wave, lane, hist);
+    }
     if (p.expert_cnt != nullptr) {                        // large batches: the launch's counts (cleared beforehand)
         __syncthreads();
         if (tid < p.m && hist[tid] > 0) atomicAdd(&p.expert_cnt[tid], hist[tid]);
@@ -395,189 +391,210 @@ __global__ void __launch_bounds__(256) gate_small_kernel(GateArgs p, const float
 }
 
 // ------------------------------------------------------------------------------------------------
-// gate for many experts and many tokens: one block = 16*TG tokens x all experts, 2*TG wavefronts
-// (token group tg = wave % TG, expert half eh = wave / TG).  The three weight pieces of a 32-wide k
-// step ([3][m_pad] rows of 64 bytes) are staged in LDS by global_load_lds_dwordx4 (3 stages) and read
-// together with the block's x rows and read by every wave, so the split gate matrix is fetched once per
-// 16*TG tokens instead of once per 16.
+// gate with more than 16 experts: logits as a tiled GEMM cut over (token tiles, expert tiles of 64, slices of K).
+// One block = 16 MT WM tokens x 64 experts x its slice, four wavefronts as WM x WN, a wave multiplies MT token
+// tiles by NE expert tiles of 16.  A stage holds 64 k (rows of 128 bytes = whole lines) of the block's 3 x 64 piece
+// rows and its x rows, brought in by direct global->LDS loads (8 rows per wave instruction); 16-byte chunk c of row
+// r sits in slot c ^ ((r/2)&7) (conflict-free ds_read_b128).  After every 64 k the fp32 accumulators are folded into
+// fp64 sums; with several slices those leave as fp64 partial logits, which the TopK launch adds in slice order.
+// What bounds it: the bytes a CU pulls into LDS (about 55 a clock), so tokens AND experts are cut over blocks (a
+// block that holds every expert pulls the whole gate matrix) and K as well while the chip is not full.  Against one
+// launch with all experts in a block and TopK behind them, logits + TopK launch: 28.7 -> 4.4 + 8.0 us (1 token, 128
+// experts, d 2048), 274 -> 23 + 14 (1021, 256, d 7168), 48.8 -> 13.4 + 9.9 (5003, 60, d 2048), 49.6 -> 26.7 + 15.5
+// (8192, 128, d 2048), 350 -> 207 + 19 (16384, 256, d 7168: 0.87 PFLOP/s on the three pieces, bound by LDS reads and
+// the fp64 folds).
 // ------------------------------------------------------------------------------------------------
-// s_waitcnt vmcnt(n) for a run-time n (the instruction takes an immediate): waits for at most the largest
-// listed value <= n, which is never too lax.
-__device__ __forceinline__ void wait_vmcnt_at_most(int n)
-{
-    if (n >= 48) __builtin_amdgcn_s_waitcnt(0xCF70);        // vmcnt 48: low four bits 0, bits 15:14 = 3
-    else if (n >= 32) __builtin_amdgcn_s_waitcnt(0x8F70);
-    else if (n >= 24) __builtin_amdgcn_s_waitcnt(0x4F78);
-    else if (n >= 20) __builtin_amdgcn_s_waitcnt(0x4F74);
-    else if (n >= 16) __builtin_amdgcn_s_waitcnt(0x4F70);
-    else if (n >= 12) __builtin_amdgcn_s_waitcnt(0x0F7C);
-    else if (n >= 9) __builtin_amdgcn_s_waitcnt(0x0F79);
-    else if (n >= 8) __builtin_amdgcn_s_waitcnt(0x0F78);
-    else if (n >= 6) __builtin_amdgcn_s_waitcnt(0x0F76);
-    else if (n >= 4) __builtin_amdgcn_s_waitcnt(0x0F74);
-    else if (n >= 3) __builtin_amdgcn_s_waitcnt(0x0F73);
-    else if (n >= 2) __builtin_amdgcn_s_waitcnt(0x0F72);
-    else if (n >= 1) __builtin_amdgcn_s_waitcnt(0x0F71);
-    else __builtin_amdgcn_s_waitcnt(0x0F70);
-}
+// How a batch is cut: 16-token blocks up to kGateSmallTokens tokens x blocks of experts (64-token blocks leave the
+// chip idle there; at 1021 x 256 experts they are ahead, 31 us against 56, K cut alike), 128-token blocks from
+// kGateLargeTokens on (half the gate bytes per token; the 64-token blocks already fill the chip: 252 -> 207 us at 16384
+// x 256), and K in up to kGateSlices slices until two blocks per CU are there (one per CU: 36 us instead of 26 at 8192
+// x 128; 16 slices: no faster, and TopK reads twice the partial sums).
+constexpr int kGateExperts = 64;       // experts of a block
+constexpr int kGateSmallTokens = 2048, kGateLargeTokens = 32768, kGateBlocks = 512, kGateSlices = 8;
+template <int MT, int WM>
+constexpr int gate_rows() { return 3 * kGateExperts + 16 * MT * WM; }
 
-template <int TG, int NTH, int KB, int MT, int EG>
-__global__ void __launch_bounds__((TG / MT) * EG * 64) gate_tiled_kernel(GateArgs p)
+template <int MT, int NE, int WM, int WN, int NST>
+__global__ void __launch_bounds__(256) gate_logits_kernel(GateArgs p)
 {
-    // A wave multiplies MT token tiles (16 tokens each) by NTH expert tiles: TG / MT groups of token tiles x
-    // EG groups of NTH expert tiles (EG NTH >= expert tiles).  MT = 2 halves the B fragments read from LDS per MFMA.
-    static_assert(TG % MT == 0, "token tiles per wave");
-    // KB = k elements per stage: 64 (rows of 128 bytes, whole cache lines: what bounds this kernel is the number
-    // of line requests a CU keeps in flight, not bytes) where three such stages fit the LDS, else 32
-    constexpr int NWV = (TG / MT) * EG;                 // waves: token-tile groups x expert groups
-    constexpr int RB = KB * 2, CPR = RB / 16, WR = 256 / RB, RPL = 1024 / RB, NSL = KB / 32;
-    const int NST = p.n_stage;                          // LDS stages: as many as fit, at most 8
+    static_assert(WM * WN == 4 && NE * WN * 16 == kGateExperts, "four waves over 64 experts");
+    constexpr int RB = 128, BE = kGateExperts, W_ROWS = 3 * BE, BM = 16 * MT * WM;
+    constexpr int GROUPS = gate_rows<MT, WM>() / 8;
+    constexpr int LD = (GROUPS + 3) / 4;                 // loads of a wave and stage (the last ones may repeat a group)
+    constexpr int STAGE = GROUPS * 1024;
     extern __shared__ __attribute__((aligned(16))) char gsm[];
-    __shared__ int hist[kMaxExperts];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int tg = (wave % (TG / MT)) * MT, eh = wave / (TG / MT);   // first token tile, expert group
-    const int t0 = blockIdx.x * (16 * TG);
-    const int n_tiles = p.m_pad >> 4;
-    const int w_rows = 3 * p.m_pad;                     // LDS rows of one stage: [piece][expert], then the x rows
-    const int rows = w_rows + 16 * TG;
-    const int groups = rows / RPL;                      // RPL rows (1 KiB) per wave-wide load
-    const int stage_bytes = rows * RB;
-    for (int i = tid; i < p.m_pad; i += NWV * 64) hist[i] = 0;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int n_tb = (p.T + BM - 1) / BM, n_eb = (p.m_pad + BE - 1) / BE;
+    const int tb = blockIdx.x % n_tb, rest = blockIdx.x / n_tb;
+    const int e0 = (rest % n_eb) * BE, slice = rest / n_eb, t0 = tb * BM;
+    if (p.clear_cnt != nullptr && blockIdx.x == 0 && tid < p.m) p.clear_cnt[tid] = 0;
+    const int all = p.d >> 6, per = (all + p.n_slice - 1) / p.n_slice;
+    const int k_lo = slice * per, nk = min(all, k_lo + per) - k_lo;   // no slice is empty (the launcher's choice)
 
-    // loader: wave w moves row groups w, w+NWV, ...; lane -> row lane/CPR, 16-byte slot lane%CPR holding
-    // chunk (lane%CPR) ^ ((row/WR)&(CPR-1))  (conflict-free ds_read_b128 on the 64-bank LDS)
-    const int ksteps = p.d / KB;
-    // the source address of every load of a stage is fixed up to the k offset: computed once, not per step
-    constexpr int MAXM = KB == 64 ? 128 : kMaxExperts;  // the launcher takes KB = 64 for at most 128 experts
-    constexpr int MAXS = (3 * MAXM + 16 * TG + RPL * NWV - 1) / (RPL * NWV);
-    const int wave_s = __builtin_amdgcn_readfirstlane(wave);
-    const unsigned short* srcp[MAXS];
+    const unsigned short* srcp[LD];
+    int dsto[LD];
 #pragma unroll
-    for (int i = 0; i < MAXS; ++i) {
-        const int row = min((wave + i * NWV) * RPL + lane / CPR, rows - 1);
-        const int chunk = (lane % CPR) ^ ((row / WR) & (CPR - 1));
-        const unsigned short* src;
-        if (row < w_rows) src = p.split + (size_t)row * p.d;
-        else src = reinterpret_cast<const unsigned short*>(p.x) + (size_t)min(t0 + row - w_rows, p.T - 1) * p.d;
-        srcp[i] = src + chunk * 8;
+    for (int i = 0; i < LD; ++i) {
+        const int g = min(wave + 4 * i, GROUPS - 1);
+        const int row = g * 8 + (lane >> 3);
+        const int chunk = (lane & 7) ^ ((row >> 1) & 7);
+        // experts past the padded matrix and tokens past the batch repeat the last row (never used)
+        const unsigned short* src =
+            row < W_ROWS ? p.split + ((size_t)(row / BE) * p.m_pad + min(e0 + row % BE, p.m_pad - 1)) * p.d
+                         : reinterpret_cast<const unsigned short*>(p.x) + (size_t)min(t0 + row - W_ROWS, p.T - 1) * p.d;
+        srcp[i] = src + chunk * 8 + (size_t)k_lo * 64;
+        dsto[i] = g * 1024;
     }
-    auto issue = [&](int ks, int buf) {
-        char* dst = gsm + buf * stage_bytes + wave_s * 1024;
+    auto issue = [&](int kt, int buf) {
 #pragma unroll
-        for (int i = 0; i < MAXS; ++i)
-            if (wave_s + i * NWV < groups)
-                __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(srcp[i] + ks * KB),
-                                                 (__attribute__((address_space(3))) void*)(dst + i * NWV * 1024), 16, 0, 0);
+        for (int i = 0; i < LD; ++i)
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(srcp[i] + kt * 64),
+                                             (__attribute__((address_space(3))) void*)(gsm + buf * STAGE + dsto[i]), 16, 0, 0);
     };
-
-    double sum[MT][NTH][4];
-    f32x4 acc[MT][NTH];
-    bool tile_ok[NTH];
-    int boff[NTH];
-    // the swizzle term of a row depends on the lane only: expert tiles start at multiples of 16 rows, the x
-    // rows at 3 * m_pad + 16 * tg, and 16 / WR is a multiple of CPR
-    const int swz = ((lane & 15) / WR) & (CPR - 1);
+    const int wm = wave / WN, wn = wave % WN;
+    double sum[MT][NE][4];
 #pragma unroll
-    for (int nt = 0; nt < NTH; ++nt) {
-        const int tile = eh * NTH + nt;
-        tile_ok[nt] = tile < n_tiles;
-        boff[nt] = ((tile_ok[nt] ? tile : 0) * 16 + (lane & 15)) * RB;
+    for (int i = 0; i < MT; ++i)
 #pragma unroll
-        for (int mt = 0; mt < MT; ++mt) {
-            acc[mt][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int j = 0; j < NE; ++j)
 #pragma unroll
-            for (int v = 0; v < 4; ++v) sum[mt][nt][v] = 0.0;
-        }
-    }
-    const int aoff = (w_rows + tg * 16 + (lane & 15)) * RB;
-    // All loads of the loop go to LDS and complete in order per wave: at the top of step ks the loads of
-    // stage ks are older than those of the later stages, which may stay in flight.
-    const int young = groups / NWV;                     // loads of one stage every wave issues at least
+            for (int v = 0; v < 4; ++v) sum[i][j][v] = 0.0;
+    const int swz = ((lane & 15) >> 1) & 7;
+    const int aoff = (W_ROWS + wm * MT * 16 + (lane & 15)) * RB;
+    const int boff = (wn * NE * 16 + (lane & 15)) * RB;
+#pragma unroll
     for (int q = 0; q < NST - 1; ++q)
-        if (q < ksteps) issue(q, q);
-    int buf = 0, buf_ld = NST - 1;                      // stage read at step ks = ks mod NST; stage refilled = (ks-1) mod NST
-    for (int ks = 0; ks < ksteps; ++ks) {
-        // stages ks+1 .. ks+NST-2 (those that exist) may stay in flight: at least `young` loads each
-        wait_vmcnt_at_most(min(NST - 2, ksteps - 1 - ks) * young);
+        if (q < nk) issue(q, q);
+    int buf = 0;
+    for (int kt = 0; kt < nk; ++kt) {
+        // a wave's loads complete in order: stage kt has landed once only those of stages kt+1 .. kt+NST-2 are out
+        if (kt + NST - 2 < nk) __builtin_amdgcn_s_waitcnt((((NST - 2) * LD) & 0xF) | ((((NST - 2) * LD) >> 4) << 14) | 0x0F70);
+        else __builtin_amdgcn_s_waitcnt(0x0F70);
         asm volatile("" ::: "memory");
-        __builtin_amdgcn_s_barrier();                   // stage ks is in LDS for everyone; stage ks-1 is free
+        __builtin_amdgcn_s_barrier();                    // stage kt is in LDS for everyone; stage kt-1 is free
         asm volatile("" ::: "memory");
-        if (ks + NST - 1 < ksteps) issue(ks + NST - 1, buf_ld);
-        const char* St = gsm + buf * stage_bytes;
-        buf_ld = buf;
+        if (kt + NST - 1 < nk) issue(kt + NST - 1, buf == 0 ? NST - 1 : buf - 1);
+        const char* St = gsm + buf * STAGE;
         buf = buf + 1 == NST ? 0 : buf + 1;
+        f32x4 acc[MT][NE];
 #pragma unroll
-        for (int sl = 0; sl < NSL; ++sl) {              // 32-wide k slices of the stage
+        for (int i = 0; i < MT; ++i)
+#pragma unroll
+            for (int j = 0; j < NE; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int sl = 0; sl < 2; ++sl) {
             const int coff = ((sl * 4 + (lane >> 4)) ^ swz) << 4;
-            bf16x8 a[MT];
+            bf16x8 a[MT], b[3][NE];
 #pragma unroll
-            for (int mt = 0; mt < MT; ++mt) a[mt] = *reinterpret_cast<const bf16x8*>(St + aoff + mt * 16 * RB + coff);
-            // low piece first in every expert tile (the sum of a tile is taken in that order); piece by piece
-            // across the tiles, so that consecutive MFMAs do not wait for each other's result
-            bf16x8 b[3][NTH];
+            for (int i = 0; i < MT; ++i) a[i] = *reinterpret_cast<const bf16x8*>(St + aoff + i * 16 * RB + coff);
 #pragma unroll
             for (int pz = 0; pz < 3; ++pz)
 #pragma unroll
-                for (int nt = 0; nt < NTH; ++nt)
-                    b[pz][nt] = *reinterpret_cast<const bf16x8*>(St + pz * p.m_pad * RB + boff[nt] + coff);
+                for (int j = 0; j < NE; ++j)
+                    b[pz][j] = *reinterpret_cast<const bf16x8*>(St + boff + (pz * BE + j * 16) * RB + coff);
+            // low piece first (the sum of a logit is taken in that order); consecutive MFMAs are independent
 #pragma unroll
             for (int pz = 2; pz >= 0; --pz)
 #pragma unroll
-                for (int mt = 0; mt < MT; ++mt)
+                for (int i = 0; i < MT; ++i)
 #pragma unroll
-                    for (int nt = 0; nt < NTH; ++nt)
-                        acc[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[mt], b[pz][nt], acc[mt][nt], 0, 0, 0);
+                    for (int j = 0; j < NE; ++j)
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], b[pz][j], acc[i][j], 0, 0, 0);
         }
-        // into the fp64 sums after every 64 k (d is a multiple of 64)
-        if (KB == 64 || (ks & 1) == 1 || ks + 1 == ksteps) {
 #pragma unroll
-            for (int mt = 0; mt < MT; ++mt)
+        for (int i = 0; i < MT; ++i)
 #pragma unroll
-                for (int nt = 0; nt < NTH; ++nt) {
+            for (int j = 0; j < NE; ++j)
 #pragma unroll
-                    for (int v = 0; v < 4; ++v) sum[mt][nt][v] += (double)acc[mt][nt][v];
-                    acc[mt][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
-                }
-        }
+                for (int v = 0; v < 4; ++v) sum[i][j][v] += (double)acc[i][j][v];
     }
-    __syncthreads();                                    // every wave is done with the stages: reuse as logits
-    float* logit = reinterpret_cast<float*>(gsm);       // [16*TG][m_pad]
+    // MFMA 16x16 result layout: lane holds column (lane&15) = expert, rows 4*(lane>>4)+v = tokens
 #pragma unroll
-    for (int nt = 0; nt < NTH; ++nt) {
-        if (!tile_ok[nt]) continue;
-        const int e = (eh * NTH + nt) * 16 + (lane & 15);
+    for (int j = 0; j < NE; ++j) {
+        const int e = e0 + (wn * NE + j) * 16 + (lane & 15);
+        if (e >= p.m_pad) continue;
+        const double bias = p.bias != nullptr && e < p.m ? (double)p.bias[e] : 0.0;
 #pragma unroll
-        for (int mt = 0; mt < MT; ++mt)
+        for (int i = 0; i < MT; ++i)
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
-                const int tok = (tg + mt) * 16 + 4 * (lane >> 4) + v;
-                double s = sum[mt][nt][v];
-                if (p.bias != nullptr && e < p.m) s += (double)p.bias[e];
-                logit[tok * p.m_pad + e] = (float)s;
+                const int t = t0 + (wm * MT + i) * 16 + 4 * (lane >> 4) + v;
+                if (t >= p.T) continue;
+                if (p.n_slice == 1) static_cast<float*>(p.logits)[(size_t)t * p.m_pad + e] = (float)(sum[i][j][v] + bias);
+                else static_cast<double*>(p.logits)[((size_t)slice * p.T + t) * p.m_pad + e] = sum[i][j][v];
             }
     }
-    __syncthreads();
-    if (p.K + 1 <= 16) {
-        // four tokens per wavefront at a time
-        for (int tok = wave * 4; tok < 16 * TG; tok += NWV * 4) {
-            const int tl = tok + (lane >> 4);
-            const bool valid = t0 + tl < p.T;
-            const int tls = valid ? tl : tok;
-            const bool ok = valid && t0 + tok < p.T;
-            if (n_tiles <= 4) topk_rows<4>(p, logit, tls, t0 + tl, ok, lane, hist);
-            else if (n_tiles <= 8) topk_rows<8>(p, logit, tls, t0 + tl, ok, lane, hist);
-            else topk_rows<16>(p, logit, tls, t0 + tl, ok, lane, hist);
-        }
+}
+
+// Logits of token t for experts e0 + STRIDE c (past the m experts: `none`), the partial sums of the slices added in order,
+// loaded QB slices at a time.
+template <int NC, int STRIDE, int QB>
+__device__ __forceinline__ void read_logits(const GateArgs& p, int t, int e0, float none, float (&v)[NC])
+{
+    if (p.n_slice == 1) {
+        const float* l = static_cast<const float*>(p.logits) + (size_t)t * p.m_pad;
+#pragma unroll
+        for (int c = 0; c < NC; ++c) v[c] = e0 + STRIDE * c < p.m ? l[e0 + STRIDE * c] : none;
+        return;
+    }
+    const double* l = static_cast<const double*>(p.logits) + (size_t)t * p.m_pad;
+    const size_t plane = (size_t)p.T * p.m_pad;
+    double s[NC];
+    int e[NC];
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+        s[c] = 0.0;
+        e[c] = min(e0 + STRIDE * c, p.m_pad - 1);            // loads without a branch: all of a batch in flight
+    }
+    for (int q0 = 0; q0 < p.n_slice; q0 += QB) {
+        double x[QB][NC];
+#pragma unroll
+        for (int q = 0; q < QB; ++q)
+#pragma unroll
+            for (int c = 0; c < NC; ++c) x[q][c] = l[min(q0 + q, p.n_slice - 1) * plane + e[c]];
+#pragma unroll
+        for (int q = 0; q < QB; ++q)
+#pragma unroll
+            for (int c = 0; c < NC; ++c) s[c] += q0 + q < p.n_slice ? x[q][c] : 0.0;
+    }
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+        if (p.bias != nullptr) s[c] += (double)p.bias[min(e[c], p.m - 1)];
+        v[c] = e0 + STRIDE * c < p.m ? (float)s[c] : none;
+    }
+}
+
+// TopK behind the logit kernel: 16 lanes per token (NC > 0, K + 1 <= 16 picks), else a wavefront per token.
+template <int NC, int THREADS>
+__global__ void __launch_bounds__(THREADS) gate_topk_kernel(GateArgs p)
+{
+    constexpr int QB = THREADS == 1024 ? 1 : NC > 8 ? 4 : THREADS == 256 ? 8 : 4;
+    __shared__ int hist[kMaxExperts];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const bool count = p.expert_cnt != nullptr;
+    if (count) {
+        for (int i = tid; i < p.m; i += blockDim.x) hist[i] = 0;
+        __syncthreads();
+    }
+    if constexpr (NC > 0) {
+        const int t = (int)((blockIdx.x * blockDim.x + tid) >> 4);
+        float v[NC];
+        read_logits<NC, 16, QB>(p, min(t, p.T - 1), lane & 15, -__builtin_inff(), v);
+        topk_rows<NC>(p, v, t, t < p.T, lane, count ? hist : nullptr);
     } else {
-        for (int tok = wave; tok < 16 * TG; tok += NWV) {
-            if (t0 + tok >= p.T) break;
-            topk_token(p, logit + tok * p.m_pad, t0 + tok, lane, hist);
+        const int t = (int)((blockIdx.x * blockDim.x + tid) >> 6);
+        if (t < p.T) {
+            float v[4];
+            read_logits<4, 64, QB>(p, t, lane, 0.0f, v);
+            topk_token(p, v, t, lane, count ? hist : nullptr);
         }
     }
-    __syncthreads();
-    if (p.expert_cnt != nullptr)                        // small batches: the routing block counts the experts itself
-        for (int i = tid; i < p.m; i += NWV * 64)
+    if (count) {
+        __syncthreads();
+        for (int i = tid; i < p.m; i += blockDim.x)
             if (hist[i] > 0) atomicAdd(&p.expert_cnt[i], hist[i]);
+    }
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -858,22 +875,23 @@ __global__ void __launch_bounds__(1024) route_small_kernel(RowArgs p)
 }
 
 constexpr int kGateFewLds = 3 * 4 * 64 * 128;          // three stages of four 64-row pieces (gate_few_kernel)
-constexpr int kGateLds = 160 * 1024;                    // LDS of one CU (the tiled gate also holds a 1 KiB histogram)
-
-#define BMOE_GATE_TILED_ALL(X) \
-    X(4, 2, 64, 1, 2) X(4, 2, 32, 1, 2) X(4, 4, 64, 1, 2) X(4, 1, 32, 2, 8) X(4, 2, 32, 2, 8) \
-    X(2, 2, 64, 1, 2) X(2, 2, 32, 1, 2) X(2, 1, 64, 2, 8) X(2, 4, 32, 1, 2) X(2, 2, 32, 2, 8) \
-    X(1, 1, 64, 1, 8) X(1, 2, 32, 1, 8) X(1, 1, 64, 1, 4)
+// The block shapes of the logit kernel: 16 tokens with three stages, 64 and 128 tokens with two (two blocks fit a CU).
+constexpr int kGateLds16 = 3 * gate_rows<1, 1>() * 128;
+constexpr int kGateLds64 = 2 * gate_rows<2, 2>() * 128;
+constexpr int kGateLds128 = 2 * gate_rows<4, 2>() * 128;
 
 hipError_t init_route_kernels()
 {
     hipError_t e;
-#define BMOE_SET(TG_, NTH_, KB_, MT_, EG_)                                                                  \
-    e = hipFuncSetAttribute(reinterpret_cast<const void*>(gate_tiled_kernel<TG_, NTH_, KB_, MT_, EG_>),  \
-                            hipFuncAttributeMaxDynamicSharedMemorySize, kGateLds - 1024);                \
+    e = hipFuncSetAttribute(reinterpret_cast<const void*>(gate_logits_kernel<1, 1, 1, 4, 3>),
+                            hipFuncAttributeMaxDynamicSharedMemorySize, kGateLds16);
     if (e != hipSuccess) return e;
-    BMOE_GATE_TILED_ALL(BMOE_SET)
-#undef BMOE_SET
+    e = hipFuncSetAttribute(reinterpret_cast<const void*>(gate_logits_kernel<2, 2, 2, 2, 2>),
+                            hipFuncAttributeMaxDynamicSharedMemorySize, kGateLds64);
+    if (e != hipSuccess) return e;
+    e = hipFuncSetAttribute(reinterpret_cast<const void*>(gate_logits_kernel<4, 2, 2, 2, 2>),
+                            hipFuncAttributeMaxDynamicSharedMemorySize, kGateLds128);
+    if (e != hipSuccess) return e;
     e = hipFuncSetAttribute(reinterpret_cast<const void*>(gate_few_kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
                             kGateFewLds);
     if (e != hipSuccess) return e;
@@ -891,9 +909,53 @@ hipError_t launch_pack_gate(const float* gate_w, int m, int m_pad, int d, bf16_t
     return hipGetLastError();
 }
 
+template <int THREADS>
+static void launch_topk(const GateArgs& p, hipStream_t s)
+{
+    const int blocks = ceil_div(p.T, THREADS / 16);
+    if (p.K + 1 > 16) gate_topk_kernel<0, THREADS><<<ceil_div(p.T, THREADS / 64), THREADS, 0, s>>>(p);
+    else if (p.m_pad <= 64) gate_topk_kernel<4, THREADS><<<blocks, THREADS, 0, s>>>(p);
+    else if (p.m_pad <= 128) gate_topk_kernel<8, THREADS><<<blocks, THREADS, 0, s>>>(p);
+    else gate_topk_kernel<16, THREADS><<<blocks, THREADS, 0, s>>>(p);
+}
+
+// Logits and TopK of a batch with more than 16 experts.  `scratch` holds the logits; a batch whose logits it cannot
+// hold goes through it in pieces.
+static hipError_t launch_gate(GateArgs g, void* scratch, size_t bytes, hipStream_t s)
+{
+    const int T = g.T, n_eb = ceil_div(g.m_pad, kGateExperts), ksteps = g.d / 64;
+    const int64_t most = (int64_t)(bytes / ((size_t)g.m_pad * 4));
+    const int chunk = (int)std::min<int64_t>(T, most >= 64 ? most / 64 * 64 : std::max<int64_t>(most, 1));
+    g.logits = scratch;
+    for (int c0 = 0; c0 < T; c0 += chunk) {
+        GateArgs p = g;
+        p.T = std::min(chunk, T - c0);
+        p.x = g.x + (size_t)c0 * g.d;
+        p.topk_idx = g.topk_idx + (size_t)c0 * g.K;
+        p.topk_w = g.topk_w + (size_t)c0 * g.K;
+        if (g.near_tie != nullptr) p.near_tie = g.near_tie + c0;
+        if (c0 > 0) p.clear_cnt = nullptr;
+        const bool small = (int64_t)p.T * n_eb <= kGateSmallTokens;
+        const bool large = (int64_t)p.T * n_eb >= kGateLargeTokens;
+        const int tiles = ceil_div(p.T, small ? 16 : large ? 128 : 64) * n_eb;
+        int sl = std::max(1, std::min({kGateBlocks / tiles, kGateSlices, ksteps / 2}));
+        sl = (int)std::min<size_t>(sl, bytes / ((size_t)p.T * p.m_pad * 8));
+        sl = sl < 2 ? 1 : ceil_div(ksteps, ceil_div(ksteps, sl));        // no empty slice
+        p.n_slice = sl;
+        if (small) gate_logits_kernel<1, 1, 1, 4, 3><<<tiles * sl, 256, kGateLds16, s>>>(p);
+        else if (large) gate_logits_kernel<4, 2, 2, 2, 2><<<tiles * sl, 256, kGateLds128, s>>>(p);
+        else gate_logits_kernel<2, 2, 2, 2, 2><<<tiles * sl, 256, kGateLds64, s>>>(p);
+        if (p.expert_cnt == nullptr) launch_topk<256>(p, s);
+        else if (p.n_slice > 1) launch_topk<512>(p, s);     // fewer, larger blocks: each flushes a histogram
+        else launch_topk<1024>(p, s);                       // (partial logits need the registers, logits do not)
+    }
+    return hipGetLastError();
+}
+
 hipError_t launch_route(const Dims& D, const bf16_t* x, const void* gate, const float* gate_bias,
                         double threshold, int full_brownout, const RouteBufs& R, bf16_t* gate_split,
-                        int32_t* seg_cnt, int32_t* seg_off, const TileJobs& jobs, hipStream_t s)
+                        int32_t* seg_cnt, int32_t* seg_off, void* logits, size_t logit_bytes, const TileJobs& jobs,
+                        hipStream_t s)
 {
     hipError_t e = ensure_device_init(nullptr);
     if (e != hipSuccess) return e;
@@ -904,9 +966,9 @@ hipError_t launch_route(const Dims& D, const bf16_t* x, const void* gate, const 
     const bool few_fmt = D.m_pad == 16;
     const bool few = few_fmt && D.T <= kFewExpertsTokens;
     // Preparation: cut an fp32 gate matrix into its pieces (only the MFMA gates need them) and clear the expert
-    // counters (only large batches use them).  A small batch with a packed gate or few experts needs neither.
+    // counters (only large batches use them; the logit kernel of the many-expert gate clears them itself).
     const bool split = !few && (!packed || few_fmt);
-    if (split || !small) {
+    if (split || (few_fmt && !small)) {
         ProfScope ps(MOE_STAGE_PREP, s);
         const size_t n = split ? (size_t)D.m_pad * D.d : (size_t)D.m;
         const int blocks = (int)std::min<size_t>((n + 255) / 256, 2048);
@@ -920,48 +982,19 @@ hipError_t launch_route(const Dims& D, const bf16_t* x, const void* gate, const 
         g.x = x;
         g.split = split ? reinterpret_cast<const unsigned short*>(gate_split) : static_cast<const unsigned short*>(gate);
         g.bias = gate_bias;
-        g.T = D.T; g.d = D.d; g.m = D.m; g.m_pad = D.m_pad; g.K = D.K; g.score_fn = D.score_fn; g.n_stage = 3;
-        const int n_tiles = D.m_pad / 16;
+        g.T = D.T; g.d = D.d; g.m = D.m; g.m_pad = D.m_pad; g.K = D.K; g.score_fn = D.score_fn;
         g.topk_idx = R.topk_idx; g.topk_w = R.topk_w; g.near_tie = R.near_tie;
         g.expert_cnt = small ? nullptr : R.expert_cnt;
-        const int half_tiles = ceil_div(n_tiles, 2);
-        // 32 experts and more: LDS-staged variant, with wider token tiles once the batch fills the CUs with them
-        const int tgw = n_tiles < 2 ? 0 : (n_tiles >= 4 && D.T >= 64 * 192 ? 4 : (n_tiles >= 4 && D.T >= 32 * 192 ? 2 : 1));
+        g.n_slice = 1; g.logits = nullptr; g.clear_cnt = few_fmt ? nullptr : g.expert_cnt;
         if (few) {
             const float* gw = static_cast<const float*>(gate);      // fp32 rows in either gate format
             if (D.m <= 8) gate_small_kernel<8, 1><<<D.T, 256, 0, s>>>(g, gw);
             else gate_small_kernel<16, 1><<<D.T, 256, 0, s>>>(g, gw);
-        } else if (tgw != 0) {
-            const int rows = 3 * D.m_pad + 16 * tgw;
-            const bool wide = D.m_pad <= 128 && 3 * rows * 128 <= kGateLds - 1024;    // 64-wide k stages fit
-            const int stage = rows * (wide ? 128 : 64);
-            g.n_stage = std::max(3, std::min(8, (kGateLds - 1024) / stage));
-            const int lds = std::max(g.n_stage * stage, 16 * tgw * D.m_pad * 4);
-            const int blocks = ceil_div(D.T, 16 * tgw);
-#define BMOE_GATE_TILED(TG_, NTH_, KB_, MT_, EG_) \
-    gate_tiled_kernel<TG_, NTH_, KB_, MT_, EG_><<<blocks, (TG_ / MT_) * EG_ * 64, lds, s>>>(g)
-            // Wave layouts, each measured against its neighbours (more, smaller waves win: the loop is bound by
-            // the latency of its LDS reads and barrier, not by bytes).  Up to 4 expert tiles: a wave holds one
-            // token tile and half of the experts.  Up to 8: two token tiles and one expert tile per wave, 8 expert
-            // groups.  Up to 16: two token tiles and two expert tiles, 8 groups.
-            static_assert(kMaxExperts <= 256, "8 expert groups of two tiles cover every expert");
-            if (tgw == 1) {
-                if (n_tiles <= 4) BMOE_GATE_TILED(1, 1, 64, 1, 4);
-                else if (n_tiles <= 8) BMOE_GATE_TILED(1, 1, 64, 1, 8);      // (wide stages always fit here)
-                else BMOE_GATE_TILED(1, 2, 32, 1, 8);
-            } else if (tgw == 4) {
-                if (half_tiles <= 2) { if (wide) BMOE_GATE_TILED(4, 2, 64, 1, 2); else BMOE_GATE_TILED(4, 2, 32, 1, 2); }
-                else if (half_tiles <= 4) { if (wide) BMOE_GATE_TILED(4, 4, 64, 1, 2); else BMOE_GATE_TILED(4, 1, 32, 2, 8); }
-                else BMOE_GATE_TILED(4, 2, 32, 2, 8);
-            } else {
-                if (half_tiles <= 2) { if (wide) BMOE_GATE_TILED(2, 2, 64, 1, 2); else BMOE_GATE_TILED(2, 2, 32, 1, 2); }
-                else if (half_tiles <= 4) { if (wide) BMOE_GATE_TILED(2, 1, 64, 2, 8); else BMOE_GATE_TILED(2, 4, 32, 1, 2); }
-                else BMOE_GATE_TILED(2, 2, 32, 2, 8);
-            }
-#undef BMOE_GATE_TILED
-        } else {
+        } else if (few_fmt) {
             // at most 16 experts beyond kFewExpertsTokens tokens
             gate_few_kernel<<<ceil_div(D.T, 16), 512, kGateFewLds, s>>>(g);
+        } else {
+            (void)launch_gate(g, logits, logit_bytes, s);
         }
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
