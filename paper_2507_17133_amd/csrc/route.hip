@@ -598,50 +598,57 @@ __global__ void __launch_bounds__(THREADS) gate_topk_kernel(GateArgs p)
 }
 
 // ------------------------------------------------------------------------------------------------
-// Algorithm 1 on the expert counts, one thread per expert (m <= 256).  Sorting is implicit: expert j
+// Algorithm 1 on the expert counts, PARTS threads per expert (m <= 256).  Sorting is implicit: expert j
 // precedes expert i in the order "count descending, id ascending" iff cnt_j > cnt_i or (equal and
 // j < i); P_i = tokens covered before i is the sum of the counts of those j.
 // ------------------------------------------------------------------------------------------------
+template <int PARTS>
 __device__ __forceinline__ void brownout_decide(const int* cnt_s, unsigned char* s2_s, int* unit_s, int m, int way,
                                                 double threshold, int full, int tid, bool write,
                                                 int32_t* expert_unit, uint8_t* expert_in_s1)
 {
-    // cnt_s: 16-byte aligned, zero from m up to the next multiple of 4 (a count of 0 adds nothing to P or S).
-    // Four counts per LDS read, and sums in 32 bits (the counts add up to T K <= 2^30): the loop is bound by the
-    // latency of its reads.
+    // cnt_s: 16-byte aligned, zero from m up to kMaxExperts (a count of 0 adds nothing to P or S).  Four counts per
+    // LDS read, and sums in 32 bits (the counts add up to T K <= 2^30): the loop is bound by the latency of its
+    // reads, so a block of 1024 threads gives each expert four neighbouring lanes that read a quarter each.
+    const int ex = tid / PARTS, part = tid % PARTS;
     bool in_s1 = false;
-    if (tid < m) {
-        const int c = cnt_s[tid];
+    if (ex < m) {
+        const int c = cnt_s[ex];
         int P = 0, S = 0;
         const int4* c4 = reinterpret_cast<const int4*>(cnt_s);
-        const int n4 = (m + 3) >> 2;
-#pragma unroll 4
-        for (int q = 0; q < n4; ++q) {
+        const int n4 = ((m + 3) >> 2) + PARTS - 1;
+#pragma unroll 8
+        for (int q = part; q < n4 / PARTS * PARTS; q += PARTS) {
             const int4 v = c4[q];
             const int j = 4 * q;
             S += (v.x + v.y) + (v.z + v.w);
-            P += (v.x > c || (v.x == c && j < tid)) ? v.x : 0;
-            P += (v.y > c || (v.y == c && j + 1 < tid)) ? v.y : 0;
-            P += (v.z > c || (v.z == c && j + 2 < tid)) ? v.z : 0;
-            P += (v.w > c || (v.w == c && j + 3 < tid)) ? v.w : 0;
+            P += (v.x > c || (v.x == c && j < ex)) ? v.x : 0;
+            P += (v.y > c || (v.y == c && j + 1 < ex)) ? v.y : 0;
+            P += (v.z > c || (v.z == c && j + 2 < ex)) ? v.z : 0;
+            P += (v.w > c || (v.w == c && j + 3 < ex)) ? v.w : 0;
+        }
+#pragma unroll
+        for (int o = 1; o < PARTS; o <<= 1) {       // lanes of one expert are all here (PARTS divides 64)
+            S += __shfl_xor(S, o);
+            P += __shfl_xor(P, o);
         }
         in_s1 = (double)P < (double)S * threshold;
-        s2_s[tid] = (!in_s1 && c > 0) ? 1 : 0;
+        if (part == 0) s2_s[ex] = (!in_s1 && c > 0) ? 1 : 0;
     }
     __syncthreads();
-    if (tid < m) {
-        const int g = tid / way, lo = g * way, hi = min(m, lo + way);
+    if (ex < m && part == 0) {
+        const int g = ex / way, lo = g * way, hi = min(m, lo + way);
         int members = 0;
         for (int i = lo; i < hi; ++i) members += s2_s[i];
-        int unit = tid;
-        if (s2_s[tid]) {
+        int unit = ex;
+        if (s2_s[ex]) {
             if (full) unit = -1;
             else if (members >= 2) unit = m + g;
         }
-        unit_s[tid] = unit;
+        unit_s[ex] = unit;
         if (write) {
-            if (expert_unit) expert_unit[tid] = unit;
-            if (expert_in_s1) expert_in_s1[tid] = in_s1 ? 1 : 0;
+            if (expert_unit) expert_unit[ex] = unit;
+            if (expert_in_s1) expert_in_s1[ex] = in_s1 ? 1 : 0;
         }
     }
     __syncthreads();
@@ -651,6 +658,7 @@ struct RowArgs {
     const int32_t* topk_idx; const float* topk_w; const int32_t* expert_cnt;
     int32_t* expert_unit; uint8_t* expert_in_s1;
     int T, K, m, way, G, Ns, U, n_seg, full;
+    int lk;                                                // log2 of the lanes a token gets: K rounded up to a power of two
     double threshold;
     int32_t* seg_cnt; int32_t* seg_off;
     int32_t* unit_cnt; int32_t* unit_off; int32_t* n_rows;
@@ -659,38 +667,102 @@ struct RowArgs {
     TileJobs jobs;                                         // GEMM tile tables to build (jobs.n == 0: none)
 };
 
-// One bit per token of the segment in bm[u]: token has a row in unit u.
-__device__ __forceinline__ void mark_units(const RowArgs& p, const int* unit_s, unsigned long long* bm, int t, int lane)
+// The row kernels give every TopK entry a lane of its own: a token's K entries lie in 2^lk neighbouring lanes (never
+// across a wavefront, K <= 32), entry e of a block is entry e mod 2^lk of its token e >> lk.  One lane per token
+// walked its entries one after the other, each a chain of global read, LDS read and atomic, and read the lists of
+// merged units K^2/2 times: 51 us for 1021 tokens of 8 entries over 256 experts in one block (now 29), 14.1 us for one
+// token over 128 (8.3); with a segment per block instead of four, the scatter of 3001 x 8 over 128 went from 18 to
+// 6.1 us (count 11 -> 10.5, bound by Algorithm 1 on the counts).
+constexpr int kEntryBatch = 8;         // entries a thread holds at a time
+static_assert(kMaxTopK <= 32 && kSegTokens * 32 <= kEntryBatch * 256, "a segment's entries fit 256 threads");
+
+// Entries first + q NT + tid, q = 0..kEntryBatch-1, of the tokens [t0, t1): expert (-1: no such entry) and weight.
+template <int NT, bool WEIGHTS>
+__device__ __forceinline__ void load_entries(const RowArgs& p, int first, int t0, int t1, int tid, int (&ex)[kEntryBatch],
+                                             float (&w)[kEntryBatch])
 {
-    if (t < p.T) {
-        const int32_t* idx = p.topk_idx + (size_t)t * p.K;
-        for (int j = 0; j < p.K; ++j) {
-            const int u = unit_s[idx[j]];
-            if (u < 0) continue;
-            atomicOr(&bm[u], 1ull << lane);   // a repeated united unit sets the same bit again
+    const int j = tid & ((1 << p.lk) - 1);                 // 2^lk divides NT: the same in every entry of the thread
+#pragma unroll
+    for (int q = 0; q < kEntryBatch; ++q) {
+        const int t = t0 + ((first + q * NT + tid) >> p.lk);
+        ex[q] = -1;
+        w[q] = 0.0f;
+        if (t < t1 && j < p.K) {
+            ex[q] = p.topk_idx[(size_t)t * p.K + j];
+            if (WEIGHTS) w[q] = p.topk_w[(size_t)t * p.K + j];
         }
-        for (int s = 0; s < p.Ns; ++s) atomicOr(&bm[p.m + p.G + s], 1ull << lane);
     }
 }
 
+// The row of one entry (token t, slot j; u: its unit or -1, w: its weight), called by whole wavefronts.  A united unit
+// that several entries of the token name gets one row, at the first of them, with the sum of their weights in TopK
+// order.  bmw: bitmaps of the token's segment, soff: rows of every unit in earlier segments.
+__device__ __forceinline__ void scatter_entry(const RowArgs& p, const unsigned long long* bmw, const int* off_s,
+                                              const int32_t* soff, int t, int j, int u, float w, bool valid, int lane)
+{
+    bool first = u >= 0;
+    if (__ballot(u >= p.m) != 0) {
+        const int base = lane & ~((1 << p.lk) - 1);
+        const float own = w;
+        for (int q = 0; q < p.K; ++q) {
+            const int uq = __shfl(u, base + q);
+            const float wq = __shfl(own, base + q);
+            if (u >= p.m && uq == u) {
+                if (q < j) first = false;
+                if (q > j) w += wq;
+            }
+        }
+    }
+    int row = -1;
+    if (first) {
+        row = off_s[u] + soff[u] + __popcll(bmw[u] & ((1ull << (t & 63)) - 1ull));
+        p.row_token[row] = t;
+        p.row_weight[row] = w;
+    }
+    if (valid) p.token_rows[(size_t)t * (p.K + p.Ns) + j] = row;
+}
+
+// Rows of the shared experts: every token has one in each, in token order.
+template <int NT>
+__device__ __forceinline__ void scatter_shared(const RowArgs& p, const int* off_s, int t0, int t1, int tid)
+{
+    for (int s = 0; s < p.Ns; ++s) {
+        const int first = off_s[p.m + p.G + s];
+        for (int t = t0 + tid; t < t1; t += NT) {
+            p.row_token[first + t] = t;
+            p.row_weight[first + t] = 1.0f;
+            p.token_rows[(size_t)t * (p.K + p.Ns) + p.K + s] = first + t;
+        }
+    }
+}
+
+// One segment (64 tokens) per block: which tokens have a row in unit u, as one bit per token, and how many.
 __global__ void __launch_bounds__(256) route_count_kernel(RowArgs p)
 {
     __shared__ __attribute__((aligned(16))) int cnt_s[kMaxExperts];
     __shared__ int unit_s[kMaxExperts];
     __shared__ unsigned char s2_s[kMaxExperts];
-    __shared__ unsigned long long bm[4][kMaxUnits];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    static_assert(kMaxExperts <= 256 && kMaxExperts % 4 == 0, "one thread per count, counts read four at a time");
-    if (tid < kMaxExperts) cnt_s[tid] = tid < p.m ? p.expert_cnt[tid] : 0;
-    for (int i = tid; i < 4 * kMaxUnits; i += 256) (&bm[0][0])[i] = 0ull;
+    __shared__ unsigned long long bm[kMaxUnits];
+    const int tid = threadIdx.x, seg = blockIdx.x;
+    const int t0 = seg * kSegTokens, t1 = min(p.T, t0 + kSegTokens);
+    static_assert(kMaxExperts == 256, "one thread per count");
+    int ex[kEntryBatch];
+    float w[kEntryBatch];
+    load_entries<256, false>(p, 0, t0, t1, tid, ex, w);    // on their way while Algorithm 1 runs
+    cnt_s[tid] = tid < p.m ? p.expert_cnt[tid] : 0;
+    for (int i = tid; i < p.U; i += 256) bm[i] = 0ull;
     __syncthreads();
-    brownout_decide(cnt_s, s2_s, unit_s, p.m, p.way, p.threshold, p.full, tid, blockIdx.x == 0, p.expert_unit,
-                    p.expert_in_s1);
-    const int seg = blockIdx.x * 4 + wave;
-    mark_units(p, unit_s, bm[wave], seg * kSegTokens + lane, lane);
+    brownout_decide<1>(cnt_s, s2_s, unit_s, p.m, p.way, p.threshold, p.full, tid, seg == 0, p.expert_unit,
+                       p.expert_in_s1);
+#pragma unroll
+    for (int q = 0; q < kEntryBatch; ++q) {
+        const int u = ex[q] >= 0 ? unit_s[ex[q]] : -1;
+        // a repeated united unit sets the same bit again
+        if (u >= 0) atomicOr(&bm[u], 1ull << (((q * 256 + tid) >> p.lk) & 63));
+    }
     __syncthreads();
-    if (seg < p.n_seg)
-        for (int u = lane; u < p.U; u += 64) p.seg_cnt[(size_t)seg * p.U + u] = __popcll(bm[wave][u]);
+    for (int u = tid; u < p.U; u += 256)
+        p.seg_cnt[(size_t)seg * p.U + u] = u < p.m + p.G ? __popcll(bm[u]) : t1 - t0;
 }
 
 // One wavefront per unit: exclusive scan of the unit's rows over the segments (lane l owns a contiguous
@@ -719,15 +791,20 @@ __global__ void __launch_bounds__(256) route_scan_kernel(RowArgs p)
     if (lane == 63) p.unit_cnt[u] = incl;
 }
 
-// Exclusive scan of unit_cnt into LDS (every block of the scatter needs all unit offsets); off_s[U] = total.
-__device__ __forceinline__ void unit_offsets(const int32_t* unit_cnt, int U, int* off_s, int* wsum, int tid)
+// Unit counts into cnt_s and their exclusive scan into off_s (every block of the scatter needs all unit offsets);
+// off_s[U] = total.
+__device__ __forceinline__ void unit_offsets(const int32_t* unit_cnt, int U, int* cnt_s, int* off_s, int* wsum, int tid)
 {
     const int lane = tid & 63, wave = tid >> 6;
+    constexpr int PER = (kMaxUnits + 255) / 256;
     const int per = (U + 255) / 256;
+    int c[PER];
     int local = 0;
-    for (int q = 0; q < per; ++q) {
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
         const int u = tid * per + q;
-        if (u < U) local += unit_cnt[u];
+        c[q] = q < per && u < U ? unit_cnt[u] : 0;
+        local += c[q];
     }
     int incl = local;
 #pragma unroll
@@ -739,82 +816,60 @@ __device__ __forceinline__ void unit_offsets(const int32_t* unit_cnt, int U, int
     __syncthreads();
     int base = incl - local;
     for (int w = 0; w < wave; ++w) base += wsum[w];
-    for (int q = 0; q < per; ++q) {
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
         const int u = tid * per + q;
-        if (u < U) {
+        if (q < per && u < U) {
             off_s[u] = base;
-            base += unit_cnt[u];
+            cnt_s[u] = c[q];
+            base += c[q];
             if (u == U - 1) off_s[U] = base;
         }
     }
     __syncthreads();
 }
 
-// Rows of token t (lane `lane` of its segment): off_s = first row of every unit, soff = rows of every unit
-// in earlier segments, bmw = the segment's token bitmaps.
-__device__ __forceinline__ void scatter_token(const RowArgs& p, const int* unit_s, const unsigned long long* bmw,
-                                              const int* off_s, const int32_t* soff, int t, int lane)
-{
-    const unsigned long long below = (1ull << lane) - 1ull;
-    const int32_t* idx = p.topk_idx + (size_t)t * p.K;
-    const float* wts = p.topk_w + (size_t)t * p.K;
-    const int slots = p.K + p.Ns;
-    for (int j = 0; j < p.K; ++j) {
-        const int u = unit_s[idx[j]];
-        int row = -1;
-        if (u >= 0) {
-            bool first = true;
-            if (u >= p.m)
-                for (int q = 0; q < j; ++q)
-                    if (unit_s[idx[q]] == u) first = false;
-            if (first) {
-                row = off_s[u] + soff[u] + __popcll(bmw[u] & below);
-                float w = wts[j];
-                if (u >= p.m)
-                    for (int q = j + 1; q < p.K; ++q)
-                        if (unit_s[idx[q]] == u) w += wts[q];     // merged entries, added in TopK order
-                p.row_token[row] = t;
-                p.row_weight[row] = w;
-            }
-        }
-        p.token_rows[(size_t)t * slots + j] = row;
-    }
-    for (int s = 0; s < p.Ns; ++s) {
-        const int u = p.m + p.G + s;
-        const int row = off_s[u] + soff[u] + __popcll(bmw[u] & below);
-        p.row_token[row] = t;
-        p.row_weight[row] = 1.0f;
-        p.token_rows[(size_t)t * slots + p.K + s] = row;
-    }
-}
-
+// One segment per block; the last block has none and writes the unit offsets and the GEMM tile tables instead.
 __global__ void __launch_bounds__(256) route_scatter_kernel(RowArgs p)
 {
     __shared__ int unit_s[kMaxExperts];
-    __shared__ unsigned long long bm[4][kMaxUnits];
-    __shared__ int off_s[kMaxUnits + 1];
+    __shared__ unsigned long long bm[kMaxUnits];
+    __shared__ int off_s[kMaxUnits + 1], ucnt_s[kMaxUnits];
     __shared__ int wsum[4];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    unit_offsets(p.unit_cnt, p.U, off_s, wsum, tid);
-    if (blockIdx.x == 0) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, seg = blockIdx.x;
+    const int t0 = seg * kSegTokens, t1 = min(p.T, t0 + kSegTokens);
+    int ex[kEntryBatch];
+    float w[kEntryBatch];
+    load_entries<256, true>(p, 0, t0, t1, tid, ex, w);
+    if (tid < p.m) unit_s[tid] = p.expert_unit[tid];
+    for (int i = tid; i < p.U; i += 256) bm[i] = 0ull;
+    unit_offsets(p.unit_cnt, p.U, ucnt_s, off_s, wsum, tid);
+    if (seg == p.n_seg) {
         for (int u = tid; u <= p.U; u += 256) p.unit_off[u] = off_s[u];
         if (tid == 0 && p.n_rows) p.n_rows[0] = off_s[p.U];
-        if (wave < p.jobs.n) build_tile_table(p.unit_cnt, off_s, p.jobs.job[wave], p.jobs.cap, lane);
+        if (wave < p.jobs.n) build_tile_table(ucnt_s, off_s, p.jobs.job[wave], p.jobs.cap, lane);
+        return;
     }
-    if (tid < p.m) unit_s[tid] = p.expert_unit[tid];
-    for (int i = tid; i < 4 * kMaxUnits; i += 256) (&bm[0][0])[i] = 0ull;
+#pragma unroll
+    for (int q = 0; q < kEntryBatch; ++q) {
+        ex[q] = ex[q] >= 0 ? unit_s[ex[q]] : -1;
+        if (ex[q] >= 0) atomicOr(&bm[ex[q]], 1ull << (((q * 256 + tid) >> p.lk) & 63));
+    }
     __syncthreads();
-    const int seg = blockIdx.x * 4 + wave;
-    const int t = seg * kSegTokens + lane;
-    mark_units(p, unit_s, bm[wave], t, lane);
-    __syncthreads();
-    if (t >= p.T) return;
-    scatter_token(p, unit_s, bm[wave], off_s, p.seg_off + (size_t)seg * p.U, t, lane);
+    const int32_t* soff = p.seg_off + (size_t)seg * p.U;
+    const int j = tid & ((1 << p.lk) - 1);
+#pragma unroll
+    for (int q = 0; q < kEntryBatch; ++q) {
+        if (q * 256 >= (kSegTokens << p.lk)) break;
+        const int t = t0 + ((q * 256 + tid) >> p.lk);
+        scatter_entry(p, bm, off_s, soff, t, j, ex[q], w[q], t < t1 && j < p.K, lane);
+    }
+    scatter_shared<256>(p, off_s, t0, t1, tid);
 }
 
 // Small batches (at most 16 segments = 1024 tokens): Algorithm 1, the per-segment bitmaps, both scans and
-// the scatter in ONE block of 16 wavefronts, one segment per wavefront, everything in LDS.  Dynamic LDS:
-// bitmaps [16][U] (8 bytes) then segment offsets [16][U] (4 bytes).
+// the scatter in ONE block of 16 wavefronts, everything in LDS.  Dynamic LDS: bitmaps [n_seg][U] (8 bytes) then
+// segment offsets [n_seg][U] (4 bytes).
 __global__ void __launch_bounds__(1024) route_small_kernel(RowArgs p)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char rsm[];
@@ -823,26 +878,48 @@ __global__ void __launch_bounds__(1024) route_small_kernel(RowArgs p)
     __shared__ unsigned char s2_s[kMaxExperts];
     __shared__ int ucnt_s[kMaxUnits];
     __shared__ int off_s[kMaxUnits + 1];
-    unsigned long long* bm = reinterpret_cast<unsigned long long*>(rsm);                      // [16][U]
-    int* segoff = reinterpret_cast<int*>(rsm + (size_t)kSmallSegs * p.U * 8);                  // [16][U]
+    unsigned long long* bm = reinterpret_cast<unsigned long long*>(rsm);                      // [n_seg][U]
+    int* segoff = reinterpret_cast<int*>(rsm + (size_t)p.n_seg * p.U * 8);                     // [n_seg][U]
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    // cnt_i (the input of Algorithm 1) straight from the TopK lists: at most 1024 tokens, one thread each
+    const int entries = p.T << p.lk;
+    constexpr int BATCH = kEntryBatch * 1024;              // up to K = 8 with 1024 tokens: read once, kept in registers
+    const bool once = entries <= BATCH;
+    int ex[kEntryBatch];
+    float w[kEntryBatch];
+    load_entries<1024, true>(p, 0, 0, p.T, tid, ex, w);
+    // cnt_i (the input of Algorithm 1) straight from the TopK lists
     if (tid < kMaxExperts) cnt_s[tid] = 0;
-    for (int i = tid; i < kSmallSegs * p.U; i += 1024) bm[i] = 0ull;
+    for (int i = tid; i < p.n_seg * p.U; i += 1024) bm[i] = 0ull;
     __syncthreads();
-    if (tid < p.T)
-        for (int j = 0; j < p.K; ++j) atomicAdd(&cnt_s[p.topk_idx[(size_t)tid * p.K + j]], 1);
+    for (int b = 0; b < entries; b += BATCH) {
+        if (!once) load_entries<1024, false>(p, b, 0, p.T, tid, ex, w);
+#pragma unroll
+        for (int q = 0; q < kEntryBatch; ++q)
+            if (ex[q] >= 0) atomicAdd(&cnt_s[ex[q]], 1);
+    }
     __syncthreads();
     if (tid < p.m) p.expert_cnt_out[tid] = cnt_s[tid];
-    brownout_decide(cnt_s, s2_s, unit_s, p.m, p.way, p.threshold, p.full, tid, true, p.expert_unit, p.expert_in_s1);
-    const int t = wave * kSegTokens + lane;
-    mark_units(p, unit_s, bm + (size_t)wave * p.U, t, lane);
+    brownout_decide<4>(cnt_s, s2_s, unit_s, p.m, p.way, p.threshold, p.full, tid, true, p.expert_unit, p.expert_in_s1);
+    for (int b = 0; b < entries; b += BATCH) {
+        if (!once) load_entries<1024, false>(p, b, 0, p.T, tid, ex, w);
+#pragma unroll
+        for (int q = 0; q < kEntryBatch; ++q) {
+            const int t = (b + q * 1024 + tid) >> p.lk;
+            const int u = ex[q] >= 0 ? unit_s[ex[q]] : -1;
+            if (u >= 0) atomicOr(&bm[(t >> 6) * p.U + u], 1ull << (t & 63));
+        }
+    }
     __syncthreads();
     for (int u = tid; u < p.U; u += 1024) {
         int run = 0;
-        for (int sgm = 0; sgm < kSmallSegs; ++sgm) {
-            segoff[sgm * p.U + u] = run;
-            run += __popcll(bm[(size_t)sgm * p.U + u]);
+        if (u < p.m + p.G) {
+#pragma unroll 4
+            for (int sgm = 0; sgm < p.n_seg; ++sgm) {
+                segoff[sgm * p.U + u] = run;
+                run += __popcll(bm[sgm * p.U + u]);
+            }
+        } else {
+            run = p.T;                                     // a shared expert: every token
         }
         ucnt_s[u] = run;
         p.unit_cnt[u] = run;
@@ -871,7 +948,19 @@ __global__ void __launch_bounds__(1024) route_small_kernel(RowArgs p)
     if (tid == 0 && p.n_rows) p.n_rows[0] = off_s[p.U];
     // the GEMM tile tables, by the last wavefronts (the first ones hold the tokens of a short batch)
     if (15 - wave < p.jobs.n) build_tile_table(ucnt_s, off_s, p.jobs.job[15 - wave], p.jobs.cap, lane);
-    if (t < p.T) scatter_token(p, unit_s, bm + (size_t)wave * p.U, off_s, segoff + wave * p.U, t, lane);
+    const int j = tid & ((1 << p.lk) - 1);
+    for (int b = 0; b < entries; b += BATCH) {
+        if (!once) load_entries<1024, true>(p, b, 0, p.T, tid, ex, w);
+#pragma unroll
+        for (int q = 0; q < kEntryBatch; ++q) {
+            const int e = b + q * 1024 + tid;
+            if (e - lane >= entries) break;                // whole wavefronts leave
+            const int t = e >> p.lk, sg = min(t >> 6, p.n_seg - 1);
+            const int u = ex[q] >= 0 ? unit_s[ex[q]] : -1;
+            scatter_entry(p, bm + sg * p.U, off_s, segoff + sg * p.U, t, j, u, w[q], t < p.T && j < p.K, lane);
+        }
+    }
+    scatter_shared<1024>(p, off_s, 0, p.T, tid);
 }
 
 constexpr int kGateFewLds = 3 * 4 * 64 * 128;          // three stages of four 64-row pieces (gate_few_kernel)
@@ -1003,19 +1092,20 @@ hipError_t launch_route(const Dims& D, const bf16_t* x, const void* gate, const 
     p.expert_unit = R.expert_unit; p.expert_in_s1 = R.expert_in_s1;
     p.T = D.T; p.K = D.K; p.m = D.m; p.way = D.way; p.G = D.G; p.Ns = D.Ns; p.U = D.U; p.n_seg = D.n_seg;
     p.full = full_brownout; p.threshold = threshold;
+    p.lk = 0;
+    while ((1 << p.lk) < D.K) ++p.lk;
     p.seg_cnt = seg_cnt; p.seg_off = seg_off; p.unit_cnt = R.unit_cnt; p.unit_off = R.unit_off; p.n_rows = R.n_rows;
     p.row_token = R.row_token; p.row_weight = R.row_weight; p.token_rows = R.token_rows;
     p.expert_cnt_out = R.expert_cnt;
     p.jobs = jobs;
     if (small) {
         ProfScope ps(MOE_STAGE_COUNT, s);
-        route_small_kernel<<<1, 1024, (size_t)kSmallSegs * D.U * 12, s>>>(p);
+        route_small_kernel<<<1, 1024, (size_t)D.n_seg * D.U * 12, s>>>(p);
         return hipGetLastError();
     }
-    const int seg_blocks = ceil_div(D.n_seg, 4);
     {
         ProfScope ps(MOE_STAGE_COUNT, s);
-        route_count_kernel<<<seg_blocks, 256, 0, s>>>(p);
+        route_count_kernel<<<D.n_seg, 256, 0, s>>>(p);
     }
     {
         ProfScope ps(MOE_STAGE_SCAN, s);
@@ -1023,7 +1113,7 @@ hipError_t launch_route(const Dims& D, const bf16_t* x, const void* gate, const 
     }
     {
         ProfScope ps(MOE_STAGE_SCATTER, s);
-        route_scatter_kernel<<<seg_blocks, 256, 0, s>>>(p);
+        route_scatter_kernel<<<D.n_seg + 1, 256, 0, s>>>(p);
     }
     return hipGetLastError();
 }
