@@ -88,22 +88,32 @@ static moe_status hip_fail(hipError_t e, const char* where)
     return MOE_ERR_HIP;
 }
 
-// GEMM tile height from the expected rows per expert when every unit gets the same height.
-static int pick_tile_rows(int64_t expected_rows_per_unit)
+// GEMM tile height from the rows per unit: `even`, every unit holds that many (calibration tokens, a shared expert), else
+// their mean over the experts.  A gate's popular experts hold several times the mean, and every further tile of a
+// unit stages its weights again, so a tile is at least one to four times the mean.  Layer forward in us at tiles of 32 / 64
+// / 128 rows, Zipf gates: DeepSeek-V3 shape, 16 rows per expert 2929 / 2627 / 2628, 32 rows 4457 / 3609 / 3508; Qwen3 shape,
+// 8 rows 210 / 218 / 231, 16 rows 251 / 234 / 248, 64 rows - / 333 / 326; uniform gate, Mixtral shape, 16 rows 525 / 507 / 563.
+static int pick_tile_rows(int64_t rows, bool even)
 {
     if (tuning().force_bm) return tuning().force_bm;
-    if (expected_rows_per_unit >= kMixedRows) return 256;
-    // one tile should hold an expert's rows with room for the spread around the mean: a second, nearly
-    // empty tile would stream the expert's weights a second time
-    if (expected_rows_per_unit >= 48) return 128;
-    if (expected_rows_per_unit >= 24) return 64;
-    return 32;
+    if (rows >= kMixedRows) return 256;
+    if (rows >= 48) return 128;
+    return rows >= (even ? 24 : 12) ? 64 : 32;
 }
 
-TilePlan make_tile_plan(int64_t expected_rows_per_unit)
+TilePlan make_tile_plan(int64_t rows, bool even)
 {
     TilePlan p;
-    p.bm = pick_tile_rows(expected_rows_per_unit);
+    p.bm = pick_tile_rows(rows, even);
+    return p;
+}
+
+// A launch of shared experts alone: with up to 128 tokens and too few 256-column blocks for the CUs, tiles of 64 rows
+// let the narrow kernel run (100 tokens over F = 5632: 44 blocks of 128 rows; layer with its routed experts 157.6 -> 124.7 us).
+static TilePlan make_shared_plan(const Dims& D, int n_cu)
+{
+    TilePlan p = make_tile_plan(D.T, true);
+    if (p.bm == 128 && !tuning().force_bm && D.T <= 128 && 2 * D.Ns * ceil_div(D.Fs, 128) < n_cu) p.bm = 64;
     return p;
 }
 
@@ -124,7 +134,7 @@ Dims make_dims(const moe_config& c, int T)
     D.tile_cap = (int)(D.row_cap / kMinTileRows) + D.U;
     // GEMM2 has few, long tiles (N = d): split K (at most 4 ways) until about four rounds of blocks fill
     // the 256 CUs; more slices only add prologues and planes for the combine to sum.
-    const int bm = pick_tile_rows((int64_t)T * D.K / D.m);
+    const int bm = pick_tile_rows((int64_t)T * D.K / D.m, false);
     const int64_t tiles2 = (D.row_cap / bm + (D.m + D.G) / 2 + D.Ns) * (int64_t)ceil_div(D.d, 256);
     int ks = 1;
     while (ks < 4 && tiles2 * ks < 1024 && (D.F / 64) / (ks * 2) >= 8) ks *= 2;
@@ -487,6 +497,9 @@ moe_status moe_forward(const moe_config* cfg, const void* x, int32_t T, const vo
     if (!workspace || workspace_bytes < W.total) return MOE_ERR_WORKSPACE;
     if (reinterpret_cast<uintptr_t>(workspace) & 255u) return MOE_ERR_ALIGNMENT;
     const RouteBufs R = resolve_route(route, workspace, W);
+    DeviceInfo dev;
+    hipError_t e = ensure_device_init(&dev);
+    if (e != hipSuccess) return hip_fail(e, "moe_forward/init");
     hipStream_t s = static_cast<hipStream_t>(stream);
     const bf16_t* xb = static_cast<const bf16_t*>(x);
     // How the rows are cut into GEMM tiles: routed + united units by the expected rows per expert; shared units
@@ -496,12 +509,11 @@ moe_status moe_forward(const moe_config* cfg, const void* x, int32_t T, const vo
     jobs.n = split_shared ? 2 : 1;
     jobs.cap = D.tile_cap;
     jobs.job[0].u_lo = 0; jobs.job[0].u_hi = split_shared ? D.m + D.G : D.U;
-    jobs.job[0].plan = make_tile_plan((int64_t)T * D.K / D.m);
+    jobs.job[0].plan = make_tile_plan((int64_t)T * D.K / D.m, false);
     jobs.job[0].table = at<int32_t>(workspace, W.tiles0);
     jobs.job[1].u_lo = D.m + D.G; jobs.job[1].u_hi = D.U;
-    jobs.job[1].plan = make_tile_plan(T);
+    jobs.job[1].plan = make_shared_plan(D, dev.n_cu);
     jobs.job[1].table = at<int32_t>(workspace, W.tiles1);
-    hipError_t e;
     if (!route) {
         e = launch_route(D, xb, gate_w, gate_bias, threshold, use_full_brownout ? 1 : 0, R,
                          at<bf16_t>(workspace, W.gate_split), at<int32_t>(workspace, W.seg_cnt),
@@ -563,7 +575,7 @@ moe_status moe_build_united(const moe_config* cfg, const moe_ffn_weights* expert
     if (!want_loss) return MOE_OK;
 
     const FfnWeights fe = to_ffn(experts), fu = to_ffn(&united_ro), fs{nullptr, nullptr, nullptr};
-    const TilePlan plan = make_tile_plan(n_calib);
+    const TilePlan plan = make_tile_plan(n_calib, true);
     bf16_t* H = at<bf16_t>(workspace, W.H);
     bf16_t* Yu = at<bf16_t>(workspace, W.Y);
     const size_t nd = (size_t)n_calib * D.d;
@@ -652,7 +664,7 @@ moe_status moe_distill_united(const moe_config* cfg, const moe_ffn_weights* expe
     Dims D = make_dims(*cfg, n_calib);
     const Workspace W = carve_workspace(D);
     D.ksplit = 1;
-    const TilePlan plan = make_tile_plan(n_calib);
+    const TilePlan plan = make_tile_plan(n_calib, true);
     const size_t fwd_bytes = align_up(W.total, 256);
     if (!workspace || workspace_bytes < fwd_bytes + distill_bytes(D, n_calib)) return MOE_ERR_WORKSPACE;
     if (reinterpret_cast<uintptr_t>(workspace) & 255u) return MOE_ERR_ALIGNMENT;

@@ -45,7 +45,7 @@ hipError_t init_route_kernels();    // route.hip
 struct TilePlan {
     int bm;      // 256, 128, 64 or 32
 };
-TilePlan make_tile_plan(int64_t expected_rows_per_unit);
+TilePlan make_tile_plan(int64_t rows_per_unit, bool even);     // even: exactly that many in every unit, else their mean
 
 // Derived sizes of one (config, T) problem.
 struct Dims {
