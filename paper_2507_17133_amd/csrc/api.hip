@@ -117,6 +117,20 @@ static TilePlan make_shared_plan(const Dims& D, int n_cu)
     return p;
 }
 
+// The taller tile that the table kernel may choose instead in a browned-out batch (0: none).  Offered where its blocks fill
+// the CUs once if no entry is dropped: the launch that gets no tiles costs 3 to 10 us, which shorter forwards would feel.
+// Layer forward in us at 40 / 80 % brownout, tiles of 64, 128 and 256 rows: DeepSeek-V3 shape, 16 rows per expert
+// 1127 / 1041, 920 / 839, 993 / 865; 32 rows 1809 / 1701, 1354 / 1290, 1223 / 1073; 94 rows (128 and 256) 3083 / 2950, 2368 / 2258;
+// Qwen3 shape, 250 rows 450 / 409, 382 / 334; with a uniform gate and 30 %, 32 rows 3355, 3360, 4077.
+static int taller_tile_rows(const Dims& D, int bm, int n_cu)
+{
+    if (tuning().force_bm) return 0;
+    const int64_t rows = (int64_t)D.T * D.K / D.m;
+    const int hi = rows >= 20 ? 256 : rows >= 5 ? 128 : 0;
+    if (hi <= bm || (int64_t)D.T * D.K / hi * ceil_div(D.F, 128) < n_cu) return 0;
+    return hi;
+}
+
 Dims make_dims(const moe_config& c, int T)
 {
     Dims D;
@@ -196,6 +210,7 @@ Workspace carve_workspace(const Dims& D)
     auto take = [&](size_t bytes) { size_t at = o; o = align_up(o + bytes, 256); return at; };
     W.tiles0 = take(16 + (size_t)D.tile_cap * 16);
     W.tiles1 = take(16 + (size_t)D.tile_cap * 16);
+    W.tiles2 = take(16 + (size_t)D.tile_cap * 16);
     W.h_rows = D.row_cap;
     W.y_rows = y_rows_bound(D);
     // one tile of rows past the end: GEMM2's ragged last tile reads (and discards) whole tiles of H
@@ -511,6 +526,11 @@ moe_status moe_forward(const moe_config* cfg, const void* x, int32_t T, const vo
     jobs.job[0].u_lo = 0; jobs.job[0].u_hi = split_shared ? D.m + D.G : D.U;
     jobs.job[0].plan = make_tile_plan((int64_t)T * D.K / D.m, false);
     jobs.job[0].table = at<int32_t>(workspace, W.tiles0);
+    // a threshold of 1 browns nothing out (a route of the caller's may, whatever threshold comes with it)
+    jobs.job[0].bm_hi = route || threshold < 1.0 ? taller_tile_rows(D, jobs.job[0].plan.bm, dev.n_cu) : 0;
+    jobs.job[0].table_hi = at<int32_t>(workspace, W.tiles2);
+    jobs.job[0].m = D.m; jobs.job[0].entries = T * D.K;
+    jobs.job[1].bm_hi = 0; jobs.job[1].table_hi = nullptr; jobs.job[1].m = 0; jobs.job[1].entries = 0;
     jobs.job[1].u_lo = D.m + D.G; jobs.job[1].u_hi = D.U;
     jobs.job[1].plan = make_shared_plan(D, dev.n_cu);
     jobs.job[1].table = at<int32_t>(workspace, W.tiles1);
@@ -519,16 +539,17 @@ moe_status moe_forward(const moe_config* cfg, const void* x, int32_t T, const vo
                          at<bf16_t>(workspace, W.gate_split), at<int32_t>(workspace, W.seg_cnt),
                          at<int32_t>(workspace, W.seg_off), at<void>(workspace, W.H), W.total - W.H, jobs, s);
         if (e != hipSuccess) return hip_fail(e, "moe_forward/route");
+    } else if ((e = launch_tile_tables(R.unit_cnt, R.unit_off, jobs, s)) != hipSuccess) {
+        return hip_fail(e, "moe_forward/tiles");
     }
-    const bool built = route == nullptr;
     const FfnWeights fe = to_ffn(experts), fu = to_ffn(united), fs = to_ffn(shared);
     bf16_t* H = at<bf16_t>(workspace, W.H);
     bf16_t* Y = at<bf16_t>(workspace, W.Y);
     float* partial = W.partial_bytes ? at<float>(workspace, W.partial) : nullptr;
     for (int j = 0; j < jobs.n; ++j) {
         const TileJob& J = jobs.job[j];
-        e = launch_ffn(D, J.u_lo, J.u_hi, j == 0 ? D.F : D.Fs, J.plan, xb, R.row_token, R.unit_cnt, R.unit_off, fe, fu,
-                       fs, J.table, built, H, Y, partial, s);
+        e = launch_ffn(D, J.u_lo, J.u_hi, j == 0 ? D.F : D.Fs, J.plan, xb, R.row_token, fe, fu, fs, J.table, H, Y, partial, s,
+                       J.bm_hi, J.table_hi);
         if (e != hipSuccess) return hip_fail(e, j == 0 ? "moe_forward/ffn" : "moe_forward/ffn_shared");
     }
     e = launch_combine(D, xb, Y, R.token_rows, R.row_weight, static_cast<bf16_t*>(out), s);
@@ -593,7 +614,7 @@ moe_status moe_build_united(const moe_config* cfg, const moe_ffn_weights* expert
     auto run_units = [&](int u0, int n0, int u1, int n1, int first_slot, bf16_t* Y) -> hipError_t {
         hipError_t err = launch_uniform_units(u0, n0, u1, n1, first_slot, n_calib, plan.bm, tiles, s);
         if (err != hipSuccess) return err;
-        return launch_ffn(D, 0, n0 + n1, D.F, plan, xb, row_token, nullptr, nullptr, fe, fu, fs, tiles, true, H, Y, partial, s);
+        return launch_ffn(D, 0, n0 + n1, D.F, plan, xb, row_token, fe, fu, fs, tiles, H, Y, partial, s);
     };
     for (int g = 0; g < G; ++g) {
         const int lo = g * way, hi = lo + way < m ? lo + way : m, k = hi - lo;
@@ -692,7 +713,7 @@ moe_status moe_distill_united(const moe_config* cfg, const moe_ffn_weights* expe
             for (int q = 0; q < batches; ++q) {
                 const int i0 = lo + (int)((int64_t)k * q / batches), i1 = lo + (int)((int64_t)k * (q + 1) / batches);
                 if ((e = launch_uniform_units(i0, i1 - i0, 0, 0, 0, n_calib, plan.bm, tiles, s)) != hipSuccess ||
-                    (e = launch_ffn(D, 0, i1 - i0, D.F, plan, xb, row_token, nullptr, nullptr, fe, fu, fs, tiles, true, H, Yo,
+                    (e = launch_ffn(D, 0, i1 - i0, D.F, plan, xb, row_token, fe, fu, fs, tiles, H, Yo,
                                     partial, s)) != hipSuccess)
                     return hip_fail(e, "moe_distill_united/teacher");
                 e = launch_teacher_stats(Yo, i1 - i0, q == 0, q == batches - 1, k, n_calib, D.d, D.F, g - g0, buf, s);

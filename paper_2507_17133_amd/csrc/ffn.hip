@@ -29,6 +29,7 @@
 
 #include <algorithm>
 #include <cstdlib>
+#include <type_traits>
 
 namespace bmoe {
 
@@ -1421,26 +1422,26 @@ static hipError_t dispatch_gemm(int bm, const GemmArgs& a, int max_mtiles, long 
     }
 }
 
+hipError_t launch_tile_tables(const int32_t* unit_cnt, const int32_t* unit_off, const TileJobs& jobs, hipStream_t s)
+{
+    ProfScope ps(MOE_STAGE_TILES, s);
+    tile_table_kernel<<<jobs.n, 64, 0, s>>>(unit_cnt, unit_off, jobs);
+    return hipGetLastError();
+}
+
 hipError_t launch_ffn(const Dims& D, int u_lo, int u_hi, int Fdim, const TilePlan& plan, const bf16_t* x,
-                      const int32_t* gather, const int32_t* unit_cnt, const int32_t* unit_off,
-                      const FfnWeights& experts, const FfnWeights& united, const FfnWeights& shared,
-                      int32_t* table, bool table_built, bf16_t* H, bf16_t* Y, float* partial, hipStream_t s)
+                      const int32_t* gather, const FfnWeights& experts, const FfnWeights& united, const FfnWeights& shared,
+                      int32_t* table, bf16_t* H, bf16_t* Y, float* partial, hipStream_t s, int bm_hi, int32_t* table_hi)
 {
     DeviceInfo dev;
     hipError_t e = ensure_device_init(&dev);
     if (e != hipSuccess) return e;
     const int n_units = u_hi - u_lo;
-    if (!table_built) {
-        ProfScope ps(MOE_STAGE_TILES, s);
-        TileJobs jobs;
-        jobs.n = 1; jobs.cap = D.tile_cap;
-        jobs.job[0].u_lo = u_lo; jobs.job[0].u_hi = u_hi; jobs.job[0].plan = plan; jobs.job[0].table = table;
-        jobs.job[1] = jobs.job[0];
-        tile_table_kernel<<<1, 64, 0, s>>>(unit_cnt, unit_off, jobs);
-    }
     // M tiles there can be at most: a unit that holds rows has one for every bm of them and a ragged one, and no more
     // units hold rows than there are rows
-    const int max_mtiles = (int)std::min<int64_t>(D.row_cap / plan.bm + std::min<int64_t>(n_units, D.row_cap), D.tile_cap);
+    auto max_mtiles = [&](int bm) {
+        return (int)std::min<int64_t>(D.row_cap / bm + std::min<int64_t>(n_units, D.row_cap), D.tile_cap);
+    };
     // M tiles of a batch that the gate routes: TopK entries over the experts (their united units take rows from them),
     // every token once per shared expert.  Chooses the kernel; the grid is sized for max_mtiles.
     const int64_t entries = u_lo < D.m + D.G ? (int64_t)D.T * D.K : 0;
@@ -1453,13 +1454,18 @@ hipError_t launch_ffn(const Dims& D, int u_lo, int u_hi, int Fdim, const TilePla
     g1.m = D.m; g1.G = D.G; g1.N = Fdim; g1.K = D.d;
     g1.out = H; g1.ldo = D.Fmax;
     g1.n_ntiles = 0;                            // set by the launcher from its tile width
-    g1.group_m = tuning().group_m ? tuning().group_m : (plan.bm == 256 ? 8 : 4);
     g1.ksplit = 1; g1.plane = 0;
     g1.partial = partial; g1.partial_cap = D.tail_blocks;
-    g1.table = table;
+    // Both heights where the table kernel chooses between two: the launch whose table got no tiles returns at once.
+    auto gemm = [&](auto swiglu, GemmArgs& g, int bm, int32_t* tab) {
+        g.table = tab;
+        g.group_m = tuning().group_m ? tuning().group_m : (bm == 256 ? 8 : 4);
+        return dispatch_gemm<decltype(swiglu)::value>(bm, g, max_mtiles(bm), likely, dev.n_cu, s);
+    };
     {
         ProfScope ps(MOE_STAGE_GEMM1, s);
-        e = dispatch_gemm<true>(plan.bm, g1, max_mtiles, likely, dev.n_cu, s);
+        e = gemm(std::true_type{}, g1, plan.bm, table);
+        if (e == hipSuccess && bm_hi > 0) e = gemm(std::true_type{}, g1, bm_hi, table_hi);
         if (e != hipSuccess) return e;
     }
     GemmArgs g2;
@@ -1469,13 +1475,12 @@ hipError_t launch_ffn(const Dims& D, int u_lo, int u_hi, int Fdim, const TilePla
     g2.m = D.m; g2.G = D.G; g2.N = D.d; g2.K = Fdim;
     g2.out = Y; g2.ldo = D.d;
     g2.n_ntiles = 0;
-    g2.group_m = g1.group_m;
     g2.ksplit = D.ksplit; g2.plane = D.y_plane;
     g2.partial = partial; g2.partial_cap = D.tail_blocks;
-    g2.table = table;
     {
         ProfScope ps(MOE_STAGE_GEMM2, s);
-        e = dispatch_gemm<false>(plan.bm, g2, max_mtiles, likely, dev.n_cu, s);
+        e = gemm(std::false_type{}, g2, plan.bm, table);
+        if (e == hipSuccess && bm_hi > 0) e = gemm(std::false_type{}, g2, bm_hi, table_hi);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
