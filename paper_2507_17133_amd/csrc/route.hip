@@ -670,9 +670,10 @@ struct RowArgs {
 // The row kernels give every TopK entry a lane of its own: a token's K entries lie in 2^lk neighbouring lanes (never
 // across a wavefront, K <= 32), entry e of a block is entry e mod 2^lk of its token e >> lk.  One lane per token
 // walked its entries one after the other, each a chain of global read, LDS read and atomic, and read the lists of
-// merged units K^2/2 times: 51 us for 1021 tokens of 8 entries over 256 experts in one block (now 29), 14.1 us for one
-// token over 128 (8.3); with a segment per block instead of four, the scatter of 3001 x 8 over 128 went from 18 to
-// 6.1 us (count 11 -> 10.5, bound by Algorithm 1 on the counts).
+// merged units K^2/2 times: 51 us for 1021 tokens of 8 entries over 256 experts in one block (now 28 to 31; three
+// launches instead take 24 and 6 more for the histogram), 14.1 us for one token over 128 (8.3); with a segment per block
+// instead of four, and Algorithm 1 on four lanes per expert, the count of 3001 x 8 over 128 went from 11 to 5.9 us and the
+// scatter from 18 to 6.2.
 constexpr int kEntryBatch = 8;         // entries a thread holds at a time
 static_assert(kMaxTopK <= 32 && kSegTokens * 32 <= kEntryBatch * 256, "a segment's entries fit 256 threads");
 
@@ -737,7 +738,7 @@ __device__ __forceinline__ void scatter_shared(const RowArgs& p, const int* off_
 }
 
 // One segment (64 tokens) per block: which tokens have a row in unit u, as one bit per token, and how many.
-__global__ void __launch_bounds__(256) route_count_kernel(RowArgs p)
+__global__ void __launch_bounds__(1024) route_count_kernel(RowArgs p)
 {
     __shared__ __attribute__((aligned(16))) int cnt_s[kMaxExperts];
     __shared__ int unit_s[kMaxExperts];
@@ -745,23 +746,22 @@ __global__ void __launch_bounds__(256) route_count_kernel(RowArgs p)
     __shared__ unsigned long long bm[kMaxUnits];
     const int tid = threadIdx.x, seg = blockIdx.x;
     const int t0 = seg * kSegTokens, t1 = min(p.T, t0 + kSegTokens);
-    static_assert(kMaxExperts == 256, "one thread per count");
     int ex[kEntryBatch];
     float w[kEntryBatch];
-    load_entries<256, false>(p, 0, t0, t1, tid, ex, w);    // on their way while Algorithm 1 runs
-    cnt_s[tid] = tid < p.m ? p.expert_cnt[tid] : 0;
-    for (int i = tid; i < p.U; i += 256) bm[i] = 0ull;
+    load_entries<1024, false>(p, 0, t0, t1, tid, ex, w);    // on their way while Algorithm 1 runs
+    if (tid < kMaxExperts) cnt_s[tid] = tid < p.m ? p.expert_cnt[tid] : 0;
+    for (int i = tid; i < p.U; i += 1024) bm[i] = 0ull;
     __syncthreads();
-    brownout_decide<1>(cnt_s, s2_s, unit_s, p.m, p.way, p.threshold, p.full, tid, seg == 0, p.expert_unit,
+    brownout_decide<4>(cnt_s, s2_s, unit_s, p.m, p.way, p.threshold, p.full, tid, seg == 0, p.expert_unit,
                        p.expert_in_s1);
 #pragma unroll
     for (int q = 0; q < kEntryBatch; ++q) {
         const int u = ex[q] >= 0 ? unit_s[ex[q]] : -1;
         // a repeated united unit sets the same bit again
-        if (u >= 0) atomicOr(&bm[u], 1ull << (((q * 256 + tid) >> p.lk) & 63));
+        if (u >= 0) atomicOr(&bm[u], 1ull << (((q * 1024 + tid) >> p.lk) & 63));
     }
     __syncthreads();
-    for (int u = tid; u < p.U; u += 256)
+    for (int u = tid; u < p.U; u += 1024)
         p.seg_cnt[(size_t)seg * p.U + u] = u < p.m + p.G ? __popcll(bm[u]) : t1 - t0;
 }
 
@@ -887,32 +887,47 @@ __global__ void __launch_bounds__(1024) route_small_kernel(RowArgs p)
     int ex[kEntryBatch];
     float w[kEntryBatch];
     load_entries<1024, true>(p, 0, 0, p.T, tid, ex, w);
-    // cnt_i (the input of Algorithm 1) straight from the TopK lists
-    if (tid < kMaxExperts) cnt_s[tid] = 0;
     for (int i = tid; i < p.n_seg * p.U; i += 1024) bm[i] = 0ull;
     __syncthreads();
-    for (int b = 0; b < entries; b += BATCH) {
-        if (!once) load_entries<1024, false>(p, b, 0, p.T, tid, ex, w);
-#pragma unroll
-        for (int q = 0; q < kEntryBatch; ++q)
-            if (ex[q] >= 0) atomicAdd(&cnt_s[ex[q]], 1);
-    }
-    __syncthreads();
-    if (tid < p.m) p.expert_cnt_out[tid] = cnt_s[tid];
-    brownout_decide<4>(cnt_s, s2_s, unit_s, p.m, p.way, p.threshold, p.full, tid, true, p.expert_unit, p.expert_in_s1);
+    // One pass of atomics: the tokens of every expert as bitmaps.  Their bits counted are cnt_i, the input of Algorithm 1
+    // (a token names an expert once); the bitmap of a united unit is the union of the experts it stands for.
     for (int b = 0; b < entries; b += BATCH) {
         if (!once) load_entries<1024, false>(p, b, 0, p.T, tid, ex, w);
 #pragma unroll
         for (int q = 0; q < kEntryBatch; ++q) {
             const int t = (b + q * 1024 + tid) >> p.lk;
-            const int u = ex[q] >= 0 ? unit_s[ex[q]] : -1;
-            if (u >= 0) atomicOr(&bm[(t >> 6) * p.U + u], 1ull << (t & 63));
+            if (ex[q] >= 0) atomicOr(&bm[(t >> 6) * p.U + ex[q]], 1ull << (t & 63));
         }
+    }
+    __syncthreads();
+    {
+        const int i = tid >> 2;
+        int c = 0;
+        if (i < p.m)
+            for (int sgm = tid & 3; sgm < p.n_seg; sgm += 4) c += __popcll(bm[sgm * p.U + i]);
+        c += __shfl_xor(c, 1);
+        c += __shfl_xor(c, 2);
+        if ((tid & 3) == 0) {
+            cnt_s[i] = c;
+            if (i < p.m) p.expert_cnt_out[i] = c;
+        }
+    }
+    __syncthreads();
+    brownout_decide<4>(cnt_s, s2_s, unit_s, p.m, p.way, p.threshold, p.full, tid, true, p.expert_unit, p.expert_in_s1);
+    for (int e = tid; e < p.n_seg * p.G; e += 1024) {
+        const int sgm = e / p.G, g = e - sgm * p.G;
+        const int lo = g * p.way, hi = min(p.m, lo + p.way);
+        unsigned long long bits = 0ull;
+        for (int i = lo; i < hi; ++i)
+            if (unit_s[i] == p.m + g) bits |= bm[sgm * p.U + i];
+        bm[sgm * p.U + p.m + g] = bits;
     }
     __syncthreads();
     for (int u = tid; u < p.U; u += 1024) {
         int run = 0;
-        if (u < p.m + p.G) {
+        if (u < p.m && unit_s[u] != u) {
+            run = 0;                                       // its tokens have a row in the united unit, or none
+        } else if (u < p.m + p.G) {
 #pragma unroll 4
             for (int sgm = 0; sgm < p.n_seg; ++sgm) {
                 segoff[sgm * p.U + u] = run;
@@ -1105,7 +1120,7 @@ hipError_t launch_route(const Dims& D, const bf16_t* x, const void* gate, const 
     }
     {
         ProfScope ps(MOE_STAGE_COUNT, s);
-        route_count_kernel<<<D.n_seg, 256, 0, s>>>(p);
+        route_count_kernel<<<D.n_seg, 1024, 0, s>>>(p);
     }
     {
         ProfScope ps(MOE_STAGE_SCAN, s);
