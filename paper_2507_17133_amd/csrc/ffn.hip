@@ -465,40 +465,40 @@ __global__ void __launch_bounds__(WM * WN * 64) ffn_gemm_kernel(GemmArgs p)
 }
 
 // ------------------------------------------------------------------------------------------------
-// Narrow kernel (4 waves, 32 or 64 rows x 64 tile columns) for launches that would leave CUs without a block: one
-// request of a model with small experts, the shared experts of a decode batch.  What bounds those is how many CUs
-// pull weights at a time, so a block takes a quarter of the columns of the kernel above and its waves split every
-// k tile instead of the columns: wave w multiplies k 16w..16w+15 of it for the whole tile, and the four partial
-// tiles are added in wave order at the end through the stage buffers.  40 KiB (32 rows) or 32 KiB of weights
-// in flight per block.
+// Narrow kernel (4 waves as 2 x 2, 32 or 64 rows x 64 tile columns, 16x16x32 MFMA) for launches that would leave CUs
+// without a block: one request of a model with small experts, the shared experts of a decode batch.  What bounds those is
+// how many CUs pull weights at a time, so a block takes a quarter of the columns of the kernel above.  40 KiB (32 rows) or
+// 32 KiB of weights in flight per block.  Every element is one chain of multiply-adds over ascending k, as in the other
+// kernels, so the kernel a launch gets does not show in the bits (waves that split each k tile instead, their four partial
+// tiles added at the end: 44.1, 98.6 and 24.2 us for the cases below, outputs 5e-5 to 3.5e-4 away).
 // Layer forward before (the kernel above) and now: one token over 128 experts of 2048 x 768 (48 and 64 blocks before, 192
-// and 256 now) 58.3 -> 43.9 us, 37 tokens with a shared expert of 2048 x 5632 (44 and 16 blocks before) 133 -> 98 us, 64 tokens
-// over 8 experts of 256 x 512 27.8 -> 23.8 us.
+// and 256 now) 58.3 -> 44.2 us, 37 tokens with a shared expert of 2048 x 5632 (44 and 16 blocks before) 133 -> 100 us, 64 tokens
+// over 8 experts of 256 x 512 27.8 -> 24.1 us.
 // ------------------------------------------------------------------------------------------------
 template <int BM, int NSTAGE, bool SWIGLU>
 __global__ void __launch_bounds__(256) ffn_gemm_narrow_kernel(GemmArgs p)
 {
-    constexpr int BK = 64, BN = 64, NW = 4, FM = BM / 32;
+    constexpr int BK = 64, BN = 64, NW = 4, TM = BM / 2, TN = BN / 2, FM = TM / 16, FN = TN / 16;
     using L = Lds<BK>;
     constexpr int RB = L::RB, RPG = L::RPG;
     constexpr int STAGE = (BM + BN) * RB;
     constexpr int LD_PER_WAVE = (BM + BN) / RPG / NW;
-    static_assert(BK / 16 == NW, "one 16-wide k step per wave");
     static_assert((BM + BN) % (RPG * NW) == 0 && BM % RPG == 0, "loader shape");
-    static_assert(NSTAGE * STAGE >= NW * FM * 2 * 4096, "the partial tiles fit the stage buffers");
     extern __shared__ __attribute__((aligned(16))) char smem[];
 
     Tile t;
     if (!decode_tile<SWIGLU ? BN / 2 : BN, SWIGLU>(p, t)) return;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int wm = wave >> 1, wn = wave & 1;
     int k_first, nk;
     k_range<BK>(p, t, k_first, nk);
 
+    // GEMM1: the two 16-column MFMA tiles of a wave are W1 and W3 of the same 16 columns
     const bf16_t* gptr[LD_PER_WAVE];
 #pragma unroll
     for (int i = 0; i < LD_PER_WAVE; ++i) {
         const int row = (wave + i * NW) * RPG + L::lane_row(lane);
-        const bf16_t* base = row < BM ? a_row_ptr(p, t, row) : b_row_ptr<BN, SWIGLU>(p, t, row - BM);
+        const bf16_t* base = row < BM ? a_row_ptr(p, t, row) : b_row_ptr<TN, SWIGLU, 16>(p, t, row - BM);
         gptr[i] = base + L::lane_chunk(lane, row) * 8 + (size_t)k_first * BK;
     }
     auto issue_loads = [&](int kt, int stage) {
@@ -509,79 +509,61 @@ __global__ void __launch_bounds__(256) ffn_gemm_narrow_kernel(GemmArgs p)
                                              (__attribute__((address_space(3))) void*)(dst + i * NW * 1024), 16, 0, 0);
     };
 
-    f32x16 acc[FM][2];
+    f32x4 acc[FM][FN];
 #pragma unroll
     for (int i = 0; i < FM; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
+        for (int j = 0; j < FN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
 #pragma unroll
     for (int q = 0; q < NSTAGE - 1; ++q)
         if (q < nk) issue_loads(q, q);
-    const int sw = ((wave * 2 + (lane >> 5)) ^ L::read_swz(lane)) << 4;
-    const int a_off = (lane & 31) * RB + sw;
+    const int a_off = (wm * TM + (lane & 15)) * RB, b_off = (BM + wn * TN + (lane & 15)) * RB;
+    const int swz = ((lane & 15) / L::WR) & (L::CPR - 1);
     int cur = 0, nxt = NSTAGE - 1;                        // stages of tile kt and of tile kt + NSTAGE - 1
     for (int kt = 0; kt < nk; ++kt) {
         if (kt + NSTAGE - 2 < nk) __builtin_amdgcn_s_waitcnt(vmcnt_imm((NSTAGE - 2) * LD_PER_WAVE));
         else __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
         lds_barrier();            // every wave's part of tile kt is in LDS; nobody still reads tile kt-1's buffer
         if (kt + NSTAGE - 1 < nk) issue_loads(kt + NSTAGE - 1, nxt);
-        const char* St = smem + cur * STAGE + a_off;
-        bf16x8 af[FM], bfr[2];
+        const char* St = smem + cur * STAGE;
+        bf16x8 af[2][FM], bfr[2][FN];
 #pragma unroll
-        for (int i = 0; i < FM; ++i) af[i] = *reinterpret_cast<const bf16x8*>(St + i * 32 * RB);
+        for (int h = 0; h < 2; ++h) {
+            const int sw = ((h * 4 + (lane >> 4)) ^ swz) << 4;
 #pragma unroll
-        for (int j = 0; j < 2; ++j) bfr[j] = *reinterpret_cast<const bf16x8*>(St + (BM + j * 32) * RB);
+            for (int i = 0; i < FM; ++i) af[h][i] = *reinterpret_cast<const bf16x8*>(St + a_off + i * 16 * RB + sw);
 #pragma unroll
-        for (int i = 0; i < FM; ++i)
+            for (int j = 0; j < FN; ++j) bfr[h][j] = *reinterpret_cast<const bf16x8*>(St + b_off + j * 16 * RB + sw);
+        }
 #pragma unroll
-            for (int j = 0; j < 2; ++j)
-                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[j], af[i], acc[i][j], 0, 0, 0);
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int i = 0; i < FM; ++i)
+#pragma unroll
+                for (int j = 0; j < FN; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bfr[h][j], af[h][i], acc[i][j], 0, 0, 0);
         cur = cur == NSTAGE - 1 ? 0 : cur + 1;
         nxt = nxt == NSTAGE - 1 ? 0 : nxt + 1;
     }
-    __syncthreads();                                      // every wave has left the stage buffers
-    // partial tile of wave w: [w][i][j][q][lane] four floats (columns 8q + 4 (lane>>5) + 0..3 of row lane & 31)
-    f32x4* red = reinterpret_cast<f32x4*>(smem);
-#pragma unroll
-    for (int i = 0; i < FM; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                f32x4 v;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) v[e] = acc[i][j][4 * q + e];
-                red[(((wave * FM + i) * 2 + j) * 4 + q) * 64 + lane] = v;
-            }
-    __syncthreads();
-    // wave w finishes column group q = w of both 32-column halves
+    // a lane holds, for output row lane & 15 of each MFMA tile, the columns 4 (lane >> 4) + 0..3
     unsigned short* out = reinterpret_cast<unsigned short*>(p.out) + (size_t)t.kslice * p.plane;
-    const int cq = t.n0 + 8 * wave + 4 * (lane >> 5);
+    const int col = t.n0 + wn * (SWIGLU ? TN / 2 : TN) + 4 * (lane >> 4);
 #pragma unroll
     for (int i = 0; i < FM; ++i) {
-        f32x4 sum[2];
-#pragma unroll
-        for (int j = 0; j < 2; ++j) {
-            sum[j] = red[((i * 2 + j) * 4 + wave) * 64 + lane];
-#pragma unroll
-            for (int w = 1; w < NW; ++w) sum[j] += red[(((w * FM + i) * 2 + j) * 4 + wave) * 64 + lane];
-        }
-        const int rl = i * 32 + (lane & 31);
+        const int rl = wm * TM + i * 16 + (lane & 15);
         if (rl >= t.nrows) continue;
-        unsigned short* orow = out + (long)(t.row0 + rl) * p.ldo;
+        unsigned short* orow = out + (long)(t.row0 + rl) * p.ldo + col;
         if (SWIGLU) {
             float h[4];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) h[e] = swiglu(sum[0][e], sum[1][e]);
-            *reinterpret_cast<uint2*>(orow + cq) = make_uint2(pack_bf16(h[0], h[1]), pack_bf16(h[2], h[3]));
+            for (int e = 0; e < 4; ++e) h[e] = swiglu(acc[i][0][e], acc[i][1][e]);
+            *reinterpret_cast<uint2*>(orow) = make_uint2(pack_bf16(h[0], h[1]), pack_bf16(h[2], h[3]));
         } else {
 #pragma unroll
-            for (int j = 0; j < 2; ++j)
-                *reinterpret_cast<uint2*>(orow + cq + j * 32) =
-                    make_uint2(pack_f16(sum[j][0], sum[j][1]), pack_f16(sum[j][2], sum[j][3]));
+            for (int j = 0; j < FN; ++j)
+                *reinterpret_cast<uint2*>(orow + j * 16) = make_uint2(pack_f16(acc[i][j][0], acc[i][j][1]),
+                                                                      pack_f16(acc[i][j][2], acc[i][j][3]));
         }
     }
 }

@@ -39,3 +39,20 @@ def test_small_tiles(T, d, F, m, K, way, Ns, Fs, threshold):
     want = O.forward_tokens(npf(L.x), idx, w, unit, way, npf(L.experts), npf(united_cpu), npf(L.shared))
     assert np.isfinite(got).all()
     assert rel_err(got, want) <= OUT_TOL
+
+
+# m, K, d, F and batch sizes whose experts' rows go through different kernels: narrow with 32 and 64 rows and the 128-row
+# kernel for few experts (28 to 56 blocks of 256 columns), narrow with 32 rows and the 64-row kernel for 64 experts.  F < 1024:
+# one K slice; the gate sums in one order at all of these sizes.
+@pytest.mark.parametrize("m,K,d,F,sizes", [(8, 2, 1024, 896, (20, 100, 600)), (64, 8, 128, 960, (3, 96))])
+def test_the_kernel_of_a_launch_does_not_show_in_the_bits(m, K, d, F, sizes):
+    print(m, K, d, F, sizes, flush=True)
+    cfg = WL.LayerConfig("narrow_bits", T=max(sizes), d=d, F=F, m=m, K=K, way=8)
+    L = WL.make_layer(cfg, 5, "cpu")
+    x, gate_w, gate_b = L.x.to("cuda"), L.gate_w.to("cuda"), None if L.gate_b is None else L.gate_b.to("cuda")
+    experts = tuple(a.to("cuda") for a in L.experts)
+    c = P.config_of(cfg)
+    out = {T: P.moe_forward(c, x[:T].contiguous(), gate_w, gate_b, experts) for T in sizes}
+    torch.cuda.synchronize()
+    for T in sizes[1:]:
+        assert torch.equal(out[T][:sizes[0]], out[sizes[0]]), T
