@@ -116,7 +116,10 @@ __device__ __forceinline__ float sum_partials(const double* part, int n, float o
 {
     double s = 0.0;
     for (int i = threadIdx.x; i < n; i += 256) s += part[i];
-    return offset + (float)fmax(block_sum(s, red) * scale, 0.0);   // sums of squares: not below zero by rounding
+    // the teachers' spread is a difference of sums and may round below zero; a comparison, so that NaN stays NaN (fmax would
+    // turn the loss of a training run that has diverged into the best one there is)
+    const double t = block_sum(s, red) * scale;
+    return offset + (float)(t < 0.0 ? 0.0 : t);
 }
 __global__ void __launch_bounds__(256) sum_partials_kernel(const char* part, size_t part_stride, int n, const char* offset,
                                                            size_t offset_stride, double scale, float* out, size_t out_stride)
