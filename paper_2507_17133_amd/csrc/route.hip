@@ -697,14 +697,16 @@ __device__ __forceinline__ void load_entries(const RowArgs& p, int first, int t0
 
 // The row of one entry (token t, slot j; u: its unit or -1, w: its weight), called by whole wavefronts.  A united unit
 // that several entries of the token name gets one row, at the first of them, with the sum of their weights in TopK
-// order.  bmw: bitmaps of the token's segment, soff: rows of every unit in earlier segments.
+// order.  An expert is named twice only where TopK ran out of logits above -infinity (or met NaN), and then all but the first
+// of its entries have no positive weight: they share the row, which keeps the weight of the last.  bmw: bitmaps of the
+// token's segment, soff: rows of every unit in earlier segments.
 __device__ __forceinline__ void scatter_entry(const RowArgs& p, const unsigned long long* bmw, const int* off_s,
                                               const int32_t* soff, int t, int j, int u, float w, bool valid, int lane)
 {
-    bool first = u >= 0;
+    bool first = u >= 0, last = true;
+    const int base = lane & ~((1 << p.lk) - 1);
+    const float own = w;
     if (__ballot(u >= p.m) != 0) {
-        const int base = lane & ~((1 << p.lk) - 1);
-        const float own = w;
         for (int q = 0; q < p.K; ++q) {
             const int uq = __shfl(u, base + q);
             const float wq = __shfl(own, base + q);
@@ -714,11 +716,17 @@ __device__ __forceinline__ void scatter_entry(const RowArgs& p, const unsigned l
             }
         }
     }
+    if (__ballot(first && !(own > 0.0f)) != 0) {
+        for (int q = 0; q < p.K; ++q)
+            if (__shfl(u, base + q) == u && u < p.m && q > j) last = false;
+    }
     int row = -1;
     if (first) {
         row = off_s[u] + soff[u] + __popcll(bmw[u] & ((1ull << (t & 63)) - 1ull));
-        p.row_token[row] = t;
-        p.row_weight[row] = w;
+        if (last) {
+            p.row_token[row] = t;
+            p.row_weight[row] = w;
+        }
     }
     if (valid) p.token_rows[(size_t)t * (p.K + p.Ns) + j] = row;
 }
@@ -878,6 +886,7 @@ __global__ void __launch_bounds__(1024) route_small_kernel(RowArgs p)
     __shared__ unsigned char s2_s[kMaxExperts];
     __shared__ int ucnt_s[kMaxUnits];
     __shared__ int off_s[kMaxUnits + 1];
+    __shared__ int wsum[16];
     unsigned long long* bm = reinterpret_cast<unsigned long long*>(rsm);                      // [n_seg][U]
     int* segoff = reinterpret_cast<int*>(rsm + (size_t)p.n_seg * p.U * 8);                     // [n_seg][U]
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -889,8 +898,8 @@ __global__ void __launch_bounds__(1024) route_small_kernel(RowArgs p)
     load_entries<1024, true>(p, 0, 0, p.T, tid, ex, w);
     for (int i = tid; i < p.n_seg * p.U; i += 1024) bm[i] = 0ull;
     __syncthreads();
-    // One pass of atomics: the tokens of every expert as bitmaps.  Their bits counted are cnt_i, the input of Algorithm 1
-    // (a token names an expert once); the bitmap of a united unit is the union of the experts it stands for.
+    // One pass of atomics: the tokens of every expert as bitmaps.  Their bits counted are cnt_i, the input of Algorithm 1,
+    // where no token names an expert twice; the bitmap of a united unit is the union of the experts it stands for.
     for (int b = 0; b < entries; b += BATCH) {
         if (!once) load_entries<1024, false>(p, b, 0, p.T, tid, ex, w);
 #pragma unroll
@@ -900,19 +909,37 @@ __global__ void __launch_bounds__(1024) route_small_kernel(RowArgs p)
         }
     }
     __syncthreads();
+    int c = 0;                                             // of expert tid >> 2
+    if ((tid >> 2) < p.m)
+        for (int sgm = tid & 3; sgm < p.n_seg; sgm += 4) c += __popcll(bm[sgm * p.U + (tid >> 2)]);
+    c += __shfl_xor(c, 1);
+    c += __shfl_xor(c, 2);
+    if ((tid & 3) == 0) cnt_s[tid >> 2] = c;
     {
-        const int i = tid >> 2;
-        int c = 0;
-        if (i < p.m)
-            for (int sgm = tid & 3; sgm < p.n_seg; sgm += 4) c += __popcll(bm[sgm * p.U + i]);
-        c += __shfl_xor(c, 1);
-        c += __shfl_xor(c, 2);
-        if ((tid & 3) == 0) {
-            cnt_s[i] = c;
-            if (i < p.m) p.expert_cnt_out[i] = c;
-        }
+        int all = c;                                       // of the wavefront's 16 experts
+#pragma unroll
+        for (int o = 4; o < 64; o <<= 1) all += __shfl_xor(all, o);
+        if (lane == 0) wsum[wave] = all;
     }
     __syncthreads();
+    {
+        int all = 0;
+#pragma unroll
+        for (int w8 = 0; w8 < 16; ++w8) all += wsum[w8];
+        if (all != p.T * p.K) {                            // the same in every thread
+            // a token that names an expert twice (see scatter_entry): cnt_i counts entries
+            if (tid < kMaxExperts) cnt_s[tid] = 0;
+            __syncthreads();
+            for (int b = 0; b < entries; b += BATCH) {
+                if (!once) load_entries<1024, false>(p, b, 0, p.T, tid, ex, w);
+#pragma unroll
+                for (int q = 0; q < kEntryBatch; ++q)
+                    if (ex[q] >= 0) atomicAdd(&cnt_s[ex[q]], 1);
+            }
+            __syncthreads();
+        }
+    }
+    if (tid < p.m) p.expert_cnt_out[tid] = cnt_s[tid];
     brownout_decide<4>(cnt_s, s2_s, unit_s, p.m, p.way, p.threshold, p.full, tid, true, p.expert_unit, p.expert_in_s1);
     for (int e = tid; e < p.n_seg * p.G; e += 1024) {
         const int sgm = e / p.G, g = e - sgm * p.G;
