@@ -1076,11 +1076,14 @@ static hipError_t launch_gate(GateArgs g, void* scratch, size_t bytes, hipStream
         if (small) gate_logits_kernel<1, 1, 1, 4, 3><<<tiles * sl, 256, kGateLds16, s>>>(p);
         else if (large) gate_logits_kernel<4, 2, 2, 2, 2><<<tiles * sl, 256, kGateLds128, s>>>(p);
         else gate_logits_kernel<2, 2, 2, 2, 2><<<tiles * sl, 256, kGateLds64, s>>>(p);
+        hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
         if (p.expert_cnt == nullptr) launch_topk<256>(p, s);
         else if (p.n_slice > 1) launch_topk<512>(p, s);     // fewer, larger blocks: each flushes a histogram
         else launch_topk<1024>(p, s);                       // (partial logits need the registers, logits do not)
+        if ((e = hipGetLastError()) != hipSuccess) return e;
     }
-    return hipGetLastError();
+    return hipSuccess;
 }
 
 hipError_t launch_route(const Dims& D, const bf16_t* x, const void* gate, const float* gate_bias,
@@ -1106,6 +1109,7 @@ hipError_t launch_route(const Dims& D, const bf16_t* x, const void* gate, const 
         prep_kernel<<<blocks, 256, 0, s>>>(split ? static_cast<const float*>(gate) : nullptr, D.m, D.m_pad, D.d,
                                            split ? reinterpret_cast<unsigned short*>(gate_split) : nullptr,
                                            small ? nullptr : R.expert_cnt);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     {
         ProfScope ps(MOE_STAGE_GATE, s);
@@ -1125,7 +1129,7 @@ hipError_t launch_route(const Dims& D, const bf16_t* x, const void* gate, const 
             // at most 16 experts beyond kFewExpertsTokens tokens
             gate_few_kernel<<<ceil_div(D.T, 16), 512, kGateFewLds, s>>>(g);
         } else {
-            (void)launch_gate(g, logits, logit_bytes, s);
+            if ((e = launch_gate(g, logits, logit_bytes, s)) != hipSuccess) return e;
         }
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }

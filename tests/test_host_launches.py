@@ -1,0 +1,34 @@
+"""The host code's launches, seen through a stand-in HIP runtime (no GPU): every launch that fails ends its call with an error,
+and no kernel runs on what the failed one should have written."""
+import os
+
+from paper_2507_17133_amd import binding as B
+from tests._fake_hip import trace
+
+if not os.path.exists(B.LIB_PATH):
+    from paper_2507_17133_amd import build as _build
+    _build.build()
+
+#       d, F, m, K, way, n_shared, F_s, score_fn, residual, gate format
+CFGS = {"few": [256, 512, 8, 2, 4, 0, 0, 0, 0, 0], "many": [1024, 256, 60, 4, 8, 1, 512, 0, 0, 0],
+        "packed": [1024, 256, 256, 8, 8, 1, 256, 0, 0, 1], "wide": [512, 1024, 40, 20, 4, 0, 0, 0, 0, 1]}
+CALLS = [dict(entry=e, cfg=c, T=T, threshold=thr) for e in ("route", "route_static", "forward") for c in CFGS.values()
+         for T in (3, 700, 3000) for thr in (1.0, 0.4)]
+CALLS = [c for c in CALLS if not (c["entry"] == "route_static" and c["cfg"] is CFGS["wide"] and c["T"] == 3000)]
+CALLS += [dict(entry="forward", cfg=CFGS["few"], T=3000, own_route=1), dict(entry="build", cfg=CFGS["many"], T=400),
+          dict(entry="distill", cfg=CFGS["few"], T=128, steps=2)]
+
+
+def test_every_failing_launch_ends_its_call(tmp_path):
+    whole = trace(CALLS, tmp_path)
+    broken, where = [], []
+    for c, r in zip(CALLS, whole):
+        assert r["status"] == 0 and len(r["launches"]) >= 2, c
+        for k in range(len(r["launches"])):
+            broken.append(dict(c, fail=k))
+            where.append(r["launches"][k]["name"])
+    for c, name, r in zip(broken, where, trace(broken, tmp_path)):
+        assert r["status"] == -6, (name, c)
+        if name.startswith(("gate_", "prep_")):
+            after = [l["name"] for l in r["launches"][c["fail"] + 1:]]
+            assert not any(n.startswith(("route_", "ffn_", "combine")) for n in after), (name, after, c)
