@@ -165,9 +165,12 @@ moe_status moe_build_united(const moe_config *cfg, const moe_ffn_weights *expert
  * run in bf16 with fp32 accumulation, teacher outputs are held in half precision.
  * loss_history (device, [G][steps+1] fp32, may be NULL) receives the loss before every
  * step and after the last.  A group with one member is not trained: its student becomes
- * a copy of that member (the minimiser, loss 0).  Workspace: moe_distill_workspace_size bytes.
+ * a copy of that member (the minimiser, loss 0).  Workspace: moe_distill_workspace_size
+ * bytes serve this n_calib and every smaller one (the size never shrinks as n_calib
+ * grows).  They hold up to eight groups, which are trained side by side where one does
+ * not fill the GPU; with fewer bytes fewer at a time, down to one, with the same results.
  * Errors: n_calib not a positive multiple of 64 (MOE_ERR_SHAPE), NULL pointers,
- * steps < 0, lr < 0 or NaN, workspace too small.
+ * steps < 0, lr < 0 or NaN, workspace too small for one group.
  */
 moe_status moe_distill_workspace_size(const moe_config *cfg, int32_t n_calib, size_t *bytes);
 moe_status moe_distill_united(const moe_config *cfg, const moe_ffn_weights *experts, const moe_ffn_weights_out *united,

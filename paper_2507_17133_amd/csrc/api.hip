@@ -661,18 +661,13 @@ static moe_status check_distill(const moe_config* cfg, int32_t n_calib)
     return check_T(cfg, n_calib);
 }
 
-static size_t distill_bytes(const Dims& D, int n_calib)
-{
-    return distill_buffer_bytes(n_calib, D.d, D.F, distill_groups_at_once(n_calib, D.d, D.F, trained_groups(D.m, D.way)));
-}
-
 moe_status moe_distill_workspace_size(const moe_config* cfg, int32_t n_calib, size_t* bytes)
 {
     if (!bytes) return MOE_ERR_INVALID_ARG;
     moe_status st = check_distill(cfg, n_calib);
     if (st != MOE_OK) return st;
     const Dims D = make_dims(*cfg, n_calib);
-    *bytes = align_up(carve_workspace(D).total, 256) + distill_bytes(D, n_calib);
+    *bytes = align_up(carve_workspace(D).total, 256) + distill_wanted_bytes(n_calib, D.d, D.F, trained_groups(D.m, D.way));
     return MOE_OK;
 }
 
@@ -697,7 +692,11 @@ moe_status moe_distill_united(const moe_config* cfg, const moe_ffn_weights* expe
     D.ksplit = 1;
     const TilePlan plan = make_tile_plan(n_calib, true);
     const size_t fwd_bytes = align_up(W.total, 256);
-    if (!workspace || workspace_bytes < fwd_bytes + distill_bytes(D, n_calib)) return MOE_ERR_WORKSPACE;
+    // groups trained side by side: as many as keep the chip busy and the workspace holds, one at least
+    const int trained = trained_groups(m, way);
+    const int at_once = !workspace || workspace_bytes < fwd_bytes ? 0 :
+                            distill_groups_that_fit(n_calib, D.d, D.F, trained, workspace_bytes - fwd_bytes);
+    if (at_once < 1) return MOE_ERR_WORKSPACE;
     if (reinterpret_cast<uintptr_t>(workspace) & 255u) return MOE_ERR_ALIGNMENT;
     void* buf = static_cast<char*>(workspace) + fwd_bytes;
     const FfnWeights fe = to_ffn(experts), fu = to_ffn(&united_ro), fs{nullptr, nullptr, nullptr};
@@ -710,8 +709,6 @@ moe_status moe_distill_united(const moe_config* cfg, const moe_ffn_weights* expe
     const size_t dF = (size_t)D.d * D.F;
     bf16_t* wu[3] = {static_cast<bf16_t*>(united->w1), static_cast<bf16_t*>(united->w3), static_cast<bf16_t*>(united->w2)};
     hipError_t e;
-    const int trained = trained_groups(m, way);
-    const int at_once = distill_groups_at_once(n_calib, D.d, D.F, trained);
     if (trained > 0 && (e = launch_repeat_tokens(row_token, n_calib, D.slots, s)) != hipSuccess)
         return hip_fail(e, "moe_distill_united/rows");
     for (int g0 = 0; g0 < trained; g0 += at_once) {

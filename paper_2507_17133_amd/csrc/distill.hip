@@ -426,7 +426,7 @@ hipError_t init_distill_kernels()
 }
 
 // Groups trained side by side: enough that the smallest of a step's GEMMs gives every CU two blocks, at most 8.
-int distill_groups_at_once(int n, int d, int F, int n_groups)
+static int distill_groups_at_once(int n, int d, int F, int n_groups)
 {
     const int64_t t = std::min((int64_t)ceil_div(n, 128) * ceil_div(F, 128), (int64_t)ceil_div(n, 128) * ceil_div(d, 128));
     return (int)std::max<int64_t>(1, std::min<int64_t>({n_groups, (512 + t - 1) / t, 8}));
@@ -467,6 +467,29 @@ static DistillLayout distill_layout(int n, int d, int F, int groups)
 }
 
 size_t distill_buffer_bytes(int n, int d, int F, int groups) { return distill_layout(n, d, F, groups).total; }
+
+// Fewer tokens ask for more groups side by side, so the bytes they would take rise and fall with n.  A workspace is sized for
+// n and every smaller number: the most that g groups take at the largest n' <= n that asks for them (from t tiles of the
+// smallest GEMM: ceil(512 / t) >= g, t (g - 1) < 512).  Beyond kSideBySide bytes the weights and moments are so large that one
+// group's kAdam fills the chip by itself (DeepSeek-V3 shape: 2688 blocks and 0.5 GB of state per step).
+constexpr size_t kSideBySide = (size_t)1 << 30;
+size_t distill_wanted_bytes(int n, int d, int F, int n_groups)
+{
+    size_t most = distill_buffer_bytes(n, d, F, 1);
+    for (int g = 2; g <= std::min(8, n_groups); ++g) {
+        const int64_t rows = 511 / ((int64_t)(g - 1) * std::min(ceil_div(F, 128), ceil_div(d, 128)));
+        if (rows < 1) break;
+        most = std::max(most, std::min(distill_buffer_bytes((int)std::min<int64_t>(n, rows * 128), d, F, g), kSideBySide));
+    }
+    return most;
+}
+
+int distill_groups_that_fit(int n, int d, int F, int n_groups, size_t bytes)
+{
+    int g = distill_groups_at_once(n, d, F, n_groups);
+    while (g > 0 && distill_buffer_bytes(n, d, F, g) > bytes) --g;
+    return g;
+}
 
 hipError_t launch_teacher_stats(const bf16_t* y_half, int b, bool first, bool last, int k, int n, int d, int F, int g, void* buf,
                                 hipStream_t s)

@@ -134,10 +134,11 @@ hipError_t launch_sqdiff(const bf16_t* yu, const bf16_t* yo, int b, size_t n, in
                          double* part, float* loss, hipStream_t s);
 
 // United-expert distillation (distill.hip).  buf: distill_buffer_bytes of device memory for `groups` groups trained
-// side by side (distill_groups_at_once).
+// side by side; one group is enough, distill_wanted_bytes hold as many as keep the chip busy (it grows with n).
 hipError_t init_distill_kernels();
-int distill_groups_at_once(int n, int d, int F, int n_groups);
 size_t distill_buffer_bytes(int n, int d, int F, int groups);
+size_t distill_wanted_bytes(int n, int d, int F, int n_groups);
+int distill_groups_that_fit(int n, int d, int F, int n_groups, size_t bytes);       // 0: not even one
 hipError_t launch_fill_f32(float* p, size_t n, float v, hipStream_t s);
 // FFN output rows (half) of b of the k teachers of group g, n*d elements apart; first / last: of the k
 hipError_t launch_teacher_stats(const bf16_t* y_half, int b, bool first, bool last, int k, int n, int d, int F, int g, void* buf,
