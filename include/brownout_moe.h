@@ -200,10 +200,12 @@ moe_status moe_route(const moe_config *cfg, const void *x, int32_t T, const void
  * moe_route for callers that cannot allocate device memory or hand over a workspace
  * (code under HIP graph capture, tight serving loops, harnesses that forbid
  * allocation): same arguments without the workspace, same results bit for bit.  Its
- * work space is a fixed 8 MiB array inside the library's device image (one per
- * GPU, held until the process ends); fields of `out` left NULL live there too.
+ * work space is a fixed 10 MiB array inside the library's device image (one per
+ * GPU, held until the process ends): 8 MiB for the routing artefacts, where fields of
+ * `out` left NULL live too, and the gate's logits in the rest (a batch they do not fit
+ * goes through it in pieces).
  * The call allocates and frees nothing (profiling, moe_profile_enable, must be off:
- * it creates events).  A batch whose routing work space exceeds 8 MiB is rejected
+ * it creates events).  A batch whose routing artefacts exceed 8 MiB is rejected
  * with MOE_ERR_WORKSPACE before anything is launched; the need is about
  * T*(K+N_s)*12 + T*K*8 + T/64*U*8 bytes, plus 6*16*ceil(m/16)*d for an unpacked gate of
  * more than 16 experts (pack it with moe_pack_gate to save that).  All calls on one GPU share the array:

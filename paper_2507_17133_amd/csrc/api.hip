@@ -14,7 +14,7 @@
 // that lives in the library's own device image.  In host code this name is only a handle for
 // hipGetSymbolAddress; the device address is looked up once per device in ensure_device_init.
 constexpr size_t kStaticScratchBytes = (size_t)8 << 20;
-// Behind it: room for the gate's logits (a larger batch goes through it in pieces).
+// Behind it: room for the gate's logits, with what the routing work space leaves (larger batches go through it in pieces).
 constexpr size_t kStaticLogitBytes = (size_t)2 << 20;
 static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes + kStaticLogitBytes];
 
@@ -476,7 +476,7 @@ moe_status moe_route_static(const moe_config* cfg, const void* x, int32_t T, con
     // the first kernel), so what an earlier call left there does not matter
     e = launch_route(D, static_cast<const bf16_t*>(x), gate_w, gate_bias, threshold, use_full_brownout ? 1 : 0, R,
                      at<bf16_t>(sp, W.gate_split), at<int32_t>(sp, W.seg_cnt), at<int32_t>(sp, W.seg_off),
-                     at<void>(sp, kStaticScratchBytes), kStaticLogitBytes, none, s);
+                     at<void>(sp, need), kStaticScratchBytes + kStaticLogitBytes - need, none, s);
     if (e != hipSuccess) return hip_fail(e, "moe_route_static");
     return MOE_OK;
 }

@@ -410,7 +410,7 @@ __global__ void __launch_bounds__(256) gate_small_kernel(GateArgs p, const float
 // x 256), and K in up to kGateSlices slices until two blocks per CU are there (one per CU: 36 us instead of 26 at 8192
 // x 128; 16 slices: no faster, and TopK reads twice the partial sums).
 constexpr int kGateExperts = 64;       // experts of a block
-constexpr int kGateSmallTokens = 2048, kGateLargeTokens = 32768, kGateBlocks = 512, kGateSlices = 8;
+constexpr int kGateSmallTokens = 2048, kGateLargeTokens = 32768, kGateBlocks = 512, kGateSlices = 8;   // kGate..Tokens: x n_eb
 template <int MT, int WM>
 constexpr int gate_rows() { return 3 * kGateExperts + 16 * MT * WM; }
 
@@ -1050,12 +1050,21 @@ static void launch_topk(const GateArgs& p, hipStream_t s)
     else gate_topk_kernel<16, THREADS><<<blocks, THREADS, 0, s>>>(p);
 }
 
+static int gate_token_tile(int64_t T, int n_eb)
+{
+    return T * n_eb <= kGateSmallTokens ? 16 : T * n_eb >= kGateLargeTokens ? 128 : 64;
+}
+
 // Logits and TopK of a batch with more than 16 experts.  `scratch` holds the logits; a batch whose logits it cannot
-// hold goes through it in pieces.
+// hold goes through it in pieces.  How K is sliced decides the order of a logit's sum, so it follows from the batch alone
+// (T, m, d): the same bits whatever the scratch holds.  The token tile of a piece does not (every tile adds up alike).
 static hipError_t launch_gate(GateArgs g, void* scratch, size_t bytes, hipStream_t s)
 {
     const int T = g.T, n_eb = ceil_div(g.m_pad, kGateExperts), ksteps = g.d / 64;
-    const int64_t most = (int64_t)(bytes / ((size_t)g.m_pad * 4));
+    int sl = std::max(1, std::min({kGateBlocks / (ceil_div(T, gate_token_tile(T, n_eb)) * n_eb), kGateSlices, ksteps / 2}));
+    sl = ceil_div(ksteps, ceil_div(ksteps, sl));                         // no empty slice
+    g.n_slice = sl;
+    const int64_t most = (int64_t)(bytes / ((size_t)g.m_pad * (sl == 1 ? 4 : 8 * sl)));
     const int chunk = (int)std::min<int64_t>(T, most >= 64 ? most / 64 * 64 : std::max<int64_t>(most, 1));
     g.logits = scratch;
     for (int c0 = 0; c0 < T; c0 += chunk) {
@@ -1066,16 +1075,10 @@ static hipError_t launch_gate(GateArgs g, void* scratch, size_t bytes, hipStream
         p.topk_w = g.topk_w + (size_t)c0 * g.K;
         if (g.near_tie != nullptr) p.near_tie = g.near_tie + c0;
         if (c0 > 0) p.clear_cnt = nullptr;
-        const bool small = (int64_t)p.T * n_eb <= kGateSmallTokens;
-        const bool large = (int64_t)p.T * n_eb >= kGateLargeTokens;
-        const int tiles = ceil_div(p.T, small ? 16 : large ? 128 : 64) * n_eb;
-        int sl = std::max(1, std::min({kGateBlocks / tiles, kGateSlices, ksteps / 2}));
-        sl = (int)std::min<size_t>(sl, bytes / ((size_t)p.T * p.m_pad * 8));
-        sl = sl < 2 ? 1 : ceil_div(ksteps, ceil_div(ksteps, sl));        // no empty slice
-        p.n_slice = sl;
-        if (small) gate_logits_kernel<1, 1, 1, 4, 3><<<tiles * sl, 256, kGateLds16, s>>>(p);
-        else if (large) gate_logits_kernel<4, 2, 2, 2, 2><<<tiles * sl, 256, kGateLds128, s>>>(p);
-        else gate_logits_kernel<2, 2, 2, 2, 2><<<tiles * sl, 256, kGateLds64, s>>>(p);
+        const int tile = gate_token_tile(p.T, n_eb), blocks = ceil_div(p.T, tile) * n_eb * sl;
+        if (tile == 16) gate_logits_kernel<1, 1, 1, 4, 3><<<blocks, 256, kGateLds16, s>>>(p);
+        else if (tile == 128) gate_logits_kernel<4, 2, 2, 2, 2><<<blocks, 256, kGateLds128, s>>>(p);
+        else gate_logits_kernel<2, 2, 2, 2, 2><<<blocks, 256, kGateLds64, s>>>(p);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
         if (p.expert_cnt == nullptr) launch_topk<256>(p, s);

@@ -27,11 +27,15 @@ def test_routing_at_the_cuts_of_the_gate(T, d, m, K):
     check_route(R, oracle_route(L, cfg, 0.5), cfg, 0.5, False)
 
 
-@pytest.mark.parametrize("T", [2048, 2049, 9000])
-def test_a_batch_in_pieces_routes_like_the_whole(T):
-    cfg = WL.LayerConfig("gate_pieces", T=T, d=128, F=1024, m=256, K=4, way=8, zipf_s=1.0)
-    L = WL.make_layer(cfg, T, "cuda")
+# d = 128: K is not sliced; the rest: two to eight slices, which the pieces of the smaller scratch have to keep
+@pytest.mark.parametrize("T,d,m", [(2048, 128, 256), (2049, 128, 256), (9000, 128, 256), (2048, 7168, 256), (8192, 2048, 128),
+                                   (300, 1088, 200), (1021, 4096, 256), (40, 1024, 17), (4999, 2048, 60)])
+def test_a_batch_in_pieces_routes_like_the_whole(T, d, m):
+    print(T, d, m, flush=True)
+    cfg = WL.LayerConfig("gate_pieces", T=T, d=d, F=1024, m=m, K=4, way=8, zipf_s=1.0)
+    L = WL.make_layer(cfg.with_(F=64), T, "cuda")
     c = P.config_of(cfg)
+    L.gate_w, c = P.pack_gate(c, L.gate_w), P.with_packed_gate(c)
     want = P.moe_route(c, L.x, L.gate_w, L.gate_b, 0.4)
     got = P.alloc_route_out(c, T)
     P.moe_route_static(c, L.x, L.gate_w, L.gate_b, 0.4, False, got)

@@ -32,3 +32,21 @@ def test_every_failing_launch_ends_its_call(tmp_path):
         if name.startswith(("gate_", "prep_")):
             after = [l["name"] for l in r["launches"][c["fail"] + 1:]]
             assert not any(n.startswith(("route_", "ffn_", "combine")) for n in after), (name, after, c)
+
+
+def test_slices_of_the_gate_do_not_depend_on_the_scratch(tmp_path):
+    """The order in which a logit is added up: the same number of K slices in moe_route, moe_forward and every piece of
+    moe_route_static."""
+    calls = [dict(entry=e, cfg=[d, 256, m, 4, 8, 0, 0, 0, 0, 1], T=T) for d, m in ((7168, 256), (2048, 128), (2048, 60), (1088, 200), (64, 17))
+             for T in (1, 40, 300, 1021, 2048, 4999, 8192) for e in ("route", "forward", "route_static")]
+    got = trace(calls, tmp_path)
+    several = 0
+    for c, r in zip(calls, got):
+        assert r["status"] == 0
+        pieces = [l for l in r["launches"] if l["name"].startswith("gate_logits")]
+        assert sum(l["T"] for l in pieces) == c["T"]
+        if c["entry"] == "route":
+            want = pieces[0]["n_slice"]
+        assert {l["n_slice"] for l in pieces} == {want}, c
+        several += want > 1 and len(pieces) > 1
+    assert several >= 3
