@@ -220,7 +220,6 @@ Workspace carve_workspace(const Dims& D)
     auto take = [&](size_t bytes) { size_t at = o; o = align_up(o + bytes, 256); return at; };
     W.tiles0 = take(16 + (size_t)D.tile_cap * 16);
     W.tiles1 = take(16 + (size_t)D.tile_cap * 16);
-    W.tiles2 = take(16 + (size_t)D.tile_cap * 16);
     W.h_rows = D.row_cap;
     W.y_rows = y_rows_bound(D);
     // one tile of rows past the end: GEMM2's ragged last tile reads (and discards) whole tiles of H
@@ -538,9 +537,8 @@ moe_status moe_forward(const moe_config* cfg, const void* x, int32_t T, const vo
     jobs.job[0].table = at<int32_t>(workspace, W.tiles0);
     // a threshold of 1 browns nothing out (a route of the caller's may, whatever threshold comes with it)
     jobs.job[0].bm_hi = route || threshold < 1.0 ? taller_tile_rows(D, jobs.job[0].plan.bm, dev.n_cu) : 0;
-    jobs.job[0].table_hi = at<int32_t>(workspace, W.tiles2);
     jobs.job[0].m = D.m; jobs.job[0].entries = T * D.K;
-    jobs.job[1].bm_hi = 0; jobs.job[1].table_hi = nullptr; jobs.job[1].m = 0; jobs.job[1].entries = 0;
+    jobs.job[1].bm_hi = 0; jobs.job[1].m = 0; jobs.job[1].entries = 0;
     jobs.job[1].u_lo = D.m + D.G; jobs.job[1].u_hi = D.U;
     jobs.job[1].plan = make_shared_plan(D, dev.n_cu);
     jobs.job[1].table = at<int32_t>(workspace, W.tiles1);
@@ -559,7 +557,7 @@ moe_status moe_forward(const moe_config* cfg, const void* x, int32_t T, const vo
     for (int j = 0; j < jobs.n; ++j) {
         const TileJob& J = jobs.job[j];
         e = launch_ffn(D, J.u_lo, J.u_hi, j == 0 ? D.F : D.Fs, J.plan, xb, R.row_token, fe, fu, fs, J.table, H, Y, partial, s,
-                       J.bm_hi, J.table_hi);
+                       J.bm_hi);
         if (e != hipSuccess) return hip_fail(e, j == 0 ? "moe_forward/ffn" : "moe_forward/ffn_shared");
     }
     e = launch_combine(D, xb, Y, R.token_rows, R.row_weight, static_cast<bf16_t*>(out), s);

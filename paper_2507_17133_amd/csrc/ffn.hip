@@ -111,10 +111,18 @@ struct Tile {
     const bf16_t *Wa, *Wb;
 };
 
-template <int BNC, bool SWIGLU>
+// M tiles of a launch with tiles of BM rows: none if the table was cut for the job's other height.
+template <int BM>
+__device__ __forceinline__ int m_tiles(const GemmArgs& p)
+{
+    const int2 head = *reinterpret_cast<const int2*>(p.table);      // one load, not two in a row
+    return head.y == BM ? head.x : 0;
+}
+
+template <int BM, int BNC, bool SWIGLU>
 __device__ __forceinline__ bool decode_tile(const GemmArgs& p, Tile& t)
 {
-    const int n_mt = p.table[0];
+    const int n_mt = m_tiles<BM>(p);
     const int tiles = n_mt * p.n_ntiles;
     const int total = tiles * p.ksplit;
     const int chunk = (total + 7) >> 3;
@@ -402,7 +410,7 @@ __global__ void __launch_bounds__(WM * WN * 64) ffn_gemm_kernel(GemmArgs p)
     extern __shared__ __attribute__((aligned(16))) char smem[];
 
     Tile t;
-    if (!decode_tile<SWIGLU ? BN / 2 : BN, SWIGLU>(p, t)) return;
+    if (!decode_tile<BM, SWIGLU ? BN / 2 : BN, SWIGLU>(p, t)) return;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave / WN, wn = wave % WN;
     int k_first, nk;
@@ -487,7 +495,7 @@ __global__ void __launch_bounds__(256) ffn_gemm_narrow_kernel(GemmArgs p)
     extern __shared__ __attribute__((aligned(16))) char smem[];
 
     Tile t;
-    if (!decode_tile<SWIGLU ? BN / 2 : BN, SWIGLU>(p, t)) return;
+    if (!decode_tile<BM, SWIGLU ? BN / 2 : BN, SWIGLU>(p, t)) return;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave >> 1, wn = wave & 1;
     int k_first, nk;
@@ -592,7 +600,7 @@ __global__ void __launch_bounds__(512) ffn_gemm_pp_kernel(GemmArgs p)
     extern __shared__ __attribute__((aligned(16))) char smem[];
 
     Tile t;
-    if (!decode_tile<SWIGLU ? BN / 2 : BN, SWIGLU>(p, t)) return;
+    if (!decode_tile<BM, SWIGLU ? BN / 2 : BN, SWIGLU>(p, t)) return;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave >> 2, wn = wave & 3;
     const int grp = wm;
@@ -795,7 +803,7 @@ template <int MODE>
 __device__ __forceinline__ Sched make_sched(const GemmArgs& p, int slots)
 {
     Sched sc;
-    sc.n_mt = p.table[0];
+    sc.n_mt = m_tiles<256>(p);
     sc.tiles = sc.n_mt * p.n_ntiles;
     if (MODE == 0 && p.partial == nullptr) {
         sc.chunk = (sc.tiles * p.ksplit + 7) >> 3;
@@ -892,7 +900,7 @@ __device__ __forceinline__ void store_partial16(float* __restrict__ dst, const f
 template <bool SWIGLU>
 __global__ void __launch_bounds__(256) gemm_tail_sum_kernel(GemmArgs p, int G)
 {
-    const int n_mt = p.table[0];
+    const int n_mt = m_tiles<256>(p);
     const int tiles = n_mt * p.n_ntiles;
     const int t_full = tiles / G * G, rem = tiles - t_full;
     const int sl = tail_split(G, rem, p.K / 64);
@@ -1413,7 +1421,7 @@ hipError_t launch_tile_tables(const int32_t* unit_cnt, const int32_t* unit_off, 
 
 hipError_t launch_ffn(const Dims& D, int u_lo, int u_hi, int Fdim, const TilePlan& plan, const bf16_t* x,
                       const int32_t* gather, const FfnWeights& experts, const FfnWeights& united, const FfnWeights& shared,
-                      int32_t* table, bf16_t* H, bf16_t* Y, float* partial, hipStream_t s, int bm_hi, int32_t* table_hi)
+                      int32_t* table, bf16_t* H, bf16_t* Y, float* partial, hipStream_t s, int bm_hi)
 {
     DeviceInfo dev;
     hipError_t e = ensure_device_init(&dev);
@@ -1430,7 +1438,7 @@ hipError_t launch_ffn(const Dims& D, int u_lo, int u_hi, int Fdim, const TilePla
     const int64_t n_shared = std::max(0, u_hi - std::max(u_lo, D.m + D.G));
     const long likely = (long)(entries / plan.bm + std::min<int64_t>(entries, D.m) + n_shared * ceil_div(D.T, plan.bm));
     GemmArgs g1;
-    g1.A = x; g1.lda = D.d; g1.gather = gather; g1.table = nullptr;
+    g1.A = x; g1.lda = D.d; g1.gather = gather; g1.table = table;
     g1.wa0 = experts.w1; g1.wa1 = united.w1; g1.wa2 = shared.w1;
     g1.wb0 = experts.w3; g1.wb1 = united.w3; g1.wb2 = shared.w3;
     g1.m = D.m; g1.G = D.G; g1.N = Fdim; g1.K = D.d;
@@ -1438,20 +1446,19 @@ hipError_t launch_ffn(const Dims& D, int u_lo, int u_hi, int Fdim, const TilePla
     g1.n_ntiles = 0;                            // set by the launcher from its tile width
     g1.ksplit = 1; g1.plane = 0;
     g1.partial = partial; g1.partial_cap = D.tail_blocks;
-    // Both heights where the table kernel chooses between two: the launch whose table got no tiles returns at once.
-    auto gemm = [&](auto swiglu, GemmArgs& g, int bm, int32_t* tab) {
-        g.table = tab;
+    // Both heights where the table kernel chooses between two: the launch of the height it did not take returns at once.
+    auto gemm = [&](auto swiglu, GemmArgs& g, int bm) {
         g.group_m = tuning().group_m ? tuning().group_m : (bm == 256 ? 8 : 4);
         return dispatch_gemm<decltype(swiglu)::value>(bm, g, max_mtiles(bm), likely, dev.n_cu, s);
     };
     {
         ProfScope ps(MOE_STAGE_GEMM1, s);
-        e = gemm(std::true_type{}, g1, plan.bm, table);
-        if (e == hipSuccess && bm_hi > 0) e = gemm(std::true_type{}, g1, bm_hi, table_hi);
+        e = gemm(std::true_type{}, g1, plan.bm);
+        if (e == hipSuccess && bm_hi > 0) e = gemm(std::true_type{}, g1, bm_hi);
         if (e != hipSuccess) return e;
     }
     GemmArgs g2;
-    g2.A = H; g2.lda = D.Fmax; g2.gather = nullptr; g2.table = nullptr;
+    g2.A = H; g2.lda = D.Fmax; g2.gather = nullptr; g2.table = table;
     g2.wa0 = experts.w2; g2.wa1 = united.w2; g2.wa2 = shared.w2;
     g2.wb0 = g2.wb1 = g2.wb2 = nullptr;
     g2.m = D.m; g2.G = D.G; g2.N = D.d; g2.K = Fdim;
@@ -1461,8 +1468,8 @@ hipError_t launch_ffn(const Dims& D, int u_lo, int u_hi, int Fdim, const TilePla
     g2.partial = partial; g2.partial_cap = D.tail_blocks;
     {
         ProfScope ps(MOE_STAGE_GEMM2, s);
-        e = gemm(std::false_type{}, g2, plan.bm, table);
-        if (e == hipSuccess && bm_hi > 0) e = gemm(std::false_type{}, g2, bm_hi, table_hi);
+        e = gemm(std::false_type{}, g2, plan.bm);
+        if (e == hipSuccess && bm_hi > 0) e = gemm(std::false_type{}, g2, bm_hi);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;

@@ -67,7 +67,7 @@ struct Workspace {
     size_t gate_split;                                // [3][m_pad][d] bf16
     size_t seg_cnt, seg_off;                          // [n_seg][U] int32
     size_t route_total;                               // bytes of the pieces above (all that routing alone needs)
-    size_t tiles0, tiles1, tiles2;                    // GEMM tile tables: int32[4] header + int4 entries
+    size_t tiles0, tiles1;                            // GEMM tile tables: int32[4] header + int4 entries
     size_t H;                                         // [h_rows][Fmax] bf16
     size_t Y;                                         // [y_rows][d], IEEE half (2 bytes; carried as bf16_t*)
     size_t ones;                                      // [T] fp32 (build_united)
@@ -110,11 +110,10 @@ struct FfnWeights { const bf16_t *w1, *w3, *w2; };
 // writes Y[row][d] = FFN(x[gather ? gather[row] : row]) (the row weights are applied by the combine).  Fdim is the FFN width of
 // these units.  Weight source of unit u: u<m experts[u]; u<m+G united[u-m]; else shared[u-m-G].
 // plan / table: how the rows are cut into M tiles and the tile table, which the routing kernels or launch_tile_tables
-// have written; bm_hi / table_hi: the other height and table of a job that leaves the choice to them (0: none).
+// have written; bm_hi: the other height of a job that leaves the choice to them (0: none).
 hipError_t launch_ffn(const Dims& D, int u_lo, int u_hi, int Fdim, const TilePlan& plan, const bf16_t* x,
                       const int32_t* gather, const FfnWeights& experts, const FfnWeights& united, const FfnWeights& shared,
-                      int32_t* table, bf16_t* H, bf16_t* Y, float* partial, hipStream_t s, int bm_hi = 0,
-                      int32_t* table_hi = nullptr);
+                      int32_t* table, bf16_t* H, bf16_t* Y, float* partial, hipStream_t s, int bm_hi = 0);
 // Tile tables from the unit counts of a route that the caller brings.
 hipError_t launch_tile_tables(const int32_t* unit_cnt, const int32_t* unit_off, const TileJobs& jobs, hipStream_t s);
 hipError_t launch_combine(const Dims& D, const bf16_t* x, const bf16_t* Y, const int32_t* token_rows,

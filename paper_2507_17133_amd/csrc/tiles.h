@@ -1,7 +1,7 @@
 // GEMM tile table, built on the device from the unit row counts (shared by the routing kernels, which know
 // the counts first, and by the stand-alone table kernel used when the caller brings its own row lists).
 //
-// int32 header {n_tiles, 0, 0, 0}, then one int4 {unit, first row, rows, 0} per M tile, units in ascending
+// int32 header {n_tiles, rows of a tile, 0, 0}, then one int4 {unit, first row, rows, 0} per M tile, units in ascending
 // order, tiles of a unit consecutive.
 #pragma once
 #include "internal.h"
@@ -12,8 +12,8 @@ struct TileJob {
     int u_lo, u_hi;          // units [u_lo, u_hi)
     TilePlan plan;
     int32_t* table;
-    int bm_hi;               // a taller tile that may suit a browned-out batch better, with a table of its own (0: none);
-    int32_t* table_hi;       // the table that is not chosen gets no tiles
+    int bm_hi;               // a taller tile that may suit a browned-out batch better (0: none): the table holds tiles of one
+                             // of the two heights and says of which, the GEMM launch for the other one finds none
     int m, entries;          // bm_hi > 0: experts, TopK entries of the batch
 };
 struct TileJobs {
@@ -40,7 +40,6 @@ __device__ __forceinline__ void build_tile_table(const int* cnt, const int* off,
         const int u = j.u_lo + lane * per + q;
         if (u < j.u_hi) local += (cnt[u] + bm - 1) / bm;
     }
-    int32_t* table = j.table;
     if (j.bm_hi > 0) {
         int hi = 0, rows = 0;
         for (int q = 0; q < per; ++q) {
@@ -57,11 +56,9 @@ __device__ __forceinline__ void build_tile_table(const int* cnt, const int* off,
             rows += __shfl_xor(rows, o);
         }
         const bool taller = rows < j.entries && (long)n_hi * tile_cost(j.bm_hi) <= (long)n_lo * tile_cost(bm);
-        if (lane < 4) (taller ? j.table : j.table_hi)[lane] = 0;
         if (taller) {
             bm = j.bm_hi;
             local = hi;
-            table = j.table_hi;
         }
     }
     int incl = local;
@@ -73,10 +70,10 @@ __device__ __forceinline__ void build_tile_table(const int* cnt, const int* off,
     int at = incl - local;
     const int total = __shfl(incl, 63);
     if (lane == 0) {
-        table[0] = total < cap ? total : cap;
-        table[1] = 0; table[2] = 0; table[3] = 0;
+        j.table[0] = total < cap ? total : cap;
+        j.table[1] = bm; j.table[2] = 0; j.table[3] = 0;
     }
-    int4* entries = reinterpret_cast<int4*>(table + 4);
+    int4* entries = reinterpret_cast<int4*>(j.table + 4);
     for (int q = 0; q < per; ++q) {
         const int u = j.u_lo + lane * per + q;
         if (u >= j.u_hi) break;

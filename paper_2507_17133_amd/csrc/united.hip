@@ -69,7 +69,7 @@ __global__ void __launch_bounds__(256) uniform_units_kernel(int u0, int n_units0
 {
     const int per = (n + bm - 1) / bm, total = per * (n_units0 + n_units1);
     const int i = blockIdx.x * 256 + threadIdx.x;
-    if (i == 0) { table[0] = total; table[1] = 0; table[2] = 0; table[3] = 0; }
+    if (i == 0) { table[0] = total; table[1] = bm; table[2] = 0; table[3] = 0; }
     if (i >= total) return;
     const int k = i / per, r = (i - k * per) * bm;
     const int unit = k < n_units0 ? u0 + k : u1 + (k - n_units0);
