@@ -158,7 +158,9 @@ Dims make_dims(const moe_config& c, int T)
     D.tile_cap = (int)(D.row_cap / kMinTileRows) + D.U;
     // GEMM2 has few, long tiles (N = d): split K (at most 4 ways) until about four rounds of blocks fill
     // the 256 CUs; more slices only add prologues and planes for the combine to sum.
-    const int bm = routed_tile_rows(D);
+    // Planes are partial sums in half precision, so their number does not follow the tile height that the rows of popular
+    // experts ask for (routed_tile_rows): it comes from the mean alone, as for even units, and taller tiles keep it.
+    const int bm = pick_tile_rows((int64_t)T * D.K / D.m, true);
     const int64_t tiles2 = (D.row_cap / bm + (D.m + D.G) / 2 + D.Ns) * (int64_t)ceil_div(D.d, 256);
     int ks = 1;
     while (ks < 4 && tiles2 * ks < 1024 && (D.F / 64) / (ks * 2) >= 8) ks *= 2;

@@ -50,3 +50,24 @@ def test_slices_of_the_gate_do_not_depend_on_the_scratch(tmp_path):
         assert {l["n_slice"] for l in pieces} == {want}, c
         several += want > 1 and len(pieces) > 1
     assert several >= 3
+
+
+def _planes(d, F, m, K, way, ns, T):
+    """K slices of GEMM2, whose partial sums are held in half precision: until 1024 tiles of the height that the mean number of
+    rows asks for, slices of at least eight k tiles."""
+    rows = T * K // m
+    bm = 256 if rows >= 384 else 128 if rows >= 48 else 64 if rows >= 24 else 32
+    tiles = (T * (K + ns) // bm + (m + -(-m // way)) // 2 + ns) * -(-d // 256)
+    ks = 1
+    while ks < 4 and tiles * ks < 1024 and F // 64 // (2 * ks) >= 8:
+        ks *= 2
+    return 1 if bm == 256 else ks
+
+
+def test_planes_of_partial_sums(tmp_path):
+    shapes = [(4096, 4096, 64, 8, 8, 0), (2048, 1408, 60, 4, 8, 1), (4096, 14336, 8, 2, 8, 0), (2048, 768, 128, 8, 8, 0),
+              (7168, 2048, 256, 8, 8, 1), (2048, 2048, 40, 4, 4, 0), (256, 512, 8, 2, 8, 0)]
+    calls = [dict(entry="forward", cfg=[d, F, m, K, way, ns, F if ns else 0, 0, 0, 0], T=T, threshold=thr)
+             for d, F, m, K, way, ns in shapes for T in (1, 20, 64, 96, 112, 150, 191, 230, 384, 900, 2048, 5000) for thr in (1.0, 0.5)]
+    for c, r in zip(calls, trace(calls, tmp_path)):
+        assert r["status"] == 0 and r["launches"][-1]["planes"] == _planes(*c["cfg"][:6], c["T"]), c
