@@ -132,6 +132,10 @@ static TilePlan make_shared_plan(const Dims& D, int n_cu)
 // Layer forward in us at 40 / 80 % brownout, tiles of 64, 128 and 256 rows: DeepSeek-V3 shape, 16 rows per expert
 // 1127 / 1041, 920 / 839, 993 / 865; 32 rows 1809 / 1701, 1354 / 1290, 1223 / 1073; 94 rows (128 and 256) 3083 / 2950, 2368 / 2258;
 // Qwen3 shape, 250 rows 450 / 409, 382 / 334; with a uniform gate and 30 %, 32 rows 3355, 3360, 4077.
+// GEMM2 keeps its planes at either height (the 256-row kernel then does not cut its tail, nor has it scratch for that below 384
+// tokens).  Still the better height there, at 30 / 80 % with 128 rows and with the choice of 256: 8 experts of 4096 x 14336, 400
+// tokens 522 / 392, 508 / 319, 1021 tokens 988 / 738, 775 / 530; at 30 / 60 % 16 experts of 2048 x 4096, 300 tokens 227 / 201, 218 /
+// 200, 64 experts of 4096 x 4096, 300 tokens 537 / 401, 567 / 367.
 static int taller_tile_rows(const Dims& D, int bm, int n_cu)
 {
     if (tuning().force_bm) return 0;
@@ -164,7 +168,7 @@ Dims make_dims(const moe_config& c, int T)
     const int64_t tiles2 = (D.row_cap / bm + (D.m + D.G) / 2 + D.Ns) * (int64_t)ceil_div(D.d, 256);
     int ks = 1;
     while (ks < 4 && tiles2 * ks < 1024 && (D.F / 64) / (ks * 2) >= 8) ks *= 2;
-    if (bm == 256) ks = 1;                                // the persistent kernel balances its tail itself
+    if (bm == 256) ks = 1;                                // the persistent kernel cuts its left-over tiles itself
     if (tuning().force_ksplit) ks = tuning().force_ksplit;
     D.ksplit = ks;
     D.y_plane = D.row_cap * (int64_t)D.d;
