@@ -562,7 +562,10 @@ moe_status moe_forward(const moe_config* cfg, const void* x, int32_t T, const vo
     float* partial = W.partial_bytes ? at<float>(workspace, W.partial) : nullptr;
     for (int j = 0; j < jobs.n; ++j) {
         const TileJob& J = jobs.job[j];
-        e = launch_ffn(D, J.u_lo, J.u_hi, j == 0 ? D.F : D.Fs, J.plan, xb, R.row_token, fe, fu, fs, J.table, H, Y, partial, s,
+        FfnUnits units{J.u_hi - J.u_lo, 0, 0};
+        if (j == 0) units.entries = (int64_t)T * D.K;
+        if (j == 1 || !split_shared) units.even = D.Ns;
+        e = launch_ffn(D, units, j == 0 ? D.F : D.Fs, J.plan, xb, R.row_token, fe, fu, fs, J.table, H, Y, partial, s,
                        J.bm_hi);
         if (e != hipSuccess) return hip_fail(e, j == 0 ? "moe_forward/ffn" : "moe_forward/ffn_shared");
     }
@@ -628,7 +631,7 @@ moe_status moe_build_united(const moe_config* cfg, const moe_ffn_weights* expert
     auto run_units = [&](int u0, int n0, int u1, int n1, int first_slot, bf16_t* Y) -> hipError_t {
         hipError_t err = launch_uniform_units(u0, n0, u1, n1, first_slot, n_calib, plan.bm, tiles, s);
         if (err != hipSuccess) return err;
-        return launch_ffn(D, 0, n0 + n1, D.F, plan, xb, row_token, fe, fu, fs, tiles, H, Y, partial, s);
+        return launch_ffn(D, FfnUnits{n0 + n1, 0, n0 + n1}, D.F, plan, xb, row_token, fe, fu, fs, tiles, H, Y, partial, s);
     };
     for (int g = 0; g < G; ++g) {
         const int lo = g * way, hi = lo + way < m ? lo + way : m, k = hi - lo;
@@ -724,7 +727,7 @@ moe_status moe_distill_united(const moe_config* cfg, const moe_ffn_weights* expe
             for (int q = 0; q < batches; ++q) {
                 const int i0 = lo + (int)((int64_t)k * q / batches), i1 = lo + (int)((int64_t)k * (q + 1) / batches);
                 if ((e = launch_uniform_units(i0, i1 - i0, 0, 0, 0, n_calib, plan.bm, tiles, s)) != hipSuccess ||
-                    (e = launch_ffn(D, 0, i1 - i0, D.F, plan, xb, row_token, fe, fu, fs, tiles, H, Yo,
+                    (e = launch_ffn(D, FfnUnits{i1 - i0, 0, i1 - i0}, D.F, plan, xb, row_token, fe, fu, fs, tiles, H, Yo,
                                     partial, s)) != hipSuccess)
                     return hip_fail(e, "moe_distill_united/teacher");
                 e = launch_teacher_stats(Yo, i1 - i0, q == 0, q == batches - 1, k, n_calib, D.d, D.F, g - g0, buf, s);

@@ -1419,24 +1419,22 @@ hipError_t launch_tile_tables(const int32_t* unit_cnt, const int32_t* unit_off, 
     return hipGetLastError();
 }
 
-hipError_t launch_ffn(const Dims& D, int u_lo, int u_hi, int Fdim, const TilePlan& plan, const bf16_t* x,
+hipError_t launch_ffn(const Dims& D, const FfnUnits& units, int Fdim, const TilePlan& plan, const bf16_t* x,
                       const int32_t* gather, const FfnWeights& experts, const FfnWeights& united, const FfnWeights& shared,
                       int32_t* table, bf16_t* H, bf16_t* Y, float* partial, hipStream_t s, int bm_hi)
 {
     DeviceInfo dev;
     hipError_t e = ensure_device_init(&dev);
     if (e != hipSuccess) return e;
-    const int n_units = u_hi - u_lo;
     // M tiles there can be at most: a unit that holds rows has one for every bm of them and a ragged one, and no more
     // units hold rows than there are rows
     auto max_mtiles = [&](int bm) {
-        return (int)std::min<int64_t>(D.row_cap / bm + std::min<int64_t>(n_units, D.row_cap), D.tile_cap);
+        return (int)std::min<int64_t>(D.row_cap / bm + std::min<int64_t>(units.n, D.row_cap), D.tile_cap);
     };
-    // M tiles of a batch that the gate routes: TopK entries over the experts (their united units take rows from them),
-    // every token once per shared expert.  Chooses the kernel; the grid is sized for max_mtiles.
-    const int64_t entries = u_lo < D.m + D.G ? (int64_t)D.T * D.K : 0;
-    const int64_t n_shared = std::max(0, u_hi - std::max(u_lo, D.m + D.G));
-    const long likely = (long)(entries / plan.bm + std::min<int64_t>(entries, D.m) + n_shared * ceil_div(D.T, plan.bm));
+    // M tiles to expect when no unit is browned out (united units take rows from the experts).  Chooses the kernel; the grid
+    // is sized for max_mtiles.
+    const long likely = (long)(units.entries / plan.bm + std::min<int64_t>(units.entries, D.m) +
+                               (int64_t)units.even * ceil_div(D.T, plan.bm));
     GemmArgs g1;
     g1.A = x; g1.lda = D.d; g1.gather = gather; g1.table = table;
     g1.wa0 = experts.w1; g1.wa1 = united.w1; g1.wa2 = shared.w1;

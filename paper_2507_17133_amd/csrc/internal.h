@@ -106,12 +106,14 @@ hipError_t launch_pack_gate(const float* gate_w, int m, int m_pad, int d, bf16_t
 
 // ---- FFN (ffn.hip) ----
 struct FfnWeights { const bf16_t *w1, *w3, *w2; };
-// Runs W2(silu(W1 x)*(W3 x)) for the rows of units [u_lo,u_hi) listed in (unit_cnt, unit_off, gather),
-// writes Y[row][d] = FFN(x[gather ? gather[row] : row]) (the row weights are applied by the combine).  Fdim is the FFN width of
-// these units.  Weight source of unit u: u<m experts[u]; u<m+G united[u-m]; else shared[u-m-G].
+// The units of a launch: how many may hold rows, the TopK entries spread over the experts among them, and how many hold
+// all T tokens each (shared experts; units on calibration tokens).
+struct FfnUnits { int n; int64_t entries; int even; };
+// Runs W2(silu(W1 x)*(W3 x)) for the rows of the tiles in `table`, writes Y[row][d] = FFN(x[gather ? gather[row] : row]) (the
+// row weights are applied by the combine).  Fdim is the FFN width of these units.  Weight source of unit u: u<m experts[u]; u<m+G united[u-m]; else shared[u-m-G].
 // plan / table: how the rows are cut into M tiles and the tile table, which the routing kernels or launch_tile_tables
 // have written; bm_hi: the other height of a job that leaves the choice to them (0: none).
-hipError_t launch_ffn(const Dims& D, int u_lo, int u_hi, int Fdim, const TilePlan& plan, const bf16_t* x,
+hipError_t launch_ffn(const Dims& D, const FfnUnits& units, int Fdim, const TilePlan& plan, const bf16_t* x,
                       const int32_t* gather, const FfnWeights& experts, const FfnWeights& united, const FfnWeights& shared,
                       int32_t* table, bf16_t* H, bf16_t* Y, float* partial, hipStream_t s, int bm_hi = 0);
 // Tile tables from the unit counts of a route that the caller brings.

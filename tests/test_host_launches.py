@@ -71,3 +71,16 @@ def test_planes_of_partial_sums(tmp_path):
              for d, F, m, K, way, ns in shapes for T in (1, 20, 64, 96, 112, 150, 191, 230, 384, 900, 2048, 5000) for thr in (1.0, 0.5)]
     for c, r in zip(calls, trace(calls, tmp_path)):
         assert r["status"] == 0 and r["launches"][-1]["planes"] == _planes(*c["cfg"][:6], c["T"]), c
+
+
+def test_calibration_batches_choose_their_kernel_by_their_own_units(tmp_path):
+    """A student and a teacher of 20 tokens at F = 4096 are 2 x 32 blocks of 256 columns in GEMM1, too few for 256 CUs, a student
+    and its eight teachers are 288; GEMM2 (d = 256) has a block per unit."""
+    calls = [dict(entry="build", cfg=[256, 4096, 8, K, 8, ns, 4096 if ns else 0, 0, 0, 0], T=20) for K, ns in ((2, 0), (8, 8))]
+    for c, r, wide in zip(calls, trace(calls, tmp_path), (False, True)):
+        gemms = [l["name"] for l in r["launches"] if l["name"].startswith("ffn_gemm")]
+        assert r["status"] == 0
+        if wide:
+            assert gemms[0] == "ffn_gemm_kernel" and gemms[1] == "ffn_gemm_narrow_kernel"
+        else:
+            assert set(gemms) == {"ffn_gemm_narrow_kernel"}
