@@ -111,10 +111,10 @@ TilePlan make_tile_plan(int64_t rows, bool even)
 // Tile height of the routed units.  Where all experts together have fewer 256-column blocks than the chip has CUs, weights are
 // few and the narrow kernel's time is its own latency: no taller tiles then (64 tokens over 8 experts of 256 x 512: 23.8 us
 // at 32 rows, 25.3 at 64).
-static int routed_tile_rows(const Dims& D)
+static int routed_tile_rows(const Dims& D, int n_cu)
 {
     const int64_t entries = (int64_t)D.T * D.K;
-    const bool few = std::min<int64_t>(entries, D.m) * ceil_div(D.F, 128) < 256;
+    const bool few = std::min<int64_t>(entries, D.m) * ceil_div(D.F, 128) < n_cu;
     return pick_tile_rows(entries / D.m, few);
 }
 
@@ -539,7 +539,7 @@ moe_status moe_forward(const moe_config* cfg, const void* x, int32_t T, const vo
     jobs.n = split_shared ? 2 : 1;
     jobs.cap = D.tile_cap;
     jobs.job[0].u_lo = 0; jobs.job[0].u_hi = split_shared ? D.m + D.G : D.U;
-    jobs.job[0].plan.bm = routed_tile_rows(D);
+    jobs.job[0].plan.bm = routed_tile_rows(D, dev.n_cu);
     jobs.job[0].table = at<int32_t>(workspace, W.tiles0);
     // a threshold of 1 browns nothing out (a route of the caller's may, whatever threshold comes with it)
     jobs.job[0].bm_hi = route || threshold < 1.0 ? taller_tile_rows(D, jobs.job[0].plan.bm, dev.n_cu) : 0;
