@@ -231,7 +231,7 @@ Workspace carve_workspace(const Dims& D)
     // one tile of rows past the end: GEMM2's ragged last tile reads (and discards) whole tiles of H
     W.H = take((size_t)(W.h_rows + 256) * D.Fmax * 2);
     W.Y = take((size_t)W.y_rows * D.d * 2);
-    W.ones = take((size_t)D.T * 4);
+    W.loss_part = take((size_t)D.T * 4);
     // K-split tail of the persistent 256-row GEMMs: one fp32 tile per block of their grid.  256-row tiles can
     // occur from kMixedRows tokens on (a shared expert, or one unit holding all calibration tokens).
     W.partial = 0;
@@ -624,9 +624,10 @@ moe_status moe_build_united(const moe_config* cfg, const moe_ffn_weights* expert
     // The workspace holds the FFN rows of K+N_s units: the student's in the first slot, kept while the teachers go
     // through the others in equal batches (one slot only: the teachers' outputs go to the second plane of Y).
     const int cap = D.slots > 1 ? D.slots - 1 : 1;
+    // one block per 2048 elements, at most as many as its piece of the workspace holds partial sums for
     const int sq_blocks = (int)std::min<size_t>({(nd / 8 + 255) / 256, (size_t)kSqdiffBlocks,
                                                  align_up((size_t)n_calib * 4, 256) / 8});
-    double* sq_part = at<double>(workspace, W.ones);
+    double* sq_part = at<double>(workspace, W.loss_part);
     if ((e = launch_repeat_tokens(row_token, n_calib, D.slots, s)) != hipSuccess) return hip_fail(e, "moe_build_united/rows");
     auto run_units = [&](int u0, int n0, int u1, int n1, int first_slot, bf16_t* Y) -> hipError_t {
         hipError_t err = launch_uniform_units(u0, n0, u1, n1, first_slot, n_calib, plan.bm, tiles, s);

@@ -63,7 +63,7 @@ __device__ __forceinline__ float swiglu(float g, float u)
 
 // ------------------------------------------------------------------------------------------------
 // Tile tables from the unit counts, when the routing kernels have not already built them (row lists brought
-// by the caller; single units of the united-expert build): one wavefront per job.
+// by the caller): one wavefront per job.
 // ------------------------------------------------------------------------------------------------
 __global__ void __launch_bounds__(64) tile_table_kernel(const int32_t* __restrict__ unit_cnt,
                                                         const int32_t* __restrict__ unit_off, TileJobs jobs)

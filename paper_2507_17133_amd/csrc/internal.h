@@ -70,7 +70,7 @@ struct Workspace {
     size_t tiles0, tiles1;                            // GEMM tile tables: int32[4] header + int4 entries
     size_t H;                                         // [h_rows][Fmax] bf16
     size_t Y;                                         // [y_rows][d], IEEE half (2 bytes; carried as bf16_t*)
-    size_t ones;                                      // [T] fp32 (build_united)
+    size_t loss_part;                                 // T*4 bytes: fp64 partial sums of build_united's loss
     size_t partial, partial_bytes;                    // fp32 tiles of GEMM2's K-split tail (256-row tiles, one plane)
     size_t total;
     int64_t h_rows, y_rows;
@@ -124,9 +124,10 @@ hipError_t launch_combine(const Dims& D, const bf16_t* x, const bf16_t* Y, const
 // ---- united experts (united.hip) ----
 hipError_t launch_united_mean(const bf16_t* w, int m, int way, size_t n_elem, bf16_t* u, hipStream_t s);
 // Tile table of n_units0 units u0, u0+1, ... and n_units1 units u1, ..., each holding the n rows r*n .. r*n+n-1
-// (r: position in that list, + first_slot), and, if row_token is given, row_token[r*n + t] = t for `slots` such units.
+// (r: position in that list, + first_slot).
 hipError_t launch_uniform_units(int u0, int n_units0, int u1, int n_units1, int first_slot, int n, int bm, int32_t* table,
                                 hipStream_t s);
+// row_token[r*n + t] = t for `slots` such units.
 hipError_t launch_repeat_tokens(int32_t* row_token, int n, int slots, hipStream_t s);
 // part[0..blocks) (+)= per-block sums of (yu - yo_i)^2 over b teachers' rows of n elements each; if last,
 // *loss = scale * sum of part.  part: kSqdiffBlocks doubles at most.

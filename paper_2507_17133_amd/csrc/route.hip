@@ -1,16 +1,16 @@
 // Routing kernels of the BrownoutMoE layer for gfx950:
-//   prep     clear the expert counters (large batches), split fp32 gate weights into three bf16 pieces
-//            (also the one-time repack behind moe_pack_gate)
-//   gate     affinities s = x.e_i on MFMA (bf16 x 3-piece weights, fp64 running sums; from 32 experts on with
-//            the pieces and the x rows staged in LDS, blocks of 16, 32 or 64 tokens) or, for at most 16
-//            experts and small batches, in plain fp64; TopK by wavefront shuffles, weights g, expert
-//            histogram                                               (Architecture of BrownoutMoE)
+//   prep     split fp32 gate weights into three bf16 pieces (also the one-time repack behind moe_pack_gate), clear the
+//            expert counters (large batches over at most 16 experts; the logit kernel does it for more)
+//   gate     affinities s = x.e_i on MFMA (bf16 x 3-piece weights, fp64 running sums, pieces and x rows staged in LDS) or,
+//            for at most 16 experts and small batches, in plain fp64; TopK by wavefront shuffles, weights g, expert
+//            histogram.  More than 16 experts: two launches, logits (blocks of 16, 64 or 128 tokens by 64 experts by a
+//            slice of K) and TopK                                    (Architecture of BrownoutMoE)
 //   count    Algorithm 1's S1/S2 split and unit map (every block, from the counts) and the rows
 //            each 64-token segment gives each unit                   (Brownout Approach, Algorithm 1)
 //   scan     offsets of segments inside units, unit totals (unit offsets: scanned by the scatter blocks)
-//   scatter  row lists: row_token, row_weight, token_rows (stable: ascending token inside a unit); its first
-//            block also writes the GEMM tile table
-//   small    at most 1024 tokens: expert counts, Algorithm 1, both scans, the scatter and the tile table
+//   scatter  row lists: row_token, row_weight, token_rows (stable: ascending token inside a unit); one more block
+//            behind those of the segments writes the unit offsets and the GEMM tile tables
+//   small    at most 1024 tokens: expert counts, Algorithm 1, both scans, the scatter and the tile tables
 //            in ONE block
 // No floating-point atomics anywhere; integer atomics only where the result does not depend on order.
 #include "internal.h"
@@ -65,8 +65,8 @@ struct GateArgs {
     const bf16_t* x; const unsigned short* split; const float* bias;
     int T, d, m, m_pad, K, score_fn;
     int32_t* topk_idx; float* topk_w; uint8_t* near_tie;
-    int32_t* expert_cnt;   // the launch's expert counts, cleared beforehand (atomics); null for small batches,
-                           // whose routing block counts the experts itself
+    int32_t* expert_cnt;   // the batch's expert counts (atomics on cleared counters); null for small batches, whose
+                           // routing block counts the experts itself
     int n_slice;           // 17 experts and more: slices of K, each leaving fp64 partial logits
     void* logits;          // one slice: [T][m_pad] fp32, bias added; else [n_slice][T][m_pad] fp64
     int32_t* clear_cnt;    // expert counters the logit kernel clears for the TopK launch behind it (or null)
