@@ -1,5 +1,6 @@
 """Browned-out batches whose GEMM tile height the device chooses from the row counts: shapes on both sides of the choice
-(skewed and uniform gates), against the oracle; a route brought by the caller gives the same bits as one made inside."""
+(skewed and uniform gates), against the oracle, with the tile table that each is expected to leave in the workspace; a route
+brought by the caller gives the same bits as one made inside."""
 import numpy as np
 import pytest
 import torch
@@ -11,13 +12,27 @@ from tests._util import OUT_TOL, check_route, npf, oracle_route, rel_err
 
 pytestmark = pytest.mark.gpu
 
+MODES = [(1.0, False), (0.6, False), (0.3, True), (0.0, False)]
 
-# T, d, F, m, K, way, n_shared, F_s, zipf: T K / m and the block count offer 128 (first two) or 256 rows
-@pytest.mark.parametrize("T,d,F,m,K,way,Ns,Fs,zipf", [
-    (300, 64, 14336, 64, 2, 8, 0, 0, 1.5), (300, 64, 14336, 64, 2, 8, 1, 64, None), (1200, 64, 4096, 64, 8, 8, 1, 4096, 1.2),
-    (1031, 128, 4096, 96, 8, 8, 0, 0, None), (4099, 64, 2048, 40, 4, 7, 0, 0, 1.2)])
-@pytest.mark.parametrize("threshold,full", [(1.0, False), (0.6, False), (0.3, True), (0.0, False)])
-def test_either_height(T, d, F, m, K, way, Ns, Fs, zipf, threshold, full):
+
+def _table(cnt, off, bm):
+    """Bytes of a tile table: header, then unit, first row and rows of every tile."""
+    tiles = [(u, off[u] + r, min(bm, cnt[u] - r), 0) for u in range(len(cnt)) for r in range(0, int(cnt[u]), bm)]
+    return np.asarray([(len(tiles), bm, 0, 0)] + tiles, np.int32).tobytes()
+
+
+# T, d, F, m, K, way, n_shared, F_s, zipf; the height the host picks and the one it offers; the height taken in each of MODES
+@pytest.mark.parametrize("T,d,F,m,K,way,Ns,Fs,zipf,lo,hi,taken", [
+    (300, 64, 14336, 64, 2, 8, 0, 0, 1.5, 32, 128, (32, 128, 128, 128)),
+    (300, 64, 14336, 64, 2, 8, 1, 64, None, 32, 128, (32, 32, 32, 128)),
+    (1200, 64, 4096, 64, 8, 8, 1, 4096, 1.2, 128, 256, (128, 256, 256, 256)),
+    (1031, 128, 4096, 96, 8, 8, 0, 0, None, 128, 256, (128, 128, 128, 256)),
+    (4099, 64, 2048, 160, 8, 7, 0, 0, 1.2, 128, 256, (128, 256, 256, 256)),
+    (900, 64, 4096, 128, 3, 8, 0, 0, 1.3, 64, 256, (64, 256, 256, 256)),
+    (900, 64, 4096, 128, 3, 4, 1, 4096, 1.0, 64, 256, (64, 64, 256, 64))])
+@pytest.mark.parametrize("mode", range(len(MODES)))
+def test_either_height(T, d, F, m, K, way, Ns, Fs, zipf, lo, hi, taken, mode):
+    threshold, full = MODES[mode]
     print(T, d, F, m, K, way, Ns, Fs, zipf, threshold, full, flush=True)
     cfg = WL.LayerConfig("choice", T=T, d=d, F=F, m=m, K=K, way=way, n_shared=Ns, F_s=Fs, zipf_s=zipf)
     L = WL.make_layer(cfg, T + m, "cpu")
@@ -28,16 +43,22 @@ def test_either_height(T, d, F, m, K, way, Ns, Fs, zipf, threshold, full):
     united_cpu = WL.make_random_united(cfg, 1, "cpu")
     united = tuple(to(a) for a in united_cpu)
     c = P.config_of(cfg)
-    ws = P.alloc_workspace(c, T)
+    ws, ws_r = P.alloc_workspace(c, T), P.alloc_workspace(c, T)
     ws.fill_(0x5A)
+    ws_r.fill_(0x5A)
     out = P.moe_forward(c, x, gate_w, gate_b, experts, united, shared, threshold, full, workspace=ws)
     R = P.moe_route(c, x, gate_w, gate_b, threshold, full)
-    out_r = P.moe_forward(c, x, gate_w, gate_b, experts, united, shared, route=R)
+    out_r = P.moe_forward(c, x, gate_w, gate_b, experts, united, shared, route=R, workspace=ws_r)
     torch.cuda.synchronize()
     assert torch.equal(out, out_r)
+    units = m + cfg.G + (Ns if Fs == F else 0)         # shared experts of another width have a table of their own
+    cnt, off = npf(R.unit_cnt)[:units], npf(R.unit_off)
+    for w in (ws, ws_r):
+        left = w.cpu().numpy().tobytes()
+        assert [bm for bm in (lo, hi) if _table(cnt, off, bm) in left] == [taken[mode]]
     idx, w, unit = check_route(R, oracle_route(L, cfg, threshold, full), cfg, threshold, full)
-    if T <= 1200 and threshold in (0.6, 0.0):       # the oracle's FFNs take seconds beyond
-        want = O.forward_tokens(npf(L.x), idx, w, unit, way, npf(L.experts), npf(united_cpu), npf(L.shared))
-        got = npf(out)
-        assert np.isfinite(got).all()
-        assert rel_err(got, want) <= OUT_TOL
+    tokens = np.unique(np.linspace(0, T - 1, 200).astype(np.int32))
+    want = O.forward_tokens(npf(L.x), idx, w, unit, way, npf(L.experts), npf(united_cpu), npf(L.shared), tokens=tokens)
+    got = npf(out)
+    assert np.isfinite(got).all()
+    assert rel_err(got[tokens], want) <= OUT_TOL

@@ -45,8 +45,33 @@ def test_loss_and_training_against_the_oracle(n, d, F, m, K, ns, way):
             continue
         w_ref, h_ref = DO.distill(xs, tuple(s[g] for s in start), teachers, steps, lr)
         assert np.allclose(hist[g], h_ref, rtol=1e-2), (g, hist[g], h_ref)
-        for u, b, s0 in zip(united, w_ref, start):
-            da, db = (f64(u[g]) - s0[g]).ravel(), (b - s0[g]).ravel()
-            # Adam's first steps have full size whatever the gradient: weights differ where its sign is rounding noise
-            assert np.abs(da - db).max() <= 2.0 * lr * steps + 2 ** -8 * np.abs(s0[g]).max()
-            assert float(da @ db / np.sqrt((da @ da) * (db @ db))) >= 0.9
+        _, grads = DO.loss_and_grads(xs, tuple(s[g] for s in start), teachers)
+        for u, b, s0, gr in zip(united, w_ref, start, grads):
+            u, s0 = f64(u[g]), s0[g]
+            da, db = u - s0, b - s0
+            # Adam's first steps have full size whatever the gradient, so a weight whose gradient is rounding noise may end up
+            # anywhere; where it is at least half its root mean square, operands rounded to bf16 (2^-9 each) change it by a few
+            # per cent, and the normalised step by as much: 15 % of the way, and the weight's own rounding to bf16.  A step left
+            # out or taken backwards is off by 100 or 200 %.
+            sure = np.abs(gr) >= 0.5 * np.sqrt((gr ** 2).mean())
+            assert sure.mean() > 0.4
+            assert (np.abs(da - db)[sure] <= 0.15 * lr * steps + 2 ** -8 * np.abs(b)[sure]).all()
+            # every 64 x 64 block (the ragged tiles end in one): in a float32 model of the trainer 0.999 at the least
+            for i in range(0, u.shape[0], 64):
+                for j in range(0, u.shape[1], 64):
+                    va, vb = da[i:i + 64, j:j + 64].ravel(), db[i:i + 64, j:j + 64].ravel()
+                    assert float(va @ vb / np.sqrt((va @ va) * (vb @ vb))) >= 0.99, (i, j)
+
+
+# fewer calibration tokens than a tile of 64 rows: either kernel of the small heights
+@pytest.mark.parametrize("n,d,F,m,K,ns,way", [(1, 64, 64, 2, 1, 0, 2), (20, 64, 320, 5, 2, 1, 2), (37, 128, 8192, 4, 4, 0, 4)])
+def test_loss_of_a_few_tokens(n, d, F, m, K, ns, way):
+    cfg = WL.LayerConfig("united_few", T=n, d=d, F=F, m=m, K=K, way=way, n_shared=ns, F_s=F)
+    L = WL.make_layer(cfg, 4, "cpu")
+    x = WL.make_activations(cfg, 4, "cpu", "calib", n)
+    united, loss = P.moe_build_united(P.config_of(cfg), tuple(t.to(DEV) for t in L.experts), x.to(DEV))
+    for g in range(cfg.G):
+        teachers = [tuple(f64(w[i]) for w in L.experts) for i in range(g * way, min(m, (g + 1) * way))]
+        want = DO.loss(f64(x), tuple(f64(u[g]) for u in united), teachers)
+        # as above, over n d >= 64 terms instead of 4096
+        assert abs(float(loss[g]) - want) <= 2e-2 * want + 1e-6
