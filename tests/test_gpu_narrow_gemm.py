@@ -1,6 +1,5 @@
 """The narrow GEMM (few blocks of small tiles): one k tile and fewer than its stages, both tile heights with full and ragged
-tiles, one and two K slices, shared experts in a launch of their own; and the tile heights around it that a threshold
-below 1 chooses."""
+tiles, one, two and four K slices, shared experts in a launch of their own; and a batch of 128-row tiles next to it."""
 import numpy as np
 import pytest
 import torch
