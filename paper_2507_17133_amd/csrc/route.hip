@@ -598,12 +598,12 @@ __global__ void __launch_bounds__(THREADS) gate_topk_kernel(GateArgs p)
 }
 
 // ------------------------------------------------------------------------------------------------
-// Algorithm 1 on the expert counts, PARTS threads per expert (m <= 256).  Sorting is implicit: expert j
+// Algorithm 1 on the expert counts, PARTS threads per expert (m <= 256); the sum of the counts into *sum_s, if given.  Sorting is implicit: expert j
 // precedes expert i in the order "count descending, id ascending" iff cnt_j > cnt_i or (equal and
 // j < i); P_i = tokens covered before i is the sum of the counts of those j.
 // ------------------------------------------------------------------------------------------------
 template <int PARTS>
-__device__ __forceinline__ void brownout_decide(const int* cnt_s, unsigned char* s2_s, int* unit_s, int m, int way,
+__device__ __forceinline__ void brownout_decide(const int* cnt_s, unsigned char* s2_s, int* unit_s, int* sum_s, int m, int way,
                                                 double threshold, int full, int tid, bool write,
                                                 int32_t* expert_unit, uint8_t* expert_in_s1)
 {
@@ -634,6 +634,7 @@ __device__ __forceinline__ void brownout_decide(const int* cnt_s, unsigned char*
         }
         in_s1 = (double)P < (double)S * threshold;
         if (part == 0) s2_s[ex] = (!in_s1 && c > 0) ? 1 : 0;
+        if (sum_s != nullptr && tid == 0) *sum_s = S;
     }
     __syncthreads();
     if (ex < m && part == 0) {
@@ -697,16 +698,14 @@ __device__ __forceinline__ void load_entries(const RowArgs& p, int first, int t0
 
 // The row of one entry (token t, slot j; u: its unit or -1, w: its weight), called by whole wavefronts.  A united unit
 // that several entries of the token name gets one row, at the first of them, with the sum of their weights in TopK
-// order.  An expert is named twice only where TopK ran out of logits above -infinity (or met NaN), and then all but the first
-// of its entries have no positive weight: they share the row, which keeps the weight of the last.  bmw: bitmaps of the
-// token's segment, soff: rows of every unit in earlier segments.
+// order.  bmw: bitmaps of the token's segment, soff: rows of every unit in earlier segments.
 __device__ __forceinline__ void scatter_entry(const RowArgs& p, const unsigned long long* bmw, const int* off_s,
                                               const int32_t* soff, int t, int j, int u, float w, bool valid, int lane)
 {
-    bool first = u >= 0, last = true;
-    const int base = lane & ~((1 << p.lk) - 1);
-    const float own = w;
+    bool first = u >= 0;
     if (__ballot(u >= p.m) != 0) {
+        const int base = lane & ~((1 << p.lk) - 1);
+        const float own = w;
         for (int q = 0; q < p.K; ++q) {
             const int uq = __shfl(u, base + q);
             const float wq = __shfl(own, base + q);
@@ -716,19 +715,33 @@ __device__ __forceinline__ void scatter_entry(const RowArgs& p, const unsigned l
             }
         }
     }
-    if (__ballot(first && !(own > 0.0f)) != 0) {
-        for (int q = 0; q < p.K; ++q)
-            if (__shfl(u, base + q) == u && u < p.m && q > j) last = false;
-    }
     int row = -1;
     if (first) {
         row = off_s[u] + soff[u] + __popcll(bmw[u] & ((1ull << (t & 63)) - 1ull));
-        if (last) {
-            p.row_token[row] = t;
-            p.row_weight[row] = w;
-        }
+        p.row_token[row] = t;
+        p.row_weight[row] = w;
     }
     if (valid) p.token_rows[(size_t)t * (p.K + p.Ns) + j] = row;
+}
+
+// A token names an expert twice only where TopK ran out of logits above -infinity (or met NaN); all but the first of those
+// entries then have no positive weight.  They share the expert's row, whose weight the lanes have written in no stated
+// order: once those writes are done, the last entry's is written over them.  A pass of its own, off the common path (looked
+// for among the shuffles of scatter_entry, with the counts' sum taken by every wavefront, it cost the one-block routing of
+// 1000 x 2 entries 0.7 us of 6.7; so 0.1).
+template <int NT>
+__device__ __forceinline__ void rewrite_repeated(const RowArgs& p, const int* unit_s, int t0, int t1, int tid)
+{
+    __syncthreads();                                       // (waits for the block's stores)
+    for (int e = tid; e < (t1 - t0) * p.K; e += NT) {
+        const int t = t0 + e / p.K, j = e % p.K;
+        const int32_t* idx = p.topk_idx + (size_t)t * p.K;
+        if (unit_s[idx[j]] != idx[j]) continue;            // united (one row with the sum of its entries) or dropped
+        bool before = false, behind = false;
+        for (int q = 0; q < p.K; ++q)
+            if (q != j && idx[q] == idx[j]) (q < j ? before : behind) = true;
+        if (before && !behind) p.row_weight[p.token_rows[(size_t)t * (p.K + p.Ns) + j]] = p.topk_w[(size_t)t * p.K + j];
+    }
 }
 
 // Rows of the shared experts: every token has one in each, in token order.
@@ -760,7 +773,7 @@ __global__ void __launch_bounds__(1024) route_count_kernel(RowArgs p)
     if (tid < kMaxExperts) cnt_s[tid] = tid < p.m ? p.expert_cnt[tid] : 0;
     for (int i = tid; i < p.U; i += 1024) bm[i] = 0ull;
     __syncthreads();
-    brownout_decide<4>(cnt_s, s2_s, unit_s, p.m, p.way, p.threshold, p.full, tid, seg == 0, p.expert_unit,
+    brownout_decide<4>(cnt_s, s2_s, unit_s, nullptr, p.m, p.way, p.threshold, p.full, tid, seg == 0, p.expert_unit,
                        p.expert_in_s1);
 #pragma unroll
     for (int q = 0; q < kEntryBatch; ++q) {
@@ -843,8 +856,9 @@ __global__ void __launch_bounds__(256) route_scatter_kernel(RowArgs p)
     __shared__ int unit_s[kMaxExperts];
     __shared__ unsigned long long bm[kMaxUnits];
     __shared__ int off_s[kMaxUnits + 1], ucnt_s[kMaxUnits];
-    __shared__ int wsum[4];
+    __shared__ int wsum[4], repeated_s;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, seg = blockIdx.x;
+    if (tid == 0) repeated_s = 0;
     const int t0 = seg * kSegTokens, t1 = min(p.T, t0 + kSegTokens);
     int ex[kEntryBatch];
     float w[kEntryBatch];
@@ -866,13 +880,18 @@ __global__ void __launch_bounds__(256) route_scatter_kernel(RowArgs p)
     __syncthreads();
     const int32_t* soff = p.seg_off + (size_t)seg * p.U;
     const int j = tid & ((1 << p.lk) - 1);
+    bool repeated = false;                                 // an entry without a positive weight may repeat its expert
 #pragma unroll
     for (int q = 0; q < kEntryBatch; ++q) {
         if (q * 256 >= (kSegTokens << p.lk)) break;
         const int t = t0 + ((q * 256 + tid) >> p.lk);
+        repeated |= ex[q] >= 0 && !(w[q] > 0.0f);
         scatter_entry(p, bm, off_s, soff, t, j, ex[q], w[q], t < t1 && j < p.K, lane);
     }
     scatter_shared<256>(p, off_s, t0, t1, tid);
+    if (repeated) repeated_s = 1;
+    __syncthreads();
+    if (repeated_s) rewrite_repeated<256>(p, unit_s, t0, t1, tid);
 }
 
 // Small batches (at most 16 segments = 1024 tokens): Algorithm 1, the per-segment bitmaps, both scans and
@@ -886,7 +905,7 @@ __global__ void __launch_bounds__(1024) route_small_kernel(RowArgs p)
     __shared__ unsigned char s2_s[kMaxExperts];
     __shared__ int ucnt_s[kMaxUnits];
     __shared__ int off_s[kMaxUnits + 1];
-    __shared__ int wsum[16];
+    __shared__ int sum_s;
     unsigned long long* bm = reinterpret_cast<unsigned long long*>(rsm);                      // [n_seg][U]
     int* segoff = reinterpret_cast<int*>(rsm + (size_t)p.n_seg * p.U * 8);                     // [n_seg][U]
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -909,38 +928,31 @@ __global__ void __launch_bounds__(1024) route_small_kernel(RowArgs p)
         }
     }
     __syncthreads();
-    int c = 0;                                             // of expert tid >> 2
-    if ((tid >> 2) < p.m)
-        for (int sgm = tid & 3; sgm < p.n_seg; sgm += 4) c += __popcll(bm[sgm * p.U + (tid >> 2)]);
-    c += __shfl_xor(c, 1);
-    c += __shfl_xor(c, 2);
-    if ((tid & 3) == 0) cnt_s[tid >> 2] = c;
     {
-        int all = c;                                       // of the wavefront's 16 experts
-#pragma unroll
-        for (int o = 4; o < 64; o <<= 1) all += __shfl_xor(all, o);
-        if (lane == 0) wsum[wave] = all;
-    }
-    __syncthreads();
-    {
-        int all = 0;
-#pragma unroll
-        for (int w8 = 0; w8 < 16; ++w8) all += wsum[w8];
-        if (all != p.T * p.K) {                            // the same in every thread
-            // a token that names an expert twice (see scatter_entry): cnt_i counts entries
-            if (tid < kMaxExperts) cnt_s[tid] = 0;
-            __syncthreads();
-            for (int b = 0; b < entries; b += BATCH) {
-                if (!once) load_entries<1024, false>(p, b, 0, p.T, tid, ex, w);
-#pragma unroll
-                for (int q = 0; q < kEntryBatch; ++q)
-                    if (ex[q] >= 0) atomicAdd(&cnt_s[ex[q]], 1);
-            }
-            __syncthreads();
+        const int i = tid >> 2;
+        int c = 0;
+        if (i < p.m)
+            for (int sgm = tid & 3; sgm < p.n_seg; sgm += 4) c += __popcll(bm[sgm * p.U + i]);
+        c += __shfl_xor(c, 1);
+        c += __shfl_xor(c, 2);
+        if ((tid & 3) == 0) {
+            cnt_s[i] = c;
+            if (i < p.m) p.expert_cnt_out[i] = c;
         }
     }
-    if (tid < p.m) p.expert_cnt_out[tid] = cnt_s[tid];
-    brownout_decide<4>(cnt_s, s2_s, unit_s, p.m, p.way, p.threshold, p.full, tid, true, p.expert_unit, p.expert_in_s1);
+    __syncthreads();
+    bool repeated = false;                                 // some token names an expert twice (see rewrite_repeated)
+    for (;;) {
+        brownout_decide<4>(cnt_s, s2_s, unit_s, &sum_s, p.m, p.way, p.threshold, p.full, tid, true, p.expert_unit,
+                           p.expert_in_s1);
+        if (repeated || sum_s == p.T * p.K) break;
+        repeated = true;                                   // cnt_i counts entries, not tokens
+        if (tid < kMaxExperts) cnt_s[tid] = 0;
+        __syncthreads();
+        for (int e = tid; e < p.T * p.K; e += 1024) atomicAdd(&cnt_s[p.topk_idx[e]], 1);
+        __syncthreads();
+        if (tid < p.m) p.expert_cnt_out[tid] = cnt_s[tid];
+    }
     for (int e = tid; e < p.n_seg * p.G; e += 1024) {
         const int sgm = e / p.G, g = e - sgm * p.G;
         const int lo = g * p.way, hi = min(p.m, lo + p.way);
@@ -1003,6 +1015,7 @@ __global__ void __launch_bounds__(1024) route_small_kernel(RowArgs p)
         }
     }
     scatter_shared<1024>(p, off_s, 0, p.T, tid);
+    if (repeated) rewrite_repeated<1024>(p, unit_s, 0, p.T, tid);
 }
 
 constexpr int kGateFewLds = 3 * 4 * 64 * 128;          // three stages of four 64-row pieces (gate_few_kernel)
