@@ -5,13 +5,11 @@
 //            for at most 16 experts and small batches, in plain fp64; TopK by wavefront shuffles, weights g, expert
 //            histogram.  More than 16 experts: two launches, logits (blocks of 16, 64 or 128 tokens by 64 experts by a
 //            slice of K) and TopK                                    (Architecture of BrownoutMoE)
-//   count    Algorithm 1's S1/S2 split and unit map (every block, from the counts) and the rows
-//            each 64-token segment gives each unit                   (Brownout Approach, Algorithm 1)
-//   scan     offsets of segments inside units, unit totals (unit offsets: scanned by the scatter blocks)
-//   scatter  row lists: row_token, row_weight, token_rows (stable: ascending token inside a unit); one more block
-//            behind those of the segments writes the unit offsets and the GEMM tile tables
-//   small    at most 1024 tokens: expert counts, Algorithm 1, both scans, the scatter and the tile tables
-//            in ONE block
+//   rows     up to 8192 tokens, one launch: expert counts, Algorithm 1's S1/S2 split and unit map (Brownout Approach,
+//            Algorithm 1), the row lists row_token, row_weight, token_rows (stable: ascending token inside a unit) and the
+//            GEMM tile tables; up to 64 tokens it takes TopK as well
+//   count, scan, scatter   the same for larger batches: the rows each 64-token segment gives each unit, offsets of segments
+//            inside units and unit totals, row lists and tile tables
 // No floating-point atomics anywhere; integer atomics only where the result does not depend on order.
 #include "internal.h"
 #include "tiles.h"
@@ -70,6 +68,9 @@ struct GateArgs {
     int n_slice;           // 17 experts and more: slices of K, each leaving fp64 partial logits
     void* logits;          // one slice: [T][m_pad] fp32, bias added; else [n_slice][T][m_pad] fp64
     int32_t* clear_cnt;    // expert counters the logit kernel clears for the TopK launch behind it (or null)
+    unsigned long long* bits;   // [n_seg][m]: which of a segment's 64 tokens name the expert (null: not wanted).  The last
+                                // segment's quarters without tokens are not written
+    int t_base;            // token of the batch that token 0 of this launch is (a multiple of 16 with bits)
 };
 
 // TopK(.,K) of one token by one wavefront: lane holds experts lane, lane+64, ...; K (+1 for the best
@@ -88,14 +89,9 @@ __device__ __forceinline__ void better(float& bv, int& bi, float ov, int oi)
     if (take) { bv = ov; bi = oi; }
 }
 
-// the same when both ids are real
-__device__ __forceinline__ void better_of_two(float& bv, int& bi, float ov, int oi)
-{
-    const bool take = ov > bv || (ov == bv && oi < bi);
-    if (take) { bv = ov; bi = oi; }
-}
-
-__device__ __forceinline__ void topk_token(const GateArgs& p, const float (&v)[4], int t, int lane, int* hist)
+// put(j, expert, weight): called by the lanes that hold a winner, besides the store to the output arrays.
+template <typename Put>
+__device__ __forceinline__ void topk_token(const GateArgs& p, const float (&v)[4], int t, int lane, Put put)
 {
     const int K = p.K;
     const int n_pick = K < p.m ? K + 1 : K;    // one extra pick: the best loser, for the near-tie flag
@@ -146,45 +142,60 @@ __device__ __forceinline__ void topk_token(const GateArgs& p, const float (&v)[4
     const bool close = lane + 1 < n_pick && (my_v - nxt) < 1e-6f;
     const unsigned long long any_close = __ballot(close);
     if (lane < K) {
+        const float w = num / den;
         p.topk_idx[(size_t)t * K + lane] = my_i;
-        p.topk_w[(size_t)t * K + lane] = num / den;
-        if (hist != nullptr) atomicAdd(&hist[my_i], 1);
+        p.topk_w[(size_t)t * K + lane] = w;
+        put(lane, my_i, w);
     }
     if (lane == 0 && p.near_tie != nullptr) p.near_tie[t] = any_close != 0ull ? 1 : 0;
 }
 
+// A logit as an integer of the same order (-0 as +0, NaN as -infinity) and back.
+__device__ __forceinline__ int order_key(float v)
+{
+    const int i = __float_as_int(v + 0.0f);
+    return v != v ? (int)0x807fffff : i ^ ((i >> 31) & 0x7fffffff);
+}
+__device__ __forceinline__ float key_value(int k) { return __int_as_float(k ^ ((k >> 31) & 0x7fffffff)); }
+// the other operand comes through the instruction itself
+template <int CTRL>
+__device__ __forceinline__ int max_dpp(int v) { return max(v, __builtin_amdgcn_update_dpp(v, v, CTRL, 0xF, 0xF, true)); }
+template <int CTRL>
+__device__ __forceinline__ int min_dpp(int v) { return min(v, __builtin_amdgcn_update_dpp(v, v, CTRL, 0xF, 0xF, true)); }
+
 // The same for four tokens at a time: token `row` = lane >> 4 of the four is handled by the 16 lanes of its
 // row, lane r of the row holding experts r, r+16, ... (NC of them: NC >= m_pad / 16); every reduction stays
 // inside the row (rotations), so the four selections run side by side.  A lane's experts that do not exist or
-// have been picked hold -infinity (logits are finite, and a row always has an expert left to pick), so a round
-// is a branch-free maximum over NC registers (first of equal values: the lower id) and four rotations.
+// have been picked hold -infinity (a row that has nothing above that left picks expert 0 again).  A round first takes the
+// maximum, over NC registers and four rotations, then the lowest id that holds it, the same way: about 6 NC / 2 + 16
+// instructions (value and id carried together: 9 a rotation; a block with 16 wavefronts is bound by their issue).
 // Needs K + 1 <= 16 (lane j of the row keeps the j-th winner).
 // v[c]: the logit of expert r + 16 c (-infinity: no such expert), t: the row's token, valid: whether it exists.
-template <int NC>
-__device__ __forceinline__ void topk_rows(const GateArgs& p, float (&v)[NC], int t, bool valid, int lane, int* hist)
+template <int NC, typename Put>
+__device__ __forceinline__ void topk_rows(const GateArgs& p, const float (&v)[NC], int t, bool valid, int lane, Put put)
 {
     const int K = p.K, r = lane & 15;
     const int n_pick = K < p.m ? K + 1 : K;
-    const float none = -__builtin_inff();
-    float my_v = 0.0f;
-    int my_i = 0;
+    constexpr int kNone = (int)0x807fffff;                  // -infinity
+    int k[NC];
+#pragma unroll
+    for (int c = 0; c < NC; ++c) k[c] = order_key(v[c]);
+    int my_k = 0, my_i = 0;
     for (int j = 0; j < n_pick; ++j) {
-        float bv = v[0];
-        int bc = 0;
+        int mx = k[0];
 #pragma unroll
-        for (int c = 1; c < NC; ++c)
-            if (v[c] > bv) { bv = v[c]; bc = c; }
-        int bi = r + 16 * bc;
-        better_of_two(bv, bi, dpp_f<0x121>(bv), dpp_i<0x121>(bi));
-        better_of_two(bv, bi, dpp_f<0x122>(bv), dpp_i<0x122>(bi));
-        better_of_two(bv, bi, dpp_f<0x124>(bv), dpp_i<0x124>(bi));
-        better_of_two(bv, bi, dpp_f<0x128>(bv), dpp_i<0x128>(bi));
-        const int wc = (bi & 15) == r ? (bi >> 4) : -1;     // the winner leaves its lane's candidates
+        for (int c = 1; c < NC; ++c) mx = max(mx, k[c]);
+        mx = max_dpp<0x128>(max_dpp<0x124>(max_dpp<0x122>(max_dpp<0x121>(mx))));
+        int id = 0x7fffffff;
 #pragma unroll
-        for (int c = 0; c < NC; ++c)
-            if (c == wc) v[c] = none;
-        if (r == j) { my_v = bv; my_i = bi; }
+        for (int c = NC - 1; c >= 0; --c) id = k[c] == mx ? 16 * c + r : id;
+        id = min_dpp<0x128>(min_dpp<0x124>(min_dpp<0x122>(min_dpp<0x121>(id))));
+        const int wc = (id & 15) == r ? (id >> 4) : -1;     // the winner leaves its lane's candidates
+#pragma unroll
+        for (int c = 0; c < NC; ++c) k[c] = c == wc ? kNone : k[c];
+        if (r == j) { my_k = mx; my_i = id; }
     }
+    const float my_v = key_value(my_k);
     const float top = __shfl(my_v, lane & ~15);
     float num = 0.0f;
     if (r < K) num = p.score_fn == 0 ? expf(my_v - top) : 1.0f / (1.0f + expf(-my_v));
@@ -198,9 +209,49 @@ __device__ __forceinline__ void topk_rows(const GateArgs& p, float (&v)[NC], int
     const unsigned long long any_close = __ballot(close);
     if (valid) {
         if (r < K) {
+            const float w = num / den;
             p.topk_idx[(size_t)t * K + r] = my_i;
-            p.topk_w[(size_t)t * K + r] = num / den;
-            if (hist != nullptr) atomicAdd(&hist[my_i], 1);
+            p.topk_w[(size_t)t * K + r] = w;
+            put(r, my_i, w);
+        }
+        if (r == 0 && p.near_tie != nullptr) p.near_tie[t] = ((any_close >> (lane & 48)) & 0xFFFFull) != 0ull ? 1 : 0;
+    }
+}
+
+// The same for at most 16 experts, lane r of the row holding expert r, with topk_token's winners and weights: an expert already
+// taken is no candidate (so experts of logit -infinity are picked one after the other, not repeated), and the weights are added
+// up in its order.
+template <typename Put>
+__device__ __forceinline__ void topk_few(const GateArgs& p, float v, int t, bool valid, int lane, Put put)
+{
+    const int K = p.K, r = lane & 15;
+    const int n_pick = K < p.m ? K + 1 : K;
+    constexpr int kTaken = (int)0x80000000;
+    int k = r < p.m ? order_key(v) : kTaken;
+    int my_k = 0, my_i = 0;
+    for (int j = 0; j < n_pick; ++j) {
+        const int mx = max_dpp<0x128>(max_dpp<0x124>(max_dpp<0x122>(max_dpp<0x121>(k))));
+        int id = k == mx ? r : 16;
+        id = min_dpp<0x128>(min_dpp<0x124>(min_dpp<0x122>(min_dpp<0x121>(id))));
+        if (id == r) k = kTaken;
+        if (r == j) { my_k = mx; my_i = id; }
+    }
+    const float my_v = key_value(my_k);
+    const float top = dpp_f<0x150>(my_v);                   // row_newbcast: lane 0 of the row
+    float num = 0.0f;
+    if (r < K) num = p.score_fn == 0 ? expf(my_v - top) : 1.0f / (1.0f + expf(-my_v));
+    float den = num;
+#pragma unroll
+    for (int off = 8; off >= 1; off >>= 1) den += __shfl_xor(den, off);
+    const float nxt = __shfl(my_v, (lane & ~15) | ((r + 1) & 15));
+    const bool close = r + 1 < n_pick && (my_v - nxt) < 1e-6f;
+    const unsigned long long any_close = __ballot(close);
+    if (valid) {
+        if (r < K) {
+            const float w = num / den;
+            p.topk_idx[(size_t)t * K + r] = my_i;
+            p.topk_w[(size_t)t * K + r] = w;
+            put(r, my_i, w);
         }
         if (r == 0 && p.near_tie != nullptr) p.near_tie[t] = ((any_close >> (lane & 48)) & 0xFFFFull) != 0ull ? 1 : 0;
     }
@@ -295,7 +346,7 @@ __global__ void __launch_bounds__(512) gate_few_kernel(GateArgs p)
         const int tl = wave * 4 + (lane >> 4);
         const bool valid = t0 + tl < p.T;
         float v[1] = {(lane & 15) < p.m ? logit[tl * 16 + (lane & 15)] : -__builtin_inff()};
-        topk_rows<1>(p, v, t0 + tl, valid, lane, hist);
+        topk_rows<1>(p, v, t0 + tl, valid, lane, [&](int, int e, float) { atomicAdd(&hist[e], 1); });
     }
     __syncthreads();
     if (p.expert_cnt != nullptr && tid < p.m && hist[tid] > 0) atomicAdd(&p.expert_cnt[tid], hist[tid]);
@@ -376,13 +427,15 @@ __global__ void __launch_bounds__(256) gate_small_kernel(GateArgs p, const float
             double s = 0.0;
             for (int i = 0; i < 32; ++i) s += part[tid][i];
             if (p.bias != nullptr) s += (double)p.bias[e];
-            logit[q][e] = (float)s;
+            if (p.logits == nullptr) logit[q][e] = (float)s;
+            else if (t0 + q < p.T) static_cast<float*>(p.logits)[(size_t)(t0 + q) * p.m_pad + e] = (float)s;
         }
     }
+    if (p.logits != nullptr) return;                      // TopK is the routing block's (batches of one segment)
     __syncthreads();
     if (wave < TPB && t0 + wave < p.T) {
         const float v[4] = {lane < p.m ? logit[wave][lane & 15] : 0.0f, 0.0f, 0.0f, 0.0f};
-        topk_token(p, v, t0 + wave, lane, hist);
+        topk_token(p, v, t0 + wave, lane, [&](int, int e, float) { atomicAdd(&hist[e], 1); });
     }
     if (p.expert_cnt != nullptr) {                        // large batches: the launch's counts (cleared beforehand)
         __syncthreads();
@@ -565,34 +618,40 @@ __device__ __forceinline__ void read_logits(const GateArgs& p, int t, int e0, fl
     }
 }
 
-// TopK behind the logit kernel: 16 lanes per token (NC > 0, K + 1 <= 16 picks), else a wavefront per token.
+// TopK behind the logit kernel: 16 lanes per token (NC > 0, K + 1 <= 16 picks), else a wavefront per token.  The experts' tokens
+// leave as bitmaps (16 tokens per block: p.bits, a quarter of a segment's 64-bit word per expert) where the row kernel
+// takes the whole batch in, else as counts.
 template <int NC, int THREADS>
 __global__ void __launch_bounds__(THREADS) gate_topk_kernel(GateArgs p)
 {
-    constexpr int QB = THREADS == 1024 ? 1 : NC > 8 ? 4 : THREADS == 256 ? 8 : 4;
-    __shared__ int hist[kMaxExperts];
+    constexpr int QB = THREADS == 1024 && NC > 0 ? 1 : NC > 8 ? 4 : THREADS == 256 ? 8 : 4;
+    __shared__ int hist[kMaxExperts];                      // counts, or 16-bit maps of the block's tokens
     const int tid = threadIdx.x, lane = tid & 63;
-    const bool count = p.expert_cnt != nullptr;
-    if (count) {
-        for (int i = tid; i < p.m; i += blockDim.x) hist[i] = 0;
-        __syncthreads();
-    }
+    const bool bits = p.bits != nullptr;
+    for (int i = tid; i < p.m; i += THREADS) hist[i] = 0;
+    __syncthreads();
+    const int per = NC > 0 ? 16 : 64;                      // lanes of a token
+    const int tl = tid / per, t = (int)blockIdx.x * (THREADS / per) + tl;
+    auto put = [&](int, int e, float) {
+        if (bits) atomicOr(&hist[e], 1 << tl);
+        else atomicAdd(&hist[e], 1);
+    };
     if constexpr (NC > 0) {
-        const int t = (int)((blockIdx.x * blockDim.x + tid) >> 4);
         float v[NC];
         read_logits<NC, 16, QB>(p, min(t, p.T - 1), lane & 15, -__builtin_inff(), v);
-        topk_rows<NC>(p, v, t, t < p.T, lane, count ? hist : nullptr);
-    } else {
-        const int t = (int)((blockIdx.x * blockDim.x + tid) >> 6);
-        if (t < p.T) {
-            float v[4];
-            read_logits<4, 64, QB>(p, t, lane, 0.0f, v);
-            topk_token(p, v, t, lane, count ? hist : nullptr);
-        }
+        topk_rows<NC>(p, v, t, t < p.T, lane, put);
+    } else if (t < p.T) {
+        float v[4];
+        read_logits<4, 64, QB>(p, t, lane, 0.0f, v);
+        topk_token(p, v, t, lane, put);
     }
-    if (count) {
-        __syncthreads();
-        for (int i = tid; i < p.m; i += blockDim.x)
+    __syncthreads();
+    if (bits) {
+        const int t16 = p.t_base / 16 + (int)blockIdx.x;
+        unsigned short* out = reinterpret_cast<unsigned short*>(p.bits) + (size_t)(t16 >> 2) * p.m * 4 + (t16 & 3);
+        for (int i = tid; i < p.m; i += THREADS) out[4 * i] = (unsigned short)hist[i];
+    } else if (p.expert_cnt != nullptr) {
+        for (int i = tid; i < p.m; i += THREADS)
             if (hist[i] > 0) atomicAdd(&p.expert_cnt[i], hist[i]);
     }
 }
@@ -664,29 +723,27 @@ struct RowArgs {
     int32_t* seg_cnt; int32_t* seg_off;
     int32_t* unit_cnt; int32_t* unit_off; int32_t* n_rows;
     int32_t* row_token; float* row_weight; int32_t* token_rows;
-    int32_t* expert_cnt_out;                               // small batches: the routing block counts the experts itself
+    int32_t* expert_cnt_out;                               // route_rows_kernel counts the experts itself
+    const unsigned long long* bits;                        // its input where it does not build them: [n_seg][m] (GateArgs::bits)
     TileJobs jobs;                                         // GEMM tile tables to build (jobs.n == 0: none)
 };
 
 // The row kernels give every TopK entry a lane of its own: a token's K entries lie in 2^lk neighbouring lanes (never
-// across a wavefront, K <= 32), entry e of a block is entry e mod 2^lk of its token e >> lk.  One lane per token
-// walked its entries one after the other, each a chain of global read, LDS read and atomic, and read the lists of
-// merged units K^2/2 times: 51 us for 1021 tokens of 8 entries over 256 experts in one block (now 28 to 31; three
-// launches instead take 24 and 6 more for the histogram), 14.1 us for one token over 128 (8.3); with a segment per block
-// instead of four, and Algorithm 1 on four lanes per expert, the count of 3001 x 8 over 128 went from 11 to 5.9 us and the
-// scatter from 18 to 6.2.
-constexpr int kEntryBatch = 8;         // entries a thread holds at a time
-static_assert(kMaxTopK <= 32 && kSegTokens * 32 <= kEntryBatch * 256, "a segment's entries fit 256 threads");
+// across a wavefront, K <= 32), entry e of a block is entry e mod 2^lk of its token e >> lk.  (One lane per token walked its
+// entries one after the other, each a chain of global read, LDS read and atomic.)
+template <int NT>
+constexpr int entry_batch() { return kSegTokens * kMaxTopK / NT; }     // entries a thread holds: a segment's fit NT threads
+static_assert(kMaxTopK <= 32, "lanes of a token");
 
-// Entries first + q NT + tid, q = 0..kEntryBatch-1, of the tokens [t0, t1): expert (-1: no such entry) and weight.
+// Entries q NT + tid, q = 0.., of the tokens [t0, t1): expert (-1: no such entry) and weight.
 template <int NT, bool WEIGHTS>
-__device__ __forceinline__ void load_entries(const RowArgs& p, int first, int t0, int t1, int tid, int (&ex)[kEntryBatch],
-                                             float (&w)[kEntryBatch])
+__device__ __forceinline__ void load_entries(const RowArgs& p, int t0, int t1, int tid, int (&ex)[entry_batch<NT>()],
+                                             float (&w)[entry_batch<NT>()])
 {
     const int j = tid & ((1 << p.lk) - 1);                 // 2^lk divides NT: the same in every entry of the thread
 #pragma unroll
-    for (int q = 0; q < kEntryBatch; ++q) {
-        const int t = t0 + ((first + q * NT + tid) >> p.lk);
+    for (int q = 0; q < entry_batch<NT>(); ++q) {
+        const int t = t0 + ((q * NT + tid) >> p.lk);
         ex[q] = -1;
         w[q] = 0.0f;
         if (t < t1 && j < p.K) {
@@ -700,7 +757,7 @@ __device__ __forceinline__ void load_entries(const RowArgs& p, int first, int t0
 // that several entries of the token name gets one row, at the first of them, with the sum of their weights in TopK
 // order.  bmw: bitmaps of the token's segment, soff: rows of every unit in earlier segments.
 __device__ __forceinline__ void scatter_entry(const RowArgs& p, const unsigned long long* bmw, const int* off_s,
-                                              const int32_t* soff, int t, int j, int u, float w, bool valid, int lane)
+                                              const int* soff, int t, int j, int u, float w, bool valid, int lane)
 {
     bool first = u >= 0;
     if (__ballot(u >= p.m) != 0) {
@@ -767,16 +824,17 @@ __global__ void __launch_bounds__(1024) route_count_kernel(RowArgs p)
     __shared__ unsigned long long bm[kMaxUnits];
     const int tid = threadIdx.x, seg = blockIdx.x;
     const int t0 = seg * kSegTokens, t1 = min(p.T, t0 + kSegTokens);
-    int ex[kEntryBatch];
-    float w[kEntryBatch];
-    load_entries<1024, false>(p, 0, t0, t1, tid, ex, w);    // on their way while Algorithm 1 runs
+    constexpr int NE = entry_batch<1024>();
+    int ex[NE];
+    float w[NE];
+    load_entries<1024, false>(p, t0, t1, tid, ex, w);       // on their way while Algorithm 1 runs
     if (tid < kMaxExperts) cnt_s[tid] = tid < p.m ? p.expert_cnt[tid] : 0;
     for (int i = tid; i < p.U; i += 1024) bm[i] = 0ull;
     __syncthreads();
     brownout_decide<4>(cnt_s, s2_s, unit_s, nullptr, p.m, p.way, p.threshold, p.full, tid, seg == 0, p.expert_unit,
                        p.expert_in_s1);
 #pragma unroll
-    for (int q = 0; q < kEntryBatch; ++q) {
+    for (int q = 0; q < NE; ++q) {
         const int u = ex[q] >= 0 ? unit_s[ex[q]] : -1;
         // a repeated united unit sets the same bit again
         if (u >= 0) atomicOr(&bm[u], 1ull << (((q * 1024 + tid) >> p.lk) & 63));
@@ -860,9 +918,10 @@ __global__ void __launch_bounds__(256) route_scatter_kernel(RowArgs p)
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, seg = blockIdx.x;
     if (tid == 0) repeated_s = 0;
     const int t0 = seg * kSegTokens, t1 = min(p.T, t0 + kSegTokens);
-    int ex[kEntryBatch];
-    float w[kEntryBatch];
-    load_entries<256, true>(p, 0, t0, t1, tid, ex, w);
+    constexpr int NE = entry_batch<256>();
+    int ex[NE];
+    float w[NE];
+    load_entries<256, true>(p, t0, t1, tid, ex, w);
     if (tid < p.m) unit_s[tid] = p.expert_unit[tid];
     for (int i = tid; i < p.U; i += 256) bm[i] = 0ull;
     unit_offsets(p.unit_cnt, p.U, ucnt_s, off_s, wsum, tid);
@@ -873,7 +932,7 @@ __global__ void __launch_bounds__(256) route_scatter_kernel(RowArgs p)
         return;
     }
 #pragma unroll
-    for (int q = 0; q < kEntryBatch; ++q) {
+    for (int q = 0; q < NE; ++q) {
         ex[q] = ex[q] >= 0 ? unit_s[ex[q]] : -1;
         if (ex[q] >= 0) atomicOr(&bm[ex[q]], 1ull << (((q * 256 + tid) >> p.lk) & 63));
     }
@@ -882,7 +941,7 @@ __global__ void __launch_bounds__(256) route_scatter_kernel(RowArgs p)
     const int j = tid & ((1 << p.lk) - 1);
     bool repeated = false;                                 // an entry without a positive weight may repeat its expert
 #pragma unroll
-    for (int q = 0; q < kEntryBatch; ++q) {
+    for (int q = 0; q < NE; ++q) {
         if (q * 256 >= (kSegTokens << p.lk)) break;
         const int t = t0 + ((q * 256 + tid) >> p.lk);
         repeated |= ex[q] >= 0 && !(w[q] > 0.0f);
@@ -894,129 +953,345 @@ __global__ void __launch_bounds__(256) route_scatter_kernel(RowArgs p)
     if (repeated_s) rewrite_repeated<256>(p, unit_s, t0, t1, tid);
 }
 
-// Small batches (at most 16 segments = 1024 tokens): Algorithm 1, the per-segment bitmaps, both scans and
-// the scatter in ONE block of 16 wavefronts, everything in LDS.  Dynamic LDS: bitmaps [n_seg][U] (8 bytes) then
-// segment offsets [n_seg][U] (4 bytes).
-__global__ void __launch_bounds__(1024) route_small_kernel(RowArgs p)
+// Workgroup barrier for what goes through LDS: the stores and loads of a wave to memory stay in flight across it (waiting for
+// the outputs of every step cost the rows kernel about 1 us a barrier).
+__device__ __forceinline__ void lds_sync()
 {
-    extern __shared__ __attribute__((aligned(16))) unsigned char rsm[];
-    __shared__ __attribute__((aligned(16))) int cnt_s[kMaxExperts];
-    __shared__ int unit_s[kMaxExperts];
-    __shared__ unsigned char s2_s[kMaxExperts];
-    __shared__ int ucnt_s[kMaxUnits];
-    __shared__ int off_s[kMaxUnits + 1];
-    __shared__ int sum_s;
-    unsigned long long* bm = reinterpret_cast<unsigned long long*>(rsm);                      // [n_seg][U]
-    int* segoff = reinterpret_cast<int*>(rsm + (size_t)p.n_seg * p.U * 8);                     // [n_seg][U]
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int entries = p.T << p.lk;
-    constexpr int BATCH = kEntryBatch * 1024;              // up to K = 8 with 1024 tokens: read once, kept in registers
-    const bool once = entries <= BATCH;
-    int ex[kEntryBatch];
-    float w[kEntryBatch];
-    load_entries<1024, true>(p, 0, 0, p.T, tid, ex, w);
-    for (int i = tid; i < p.n_seg * p.U; i += 1024) bm[i] = 0ull;
-    __syncthreads();
-    // One pass of atomics: the tokens of every expert as bitmaps.  Their bits counted are cnt_i, the input of Algorithm 1,
-    // where no token names an expert twice; the bitmap of a united unit is the union of the experts it stands for.
-    for (int b = 0; b < entries; b += BATCH) {
-        if (!once) load_entries<1024, false>(p, b, 0, p.T, tid, ex, w);
-#pragma unroll
-        for (int q = 0; q < kEntryBatch; ++q) {
-            const int t = (b + q * 1024 + tid) >> p.lk;
-            if (ex[q] >= 0) atomicOr(&bm[(t >> 6) * p.U + ex[q]], 1ull << (t & 63));
-        }
-    }
-    __syncthreads();
-    {
-        const int i = tid >> 2;
-        int c = 0;
-        if (i < p.m)
-            for (int sgm = tid & 3; sgm < p.n_seg; sgm += 4) c += __popcll(bm[sgm * p.U + i]);
-        c += __shfl_xor(c, 1);
-        c += __shfl_xor(c, 2);
-        if ((tid & 3) == 0) {
-            cnt_s[i] = c;
-            if (i < p.m) p.expert_cnt_out[i] = c;
-        }
-    }
-    __syncthreads();
-    bool repeated = false;                                 // some token names an expert twice (see rewrite_repeated)
-    for (;;) {
-        brownout_decide<4>(cnt_s, s2_s, unit_s, &sum_s, p.m, p.way, p.threshold, p.full, tid, true, p.expert_unit,
-                           p.expert_in_s1);
-        if (repeated || sum_s == p.T * p.K) break;
-        repeated = true;                                   // cnt_i counts entries, not tokens
-        if (tid < kMaxExperts) cnt_s[tid] = 0;
-        __syncthreads();
-        for (int e = tid; e < p.T * p.K; e += 1024) atomicAdd(&cnt_s[p.topk_idx[e]], 1);
-        __syncthreads();
-        if (tid < p.m) p.expert_cnt_out[tid] = cnt_s[tid];
-    }
-    for (int e = tid; e < p.n_seg * p.G; e += 1024) {
-        const int sgm = e / p.G, g = e - sgm * p.G;
-        const int lo = g * p.way, hi = min(p.m, lo + p.way);
-        unsigned long long bits = 0ull;
-        for (int i = lo; i < hi; ++i)
-            if (unit_s[i] == p.m + g) bits |= bm[sgm * p.U + i];
-        bm[sgm * p.U + p.m + g] = bits;
-    }
-    __syncthreads();
-    for (int u = tid; u < p.U; u += 1024) {
-        int run = 0;
-        if (u < p.m && unit_s[u] != u) {
-            run = 0;                                       // its tokens have a row in the united unit, or none
-        } else if (u < p.m + p.G) {
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+}
+
+// Algorithm 1 as in brownout_decide, in 1024 threads, four neighbouring lanes per expert.  What bounds it is the issue of m^2
+// comparisons on one CU: a wave's 16 experts lie in step `wave` of its walk over the counts, so in all other steps the order
+// "count descending, id ascending" is one comparison with c or c - 1.  grp_s: zero; *any_s is set where a unit is united.
+__device__ __forceinline__ void decide_rows(const int* cnt_s, int* unit_s, int* grp_s, int* sum_s, int* any_s, const RowArgs& p,
+                                            int tid, bool write)
+{
+    const int ex = tid >> 2, part = tid & 3;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    bool in_s1 = false, s2 = false;
+    int gr = 0;
+    if (ex < p.m) {
+        const int c = cnt_s[ex];
+        int P = 0, S = 0;
+        const int4* c4 = reinterpret_cast<const int4*>(cnt_s) + part;
+        const int steps = (p.m + 15) >> 4;                  // (counts past m are zero)
+        gr = ex / p.way;
+        auto add = [&](int it, int th) {
+            const int4 v = c4[4 * it];
+            S += (v.x + v.y) + (v.z + v.w);
+            P += (v.x > th ? v.x : 0) + (v.y > th ? v.y : 0);
+            P += (v.z > th ? v.z : 0) + (v.w > th ? v.w : 0);
+        };
 #pragma unroll 4
-            for (int sgm = 0; sgm < p.n_seg; ++sgm) {
-                segoff[sgm * p.U + u] = run;
-                run += __popcll(bm[sgm * p.U + u]);
+        for (int it = 0; it < wave; ++it) add(it, c - 1);
+        {
+            const int4 v = c4[4 * wave];
+            const int j = 16 * wave + 4 * part;
+            S += (v.x + v.y) + (v.z + v.w);
+            P += v.x > c - (j < ex) ? v.x : 0;
+            P += v.y > c - (j + 1 < ex) ? v.y : 0;
+            P += v.z > c - (j + 2 < ex) ? v.z : 0;
+            P += v.w > c - (j + 3 < ex) ? v.w : 0;
+        }
+#pragma unroll 4
+        for (int it = wave + 1; it < steps; ++it) add(it, c);
+        S += dpp_i<0xB1>(S);                                // quad_perm: lanes l ^ 1, then l ^ 2
+        P += dpp_i<0xB1>(P);
+        S += dpp_i<0x4E>(S);
+        P += dpp_i<0x4E>(P);
+        in_s1 = (double)P < (double)S * p.threshold;
+        s2 = !in_s1 && c > 0;
+        if (part == 0 && s2) atomicAdd(&grp_s[gr], 1);
+        if (tid == 0) *sum_s = S;
+    }
+    lds_sync();
+    if (ex < p.m && part == 0) {
+        const int unit = !s2 ? ex : p.full ? -1 : grp_s[gr] >= 2 ? p.m + gr : ex;
+        unit_s[ex] = unit;
+        if (unit >= p.m) *any_s = 1;
+        if (write) {
+            if (p.expert_unit) p.expert_unit[ex] = unit;
+            if (p.expert_in_s1) p.expert_in_s1[ex] = in_s1 ? 1 : 0;
+        }
+    }
+    lds_sync();
+}
+
+// Batches whose bitmaps fit a block's LDS: everything behind the TopK lists in one launch, a block per segment and one more that
+// writes what the whole batch has one of (counts, unit maps and offsets, tile tables).  Nothing passes between blocks: each
+// counts the whole batch from the bitmaps of its TopK entries (token t of segment g names expert i: bit t mod 64 of word
+// [g][i]), takes Algorithm 1's decision and the unit offsets from that and scatters its own segment.
+//   kBits  the bitmaps come from the TopK launch
+//   kLists every block makes them from the TopK lists (at most 16 experts: a ballot per expert; more: LDS atomics)
+//   kTopK  one segment: the block takes TopK of the logits itself and is the only one (NC: 1 topk_few, more topk_rows, 0
+//          topk_token)
+// Bound by latency: some ten barriers, two trips to the L2 and what a block reads of the bitmaps (8 m bytes per segment).  TopK
+// and rows in us, before (TopK launch, then one block up to 1024 tokens or three launches) and now: 1 token x 8 of 128
+// experts 8.6 + 9.2, 9.4; 37 x 4 of 60 4.8 + 8.2, 10.9; 1021 x 8 of 256 14.7 + 32.2, 13.8 + 14.4; 3001 x 8 of 128 12.3 + 6.0 + 3.0 +
+// 6.4, 7.9 + 9.0; 8192 x 8 of 128 16.3 + 7.2 + 5.0 + 10.6, 11.2 + 18.5.
+enum { kBits, kLists, kTopK };
+// A row of bitmaps in LDS: a word of padding after every eight, so that lanes that walk groups of eight experts find
+// different banks.
+__host__ __device__ constexpr int bit_slot(int e) { return e + (e >> 3); }
+__host__ __device__ constexpr int bit_pitch(int m) { return m + (m >> 3) + 1; }
+
+template <int SRC, int NC>
+__global__ void __launch_bounds__(1024) route_rows_kernel(RowArgs p, GateArgs g)
+{
+    extern __shared__ __attribute__((aligned(16))) unsigned char rsm[];      // bitmaps [n_seg][bit_pitch(m)]; kTopK: logits
+    __shared__ __attribute__((aligned(16))) int cnt_s[kMaxExperts], wsum[16];
+    __shared__ int unit_s[kMaxExperts], tok_s[kMaxExperts], grp_s[kMaxExperts];
+    __shared__ unsigned long long bm[kMaxUnits];           // this block's segment
+    __shared__ int ucnt_s[kMaxUnits], pre_s[kMaxUnits];    // rows of a unit: in all, in earlier segments
+    __shared__ int off_s[kMaxUnits + 1], sum_s, any_s;
+    __shared__ int ex_s[SRC == kTopK ? kSegTokens * kMaxTopK : 1];
+    __shared__ float w_s[SRC == kTopK ? kSegTokens * kMaxTopK : 1];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, seg = blockIdx.x;
+    const int t0 = seg * kSegTokens, t1 = min(p.T, t0 + kSegTokens);
+    const bool writer = SRC == kTopK || seg == p.n_seg;
+    unsigned long long* local = reinterpret_cast<unsigned long long*>(rsm);
+    const int bp = bit_pitch(p.m);
+    int ex[entry_batch<1024>()];
+    float w[entry_batch<1024>()];
+    if (SRC != kTopK) load_entries<1024, true>(p, t0, t1, tid, ex, w);
+    if (tid < p.U) {
+        bm[tid] = 0ull;
+        ucnt_s[tid] = 0;
+        pre_s[tid] = 0;
+    }
+    if (tid < kMaxExperts) { cnt_s[tid] = 0; tok_s[tid] = 0; grp_s[tid] = 0; }
+    if (tid == 0) any_s = 0;
+    if (SRC == kLists && p.m > 16)
+        for (int i = tid; i < p.n_seg * bp; i += 1024) local[i] = 0ull;
+    lds_sync();
+
+    // bitmaps, and the tokens of every expert
+    if constexpr (SRC == kTopK) {
+        constexpr int per = NC > 0 ? 16 : 64;
+        const int pitch = g.m_pad + 16;                    // floats: the four tokens of a wavefront on different banks
+        float* logit_s = reinterpret_cast<float*>(rsm);
+        if constexpr (NC != 1) {
+            // a thread per logit: the slices' partial sums, four tokens' at a time in flight, added in order
+            const float none = NC > 0 ? -__builtin_inff() : 0.0f;
+            int lm = 5;
+            while ((1 << lm) < g.m_pad) ++lm;
+            const int e = tid & ((1 << lm) - 1), tq = tid >> lm, rows = 1024 >> lm;
+            const int eb = min(e, g.m_pad - 1), plane = p.T * g.m_pad;
+            const double bias = g.bias != nullptr && e < p.m ? (double)g.bias[e] : 0.0;
+            if (g.n_slice == 1) {
+                for (int t = tq; t < p.T; t += rows)
+                    if (e < g.m_pad) logit_s[t * pitch + e] = e < p.m ? static_cast<const float*>(g.logits)[t * g.m_pad + e] : none;
+            } else {
+                const double* l = static_cast<const double*>(g.logits);
+                for (int tb = 0; tb < p.T; tb += 4 * rows) {
+                    double x[4][kGateSlices];
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        if (tb + q * rows >= p.T) break;
+                        const int at = min(tb + q * rows + tq, p.T - 1) * g.m_pad + eb;
+#pragma unroll
+                        for (int sl = 0; sl < kGateSlices; ++sl) x[q][sl] = l[min(sl, g.n_slice - 1) * plane + at];
+                    }
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const int t = tb + q * rows + tq;
+                        double v = 0.0;
+#pragma unroll
+                        for (int sl = 0; sl < kGateSlices; ++sl) v += sl < g.n_slice ? x[q][sl] : 0.0;
+                        if (g.bias != nullptr) v += bias;
+                        if (t < p.T && e < g.m_pad) logit_s[t * pitch + e] = e < p.m ? (float)v : none;
+                    }
+                }
+            }
+            lds_sync();
+        }
+        for (int t = tid / per; t < (p.T + 64 / per - 1) / (64 / per) * (64 / per); t += 1024 / per) {      // whole wavefronts
+            auto put = [&](int j, int e, float wt) {
+                ex_s[t * kMaxTopK + j] = e;
+                w_s[t * kMaxTopK + j] = wt;
+                atomicOr(&bm[e], 1ull << t);
+            };
+            const int r = lane & (per - 1), tt = min(t, p.T - 1);
+            if constexpr (NC == 1) {
+                topk_few(g, r < p.m ? static_cast<const float*>(g.logits)[(size_t)tt * 16 + r] : 0.0f, t, t < p.T, lane, put);
+            } else {
+                constexpr int N = NC > 0 ? NC : 4;
+                float v[N];
+#pragma unroll
+                for (int c = 0; c < N; ++c)
+                    v[c] = r + per * c < g.m_pad ? logit_s[tt * pitch + r + per * c] : NC > 0 ? -__builtin_inff() : 0.0f;
+                if constexpr (NC > 0) topk_rows<NC>(g, v, t, t < p.T, lane, put);
+                else topk_token(g, v, t, lane, put);
+            }
+        }
+        lds_sync();
+        if (tid < p.m) cnt_s[tid] = tok_s[tid] = __popcll(bm[tid]);
+    } else {
+        if constexpr (SRC == kLists) {
+            if (p.m <= 16) {
+                for (int sgm = wave; sgm < p.n_seg; sgm += 16) {
+                    const int t = sgm * kSegTokens + lane;
+                    unsigned long long mine = 0ull;
+                    int next = t < p.T ? p.topk_idx[(size_t)t * p.K] : -1;
+                    for (int j = 0; j < p.K; ++j) {
+                        const int e = next;
+                        if (j + 1 < p.K) next = t < p.T ? p.topk_idx[(size_t)t * p.K + j + 1] : -1;
+                        for (int i = 0; i < p.m; ++i) {
+                            const unsigned long long b = __ballot(e == i);
+                            if (lane == i) mine |= b;
+                        }
+                    }
+                    if (lane < p.m) local[sgm * bp + bit_slot(lane)] = mine;
+                }
+            } else {
+                for (int e = tid; e < p.T * p.K; e += 1024) {
+                    const int t = e / p.K;
+                    atomicOr(&local[(t >> 6) * bp + bit_slot(p.topk_idx[e])], 1ull << (t & 63));
+                }
+            }
+            lds_sync();
+        }
+        // an expert's segments are shared out to 1024 / 2^lm threads (2^lm: m up to a power of two)
+        int lm = 0;
+        while ((1 << lm) < p.m) ++lm;
+        const int e = tid & ((1 << lm) - 1), parts = 1024 >> lm;
+        const unsigned long long last = (p.T & 63) ? (1ull << (p.T & 63)) - 1ull : ~0ull;     // tokens of the last segment
+        if (e < p.m) {
+            int c = 0, pre = 0;
+#pragma unroll 8
+            for (int sgm = tid >> lm; sgm < p.n_seg; sgm += parts) {
+                unsigned long long b;
+                if constexpr (SRC == kLists) {
+                    b = local[sgm * bp + bit_slot(e)];
+                } else {
+                    b = p.bits[(size_t)sgm * p.m + e];
+                    if (sgm == p.n_seg - 1) b &= last;
+                    local[sgm * bp + bit_slot(e)] = b;
+                }
+                const int n = __popcll(b);
+                c += n;
+                pre += sgm < seg ? n : 0;
+                if (sgm == seg) bm[e] = b;
+            }
+            if (c > 0) atomicAdd(&cnt_s[e], c);
+            if (pre > 0) atomicAdd(&pre_s[e], pre);
+        }
+        lds_sync();
+        if (tid < p.m) tok_s[tid] = cnt_s[tid];
+    }
+    lds_sync();
+
+    // Algorithm 1.  Its input counts entries: where a token names an expert twice (see rewrite_repeated) these are more than
+    // the tokens.
+    bool repeated = false;
+    for (;;) {
+        decide_rows(cnt_s, unit_s, grp_s, &sum_s, &any_s, p, tid, writer);
+        if (repeated || sum_s == p.T * p.K) break;
+        repeated = true;
+        lds_sync();                                        // everyone has read the sum
+        if (tid < kMaxExperts) { cnt_s[tid] = 0; grp_s[tid] = 0; }
+        if (tid == 0) any_s = 0;
+        lds_sync();
+        for (int e = tid; e < p.T * p.K; e += 1024)
+            atomicAdd(&cnt_s[SRC == kTopK ? ex_s[e / p.K * kMaxTopK + e % p.K] : p.topk_idx[e]], 1);
+        lds_sync();
+    }
+    if (writer && tid < p.m) p.expert_cnt_out[tid] = cnt_s[tid];
+
+    // united units: the union of the bitmaps of the experts they stand for
+    if (any_s) {
+        if constexpr (SRC == kTopK) {
+            if (tid < p.G) {
+                const int lo = tid * p.way, hi = min(p.m, lo + p.way);
+                unsigned long long b = 0ull;
+#pragma unroll 4
+                for (int i = lo; i < hi; ++i) b |= unit_s[i] == p.m + tid ? bm[i] : 0ull;
+                bm[p.m + tid] = b;
+                ucnt_s[p.m + tid] = __popcll(b);
             }
         } else {
-            run = p.T;                                     // a shared expert: every token
+            int lg = 0;
+            while ((1 << lg) < p.G) ++lg;
+            const int gr = tid & ((1 << lg) - 1), parts = 1024 >> lg;
+            if (gr < p.G) {
+                const int lo = gr * p.way, hi = min(p.m, lo + p.way);
+                int c = 0, pre = 0;
+                for (int sgm = tid >> lg; sgm < p.n_seg; sgm += parts) {
+                    unsigned long long b = 0ull;
+#pragma unroll 4
+                    for (int i = lo; i < hi; ++i) b |= unit_s[i] == p.m + gr ? local[sgm * bp + bit_slot(i)] : 0ull;
+                    const int n = __popcll(b);
+                    c += n;
+                    pre += sgm < seg ? n : 0;
+                    if (sgm == seg) bm[p.m + gr] = b;
+                }
+                if (c > 0) atomicAdd(&ucnt_s[p.m + gr], c);
+                if (pre > 0) atomicAdd(&pre_s[p.m + gr], pre);
+            }
         }
-        ucnt_s[u] = run;
-        p.unit_cnt[u] = run;
+        lds_sync();
     }
-    __syncthreads();
-    if (wave == 0) {                                     // exclusive scan of the unit counts by one wavefront
-        const int per = (p.U + 63) / 64;
-        const int lo = min(p.U, lane * per), hi = min(p.U, lo + per);
-        int local = 0;
-        for (int u = lo; u < hi; ++u) local += ucnt_s[u];
-        int incl = local;
+
+    // rows of every unit and their exclusive scan, a thread per unit
+    {
+        const int u = tid;
+        int c = 0;
+        if (u < p.m) c = unit_s[u] == u ? tok_s[u] : 0;    // else its tokens have a row in the united unit, or none
+        else if (u < p.m + p.G) c = ucnt_s[u];
+        else if (u < p.U) c = p.T;                         // a shared expert: every token
+        int incl = c;
 #pragma unroll
         for (int off = 1; off < 64; off <<= 1) {
             const int o = __shfl_up(incl, off);
             if (lane >= off) incl += o;
         }
-        int run = incl - local;
-        for (int u = lo; u < hi; ++u) {
-            off_s[u] = run;
-            run += ucnt_s[u];
-        }
-        if (lane == 63) off_s[p.U] = incl;
-    }
-    __syncthreads();
-    for (int u = tid; u <= p.U; u += 1024) p.unit_off[u] = off_s[u];
-    if (tid == 0 && p.n_rows) p.n_rows[0] = off_s[p.U];
-    // the GEMM tile tables, by the last wavefronts (the first ones hold the tokens of a short batch)
-    if (15 - wave < p.jobs.n) build_tile_table(ucnt_s, off_s, p.jobs.job[15 - wave], p.jobs.cap, lane);
-    const int j = tid & ((1 << p.lk) - 1);
-    for (int b = 0; b < entries; b += BATCH) {
-        if (!once) load_entries<1024, true>(p, b, 0, p.T, tid, ex, w);
+        if (lane == 63) wsum[wave] = incl;
+        lds_sync();
+        static_assert(kMaxUnits <= 12 * 64, "units lie in the first 12 wavefronts");
+        int base = 0;
 #pragma unroll
-        for (int q = 0; q < kEntryBatch; ++q) {
-            const int e = b + q * 1024 + tid;
-            if (e - lane >= entries) break;                // whole wavefronts leave
-            const int t = e >> p.lk, sg = min(t >> 6, p.n_seg - 1);
-            const int u = ex[q] >= 0 ? unit_s[ex[q]] : -1;
-            scatter_entry(p, bm + sg * p.U, off_s, segoff + sg * p.U, t, j, u, w[q], t < p.T && j < p.K, lane);
+        for (int q = 0; q < 3; ++q) {
+            const int4 v = reinterpret_cast<const int4*>(wsum)[q];
+            base += (4 * q < wave ? v.x : 0) + (4 * q + 1 < wave ? v.y : 0) + (4 * q + 2 < wave ? v.z : 0) +
+                    (4 * q + 3 < wave ? v.w : 0);
         }
+        if (u < p.U) {
+            ucnt_s[u] = c;
+            off_s[u] = base + incl - c;
+            if (writer) { p.unit_cnt[u] = c; p.unit_off[u] = base + incl - c; }
+            if (u == p.U - 1) {
+                off_s[p.U] = base + incl;
+                if (writer) {
+                    p.unit_off[p.U] = base + incl;
+                    if (p.n_rows) p.n_rows[0] = base + incl;
+                }
+            }
+        }
+        lds_sync();
     }
-    scatter_shared<1024>(p, off_s, 0, p.T, tid);
-    if (repeated) rewrite_repeated<1024>(p, unit_s, 0, p.T, tid);
+    // the GEMM tile tables, by the last wavefronts (with kTopK the first ones hold the tokens of a short batch)
+    if (writer && 15 - wave < p.jobs.n) build_tile_table(ucnt_s, off_s, p.jobs.job[15 - wave], p.jobs.cap, lane);
+    if (SRC != kTopK && writer) return;
+
+    const int j = tid & ((1 << p.lk) - 1);
+#pragma unroll
+    for (int q = 0; q < entry_batch<1024>(); ++q) {
+        if (q * 1024 + tid - lane >= (t1 - t0) << p.lk) break;                     // whole wavefronts leave
+        const int tl = (q * 1024 + tid) >> p.lk;
+        const bool valid = t0 + tl < t1 && j < p.K;
+        if (SRC == kTopK) {
+            ex[q] = valid ? ex_s[tl * kMaxTopK + j] : -1;
+            w[q] = valid ? w_s[tl * kMaxTopK + j] : 0.0f;
+        }
+        scatter_entry(p, bm, off_s, pre_s, t0 + tl, j, ex[q] >= 0 ? unit_s[ex[q]] : -1, w[q], valid, lane);
+    }
+    scatter_shared<1024>(p, off_s, t0, t1, tid);
+    if (repeated) rewrite_repeated<1024>(p, unit_s, t0, t1, tid);
 }
+
+// Where the rows kernel takes a batch: up to kRowSegs segments whose bitmaps fit the LDS beside what it declares.
+constexpr int kRowSegs = 128, kRowLds = 145 * 1024;
+static bool rows_fit(int n_seg, int m) { return n_seg <= kRowSegs && (size_t)n_seg * bit_pitch(m) * 8 <= kRowLds; }
 
 constexpr int kGateFewLds = 3 * 4 * 64 * 128;          // three stages of four 64-row pieces (gate_few_kernel)
 // The block shapes of the logit kernel: 16 tokens with three stages, 64 and 128 tokens with two (two blocks fit a CU).
@@ -1036,11 +1311,19 @@ hipError_t init_route_kernels()
     e = hipFuncSetAttribute(reinterpret_cast<const void*>(gate_logits_kernel<4, 2, 2, 2, 2>),
                             hipFuncAttributeMaxDynamicSharedMemorySize, kGateLds128);
     if (e != hipSuccess) return e;
-    e = hipFuncSetAttribute(reinterpret_cast<const void*>(gate_few_kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
-                            kGateFewLds);
-    if (e != hipSuccess) return e;
-    return hipFuncSetAttribute(reinterpret_cast<const void*>(route_small_kernel),
-                               hipFuncAttributeMaxDynamicSharedMemorySize, kSmallSegs * kMaxUnits * 12);
+    const void* topk[] = {reinterpret_cast<const void*>(route_rows_kernel<kTopK, 0>),
+                          reinterpret_cast<const void*>(route_rows_kernel<kTopK, 4>),
+                          reinterpret_cast<const void*>(route_rows_kernel<kTopK, 8>),
+                          reinterpret_cast<const void*>(route_rows_kernel<kTopK, 16>)};
+    for (const void* k : topk)
+        if ((e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, kSegTokens * (kMaxExperts + 16) * 4)) != hipSuccess)
+            return e;
+    const void* rows[] = {reinterpret_cast<const void*>(route_rows_kernel<kBits, 0>),
+                          reinterpret_cast<const void*>(route_rows_kernel<kLists, 0>)};
+    for (const void* k : rows)
+        if ((e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, kRowLds)) != hipSuccess) return e;
+    return hipFuncSetAttribute(reinterpret_cast<const void*>(gate_few_kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+                               kGateFewLds);
 }
 
 hipError_t launch_pack_gate(const float* gate_w, int m, int m_pad, int d, bf16_t* packed, hipStream_t s)
@@ -1057,7 +1340,7 @@ template <int THREADS>
 static void launch_topk(const GateArgs& p, hipStream_t s)
 {
     const int blocks = ceil_div(p.T, THREADS / 16);
-    if (p.K + 1 > 16) gate_topk_kernel<0, THREADS><<<ceil_div(p.T, THREADS / 64), THREADS, 0, s>>>(p);
+    if (p.K + 1 > 16) gate_topk_kernel<0, 1024><<<ceil_div(p.T, 16), 1024, 0, s>>>(p);
     else if (p.m_pad <= 64) gate_topk_kernel<4, THREADS><<<blocks, THREADS, 0, s>>>(p);
     else if (p.m_pad <= 128) gate_topk_kernel<8, THREADS><<<blocks, THREADS, 0, s>>>(p);
     else gate_topk_kernel<16, THREADS><<<blocks, THREADS, 0, s>>>(p);
@@ -1068,38 +1351,61 @@ static int gate_token_tile(int64_t T, int n_eb)
     return T * n_eb <= kGateSmallTokens ? 16 : T * n_eb >= kGateLargeTokens ? 128 : 64;
 }
 
-// Logits and TopK of a batch with more than 16 experts.  `scratch` holds the logits; a batch whose logits it cannot
-// hold goes through it in pieces.  How K is sliced decides the order of a logit's sum, so it follows from the batch alone
-// (T, m, d): the same bits whatever the scratch holds.  The token tile of a piece does not (every tile adds up alike).
-static hipError_t launch_gate(GateArgs g, void* scratch, size_t bytes, hipStream_t s)
+// How a batch with more than 16 experts goes through the gate.  The order of a logit's sum follows from n_slice, so that
+// comes from the batch alone (T, m, d): the same bits whatever the scratch holds.  A batch whose logits the scratch cannot hold
+// goes through it in pieces of `chunk` tokens (the token tile of a piece does not show: every tile adds up alike).
+struct GatePlan { int n_slice, chunk; };
+static GatePlan plan_gate(int T, int m_pad, int d, size_t bytes)
 {
-    const int T = g.T, n_eb = ceil_div(g.m_pad, kGateExperts), ksteps = g.d / 64;
-    int sl = std::max(1, std::min({kGateBlocks / (ceil_div(T, gate_token_tile(T, n_eb)) * n_eb), kGateSlices, ksteps / 2}));
-    sl = ceil_div(ksteps, ceil_div(ksteps, sl));                         // no empty slice
-    g.n_slice = sl;
-    const int64_t most = (int64_t)(bytes / ((size_t)g.m_pad * (sl == 1 ? 4 : 8 * sl)));
-    const int chunk = (int)std::min<int64_t>(T, most >= 64 ? most / 64 * 64 : std::max<int64_t>(most, 1));
-    g.logits = scratch;
-    for (int c0 = 0; c0 < T; c0 += chunk) {
+    const int n_eb = ceil_div(m_pad, kGateExperts), ksteps = d / 64;
+    const int sl = std::max(1, std::min({kGateBlocks / (ceil_div(T, gate_token_tile(T, n_eb)) * n_eb), kGateSlices, ksteps / 2}));
+    GatePlan P;
+    P.n_slice = ceil_div(ksteps, ceil_div(ksteps, sl));                  // no empty slice
+    const int64_t most = (int64_t)(bytes / ((size_t)m_pad * (P.n_slice == 1 ? 4 : 8 * P.n_slice)));
+    const int64_t unit = most >= 64 ? 64 : most >= 16 ? 16 : 1;
+    P.chunk = (int)std::min<int64_t>(T, std::max<int64_t>(most / unit * unit, 1));
+    return P;
+}
+
+// Logits, and TopK of them unless the routing block takes it (g.topk_idx null).
+static hipError_t launch_gate(GateArgs g, const GatePlan& plan, bool topk, hipStream_t s)
+{
+    const int T = g.T, n_eb = ceil_div(g.m_pad, kGateExperts);
+    g.n_slice = plan.n_slice;
+    for (int c0 = 0; c0 < T; c0 += plan.chunk) {
         GateArgs p = g;
-        p.T = std::min(chunk, T - c0);
+        p.T = std::min(plan.chunk, T - c0);
+        p.t_base = c0;
         p.x = g.x + (size_t)c0 * g.d;
         p.topk_idx = g.topk_idx + (size_t)c0 * g.K;
         p.topk_w = g.topk_w + (size_t)c0 * g.K;
         if (g.near_tie != nullptr) p.near_tie = g.near_tie + c0;
         if (c0 > 0) p.clear_cnt = nullptr;
-        const int tile = gate_token_tile(p.T, n_eb), blocks = ceil_div(p.T, tile) * n_eb * sl;
+        const int tile = gate_token_tile(p.T, n_eb), blocks = ceil_div(p.T, tile) * n_eb * p.n_slice;
         if (tile == 16) gate_logits_kernel<1, 1, 1, 4, 3><<<blocks, 256, kGateLds16, s>>>(p);
         else if (tile == 128) gate_logits_kernel<4, 2, 2, 2, 2><<<blocks, 256, kGateLds128, s>>>(p);
         else gate_logits_kernel<2, 2, 2, 2, 2><<<blocks, 256, kGateLds64, s>>>(p);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
+        if (!topk) continue;
         if (p.expert_cnt == nullptr) launch_topk<256>(p, s);
         else if (p.n_slice > 1) launch_topk<512>(p, s);     // fewer, larger blocks: each flushes a histogram
         else launch_topk<1024>(p, s);                       // (partial logits need the registers, logits do not)
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     return hipSuccess;
+}
+
+// The block that takes TopK of a batch of one segment and routes it.
+static hipError_t launch_route_topk(const GateArgs& g, const RowArgs& p, hipStream_t s)
+{
+    const size_t lds = g.m_pad == 16 ? 0 : (size_t)p.T * (g.m_pad + 16) * 4;     // the logits
+    if (g.m_pad == 16) route_rows_kernel<kTopK, 1><<<1, 1024, lds, s>>>(p, g);
+    else if (g.K + 1 > 16) route_rows_kernel<kTopK, 0><<<1, 1024, lds, s>>>(p, g);
+    else if (g.m_pad <= 64) route_rows_kernel<kTopK, 4><<<1, 1024, lds, s>>>(p, g);
+    else if (g.m_pad <= 128) route_rows_kernel<kTopK, 8><<<1, 1024, lds, s>>>(p, g);
+    else route_rows_kernel<kTopK, 16><<<1, 1024, lds, s>>>(p, g);
+    return hipGetLastError();
 }
 
 hipError_t launch_route(const Dims& D, const bf16_t* x, const void* gate, const float* gate_bias,
@@ -1109,34 +1415,46 @@ hipError_t launch_route(const Dims& D, const bf16_t* x, const void* gate, const 
 {
     hipError_t e = ensure_device_init(nullptr);
     if (e != hipSuccess) return e;
-    const bool small = D.n_seg <= kSmallSegs;            // one block routes the whole batch (and counts the experts)
     const bool packed = D.gate_format == MOE_GATE_PACKED;
     // At most 16 experts: the gate matrix is fp32 rows in either format, and up to kFewExpertsTokens tokens the
     // plain fp64 gate reads them as they are (larger batches: cut here on every call, 6 us, then the MFMA gate).
     const bool few_fmt = D.m_pad == 16;
     const bool few = few_fmt && D.T <= kFewExpertsTokens;
+    // Who makes the row lists: one block that takes TopK of one segment's logits as well, a block per segment on the whole
+    // batch's bitmaps, or beyond kRowSegs segments the count, scan and scatter launches.
+    GatePlan plan{1, D.T};
+    if (!few_fmt) plan = plan_gate(D.T, D.m_pad, D.d, logit_bytes);
+    const bool whole = plan.chunk >= D.T;
+    enum { kOneBlock, kFromBits, kFromLists, kThreeLaunches } how = kThreeLaunches;
+    if (D.n_seg == 1 && whole) how = kOneBlock;
+    else if (!few_fmt && rows_fit(D.n_seg, D.m) && (whole || plan.chunk % 16 == 0)) how = kFromBits;
+    else if (rows_fit(D.n_seg, D.m) && (few_fmt || D.n_seg == 1)) how = kFromLists;
+    int32_t* counters = how == kThreeLaunches ? R.expert_cnt : nullptr;
     // Preparation: cut an fp32 gate matrix into its pieces (only the MFMA gates need them) and clear the expert
-    // counters (only large batches use them; the logit kernel of the many-expert gate clears them itself).
+    // counters, if used (the logit kernel of the many-expert gate clears them itself).
     const bool split = !few && (!packed || few_fmt);
-    if (split || (few_fmt && !small)) {
+    if (split || (few_fmt && counters != nullptr)) {
         ProfScope ps(MOE_STAGE_PREP, s);
         const size_t n = split ? (size_t)D.m_pad * D.d : (size_t)D.m;
         const int blocks = (int)std::min<size_t>((n + 255) / 256, 2048);
         prep_kernel<<<blocks, 256, 0, s>>>(split ? static_cast<const float*>(gate) : nullptr, D.m, D.m_pad, D.d,
-                                           split ? reinterpret_cast<unsigned short*>(gate_split) : nullptr,
-                                           small ? nullptr : R.expert_cnt);
+                                           split ? reinterpret_cast<unsigned short*>(gate_split) : nullptr, counters);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
+    GateArgs g;
+    g.x = x;
+    g.split = split ? reinterpret_cast<const unsigned short*>(gate_split) : static_cast<const unsigned short*>(gate);
+    g.bias = gate_bias;
+    g.T = D.T; g.d = D.d; g.m = D.m; g.m_pad = D.m_pad; g.K = D.K; g.score_fn = D.score_fn;
+    g.topk_idx = R.topk_idx; g.topk_w = R.topk_w; g.near_tie = R.near_tie;
+    g.expert_cnt = counters;
+    g.n_slice = plan.n_slice; g.clear_cnt = few_fmt ? nullptr : counters;
+    g.logits = few_fmt && how != kOneBlock ? nullptr : logits;
+    // the bitmaps take the place of the segment counts and offsets, which only the three launches use
+    g.bits = how == kFromBits ? reinterpret_cast<unsigned long long*>(seg_cnt) : nullptr;
+    g.t_base = 0;
     {
         ProfScope ps(MOE_STAGE_GATE, s);
-        GateArgs g;
-        g.x = x;
-        g.split = split ? reinterpret_cast<const unsigned short*>(gate_split) : static_cast<const unsigned short*>(gate);
-        g.bias = gate_bias;
-        g.T = D.T; g.d = D.d; g.m = D.m; g.m_pad = D.m_pad; g.K = D.K; g.score_fn = D.score_fn;
-        g.topk_idx = R.topk_idx; g.topk_w = R.topk_w; g.near_tie = R.near_tie;
-        g.expert_cnt = small ? nullptr : R.expert_cnt;
-        g.n_slice = 1; g.logits = nullptr; g.clear_cnt = few_fmt ? nullptr : g.expert_cnt;
         if (few) {
             const float* gw = static_cast<const float*>(gate);      // fp32 rows in either gate format
             if (D.m <= 8) gate_small_kernel<8, 1><<<D.T, 256, 0, s>>>(g, gw);
@@ -1145,7 +1463,7 @@ hipError_t launch_route(const Dims& D, const bf16_t* x, const void* gate, const 
             // at most 16 experts beyond kFewExpertsTokens tokens
             gate_few_kernel<<<ceil_div(D.T, 16), 512, kGateFewLds, s>>>(g);
         } else {
-            if ((e = launch_gate(g, logits, logit_bytes, s)) != hipSuccess) return e;
+            if ((e = launch_gate(g, plan, how != kOneBlock, s)) != hipSuccess) return e;
         }
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
@@ -1158,11 +1476,14 @@ hipError_t launch_route(const Dims& D, const bf16_t* x, const void* gate, const 
     while ((1 << p.lk) < D.K) ++p.lk;
     p.seg_cnt = seg_cnt; p.seg_off = seg_off; p.unit_cnt = R.unit_cnt; p.unit_off = R.unit_off; p.n_rows = R.n_rows;
     p.row_token = R.row_token; p.row_weight = R.row_weight; p.token_rows = R.token_rows;
-    p.expert_cnt_out = R.expert_cnt;
+    p.expert_cnt_out = R.expert_cnt; p.bits = g.bits;
     p.jobs = jobs;
-    if (small) {
+    if (how != kThreeLaunches) {
         ProfScope ps(MOE_STAGE_COUNT, s);
-        route_small_kernel<<<1, 1024, (size_t)D.n_seg * D.U * 12, s>>>(p);
+        if (how == kOneBlock) return launch_route_topk(g, p, s);
+        const size_t lds = (size_t)D.n_seg * bit_pitch(D.m) * 8;
+        if (how == kFromBits) route_rows_kernel<kBits, 0><<<D.n_seg + 1, 1024, lds, s>>>(p, g);
+        else route_rows_kernel<kLists, 0><<<D.n_seg + 1, 1024, lds, s>>>(p, g);
         return hipGetLastError();
     }
     {
