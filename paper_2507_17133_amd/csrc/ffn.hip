@@ -21,7 +21,7 @@
 //                                  further blocks of the same launch take the tiles left over after the last
 //                                  full round: cut along K (fp32 partial tiles, summed by
 //                                  gemm_tail_sum_kernel) or in two along N
-//   128 rows  ffn_gemm_pp_kernel   eight waves in two groups that alternate memory and MFMA phases
+//   128 rows  ffn_gemm_ws_kernel   four waves that load and four that multiply, persistent
 //   64, 32    ffn_gemm_kernel      four waves, plain multi-stage ring (decode: weight streaming bound);
 //             ffn_gemm_narrow_kernel  a quarter of the columns per block, where that kernel would have too few blocks
 #include "internal.h"
@@ -577,153 +577,212 @@ __global__ void __launch_bounds__(256) ffn_gemm_narrow_kernel(GemmArgs p)
 }
 
 // ------------------------------------------------------------------------------------------------
-// Large-tile kernel (BM x 256, 8 waves as 2 x 4), ping-pong: the two wave groups (wm = 0 / 1, one wave of
-// each per SIMD) run half a step out of phase, separated by barriers: while one group issues its 16
-// MFMAs for a 32-wide k step, the other reads its fragments of the next step from LDS and queues
-// global->LDS loads, so every SIMD's matrix pipe always has a wave feeding it.  Group 1 starts one
-// barrier late and group 0 ends one late.  k tiles of BK = 64 (full 128-byte lines per row), NSTAGE
-// LDS buffers; a tile is P = BK/32 steps.
+// Streaming kernel (128 rows, 16x16x32 MFMA, persistent): four waves load and four multiply, one of each per SIMD.  A CU keeps about
+// 32 KiB of loads that miss its L2 in flight (46 GB/s, whatever is queued behind them), and a wave that issues more waits in the
+// issue, its MFMAs with it.  Here the MFMAs do not show in the time where weights stream (8 units of 64 rows, 28672 x 4096: 354 us
+// with and without them), and the loaders run up to NST - 1 k tiles ahead, on into the next output tile while the others store
+// the last.  Against eight waves that load and multiply in turns (two groups out of phase, a block per tile): one unit of 256
+// rows 79 -> 69.6 us (28672 x 4096) and 62.8 -> 44.0 (4096 x 14336), 8 units of 64 rows 360 -> 338 and 177 -> 170; layer
+// forward of 1400 Mixtral-shaped tokens 1383 -> 1272, 4000 of the Qwen3 shape 558 -> 497, 2000 of the DeepSeek-V3 shape 4670
+// -> 4490.  (A wave that has both roles but reads its fragments a step ahead, as in the 256-row kernel: 94.5 and 76.8 us for
+// the one unit.  Starts of the k walk spread over the blocks, so that rows a power of two apart are not read at the same k:
+// 338 -> 354 us.)
+// One barrier per k tile, in the middle of the step before: tile c has landed, and everyone has read tile c-1, whose stage takes
+// tile c+NST-1.  What a loader needs of the next tile comes through the scalar cache: a vector load's wait would be one for every
+// load in flight.
 // ------------------------------------------------------------------------------------------------
-template <int BM, int BK, int NSTAGE, bool SWIGLU>
-__global__ void __launch_bounds__(512) ffn_gemm_pp_kernel(GemmArgs p)
+// Tile L of a launch whose blocks walk over several (L counts the tiles of all K slices).
+template <bool SWIGLU>
+__device__ __forceinline__ void tile_at(const GemmArgs& p, int n_mt, int n_ntiles, int bnc, int L, Tile& t)
 {
-    constexpr int BN = 256, WN = 4, NW = 8;
+    const int tiles = n_mt * n_ntiles;
+    t.kslice = p.ksplit > 1 ? L / tiles : 0;
+    t.ks = p.ksplit;
+    t.part = -1;
+    t.half = 0;
+    L -= t.kslice * tiles;
+    const int gspan = p.group_m * n_ntiles;
+    const int gi = L / gspan, rem = L - gi * gspan;
+    const int mt_first = gi * p.group_m;
+    const int gsz = min(p.group_m, n_mt - mt_first);
+    t.nt = rem / gsz;
+    const int mt = __builtin_amdgcn_readfirstlane(mt_first + (rem - t.nt * gsz));
+    typedef const __attribute__((address_space(4))) int* scalar_ptr;
+    const scalar_ptr te = (scalar_ptr)(unsigned long)(p.table + 4 + 4 * mt);
+    t.unit = te[0]; t.row0 = te[1]; t.nrows = te[2];
+    const int src = t.unit < p.m ? 0 : (t.unit < p.m + p.G ? 1 : 2);
+    const int widx = t.unit - (src == 0 ? 0 : (src == 1 ? p.m : p.m + p.G));
+    const size_t wsz = (size_t)p.N * p.K;
+    t.Wa = (src == 0 ? p.wa0 : (src == 1 ? p.wa1 : p.wa2)) + (size_t)widx * wsz;
+    t.Wb = SWIGLU ? (src == 0 ? p.wb0 : (src == 1 ? p.wb1 : p.wb2)) + (size_t)widx * wsz : nullptr;
+    t.n0 = t.nt * bnc;
+}
+
+constexpr int kWsStore = 16384;                          // 4 KiB of LDS per storing wave, beside the stages
+
+template <int BM, int BN, int WM, int WN, int NST, bool SWIGLU>
+__device__ __forceinline__ void ws_block(const GemmArgs& p, const int n_mt, const int n_ntiles)
+{
+    constexpr int BK = 64, NW = 4;                       // loaders, and as many (WM x WN) that multiply
     using L = Lds<BK>;
-    constexpr int TM = BM / 2, TN = BN / WN, FM = TM / 32, FN = TN / 32;
-    constexpr int RB = L::RB, RPG = L::RPG;
-    constexpr int STAGE = (BM + BN) * RB;
-    constexpr int GROUPS = (BM + BN) / RPG;
-    constexpr int LD_PER_WAVE = GROUPS / NW;
-    constexpr int P = BK / 32;
-    static_assert(GROUPS % NW == 0 && NSTAGE >= 2 && BK % 32 == 0, "loader shape");
-    static_assert(NSTAGE * STAGE <= 160 * 1024, "LDS budget of one CU");
+    constexpr int TM = BM / WM, TN = BN / WN, FM = TM / 16, FN = TN / 16;
+    constexpr int RB = L::RB, RPG = L::RPG, STAGE = (BM + BN) * RB, BNC = SWIGLU ? BN / 2 : BN;
+    constexpr int LA = BM / RPG / NW, LB = BN / RPG / NW, LD = LA + LB;       // loads of a loader and k tile
+    constexpr int NM = FM * FN, NRD = FM + FN, RV = NM / NRD;                 // a step: MFMAs, fragment reads, MFMAs per read
+    static_assert(WM * WN == NW && BM % 64 == 0 && BN % 64 == 0 && RV >= 1 && NST >= 3 && (NST - 1) * LD <= 63, "shape");
+    static_assert(NST * STAGE + kWsStore <= 160 * 1024, "LDS of a CU");
     extern __shared__ __attribute__((aligned(16))) char smem[];
+    typedef const __attribute__((address_space(4))) int* scalar_ptr;
 
-    Tile t;
-    if (!decode_tile<BM, SWIGLU ? BN / 2 : BN, SWIGLU>(p, t)) return;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wm = wave >> 2, wn = wave & 3;
-    const int grp = wm;
-    int k_first, nk;
-    k_range<BK>(p, t, k_first, nk);
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int total = n_mt * n_ntiles * p.ksplit;
+    // block id mod 8 = XCD: a contiguous range of tiles each, which its blocks sweep together
+    const int chunk = (total + 7) >> 3, slots = gridDim.x >> 3;
+    const int first = (blockIdx.x & 7) * chunk + (blockIdx.x >> 3), end = min(total, ((int)blockIdx.x & 7) * chunk + chunk);
 
-    const bf16_t* gptr[LD_PER_WAVE];
+    if (wave >= NW) {
+        const int lw = wave - NW;
+        const bf16_t *ga[LA], *gb[LB];
+        int next = first, kt = 0, nk = 0, stage = 0;
+        auto set_up = [&](const Tile& t) {
+            int k_first;
+            k_range<BK>(p, t, k_first, nk);
+            kt = 0;
+            if (nk <= 0) return;
+            const int r8 = lane >> 3;
 #pragma unroll
-    for (int i = 0; i < LD_PER_WAVE; ++i) {
-        const int row = (wave + i * NW) * RPG + L::lane_row(lane);
-        const bf16_t* base = row < BM ? a_row_ptr(p, t, row) : b_row_ptr<TN, SWIGLU>(p, t, row - BM);
-        gptr[i] = base + L::lane_chunk(lane, row) * 8 + (size_t)k_first * BK;
+            for (int i = 0; i < LA; ++i) {
+                const int row = (lw + i * NW) * RPG;      // rows row .. row + 7; past the tile's rows: its last one again
+                int src = t.row0 + min(row + r8, t.nrows - 1);
+                if (SWIGLU) {
+                    const scalar_ptr gi = (scalar_ptr)(unsigned long)(p.gather + t.row0);
+                    if (row + 8 <= t.nrows) {
+#pragma unroll
+                        for (int q = 0; q < 8; ++q) src = r8 == q ? gi[row + q] : src;
+                    } else {
+                        src = gi[t.nrows - 1];
+                        for (int q = 0; row + q < t.nrows; ++q) src = r8 == q ? gi[row + q] : src;
+                    }
+                }
+                ga[i] = p.A + (long)src * p.lda + L::lane_chunk(lane, row + r8) * 8 + (size_t)k_first * BK;
+                __builtin_amdgcn_sched_barrier(0);        // one group's indices at a time in scalar registers
+            }
+#pragma unroll
+            for (int i = 0; i < LB; ++i) {
+                const int row = (lw + i * NW) * RPG + r8;
+                gb[i] = b_row_ptr<TN, SWIGLU, 16>(p, t, row) + L::lane_chunk(lane, BM + row) * 8 + (size_t)k_first * BK;
+            }
+        };
+        auto issue_next = [&]() -> bool {
+            while (kt >= nk) {                            // on to the next tile that has any k
+                if (next >= end) return false;
+                Tile t;
+                tile_at<SWIGLU>(p, n_mt, n_ntiles, BNC, next, t);
+                next += slots;
+                set_up(t);
+            }
+                char* dst = smem + stage * STAGE + lw * 1024;
+#pragma unroll
+            for (int i = 0; i < LB; ++i)
+                __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(gb[i] + kt * BK),
+                                                 (__attribute__((address_space(3))) void*)(dst + BM * RB + i * NW * 1024), 16, 0, 0);
+#pragma unroll
+            for (int i = 0; i < LA; ++i)
+                __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(ga[i] + kt * BK),
+                                                 (__attribute__((address_space(3))) void*)(dst + i * NW * 1024), 16, 0, 0);
+            stage = stage == NST - 1 ? 0 : stage + 1;
+            ++kt;
+            return true;
+        };
+        int issued = 0;
+        while (issued < NST - 1 && issue_next()) ++issued;
+        for (int c = 0; c < issued; ++c) {
+            if (issued - c - 1 >= NST - 2) __builtin_amdgcn_s_waitcnt(vmcnt_imm((NST - 2) * LD));
+            else __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+            lds_barrier();                                // k tile c
+            if (issue_next()) ++issued;
+        }
+        return;
     }
-    auto issue_loads = [&](int kt) {
-        char* dst = smem + (kt % NSTAGE) * STAGE + wave * 1024;
-#pragma unroll
-        for (int i = 0; i < LD_PER_WAVE; ++i)
-            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(gptr[i] + kt * BK),
-                                             (__attribute__((address_space(3))) void*)(dst + i * NW * 1024), 16, 0, 0);
-    };
 
-    f32x16 acc[FM][FN];
-#pragma unroll
-    for (int i = 0; i < FM; ++i)
-#pragma unroll
-        for (int j = 0; j < FN; ++j)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
-
-#pragma unroll
-    for (int q = 0; q < NSTAGE - 1; ++q)
-        if (q < nk) issue_loads(q);
-    const int a_off = (wm * TM + (lane & 31)) * RB;
-    const int b_off = BM * RB + (wn * TN + (lane & 31)) * RB;
-    const int swz = L::read_swz(lane);
-    if (NSTAGE - 2 < nk && NSTAGE > 2) __builtin_amdgcn_s_waitcnt(vmcnt_imm((NSTAGE - 2) * LD_PER_WAVE));
-    else __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
-    lds_barrier();                                        // tile 0 is in LDS for everyone
-    // Loads of a tile are issued between the MFMAs of a compute phase, one per EV MFMAs, so the texture
-    // path sees a steady trickle instead of a burst that would hold the issuing wave (and with it the
-    // barrier the other group waits at).  The buffer of tile kt-1 is free once both groups have read its
-    // last fragments: group 1 (which runs one barrier late) refills it with tile kt+NSTAGE-1 during the last
-    // compute phase of tile kt-1, group 0 during the first compute phase of tile kt.
-    auto issue_one = [&](int kt, int i) {
-        char* dst = smem + (kt % NSTAGE) * STAGE + wave * 1024;
-        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(gptr[i] + kt * BK),
-                                         (__attribute__((address_space(3))) void*)(dst + i * NW * 1024), 16, 0, 0);
+    const int wm = wave / WN, wn = wave % WN;
+    const int a_off = (wm * TM + (lane & 15)) * RB, b_off = (BM + wn * TN + (lane & 15)) * RB;
+    const int swz = ((lane & 15) / L::WR) & (L::CPR - 1);
+    const int sw[2] = {((lane >> 4) ^ swz) << 4, ((4 + (lane >> 4)) ^ swz) << 4};
+    bf16x8 fa[2][FM], fb[2][FN];
+    auto read_frag = [&](const char* St, int half, int r) {
+        if (r < FN) fb[half][r] = *reinterpret_cast<const bf16x8*>(St + b_off + r * 16 * RB + sw[half]);
+        else fa[half][r - FN] = *reinterpret_cast<const bf16x8*>(St + a_off + (r - FN) * 16 * RB + sw[half]);
     };
-    auto main_loop = [&](auto grp_tag) {
-        constexpr int GRP = decltype(grp_tag)::value;
-        constexpr int NM = 2 * FM * FN;                                   // MFMAs of one compute phase
-        constexpr int EV = NM / LD_PER_WAVE > 0 ? NM / LD_PER_WAVE : 1;
-        static_assert(LD_PER_WAVE <= NM, "one load slot per MFMA at most");
+    // k tiles of all of the block's tiles: as many barriers
+    int left = 0;
+    for (int q = first; q < end; q += slots) {
+        Tile t;
+        int k_first, nk;
+        t.ks = p.ksplit;
+        t.kslice = p.ksplit > 1 ? q / (n_mt * n_ntiles) : 0;
+        k_range<BK>(p, t, k_first, nk);
+        left += nk;
+    }
+    int stage = 0;
+    if (left > 0) {
+        lds_barrier();
+#pragma unroll
+        for (int r = 0; r < NRD; ++r) read_frag(smem, 0, r);
+    }
+    for (int next = first; next < end; next += slots) {
+        Tile t;
+        tile_at<SWIGLU>(p, n_mt, n_ntiles, BNC, next, t);
+        int k_first, nk;
+        k_range<BK>(p, t, k_first, nk);
+        f32x4 acc[FM][FN];
+#pragma unroll
+        for (int i = 0; i < FM; ++i)
+#pragma unroll
+            for (int j = 0; j < FN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
         for (int kt = 0; kt < nk; ++kt) {
-            const char* St = smem + (kt % NSTAGE) * STAGE;
-            const int lt = GRP == 0 ? kt + NSTAGE - 1 : kt + NSTAGE;      // tile this wave loads during tile kt
-            const bool ld = lt < nk;
+            const char* St = smem + stage * STAGE;
+            stage = stage == NST - 1 ? 0 : stage + 1;
+            const char* Sn = smem + stage * STAGE;
 #pragma unroll
-            for (int ph = 0; ph < P; ++ph) {
-                // -- memory phase: fragments of this step from LDS
-                bf16x8 af[2][FM], bfr[2][FN];
+            for (int st = 0; st < 2; ++st) {
 #pragma unroll
-                for (int kk = 0; kk < 2; ++kk) {
-                    const int sw = (((ph * 2 + kk) * 2 + (lane >> 5)) ^ swz) << 4;
+                for (int i = 0; i < FM; ++i)
 #pragma unroll
-                    for (int i = 0; i < FM; ++i)
-                        af[kk][i] = *reinterpret_cast<const bf16x8*>(St + a_off + i * 32 * RB + sw);
-#pragma unroll
-                    for (int j = 0; j < FN; ++j)
-                        bfr[kk][j] = *reinterpret_cast<const bf16x8*>(St + b_off + j * 32 * RB + sw);
-                }
-                // fragments are in registers (lgkmcnt 0).  Group 1's last memory phase of tile kt is the last
-                // thing before group 0 reads tile kt+1: its loads of that tile must have landed.
-                if (GRP == 1 && ph == P - 1) {
-                    if (NSTAGE > 2 && kt + NSTAGE - 1 < nk)
-                        __builtin_amdgcn_s_waitcnt(vmcnt_lgkm0_imm((NSTAGE - 2) * LD_PER_WAVE));
-                    else __builtin_amdgcn_s_waitcnt(vmcnt_lgkm0_imm(0));
-                } else {
-                    __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0) only
-                }
-                __builtin_amdgcn_sched_barrier(0);
-                lds_barrier();
-                __builtin_amdgcn_sched_barrier(0);
-                // -- compute phase
-                const bool load_phase = GRP == 0 ? ph == 0 : ph == P - 1;
-                __builtin_amdgcn_s_setprio(1);
-#pragma unroll
-                for (int kk = 0; kk < 2; ++kk)
-#pragma unroll
-                    for (int i = 0; i < FM; ++i)
-#pragma unroll
-                        for (int j = 0; j < FN; ++j) {
-                            acc[i][j] =
-                                __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[kk][j], af[kk][i], acc[i][j], 0, 0, 0);
-                            const int mi = (kk * FM + i) * FN + j;
-                            if (load_phase && mi % EV == 0 && mi / EV < LD_PER_WAVE) {
-                                __builtin_amdgcn_sched_barrier(0);
-                                if (ld) issue_one(lt, mi / EV);
-                                __builtin_amdgcn_sched_barrier(0);
-                            }
+                    for (int j = 0; j < FN; ++j) {
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[st][j], fa[st][i], acc[i][j], 0, 0, 0);
+                        const int mi = i * FN + j;
+                        if (mi % RV == 0 && mi / RV < NRD) {
+                            __builtin_amdgcn_sched_barrier(0);
+                            read_frag(st == 0 ? St : Sn, st ^ 1, mi / RV);
+                            __builtin_amdgcn_sched_barrier(0);
                         }
-                __builtin_amdgcn_s_setprio(0);
-                // group 0's last compute phase of tile kt ends right before it reads tile kt+1
-                if (GRP == 0 && ph == P - 1) {
-                    if (NSTAGE > 2 && kt + NSTAGE - 1 < nk) __builtin_amdgcn_s_waitcnt(vmcnt_imm((NSTAGE - 2) * LD_PER_WAVE));
-                    else __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+                    }
+                if (st == 0) {
+                    // my reads of this k tile are done; the next one has landed (behind the last, what is read is not used)
+                    __builtin_amdgcn_sched_barrier(0);
+                    __builtin_amdgcn_s_waitcnt(0xC07F);
+                    if (--left > 0) lds_barrier();
+                    __builtin_amdgcn_sched_barrier(0);
                 }
-                __builtin_amdgcn_sched_barrier(0);
-                lds_barrier();
-                __builtin_amdgcn_sched_barrier(0);
             }
         }
-    };
-    if (grp == 0) {
-        main_loop(std::integral_constant<int, 0>{});
-        lds_barrier();
-    } else {
-        if (NSTAGE - 1 < nk) issue_loads(NSTAGE - 1);     // its "compute phase before tile 0"
-        lds_barrier();
-        main_loop(std::integral_constant<int, 1>{});
+        store_tile16_lines<FM, FN, TM, TN, SWIGLU>(p, t, acc, wm, wn, lane, smem + NST * STAGE + wave * 1024);
     }
-    lds_barrier();                                        // every wave has left the stage buffers
-    store_tile_lines<FM, FN, TM, TN, SWIGLU>(p, t, acc, wm, wn, lane, smem + wave * 8192);
+}
+
+// Tiles of 128 x 256 or, where those would leave CUs idle in fewer rounds, of 128 x 128: a round of the narrow ones pulls two
+// thirds of the bytes.  Only the table says how many rows there are, so the choice is the kernel's (one unit of 256 rows, K 14336
+// in four slices: 128 tiles 59 us, 256 narrow ones 44; 28672 x 4096: 224 tiles 70 us, 448 narrow ones 87).
+template <bool SWIGLU>
+__global__ void __launch_bounds__(512) ffn_gemm_ws_kernel(GemmArgs p)
+{
+    const int n_mt = m_tiles<128>(p);
+    const int wide = (p.N + (SWIGLU ? 127 : 255)) / (SWIGLU ? 128 : 256), narrow = (p.N + (SWIGLU ? 63 : 127)) / (SWIGLU ? 64 : 128);
+    const int G = gridDim.x, tw = n_mt * wide * p.ksplit, tn = n_mt * narrow * p.ksplit;
+    if (3 * ((tw + G - 1) / G) <= 2 * ((tn + G - 1) / G)) ws_block<128, 256, 2, 2, 3, SWIGLU>(p, n_mt, wide);
+    else if constexpr (SWIGLU) ws_block<128, 128, 4, 1, 4, SWIGLU>(p, n_mt, narrow);
+    else ws_block<128, 128, 2, 2, 4, SWIGLU>(p, n_mt, narrow);
 }
 
 // Tells the compiler that a pointer is the same in every lane (keeps it in scalar registers).
@@ -1318,8 +1377,8 @@ constexpr int small_lds() { return NSTAGE * (BM + BN) * BK * 2; }
 template <int BM, int NSTAGE>
 constexpr int narrow_lds() { return NSTAGE * (BM + 64) * 64 * 2; }
 constexpr int kNarrow32 = 6, kNarrow64 = 5;              // stages: two blocks of either height fit a CU
-constexpr int kPpLds = 3 * (128 + 256) * 64 * 2;
 constexpr int kW4Lds = 160 * 1024;
+constexpr int kWsLds = 3 * (128 + 256) * 128 + kWsStore;
 
 template <typename Kern>
 static hipError_t set_lds(Kern kern, int lds)
@@ -1338,8 +1397,8 @@ hipError_t init_ffn_kernels()
     if ((e = set_lds(ffn_gemm_narrow_kernel<32, kNarrow32, false>, narrow_lds<32, kNarrow32>())) != hipSuccess) return e;
     if ((e = set_lds(ffn_gemm_narrow_kernel<64, kNarrow64, true>, narrow_lds<64, kNarrow64>())) != hipSuccess) return e;
     if ((e = set_lds(ffn_gemm_narrow_kernel<64, kNarrow64, false>, narrow_lds<64, kNarrow64>())) != hipSuccess) return e;
-    if ((e = set_lds(ffn_gemm_pp_kernel<128, 64, 3, true>, kPpLds)) != hipSuccess) return e;
-    if ((e = set_lds(ffn_gemm_pp_kernel<128, 64, 3, false>, kPpLds)) != hipSuccess) return e;
+    if ((e = set_lds(ffn_gemm_ws_kernel<true>, kWsLds)) != hipSuccess) return e;
+    if ((e = set_lds(ffn_gemm_ws_kernel<false>, kWsLds)) != hipSuccess) return e;
     if ((e = set_lds(ffn_gemm_w4_kernel<true>, kW4Lds)) != hipSuccess) return e;
     if ((e = set_lds(ffn_gemm_w4_kernel<false>, kW4Lds)) != hipSuccess) return e;
     return hipSuccess;
@@ -1372,9 +1431,13 @@ static hipError_t launch_narrow(const GemmArgs& a, int max_mtiles, hipStream_t s
 }
 
 template <bool SWIGLU>
-static hipError_t launch_pp(const GemmArgs& a, int max_mtiles, hipStream_t s)
+static hipError_t launch_ws(const GemmArgs& a, int max_mtiles, int n_cu, hipStream_t s)
 {
-    return launch_tiles(ffn_gemm_pp_kernel<128, 64, 3, SWIGLU>, 512, kPpLds, SWIGLU ? 128 : 256, a, max_mtiles, s);
+    // one block per CU (the LDS footprint allows no second one), a multiple of 8 so that every XCD has the same number
+    const long total = (long)max_mtiles * ceil_div(a.N, SWIGLU ? 64 : 128) * a.ksplit;
+    const int grid = (int)std::min<long>((total + 7) / 8 * 8, std::max(8, n_cu / 8 * 8));
+    ffn_gemm_ws_kernel<SWIGLU><<<grid, 512, kWsLds, s>>>(a);
+    return hipGetLastError();
 }
 
 template <bool SWIGLU>
@@ -1406,7 +1469,7 @@ static hipError_t dispatch_gemm(int bm, const GemmArgs& a, int max_mtiles, long 
     if (narrow) return launch_narrow<32, kNarrow32, SWIGLU>(a, max_mtiles, s);
     switch (bm) {
         case 256: return launch_w4<SWIGLU>(a, max_mtiles, n_cu, s);
-        case 128: return launch_pp<SWIGLU>(a, max_mtiles, s);
+        case 128: return launch_ws<SWIGLU>(a, max_mtiles, n_cu, s);
         case 64: return launch_small<64, 256, 1, 4, 64, 3, SWIGLU>(a, max_mtiles, s);
         default: return launch_small<32, 256, 1, 4, 64, 4, SWIGLU>(a, max_mtiles, s);
     }
