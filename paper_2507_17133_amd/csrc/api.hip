@@ -560,15 +560,16 @@ moe_status moe_forward(const moe_config* cfg, const void* x, int32_t T, const vo
     bf16_t* H = at<bf16_t>(workspace, W.H);
     bf16_t* Y = at<bf16_t>(workspace, W.Y);
     float* partial = W.partial_bytes ? at<float>(workspace, W.partial) : nullptr;
+    FfnProblem problems[2];
     for (int j = 0; j < jobs.n; ++j) {
         const TileJob& J = jobs.job[j];
         FfnUnits units{J.u_hi - J.u_lo, 0, 0};
         if (j == 0) units.entries = (int64_t)T * D.K;
         if (j == 1 || !split_shared) units.even = D.Ns;
-        e = launch_ffn(D, units, j == 0 ? D.F : D.Fs, J.plan, xb, R.row_token, fe, fu, fs, J.table, H, Y, partial, s,
-                       J.bm_hi);
-        if (e != hipSuccess) return hip_fail(e, j == 0 ? "moe_forward/ffn" : "moe_forward/ffn_shared");
+        problems[j] = FfnProblem{units, j == 0 ? D.F : D.Fs, J.plan, J.bm_hi, J.table};
     }
+    e = launch_ffn(D, problems, jobs.n, xb, R.row_token, fe, fu, fs, H, Y, partial, s);
+    if (e != hipSuccess) return hip_fail(e, "moe_forward/ffn");
     e = launch_combine(D, xb, Y, R.token_rows, R.row_weight, static_cast<bf16_t*>(out), s);
     if (e != hipSuccess) return hip_fail(e, "moe_forward/combine");
     return MOE_OK;
@@ -632,7 +633,8 @@ moe_status moe_build_united(const moe_config* cfg, const moe_ffn_weights* expert
     auto run_units = [&](int u0, int n0, int u1, int n1, int first_slot, bf16_t* Y) -> hipError_t {
         hipError_t err = launch_uniform_units(u0, n0, u1, n1, first_slot, n_calib, plan.bm, tiles, s);
         if (err != hipSuccess) return err;
-        return launch_ffn(D, FfnUnits{n0 + n1, 0, n0 + n1}, D.F, plan, xb, row_token, fe, fu, fs, tiles, H, Y, partial, s);
+        const FfnProblem units{FfnUnits{n0 + n1, 0, n0 + n1}, D.F, plan, 0, tiles};
+        return launch_ffn(D, &units, 1, xb, row_token, fe, fu, fs, H, Y, partial, s);
     };
     for (int g = 0; g < G; ++g) {
         const int lo = g * way, hi = lo + way < m ? lo + way : m, k = hi - lo;
@@ -727,9 +729,9 @@ moe_status moe_distill_united(const moe_config* cfg, const moe_ffn_weights* expe
             const int batches = ceil_div(k, D.slots);
             for (int q = 0; q < batches; ++q) {
                 const int i0 = lo + (int)((int64_t)k * q / batches), i1 = lo + (int)((int64_t)k * (q + 1) / batches);
+                const FfnProblem units{FfnUnits{i1 - i0, 0, i1 - i0}, D.F, plan, 0, tiles};
                 if ((e = launch_uniform_units(i0, i1 - i0, 0, 0, 0, n_calib, plan.bm, tiles, s)) != hipSuccess ||
-                    (e = launch_ffn(D, FfnUnits{i1 - i0, 0, i1 - i0}, D.F, plan, xb, row_token, fe, fu, fs, tiles, H, Yo,
-                                    partial, s)) != hipSuccess)
+                    (e = launch_ffn(D, &units, 1, xb, row_token, fe, fu, fs, H, Yo, partial, s)) != hipSuccess)
                     return hip_fail(e, "moe_distill_united/teacher");
                 e = launch_teacher_stats(Yo, i1 - i0, q == 0, q == batches - 1, k, n_calib, D.d, D.F, g - g0, buf, s);
                 if (e != hipSuccess) return hip_fail(e, "moe_distill_united/mean");

@@ -120,15 +120,15 @@ __device__ __forceinline__ int m_tiles(const GemmArgs& p)
 }
 
 template <int BM, int BNC, bool SWIGLU>
-__device__ __forceinline__ bool decode_tile(const GemmArgs& p, Tile& t)
+__device__ __forceinline__ bool decode_tile(const GemmArgs& p, int block, Tile& t)
 {
     const int n_mt = m_tiles<BM>(p);
     const int tiles = n_mt * p.n_ntiles;
     const int total = tiles * p.ksplit;
     const int chunk = (total + 7) >> 3;
-    const int bi = blockIdx.x >> 3;
+    const int bi = block >> 3;
     if (bi >= chunk) return false;
-    const int Lfull = (blockIdx.x & 7) * chunk + bi;           // block id mod 8 = XCD: contiguous range per XCD
+    const int Lfull = (block & 7) * chunk + bi;                // block id mod 8 = XCD: contiguous range per XCD
     if (Lfull >= total) return false;
     t.kslice = Lfull / tiles;
     t.ks = p.ksplit;
@@ -396,7 +396,7 @@ struct Lds {
 // flight while tile kt is multiplied.  Used when experts hold few rows (decode): weight streaming bound.
 // ------------------------------------------------------------------------------------------------
 template <int BM, int BN, int WM, int WN, int BK, int NSTAGE, bool SWIGLU>
-__global__ void __launch_bounds__(WM * WN * 64) ffn_gemm_kernel(GemmArgs p)
+__device__ __forceinline__ void small_block(const GemmArgs& p, const int block)
 {
     using L = Lds<BK>;
     constexpr int TM = BM / WM, TN = BN / WN, FM = TM / 32, FN = TN / 32;
@@ -410,7 +410,7 @@ __global__ void __launch_bounds__(WM * WN * 64) ffn_gemm_kernel(GemmArgs p)
     extern __shared__ __attribute__((aligned(16))) char smem[];
 
     Tile t;
-    if (!decode_tile<BM, SWIGLU ? BN / 2 : BN, SWIGLU>(p, t)) return;
+    if (!decode_tile<BM, SWIGLU ? BN / 2 : BN, SWIGLU>(p, block, t)) return;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave / WN, wn = wave % WN;
     int k_first, nk;
@@ -472,6 +472,12 @@ __global__ void __launch_bounds__(WM * WN * 64) ffn_gemm_kernel(GemmArgs p)
     store_tile_lines<FM, FN, TM, TN, SWIGLU>(p, t, acc, wm, wn, lane, smem + wave * 8192);
 }
 
+template <int BM, int BN, int WM, int WN, int BK, int NSTAGE, bool SWIGLU>
+__global__ void __launch_bounds__(WM * WN * 64) ffn_gemm_kernel(GemmArgs p)
+{
+    small_block<BM, BN, WM, WN, BK, NSTAGE, SWIGLU>(p, blockIdx.x);
+}
+
 // ------------------------------------------------------------------------------------------------
 // Narrow kernel (4 waves as 2 x 2, 32 or 64 rows x 64 tile columns, 16x16x32 MFMA) for launches that would leave CUs
 // without a block: one request of a model with small experts, the shared experts of a decode batch.  What bounds those is
@@ -484,7 +490,7 @@ __global__ void __launch_bounds__(WM * WN * 64) ffn_gemm_kernel(GemmArgs p)
 // over 8 experts of 256 x 512 27.8 -> 24.1 us.
 // ------------------------------------------------------------------------------------------------
 template <int BM, int NSTAGE, bool SWIGLU>
-__global__ void __launch_bounds__(256) ffn_gemm_narrow_kernel(GemmArgs p)
+__device__ __forceinline__ void narrow_block(const GemmArgs& p, const int block)
 {
     constexpr int BK = 64, BN = 64, NW = 4, TM = BM / 2, TN = BN / 2, FM = TM / 16, FN = TN / 16;
     using L = Lds<BK>;
@@ -495,7 +501,7 @@ __global__ void __launch_bounds__(256) ffn_gemm_narrow_kernel(GemmArgs p)
     extern __shared__ __attribute__((aligned(16))) char smem[];
 
     Tile t;
-    if (!decode_tile<BM, SWIGLU ? BN / 2 : BN, SWIGLU>(p, t)) return;
+    if (!decode_tile<BM, SWIGLU ? BN / 2 : BN, SWIGLU>(p, block, t)) return;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave >> 1, wn = wave & 1;
     int k_first, nk;
@@ -574,6 +580,31 @@ __global__ void __launch_bounds__(256) ffn_gemm_narrow_kernel(GemmArgs p)
                                                                       pack_f16(acc[i][j][2], acc[i][j][3]));
         }
     }
+}
+
+template <int BM, int NSTAGE, bool SWIGLU>
+__global__ void __launch_bounds__(256) ffn_gemm_narrow_kernel(GemmArgs p)
+{
+    narrow_block<BM, NSTAGE, SWIGLU>(p, blockIdx.x);
+}
+
+// Stages of the kernels for 32 and 64 rows; two narrow blocks of either height fit a CU.
+template <int BM>
+constexpr int small_stages() { return BM == 32 ? 4 : 3; }
+template <int BM>
+constexpr int narrow_stages() { return BM == 32 ? 6 : 5; }
+
+// Shared experts of a width of their own (ps: the first n_s blocks) beside the routed and united units (pr) in one launch.  A launch
+// each left most CUs idle at the ends of both: the shared GEMM2 of 37 tokens of the 60-expert shape (K = 5632) is 64 blocks of 44 k
+// tiles, 15.7 us, the routed one 13.5 us of 256-column blocks with 11.  Layer forward of that shape in two launches per GEMM and in
+// one: 1 token 63 -> 51 us, 8 at 0.6 brownout 83 -> 68, 37 98 -> 88, 120 251 -> 228.
+template <int BMR, bool NARROW, int BMS, bool SWIGLU>
+__global__ void __launch_bounds__(256) ffn_gemm_pair_kernel(GemmArgs ps, GemmArgs pr, int n_s)
+{
+    const int b = blockIdx.x;
+    if (b < n_s) narrow_block<BMS, narrow_stages<BMS>(), SWIGLU>(ps, b);
+    else if constexpr (NARROW) narrow_block<BMR, narrow_stages<BMR>(), SWIGLU>(pr, b - n_s);
+    else small_block<BMR, 256, 1, 4, 64, small_stages<BMR>(), SWIGLU>(pr, b - n_s);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -1372,11 +1403,10 @@ __global__ void __launch_bounds__(256) combine_kernel(const bf16_t* __restrict__
 // Launchers.  Kernels that need more dynamic LDS than the default limit get the attribute once per device in
 // init_ffn_kernels (never inside a launch path: the call is not allowed under stream capture).
 // ------------------------------------------------------------------------------------------------
-template <int BM, int BN, int WM, int WN, int BK, int NSTAGE>
-constexpr int small_lds() { return NSTAGE * (BM + BN) * BK * 2; }
-template <int BM, int NSTAGE>
-constexpr int narrow_lds() { return NSTAGE * (BM + 64) * 64 * 2; }
-constexpr int kNarrow32 = 6, kNarrow64 = 5;              // stages: two blocks of either height fit a CU
+template <int BM>
+constexpr int small_lds() { return small_stages<BM>() * (BM + 256) * 128; }
+template <int BM>
+constexpr int narrow_lds() { return narrow_stages<BM>() * (BM + 64) * 128; }
 constexpr int kW4Lds = 160 * 1024;
 constexpr int kWsLds = 3 * (128 + 256) * 128 + kWsStore;
 
@@ -1386,93 +1416,119 @@ static hipError_t set_lds(Kern kern, int lds)
     return hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
 }
 
-hipError_t init_ffn_kernels()
+template <int BM, bool SWIGLU>
+constexpr auto small_kernel() { return ffn_gemm_kernel<BM, 256, 1, 4, 64, small_stages<BM>(), SWIGLU>; }
+template <int BM, bool SWIGLU>
+constexpr auto narrow_kernel() { return ffn_gemm_narrow_kernel<BM, narrow_stages<BM>(), SWIGLU>; }
+template <int BMR, bool NARROW, int BMS>
+constexpr int pair_lds() { return std::max(NARROW ? narrow_lds<BMR>() : small_lds<BMR>(), narrow_lds<BMS>()); }
+
+template <bool SWIGLU>
+static hipError_t init_gemms()
 {
     hipError_t e;
-    if ((e = set_lds(ffn_gemm_kernel<64, 256, 1, 4, 64, 3, true>, small_lds<64, 256, 1, 4, 64, 3>())) != hipSuccess) return e;
-    if ((e = set_lds(ffn_gemm_kernel<64, 256, 1, 4, 64, 3, false>, small_lds<64, 256, 1, 4, 64, 3>())) != hipSuccess) return e;
-    if ((e = set_lds(ffn_gemm_kernel<32, 256, 1, 4, 64, 4, true>, small_lds<32, 256, 1, 4, 64, 4>())) != hipSuccess) return e;
-    if ((e = set_lds(ffn_gemm_kernel<32, 256, 1, 4, 64, 4, false>, small_lds<32, 256, 1, 4, 64, 4>())) != hipSuccess) return e;
-    if ((e = set_lds(ffn_gemm_narrow_kernel<32, kNarrow32, true>, narrow_lds<32, kNarrow32>())) != hipSuccess) return e;
-    if ((e = set_lds(ffn_gemm_narrow_kernel<32, kNarrow32, false>, narrow_lds<32, kNarrow32>())) != hipSuccess) return e;
-    if ((e = set_lds(ffn_gemm_narrow_kernel<64, kNarrow64, true>, narrow_lds<64, kNarrow64>())) != hipSuccess) return e;
-    if ((e = set_lds(ffn_gemm_narrow_kernel<64, kNarrow64, false>, narrow_lds<64, kNarrow64>())) != hipSuccess) return e;
-    if ((e = set_lds(ffn_gemm_ws_kernel<true>, kWsLds)) != hipSuccess) return e;
-    if ((e = set_lds(ffn_gemm_ws_kernel<false>, kWsLds)) != hipSuccess) return e;
-    if ((e = set_lds(ffn_gemm_w4_kernel<true>, kW4Lds)) != hipSuccess) return e;
-    if ((e = set_lds(ffn_gemm_w4_kernel<false>, kW4Lds)) != hipSuccess) return e;
-    return hipSuccess;
+    if ((e = set_lds(small_kernel<64, SWIGLU>(), small_lds<64>())) != hipSuccess) return e;
+    if ((e = set_lds(small_kernel<32, SWIGLU>(), small_lds<32>())) != hipSuccess) return e;
+    if ((e = set_lds(narrow_kernel<64, SWIGLU>(), narrow_lds<64>())) != hipSuccess) return e;
+    if ((e = set_lds(narrow_kernel<32, SWIGLU>(), narrow_lds<32>())) != hipSuccess) return e;
+    if ((e = set_lds(ffn_gemm_pair_kernel<32, false, 32, SWIGLU>, pair_lds<32, false, 32>())) != hipSuccess) return e;
+    if ((e = set_lds(ffn_gemm_pair_kernel<32, false, 64, SWIGLU>, pair_lds<32, false, 64>())) != hipSuccess) return e;
+    if ((e = set_lds(ffn_gemm_pair_kernel<64, false, 64, SWIGLU>, pair_lds<64, false, 64>())) != hipSuccess) return e;
+    if ((e = set_lds(ffn_gemm_pair_kernel<32, true, 32, SWIGLU>, pair_lds<32, true, 32>())) != hipSuccess) return e;
+    if ((e = set_lds(ffn_gemm_pair_kernel<32, true, 64, SWIGLU>, pair_lds<32, true, 64>())) != hipSuccess) return e;
+    if ((e = set_lds(ffn_gemm_pair_kernel<64, true, 64, SWIGLU>, pair_lds<64, true, 64>())) != hipSuccess) return e;
+    if ((e = set_lds(ffn_gemm_ws_kernel<SWIGLU>, kWsLds)) != hipSuccess) return e;
+    return set_lds(ffn_gemm_w4_kernel<SWIGLU>, kW4Lds);
 }
 
-template <typename Kern>
-static hipError_t launch_tiles(Kern kern, int threads, int lds, int bn_cols, GemmArgs a, int max_mtiles, hipStream_t s)
+hipError_t init_ffn_kernels()
 {
-    a.n_ntiles = ceil_div(a.N, bn_cols);
-    const long total = (long)max_mtiles * a.n_ntiles * a.ksplit;
-    const int grid = (int)((total + 7) / 8 * 8);
-    kern<<<grid, threads, lds, s>>>(a);
-    return hipGetLastError();
+    const hipError_t e = init_gemms<true>();
+    return e != hipSuccess ? e : init_gemms<false>();
 }
 
-template <int BM, int BN, int WM, int WN, int BK, int NSTAGE, bool SWIGLU>
-static hipError_t launch_small(const GemmArgs& a, int max_mtiles, hipStream_t s)
-{
-    constexpr int LDS = small_lds<BM, BN, WM, WN, BK, NSTAGE>();
-    static_assert(LDS <= 160 * 1024, "LDS budget of one CU");
-    return launch_tiles(ffn_gemm_kernel<BM, BN, WM, WN, BK, NSTAGE, SWIGLU>, WM * WN * 64, LDS, SWIGLU ? BN / 2 : BN, a,
-                        max_mtiles, s);
-}
+// One GEMM of one group of units: the kernel its tile height and its expected number of blocks ask for.
+enum GemmKind { kSmall32, kSmall64, kNarrow32, kNarrow64, kWs, kW4 };
+struct GemmLaunch {
+    GemmArgs a;
+    int max_mtiles;                              // M tiles there can be at most
+    GemmKind kind;
+};
 
-template <int BM, int NSTAGE, bool SWIGLU>
-static hipError_t launch_narrow(const GemmArgs& a, int max_mtiles, hipStream_t s)
+template <bool SWIGLU>
+constexpr int tile_columns(GemmKind k) { return (k == kNarrow32 || k == kNarrow64 ? 64 : 256) / (SWIGLU ? 2 : 1); }
+
+// Blocks of the kernels that take a tile per block.
+static int tile_grid(const GemmArgs& a, int max_mtiles)
 {
-    return launch_tiles(ffn_gemm_narrow_kernel<BM, NSTAGE, SWIGLU>, 256, narrow_lds<BM, NSTAGE>(), SWIGLU ? 32 : 64, a,
-                        max_mtiles, s);
+    return (int)(((long)max_mtiles * a.n_ntiles * a.ksplit + 7) / 8 * 8);
 }
 
 template <bool SWIGLU>
-static hipError_t launch_ws(const GemmArgs& a, int max_mtiles, int n_cu, hipStream_t s)
+static hipError_t launch_gemm(const GemmLaunch& l, int n_cu, hipStream_t s)
 {
-    // one block per CU (the LDS footprint allows no second one), a multiple of 8 so that every XCD has the same number
-    const long total = (long)max_mtiles * ceil_div(a.N, SWIGLU ? 64 : 128) * a.ksplit;
-    const int grid = (int)std::min<long>((total + 7) / 8 * 8, std::max(8, n_cu / 8 * 8));
-    ffn_gemm_ws_kernel<SWIGLU><<<grid, 512, kWsLds, s>>>(a);
-    return hipGetLastError();
-}
-
-template <bool SWIGLU>
-static hipError_t launch_w4(const GemmArgs& a, int max_mtiles, int n_cu, hipStream_t s)
-{
-    auto kern = ffn_gemm_w4_kernel<SWIGLU>;
-    GemmArgs g = a;
-    g.n_ntiles = ceil_div(g.N, SWIGLU ? 128 : 256);
-    const long total = (long)max_mtiles * g.n_ntiles * g.ksplit;
-    // one block per CU (the LDS footprint allows no second one), a multiple of 8 so every XCD has the same
-    // number of blocks; fewer when there cannot be that many tiles
-    const int grid = (int)std::min<long>((total + 7) / 8 * 8, std::max(8, n_cu / 8 * 8));
-    if (g.ksplit != 1 || grid > g.partial_cap) g.partial = nullptr;
-    // at most grid - 1 tiles are left over after the last full round of `grid` tiles
-    const int max_tail = (int)std::min<long>(total, grid - 1);
-    if (max_tail <= 0) g.partial = nullptr;
-    kern<<<g.partial ? 3 * grid : grid, 256, kW4Lds, s>>>(g);
-    if (g.partial) gemm_tail_sum_kernel<SWIGLU><<<std::min(max_tail * 64, 2048), 256, 0, s>>>(g, grid);
-    return hipGetLastError();
-}
-
-// likely: M tiles the batch has at most when no unit is browned out.  Tiles of 64 or 32 rows whose 256-column blocks
-// would not give every CU one go to the narrow kernel.
-template <bool SWIGLU>
-static hipError_t dispatch_gemm(int bm, const GemmArgs& a, int max_mtiles, long likely, int n_cu, hipStream_t s)
-{
-    const bool narrow = bm <= 64 && likely * ceil_div(a.N, SWIGLU ? 128 : 256) * a.ksplit < n_cu;
-    if (narrow && bm == 64) return launch_narrow<64, kNarrow64, SWIGLU>(a, max_mtiles, s);
-    if (narrow) return launch_narrow<32, kNarrow32, SWIGLU>(a, max_mtiles, s);
-    switch (bm) {
-        case 256: return launch_w4<SWIGLU>(a, max_mtiles, n_cu, s);
-        case 128: return launch_ws<SWIGLU>(a, max_mtiles, n_cu, s);
-        case 64: return launch_small<64, 256, 1, 4, 64, 3, SWIGLU>(a, max_mtiles, s);
-        default: return launch_small<32, 256, 1, 4, 64, 4, SWIGLU>(a, max_mtiles, s);
+    GemmArgs a = l.a;
+    a.n_ntiles = ceil_div(a.N, tile_columns<SWIGLU>(l.kind));
+    const int grid = tile_grid(a, l.max_mtiles);
+    switch (l.kind) {
+        case kNarrow32: narrow_kernel<32, SWIGLU>()<<<grid, 256, narrow_lds<32>(), s>>>(a); break;
+        case kNarrow64: narrow_kernel<64, SWIGLU>()<<<grid, 256, narrow_lds<64>(), s>>>(a); break;
+        case kSmall32: small_kernel<32, SWIGLU>()<<<grid, 256, small_lds<32>(), s>>>(a); break;
+        case kSmall64: small_kernel<64, SWIGLU>()<<<grid, 256, small_lds<64>(), s>>>(a); break;
+        case kWs: {
+            // persistent, one block per CU, a multiple of 8; its tiles are 128 columns (GEMM1: 64) at the narrowest
+            const long total = (long)l.max_mtiles * ceil_div(a.N, SWIGLU ? 64 : 128) * a.ksplit;
+            const int blocks = (int)std::min<long>((total + 7) / 8 * 8, std::max(8, n_cu / 8 * 8));
+            ffn_gemm_ws_kernel<SWIGLU><<<blocks, 512, kWsLds, s>>>(a);
+            break;
+        }
+        case kW4: {
+            // one block per CU (the LDS footprint allows no second one), a multiple of 8 so every XCD has the same number of
+            // blocks; fewer when there cannot be that many tiles.  At most blocks - 1 tiles are left over after the last full
+            // round of `blocks` tiles
+            const long total = (long)l.max_mtiles * a.n_ntiles * a.ksplit;
+            const int blocks = (int)std::min<long>((total + 7) / 8 * 8, std::max(8, n_cu / 8 * 8));
+            const int max_tail = (int)std::min<long>(total, blocks - 1);
+            if (a.ksplit != 1 || blocks > a.partial_cap || max_tail <= 0) a.partial = nullptr;
+            ffn_gemm_w4_kernel<SWIGLU><<<a.partial ? 3 * blocks : blocks, 256, kW4Lds, s>>>(a);
+            if (a.partial == nullptr) break;
+            const hipError_t e = hipGetLastError();
+            if (e != hipSuccess) return e;
+            gemm_tail_sum_kernel<SWIGLU><<<std::min(max_tail * 64, 2048), 256, 0, s>>>(a, blocks);
+            break;
+        }
     }
+    return hipGetLastError();
+}
+
+// The shared experts' GEMM and the routed units' in one launch, where there is a kernel for the two kinds (decode-sized batches; two
+// 256-row problems in one launch gain nothing: power sets their time).
+static bool pairable(GemmKind shared, GemmKind routed)
+{
+    return (shared == kNarrow64 && routed < kWs) || (shared == kNarrow32 && (routed == kSmall32 || routed == kNarrow32));
+}
+
+template <bool SWIGLU>
+static hipError_t launch_gemm_pair(const GemmLaunch& sh, const GemmLaunch& ro, hipStream_t s)
+{
+    GemmArgs a = sh.a, r = ro.a;
+    a.n_ntiles = ceil_div(a.N, tile_columns<SWIGLU>(sh.kind));
+    r.n_ntiles = ceil_div(r.N, tile_columns<SWIGLU>(ro.kind));
+    const int n_s = tile_grid(a, sh.max_mtiles), n = n_s + tile_grid(r, ro.max_mtiles);
+    const bool s32 = sh.kind == kNarrow32;
+    switch (ro.kind) {
+        case kSmall32:
+            if (s32) ffn_gemm_pair_kernel<32, false, 32, SWIGLU><<<n, 256, pair_lds<32, false, 32>(), s>>>(a, r, n_s);
+            else ffn_gemm_pair_kernel<32, false, 64, SWIGLU><<<n, 256, pair_lds<32, false, 64>(), s>>>(a, r, n_s);
+            break;
+        case kNarrow32:
+            if (s32) ffn_gemm_pair_kernel<32, true, 32, SWIGLU><<<n, 256, pair_lds<32, true, 32>(), s>>>(a, r, n_s);
+            else ffn_gemm_pair_kernel<32, true, 64, SWIGLU><<<n, 256, pair_lds<32, true, 64>(), s>>>(a, r, n_s);
+            break;
+        case kSmall64: ffn_gemm_pair_kernel<64, false, 64, SWIGLU><<<n, 256, pair_lds<64, false, 64>(), s>>>(a, r, n_s); break;
+        default: ffn_gemm_pair_kernel<64, true, 64, SWIGLU><<<n, 256, pair_lds<64, true, 64>(), s>>>(a, r, n_s); break;
+    }
+    return hipGetLastError();
 }
 
 hipError_t launch_tile_tables(const int32_t* unit_cnt, const int32_t* unit_off, const TileJobs& jobs, hipStream_t s)
@@ -1482,58 +1538,72 @@ hipError_t launch_tile_tables(const int32_t* unit_cnt, const int32_t* unit_off, 
     return hipGetLastError();
 }
 
-hipError_t launch_ffn(const Dims& D, const FfnUnits& units, int Fdim, const TilePlan& plan, const bf16_t* x,
-                      const int32_t* gather, const FfnWeights& experts, const FfnWeights& united, const FfnWeights& shared,
-                      int32_t* table, bf16_t* H, bf16_t* Y, float* partial, hipStream_t s, int bm_hi)
+hipError_t launch_ffn(const Dims& D, const FfnProblem* problems, int n_problems, const bf16_t* x, const int32_t* gather,
+                      const FfnWeights& experts, const FfnWeights& united, const FfnWeights& shared, bf16_t* H, bf16_t* Y,
+                      float* partial, hipStream_t s)
 {
     DeviceInfo dev;
     hipError_t e = ensure_device_init(&dev);
     if (e != hipSuccess) return e;
-    // M tiles there can be at most: a unit that holds rows has one for every bm of them and a ragged one, and no more
-    // units hold rows than there are rows
-    auto max_mtiles = [&](int bm) {
-        return (int)std::min<int64_t>(D.row_cap / bm + std::min<int64_t>(units.n, D.row_cap), D.tile_cap);
-    };
-    // M tiles to expect when no unit is browned out (united units take rows from the experts).  Chooses the kernel; the grid
-    // is sized for max_mtiles.
-    const long likely = (long)(units.entries / plan.bm + std::min<int64_t>(units.entries, D.m) +
-                               (int64_t)units.even * ceil_div(D.T, plan.bm));
-    GemmArgs g1;
-    g1.A = x; g1.lda = D.d; g1.gather = gather; g1.table = table;
-    g1.wa0 = experts.w1; g1.wa1 = united.w1; g1.wa2 = shared.w1;
-    g1.wb0 = experts.w3; g1.wb1 = united.w3; g1.wb2 = shared.w3;
-    g1.m = D.m; g1.G = D.G; g1.N = Fdim; g1.K = D.d;
-    g1.out = H; g1.ldo = D.Fmax;
-    g1.n_ntiles = 0;                            // set by the launcher from its tile width
-    g1.ksplit = 1; g1.plane = 0;
-    g1.partial = partial; g1.partial_cap = D.tail_blocks;
-    // Both heights where the table kernel chooses between two: the launch of the height it did not take returns at once.
-    auto gemm = [&](auto swiglu, GemmArgs& g, int bm) {
+    auto plan = [&](auto swiglu, const FfnProblem& P, int bm) {
+        constexpr bool SWIGLU = decltype(swiglu)::value;
+        GemmLaunch l;
+        GemmArgs& g = l.a;
+        g.table = P.table;
+        g.m = D.m; g.G = D.G;
+        if (SWIGLU) {
+            g.A = x; g.lda = D.d; g.gather = gather;
+            g.wa0 = experts.w1; g.wa1 = united.w1; g.wa2 = shared.w1;
+            g.wb0 = experts.w3; g.wb1 = united.w3; g.wb2 = shared.w3;
+            g.N = P.F; g.K = D.d;
+            g.out = H; g.ldo = D.Fmax;
+            g.ksplit = 1; g.plane = 0;
+        } else {
+            g.A = H; g.lda = D.Fmax; g.gather = nullptr;
+            g.wa0 = experts.w2; g.wa1 = united.w2; g.wa2 = shared.w2;
+            g.wb0 = g.wb1 = g.wb2 = nullptr;
+            g.N = D.d; g.K = P.F;
+            g.out = Y; g.ldo = D.d;
+            g.ksplit = D.ksplit; g.plane = D.y_plane;
+        }
+        g.n_ntiles = 0;                           // set at the launch from the kernel's tile width
         g.group_m = tuning().group_m ? tuning().group_m : (bm == 256 ? 8 : 4);
-        return dispatch_gemm<decltype(swiglu)::value>(bm, g, max_mtiles(bm), likely, dev.n_cu, s);
+        g.partial = partial; g.partial_cap = D.tail_blocks;
+        // M tiles there can be at most: a unit that holds rows has one for every bm of them and a ragged one, and no more
+        // units hold rows than there are rows
+        l.max_mtiles = (int)std::min<int64_t>(D.row_cap / bm + std::min<int64_t>(P.units.n, D.row_cap), D.tile_cap);
+        // M tiles to expect when no unit is browned out (united units take rows from the experts).  Chooses the kernel, the grid
+        // is sized for max_mtiles: tiles of 64 or 32 rows whose 256-column blocks would not give every CU one go to the narrow
+        // kernel.
+        const long likely = (long)(P.units.entries / P.plan.bm + std::min<int64_t>(P.units.entries, D.m) +
+                                   (int64_t)P.units.even * ceil_div(D.T, P.plan.bm));
+        const bool narrow = likely * ceil_div(g.N, SWIGLU ? 128 : 256) * g.ksplit < dev.n_cu;
+        l.kind = bm == 256 ? kW4 : bm == 128 ? kWs : bm == 64 ? (narrow ? kNarrow64 : kSmall64) : narrow ? kNarrow32 : kSmall32;
+        return l;
     };
-    {
-        ProfScope ps(MOE_STAGE_GEMM1, s);
-        e = gemm(std::true_type{}, g1, plan.bm);
-        if (e == hipSuccess && bm_hi > 0) e = gemm(std::true_type{}, g1, bm_hi);
-        if (e != hipSuccess) return e;
-    }
-    GemmArgs g2;
-    g2.A = H; g2.lda = D.Fmax; g2.gather = nullptr; g2.table = table;
-    g2.wa0 = experts.w2; g2.wa1 = united.w2; g2.wa2 = shared.w2;
-    g2.wb0 = g2.wb1 = g2.wb2 = nullptr;
-    g2.m = D.m; g2.G = D.G; g2.N = D.d; g2.K = Fdim;
-    g2.out = Y; g2.ldo = D.d;
-    g2.n_ntiles = 0;
-    g2.ksplit = D.ksplit; g2.plane = D.y_plane;
-    g2.partial = partial; g2.partial_cap = D.tail_blocks;
-    {
-        ProfScope ps(MOE_STAGE_GEMM2, s);
-        e = gemm(std::false_type{}, g2, plan.bm);
-        if (e == hipSuccess && bm_hi > 0) e = gemm(std::false_type{}, g2, bm_hi);
-        if (e != hipSuccess) return e;
-    }
-    return hipSuccess;
+    // Both heights where the table kernel chooses between two: the launch of the height it did not take returns at once.
+    auto gemm = [&](auto swiglu) -> hipError_t {
+        constexpr bool SWIGLU = decltype(swiglu)::value;
+        ProfScope ps(SWIGLU ? MOE_STAGE_GEMM1 : MOE_STAGE_GEMM2, s);
+        GemmLaunch todo[4];
+        int n = 0;
+        for (int j = 0; j < n_problems; ++j) {
+            todo[n++] = plan(swiglu, problems[j], problems[j].plan.bm);
+            if (problems[j].bm_hi > 0) todo[n++] = plan(swiglu, problems[j], problems[j].bm_hi);
+        }
+        int paired = -1;                          // the routed launch that takes the shared experts (the last one) along
+        if (n_problems == 2)
+            for (int i = 0; i < n - 1; ++i)
+                if (pairable(todo[n - 1].kind, todo[i].kind)) paired = i;
+        hipError_t err;
+        for (int i = 0; i < n - (paired >= 0 ? 1 : 0); ++i) {
+            err = i == paired ? launch_gemm_pair<SWIGLU>(todo[n - 1], todo[i], s) : launch_gemm<SWIGLU>(todo[i], dev.n_cu, s);
+            if (err != hipSuccess) return err;
+        }
+        return hipSuccess;
+    };
+    if ((e = gemm(std::true_type{})) != hipSuccess) return e;
+    return gemm(std::false_type{});
 }
 
 hipError_t launch_combine(const Dims& D, const bf16_t* x, const bf16_t* Y, const int32_t* token_rows,

@@ -108,13 +108,15 @@ struct FfnWeights { const bf16_t *w1, *w3, *w2; };
 // The units of a launch: how many may hold rows, the TopK entries spread over the experts among them, and how many hold
 // all T tokens each (shared experts; units on calibration tokens).
 struct FfnUnits { int n; int64_t entries; int even; };
-// Runs W2(silu(W1 x)*(W3 x)) for the rows of the tiles in `table`, writes Y[row][d] = FFN(x[gather ? gather[row] : row]) (the
-// row weights are applied by the combine).  Fdim is the FFN width of these units.  Weight source of unit u: u<m experts[u]; u<m+G united[u-m]; else shared[u-m-G].
-// plan / table: how the rows are cut into M tiles and the tile table, which the routing kernels or launch_tile_tables
-// have written; bm_hi: the other height of a job that leaves the choice to them (0: none).
-hipError_t launch_ffn(const Dims& D, const FfnUnits& units, int Fdim, const TilePlan& plan, const bf16_t* x,
-                      const int32_t* gather, const FfnWeights& experts, const FfnWeights& united, const FfnWeights& shared,
-                      int32_t* table, bf16_t* H, bf16_t* Y, float* partial, hipStream_t s, int bm_hi = 0);
+// Units of one width: how their rows are cut into M tiles, and the tile table, which the routing kernels or
+// launch_tile_tables have written; bm_hi: the other height of a job that leaves the choice to them (0: none).
+struct FfnProblem { FfnUnits units; int F; TilePlan plan; int bm_hi; int32_t* table; };
+// Runs W2(silu(W1 x)*(W3 x)) for the rows of the tiles in the tables of one problem, or of the routed and united units and then the
+// shared experts; writes Y[row][d] = FFN(x[gather ? gather[row] : row]) (the row weights are applied by the combine).  Weight
+// source of unit u: u<m experts[u]; u<m+G united[u-m]; else shared[u-m-G].
+hipError_t launch_ffn(const Dims& D, const FfnProblem* problems, int n_problems, const bf16_t* x, const int32_t* gather,
+                      const FfnWeights& experts, const FfnWeights& united, const FfnWeights& shared, bf16_t* H, bf16_t* Y,
+                      float* partial, hipStream_t s);
 // Tile tables from the unit counts of a route that the caller brings.
 hipError_t launch_tile_tables(const int32_t* unit_cnt, const int32_t* unit_off, const TileJobs& jobs, hipStream_t s);
 hipError_t launch_combine(const Dims& D, const bf16_t* x, const bf16_t* Y, const int32_t* token_rows,
