@@ -163,6 +163,34 @@ __device__ __forceinline__ int max_dpp(int v) { return max(v, __builtin_amdgcn_u
 template <int CTRL>
 __device__ __forceinline__ int min_dpp(int v) { return min(v, __builtin_amdgcn_update_dpp(v, v, CTRL, 0xF, 0xF, true)); }
 
+// Weights and outputs of four tokens, a row of 16 lanes each: lane j of a row holds the key and the id of the j-th winner.
+template <typename Put>
+__device__ __forceinline__ void weights_rows(const GateArgs& p, int my_k, int my_i, int t, bool valid, int lane, Put put)
+{
+    const int K = p.K, r = lane & 15, n_pick = K < p.m ? K + 1 : K;
+    const float my_v = key_value(my_k);
+    const float top = __shfl(my_v, lane & ~15);
+    float num = 0.0f;
+    if (r < K) num = p.score_fn == 0 ? expf(my_v - top) : 1.0f / (1.0f + expf(-my_v));
+    float den = num;
+    den += dpp_f<0x121>(den);
+    den += dpp_f<0x122>(den);
+    den += dpp_f<0x124>(den);
+    den += dpp_f<0x128>(den);
+    const float nxt = __shfl(my_v, (lane & ~15) | ((r + 1) & 15));
+    const bool close = r + 1 < n_pick && (my_v - nxt) < 1e-6f;
+    const unsigned long long any_close = __ballot(close);
+    if (valid) {
+        if (r < K) {
+            const float w = num / den;
+            p.topk_idx[(size_t)t * K + r] = my_i;
+            p.topk_w[(size_t)t * K + r] = w;
+            put(r, my_i, w);
+        }
+        if (r == 0 && p.near_tie != nullptr) p.near_tie[t] = ((any_close >> (lane & 48)) & 0xFFFFull) != 0ull ? 1 : 0;
+    }
+}
+
 // The same for four tokens at a time: token `row` = lane >> 4 of the four is handled by the 16 lanes of its
 // row, lane r of the row holding experts r, r+16, ... (NC of them: NC >= m_pad / 16); every reduction stays
 // inside the row (rotations), so the four selections run side by side.  A lane's experts that do not exist or
@@ -195,27 +223,7 @@ __device__ __forceinline__ void topk_rows(const GateArgs& p, const float (&v)[NC
         for (int c = 0; c < NC; ++c) k[c] = c == wc ? kNone : k[c];
         if (r == j) { my_k = mx; my_i = id; }
     }
-    const float my_v = key_value(my_k);
-    const float top = __shfl(my_v, lane & ~15);
-    float num = 0.0f;
-    if (r < K) num = p.score_fn == 0 ? expf(my_v - top) : 1.0f / (1.0f + expf(-my_v));
-    float den = num;
-    den += dpp_f<0x121>(den);
-    den += dpp_f<0x122>(den);
-    den += dpp_f<0x124>(den);
-    den += dpp_f<0x128>(den);
-    const float nxt = __shfl(my_v, (lane & ~15) | ((r + 1) & 15));
-    const bool close = r + 1 < n_pick && (my_v - nxt) < 1e-6f;
-    const unsigned long long any_close = __ballot(close);
-    if (valid) {
-        if (r < K) {
-            const float w = num / den;
-            p.topk_idx[(size_t)t * K + r] = my_i;
-            p.topk_w[(size_t)t * K + r] = w;
-            put(r, my_i, w);
-        }
-        if (r == 0 && p.near_tie != nullptr) p.near_tie[t] = ((any_close >> (lane & 48)) & 0xFFFFull) != 0ull ? 1 : 0;
-    }
+    weights_rows(p, my_k, my_i, t, valid, lane, put);
 }
 
 // The same for at most 16 experts, lane r of the row holding expert r, with topk_token's winners and weights: an expert already
@@ -391,21 +399,27 @@ __global__ void __launch_bounds__(256) gate_small_kernel(GateArgs p, const float
                 xv[q][2 * c + 1] = (double)__uint_as_float(w[c] & 0xFFFF0000u);
             }
         }
+        // eight rows of the gate matrix on their way at a time (past the last one: that one again, the sums are not used)
 #pragma unroll
-        for (int e = 0; e < M; ++e) {
-            double wv[8];
-            if (e < p.m) {
-                {
-                    const float4 a = *reinterpret_cast<const float4*>(gate_w + (size_t)e * p.d + k);
-                    const float4 b = *reinterpret_cast<const float4*>(gate_w + (size_t)e * p.d + k + 4);
-                    wv[0] = a.x; wv[1] = a.y; wv[2] = a.z; wv[3] = a.w;
-                    wv[4] = b.x; wv[5] = b.y; wv[6] = b.z; wv[7] = b.w;
-                }
+        for (int e0 = 0; e0 < M; e0 += 8) {
+            float4 wv[8][2];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const float* row = gate_w + (size_t)min(e0 + e, p.m - 1) * p.d + k;
+                wv[e][0] = *reinterpret_cast<const float4*>(row);
+                wv[e][1] = *reinterpret_cast<const float4*>(row + 4);
+            }
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
 #pragma unroll
                 for (int q = 0; q < TPB; ++q)
 #pragma unroll
-                    for (int c = 0; c < 8; ++c) acc[q][e] = fma(xv[q][c], wv[c], acc[q][e]);
-            }
+                    for (int h = 0; h < 2; ++h) {
+                        acc[q][e0 + e] = fma(xv[q][4 * h], (double)wv[e][h].x, acc[q][e0 + e]);
+                        acc[q][e0 + e] = fma(xv[q][4 * h + 1], (double)wv[e][h].y, acc[q][e0 + e]);
+                        acc[q][e0 + e] = fma(xv[q][4 * h + 2], (double)wv[e][h].z, acc[q][e0 + e]);
+                        acc[q][e0 + e] = fma(xv[q][4 * h + 3], (double)wv[e][h].w, acc[q][e0 + e]);
+                    }
         }
     }
     // the 256 partial sums of a pair: eight neighbouring lanes first (three exchange steps), then the 32 group
@@ -434,8 +448,8 @@ __global__ void __launch_bounds__(256) gate_small_kernel(GateArgs p, const float
     if (p.logits != nullptr) return;                      // TopK is the routing block's (batches of one segment)
     __syncthreads();
     if (wave < TPB && t0 + wave < p.T) {
-        const float v[4] = {lane < p.m ? logit[wave][lane & 15] : 0.0f, 0.0f, 0.0f, 0.0f};
-        topk_token(p, v, t0 + wave, lane, [&](int, int e, float) { atomicAdd(&hist[e], 1); });
+        topk_few(p, (lane & 15) < p.m ? logit[wave][lane & 15] : 0.0f, t0 + wave, lane < 16, lane,
+                 [&](int, int e, float) { atomicAdd(&hist[e], 1); });
     }
     if (p.expert_cnt != nullptr) {                        // large batches: the launch's counts (cleared beforehand)
         __syncthreads();
@@ -960,6 +974,19 @@ __device__ __forceinline__ void lds_sync()
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
+// Inclusive sum over the lanes of a wavefront: four shifts inside the rows of 16 lanes, then the rows' last lanes passed on (cross-lane
+// reads through the LDS crossbar take some 100 cycles a step).
+__device__ __forceinline__ int wave_scan(int v)
+{
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false);       // row_shr:1
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false);       // row_shr:2
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false);       // row_shr:4
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false);       // row_shr:8
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false);       // row_bcast:15 into rows 1 and 3
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false);       // row_bcast:31 into rows 2 and 3
+    return v;
+}
+
 // Algorithm 1 as in brownout_decide, in 1024 threads, four neighbouring lanes per expert.  What bounds it is the issue of m^2
 // comparisons on one CU: a wave's 16 experts lie in step `wave` of its walk over the counts, so in all other steps the order
 // "count descending, id ascending" is one comparison with c or c - 1.  grp_s: zero; *any_s is set where a unit is united.
@@ -970,7 +997,15 @@ __device__ __forceinline__ void decide_rows(const int* cnt_s, int* unit_s, int* 
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     bool in_s1 = false, s2 = false;
     int gr = 0;
-    if (ex < p.m) {
+    if (p.threshold == 1.0) {
+        // P < S but for experts without tokens: nobody is browned out.  The sum of the counts, for the caller
+        if (ex < p.m) in_s1 = cnt_s[ex] > 0;
+        if (wave == 15) {
+            const int4 v = reinterpret_cast<const int4*>(cnt_s)[tid & 63];
+            const int S = wave_scan((v.x + v.y) + (v.z + v.w));
+            if ((tid & 63) == 63) *sum_s = S;
+        }
+    } else if (ex < p.m) {
         const int c = cnt_s[ex];
         int P = 0, S = 0;
         const int4* c4 = reinterpret_cast<const int4*>(cnt_s) + part;
@@ -1070,6 +1105,15 @@ __global__ void __launch_bounds__(1024) route_rows_kernel(RowArgs p, GateArgs g)
         constexpr int per = NC > 0 ? 16 : 64;
         const int pitch = g.m_pad + 16;                    // floats: the four tokens of a wavefront on different banks
         float* logit_s = reinterpret_cast<float*>(rsm);
+        // A few tokens leave lanes for every (token, expert) pair: four lanes count the experts ahead of theirs, and there is no
+        // round per winner (one token, 8 of 128 experts: 2.4 us in rounds, 0.8 so).  LDS then holds the logits' keys.
+        bool by_rank = false;
+        int l_m = 5;                                       // log2 of the lanes' experts: m_pad up to a power of two
+        if constexpr (NC > 1) {
+            while ((1 << l_m) < g.m_pad) ++l_m;
+            by_rank = p.T << (l_m + 2) <= 1024;
+        }
+        auto keep = [&](float v) { return by_rank ? __int_as_float(order_key(v)) : v; };
         if constexpr (NC != 1) {
             // a thread per logit: the slices' partial sums, four tokens' at a time in flight, added in order
             const float none = NC > 0 ? -__builtin_inff() : 0.0f;
@@ -1080,7 +1124,7 @@ __global__ void __launch_bounds__(1024) route_rows_kernel(RowArgs p, GateArgs g)
             const double bias = g.bias != nullptr && e < p.m ? (double)g.bias[e] : 0.0;
             if (g.n_slice == 1) {
                 for (int t = tq; t < p.T; t += rows)
-                    if (e < g.m_pad) logit_s[t * pitch + e] = e < p.m ? static_cast<const float*>(g.logits)[t * g.m_pad + e] : none;
+                    if (e < g.m_pad) logit_s[t * pitch + e] = keep(e < p.m ? static_cast<const float*>(g.logits)[t * g.m_pad + e] : none);
             } else {
                 const double* l = static_cast<const double*>(g.logits);
                 for (int tb = 0; tb < p.T; tb += 4 * rows) {
@@ -1099,11 +1143,41 @@ __global__ void __launch_bounds__(1024) route_rows_kernel(RowArgs p, GateArgs g)
 #pragma unroll
                         for (int sl = 0; sl < kGateSlices; ++sl) v += sl < g.n_slice ? x[q][sl] : 0.0;
                         if (g.bias != nullptr) v += bias;
-                        if (t < p.T && e < g.m_pad) logit_s[t * pitch + e] = e < p.m ? (float)v : none;
+                        if (t < p.T && e < g.m_pad) logit_s[t * pitch + e] = keep(e < p.m ? (float)v : none);
                     }
                 }
             }
             lds_sync();
+        }
+        bool ranked = false;
+        if constexpr (NC > 1) {
+            if (by_rank) {
+                const int part = tid & 3, e = (tid >> 2) & ((1 << l_m) - 1), t = tid >> (l_m + 2);
+                if (t < p.T && e < p.m) {
+                    const int* row = reinterpret_cast<const int*>(logit_s) + t * pitch;
+                    const int key = row[e];
+                    int rank = 0;
+#pragma unroll 4
+                    for (int q = 4 * part; q < g.m_pad; q += 16) {
+                        const int4 v = *reinterpret_cast<const int4*>(row + q);
+                        rank += v.x > key - (q < e ? 1 : 0);
+                        rank += v.y > key - (q + 1 < e ? 1 : 0);
+                        rank += v.z > key - (q + 2 < e ? 1 : 0);
+                        rank += v.w > key - (q + 3 < e ? 1 : 0);
+                    }
+                    rank += dpp_i<0xB1>(rank);
+                    rank += dpp_i<0x4E>(rank);
+                    if (part == 0 && rank < (g.K < p.m ? g.K + 1 : g.K)) {
+                        ex_s[t * kMaxTopK + rank] = e;
+                        w_s[t * kMaxTopK + rank] = __int_as_float(key);
+                        if (key == (int)0x807fffff) any_s = 1;      // a winner of logit -infinity: the rounds decide
+                    }
+                }
+                lds_sync();
+                ranked = any_s == 0;
+                lds_sync();
+                if (tid == 0) any_s = 0;
+            }
         }
         for (int t = tid / per; t < (p.T + 64 / per - 1) / (64 / per) * (64 / per); t += 1024 / per) {      // whole wavefronts
             auto put = [&](int j, int e, float wt) {
@@ -1111,6 +1185,11 @@ __global__ void __launch_bounds__(1024) route_rows_kernel(RowArgs p, GateArgs g)
                 w_s[t * kMaxTopK + j] = wt;
                 atomicOr(&bm[e], 1ull << t);
             };
+            if (ranked) {
+                const int at = min(t, p.T - 1) * kMaxTopK + (lane & 15);
+                weights_rows(g, __float_as_int(w_s[at]), ex_s[at], t, t < p.T, lane, put);
+                continue;
+            }
             const int r = lane & (per - 1), tt = min(t, p.T - 1);
             if constexpr (NC == 1) {
                 topk_few(g, r < p.m ? static_cast<const float*>(g.logits)[(size_t)tt * 16 + r] : 0.0f, t, t < p.T, lane, put);
@@ -1120,6 +1199,11 @@ __global__ void __launch_bounds__(1024) route_rows_kernel(RowArgs p, GateArgs g)
 #pragma unroll
                 for (int c = 0; c < N; ++c)
                     v[c] = r + per * c < g.m_pad ? logit_s[tt * pitch + r + per * c] : NC > 0 ? -__builtin_inff() : 0.0f;
+                if (NC > 1 && by_rank) {
+#pragma unroll
+                    for (int c = 0; c < N; ++c)
+                        if (r + per * c < g.m_pad) v[c] = key_value(__float_as_int(v[c]));
+                }
                 if constexpr (NC > 0) topk_rows<NC>(g, v, t, t < p.T, lane, put);
                 else topk_token(g, v, t, lane, put);
             }
@@ -1239,12 +1323,7 @@ __global__ void __launch_bounds__(1024) route_rows_kernel(RowArgs p, GateArgs g)
         if (u < p.m) c = unit_s[u] == u ? tok_s[u] : 0;    // else its tokens have a row in the united unit, or none
         else if (u < p.m + p.G) c = ucnt_s[u];
         else if (u < p.U) c = p.T;                         // a shared expert: every token
-        int incl = c;
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-            const int o = __shfl_up(incl, off);
-            if (lane >= off) incl += o;
-        }
+        const int incl = wave_scan(c);
         if (lane == 63) wsum[wave] = incl;
         lds_sync();
         static_assert(kMaxUnits <= 12 * 64, "units lie in the first 12 wavefronts");

@@ -1,4 +1,4 @@
-"""Routing where the choice of its kernels changes: TopK inside the routing block (up to 64 tokens) or before it, bitmaps from the
+"""Routing where the choice of its kernels changes: TopK inside the routing block (up to 64 tokens; a few by rank) or before it, bitmaps from the
 TopK launch or from the lists, one launch for the rows or three, logits that do not fit the scratch in one piece."""
 import pytest
 import torch
@@ -13,6 +13,8 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("T,m,K,way,Ns,d", [
     (64, 16, 16, 3, 1, 64), (64, 16, 15, 8, 0, 64), (64, 17, 16, 4, 0, 64), (64, 256, 15, 8, 2, 64), (33, 200, 20, 7, 1, 1024),
     (5, 130, 8, 8, 0, 2048),                                                    # one block, 8 slices of K
+    (1, 128, 8, 8, 0, 2048), (2, 120, 15, 8, 0, 64), (3, 128, 8, 8, 0, 64), (4, 60, 4, 8, 1, 2048), (5, 64, 4, 8, 0, 64),
+    (1, 256, 8, 8, 1, 1024), (8, 17, 8, 2, 0, 64),                              # winners by rank, and just too many tokens for it
     (12, 256, 1, 8, 0, 1024), (31, 256, 1, 8, 0, 1024),                         # pieces of 8 (lists) and of 16 tokens (bits)
     (65, 17, 2, 2, 0, 64), (127, 64, 1, 64, 0, 64), (2049, 16, 2, 8, 1, 64),    # lists of few experts, both gates
     (8192, 128, 2, 8, 0, 64), (8193, 40, 2, 8, 1, 64),                          # 128 segments and one more
