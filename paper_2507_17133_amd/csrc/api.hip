@@ -110,20 +110,36 @@ TilePlan make_tile_plan(int64_t rows, bool even)
 
 // Tile height of the routed units.  Where all experts together have fewer 256-column blocks than the chip has CUs, weights are
 // few and the narrow kernel's time is its own latency: no taller tiles then (64 tokens over 8 experts of 256 x 512: 23.8 us
-// at 32 rows, 25.3 at 64).
+// at 32 rows, 25.3 at 64).  With many experts whose weights take some k tiles to stream, padding costs nothing (the MFMAs hide
+// behind the weights) and the fuller units want it: the next height from a third of the rows on.  Layer forward at 32 / 64 / 128
+// rows of a tile: Qwen3 shape at 0.5 brownout, 8 rows per expert 97 / 70 / 75 us; without brownout 8 rows 204 / 207 / 209, 16 rows
+// - / 242 / 226, 28 rows - / 263 / 254, 44 rows - / 294 / 278 (at 0.4 brownout 156 / 137); DeepSeek-V3 shape 4 rows 1684 / 1582 /
+// 1613 (at 0.5 752 / 653 / 714), 12 rows 2401 / 2411 / 2311, 32 rows - / 3446 / 3329.  Few experts hold near the mean: Mixtral
+// shape at 0.5, 30 rows - / 354 / 392.  Shared experts of a width of their own go out with tiles of up to 64 rows only: 250 tokens
+// of the 60-expert shape, 17 rows, 270 at 64 and 296 at 128.
+constexpr int kBesideTokens = 256;
 static int routed_tile_rows(const Dims& D, int n_cu)
 {
-    const int64_t entries = (int64_t)D.T * D.K;
+    const int64_t entries = (int64_t)D.T * D.K, rows = entries / D.m;
     const bool few = std::min<int64_t>(entries, D.m) * ceil_div(D.F, 128) < n_cu;
-    return pick_tile_rows(entries / D.m, few);
+    const int bm = pick_tile_rows(rows, few);
+    if (few || tuning().force_bm || D.m <= 16 || D.d < 1024) return bm;
+    const bool beside = D.Ns > 0 && D.Fs != D.F && D.T <= kBesideTokens;
+    if (bm == 64 && rows >= 12 && !beside) return 128;
+    if (bm == 32 && rows >= 4) return 64;
+    return bm;
 }
 
-// A launch of shared experts alone: with up to 128 tokens and too few 256-column blocks for the CUs, tiles of 64 rows
-// let the narrow kernel run (100 tokens over F = 5632: 44 blocks of 128 rows; layer with its routed experts 157.6 -> 124.7 us).
+// A launch of shared experts alone.  Up to kBesideTokens tokens of few enough 64-row blocks go to the narrow kernel, in one launch
+// with the routed units (100 tokens over F = 5632, 44 blocks of 128 rows: layer with its routed experts 157.6 -> 124.7 us; 250
+// tokens 285 -> 270), and 256 rows need a tile for every CU (500 tokens at 0.6 brownout: 205 us with them, 156 with 128).
 static TilePlan make_shared_plan(const Dims& D, int n_cu)
 {
     TilePlan p = make_tile_plan(D.T, true);
-    if (p.bm == 128 && !tuning().force_bm && D.T <= 128 && 2 * D.Ns * ceil_div(D.Fs, 128) < n_cu) p.bm = 64;
+    if (tuning().force_bm) return p;
+    const int cols = D.Ns * ceil_div(D.Fs, 128);
+    if (p.bm == 256 && ceil_div(D.T, 256) * cols < n_cu) p.bm = 128;
+    if (p.bm == 128 && D.T <= kBesideTokens && ceil_div(D.T, 64) * cols < n_cu) p.bm = 64;
     return p;
 }
 

@@ -16,7 +16,8 @@ CASES = [(1, 128, 64, 8, 2, 4, 1, 192, "32,1,32", "32,1,32"), (20, 512, 1024, 64
          (37, 256, 1088, 60, 4, 8, 1, 2112, "32,0,64", "32,1,64"), (64, 128, 192, 4, 1, 2, 2, 320, "32,1,64", "32,1,64"),
          (100, 192, 2112, 64, 8, 8, 1, 1088, "64,0,64", "64,0,64"),
          (100, 256, 1408, 24, 4, 8, 1, 1088, "64,0,64", "64,1,64"), (128, 640, 128, 24, 4, 8, 1, 64, "32,1,64", "32,1,64"),
-         (129, 256, 128, 24, 4, 8, 1, 320, None, None), (383, 64, 128, 24, 4, 8, 1, 320, None, None)]
+         (256, 256, 128, 24, 4, 8, 1, 320, "64,1,64", "64,1,64"),
+         (257, 256, 128, 24, 4, 8, 1, 320, None, None), (383, 64, 128, 24, 4, 8, 1, 320, None, None)]
 
 
 def _pairs(launches):
