@@ -14,12 +14,15 @@
 // The contractions over tokens read K-contiguous operands that the earlier epilogues have written transposed.
 // Why: with each of these as a pass of its own (64-row GEMM tiles with fp32 results, transposes, SwiGLU, Adam, the loss
 // summed by one block) a pass over two groups of 8 and 4 teachers at n = d = 2048, F = 1408 with 8 steps took 56.9 ms,
-// 50 of them in the one-block sums and 3.4 in the GEMMs; now 3.58 ms.  Of those a step's four launches take 0.38 ms
-// (kSwiglu 78 us, kResidual 45, kBackward 59, kAdam 194 of which 484 MB of masters and moments are 107 us at the rate
-// of a large copy).
+// 50 of them in the one-block sums and 3.4 in the GEMMs; now 3.4 ms.  Of those a step's four launches take 0.36 ms
+// (kSwiglu 80 us, kResidual 47, kBackward 59, kAdam 170 of which 484 MB of masters and moments are 94 us at the rate
+// of a large copy; 197 while its epilogue read and wrote them in pieces of 64 bytes).  The k loop pulls 40 to 50 GB/s per CU
+// whatever the lead of its loads (two more k tiles in registers: no change), for the blocks of an XCD reach each slab of
+// their panels together.
 #include "internal.h"
 
 #include <algorithm>
+#include <type_traits>
 
 namespace bmoe {
 
@@ -155,7 +158,9 @@ struct DGemm {
 };
 
 constexpr int kImgPitch = 272;                             // bytes per row of a 128 x 128 bf16 image in LDS
-constexpr int kDGemmLds = 2 * 128 * kImgPitch;             // two images; the two stages of the k loop need 64 KiB
+// kAdam: per wave 32 rows x 64 columns of products (272 bytes a row) and a transposed bf16 image of its 64 x 64 (144 a column)
+constexpr int kAdamRow = 272, kAdamCol = 144, kAdamWave = 32 * kAdamRow + 64 * kAdamCol;
+constexpr int dgemm_lds(int epi) { return epi == kAdam ? 4 * kAdamWave : 2 * 128 * kImgPitch; }    // else two images; the k loop: 64 KiB
 
 // 128 x 128 x 64 tiles, four waves (64 x 64 each, 16x16x32 MFMA), two LDS stages filled by direct global->LDS
 // loads, two blocks per CU: the second block's waves cover the barrier and the load latency of the first.
@@ -353,49 +358,90 @@ __global__ void __launch_bounds__(256, 2) distill_gemm_kernel(DGemm p)
         }
     } else {
         // r: master, first and second moment (fp32 [M][N]), the bf16 copy [M][N], its transpose [N][M] or null.
-        // Adam with bias correction; the first step starts from the bf16 copy and zero moments.
+        // Adam with bias correction; the first step starts from the bf16 copy and zero moments.  32 rows x 64 columns of products
+        // at a time go through LDS of the wave's own, and a lane works on rows 4 q + (lane >> 4), columns 4 (lane & 15) + 0..3: 256
+        // bytes of a row at a time, and the state of the next 16 rows is on its way meanwhile.
         float* W = J.r[0].at<float>(g);
         float* Mo = J.r[1].at<float>(g);
         float* V = J.r[2].at<float>(g);
         unsigned short* wb = J.r[3].at<unsigned short>(g);
         const float beta1 = 0.9f, beta2 = 0.999f, eps = 1e-8f;
+        char* own = smem + wave * kAdamWave;
+        char* img = own + 32 * kAdamRow;
+        const int cr = lane >> 4, cc = 4 * (lane & 15);
+        const size_t at0 = (size_t)(m0 + wm * 64 + cr) * J.N + n0 + wn * 64 + cc;
+        // (the first step by itself, so that the loads in flight can be counted)
+        auto update = [&](auto first) {
+            f32x4 have[4][3], next[4][3];
+            auto fetch = [&](int row, f32x4 (&to)[4][3]) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int r = r_l + i * 16, c = wn * 64 + j * 16 + c4;
-                const size_t at = (size_t)(m0 + r) * J.N + n0 + c;
-                unsigned short o[4] = {0, 0, 0, 0};
-                if (w_in) {
-                    f32x4 w, m, v;
-                    if (p.first) {
+                for (int q = 0; q < 4; ++q) {
+                    const size_t at = at0 + (size_t)(row + 4 * q) * J.N;
+                    if constexpr (decltype(first)::value) {
                         const uint2 b = *reinterpret_cast<const uint2*>(wb + at);
-                        w = f32x4{bf_to_f(b.x & 0xFFFF), bf_to_f(b.x >> 16), bf_to_f(b.y & 0xFFFF), bf_to_f(b.y >> 16)};
-                        m = f32x4{0.f, 0.f, 0.f, 0.f};
-                        v = m;
+                        to[q][0] = f32x4{bf_to_f(b.x & 0xFFFF), bf_to_f(b.x >> 16), bf_to_f(b.y & 0xFFFF), bf_to_f(b.y >> 16)};
+                        to[q][1] = to[q][2] = f32x4{0.f, 0.f, 0.f, 0.f};
                     } else {
-                        w = *reinterpret_cast<const f32x4*>(W + at);
-                        m = *reinterpret_cast<const f32x4*>(Mo + at);
-                        v = *reinterpret_cast<const f32x4*>(V + at);
+                        to[q][0] = *reinterpret_cast<const f32x4*>(W + at);
+                        to[q][1] = *reinterpret_cast<const f32x4*>(Mo + at);
+                        to[q][2] = *reinterpret_cast<const f32x4*>(V + at);
+                    }
+                }
+            };
+            fetch(0, have);
+#pragma unroll
+            for (int rg = 0; rg < 2; ++rg) {
+#pragma unroll
+                for (int i = 0; i < 2; ++i)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j)
+                        *reinterpret_cast<f32x4*>(own + (i * 16 + (lane & 15)) * kAdamRow + (j * 16 + c4) * 4) = acc[rg * 2 + i][j];
+#pragma unroll
+                for (int ps = 0; ps < 2; ++ps) {
+                    if (rg * 32 + ps * 16 + 16 < 64) fetch(rg * 32 + ps * 16 + 16, next);
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const int rl = ps * 16 + 4 * q + cr;
+                        const size_t at = at0 + (size_t)(rg * 32 + ps * 16 + 4 * q) * J.N;
+                        const f32x4 prod = *reinterpret_cast<const f32x4*>(own + rl * kAdamRow + cc * 4);
+                        f32x4 &w = have[q][0], &m = have[q][1], &v = have[q][2];
+                        unsigned short o[4];
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            const float gr = prod[e] * p.gscale;
+                            m[e] = fmaf(beta1, m[e], (1.0f - beta1) * gr);
+                            v[e] = fmaf(beta2, v[e], (1.0f - beta2) * gr * gr);
+                            w[e] = w[e] - p.lr * (m[e] * p.c1) / (sqrtf(v[e] * p.c2) + eps);
+                            o[e] = f_to_bf(w[e]);
+                        }
+                        *reinterpret_cast<f32x4*>(W + at) = w;
+                        *reinterpret_cast<f32x4*>(Mo + at) = m;
+                        *reinterpret_cast<f32x4*>(V + at) = v;
+                        *reinterpret_cast<uint2*>(wb + at) = pack4(o);
+                        if (J.r[4].p)
+#pragma unroll
+                            for (int e = 0; e < 4; ++e)
+                                *reinterpret_cast<unsigned short*>(img + (cc + e) * kAdamCol + (rg * 32 + rl) * 2) = o[e];
                     }
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const float gr = acc[i][j][e] * p.gscale;
-                        m[e] = beta1 * m[e] + (1.0f - beta1) * gr;
-                        v[e] = beta2 * v[e] + (1.0f - beta2) * gr * gr;
-                        w[e] = w[e] - p.lr * (m[e] * p.c1) / (sqrtf(v[e] * p.c2) + eps);
-                        o[e] = f_to_bf(w[e]);
-                    }
-                    *reinterpret_cast<f32x4*>(W + at) = w;
-                    *reinterpret_cast<f32x4*>(Mo + at) = m;
-                    *reinterpret_cast<f32x4*>(V + at) = v;
+                    for (int q = 0; q < 4; ++q)
+#pragma unroll
+                        for (int k = 0; k < 3; ++k) have[q][k] = next[q][k];
                 }
-                put_row(rows, r, c, o);
-                if (J.r[4].p) put_col(cols, r, c, o);
             }
-        __syncthreads();
-        flush(rows, 128, 128, wb, J.N, m0, J.M, n0, J.N);
-        if (J.r[4].p) flush(cols, 128, 128, J.r[4].at<unsigned short>(g), J.M, n0, J.N, m0, J.M);
+        };
+        if (w_in) {
+            if (p.first) update(std::true_type{});
+            else update(std::false_type{});
+            if (J.r[4].p) {
+                unsigned short* out = J.r[4].at<unsigned short>(g) + (size_t)(n0 + wn * 64) * J.M + m0 + wm * 64;
+#pragma unroll
+                for (int q = 0; q < 8; ++q) {
+                    const int c = q * 8 + (lane >> 3), r = 8 * (lane & 7);
+                    *reinterpret_cast<uint4*>(out + (size_t)c * J.M + r) = *reinterpret_cast<const uint4*>(img + c * kAdamCol + r * 2);
+                }
+            }
+        }
     }
 }
 
@@ -408,7 +454,7 @@ static hipError_t launch_dgemm(DGemm& p, int groups, hipStream_t s)
     }
     p.tiles = p.job[0].mt * p.job[0].nt;
     p.total = groups * p.n_jobs * p.tiles;
-    distill_gemm_kernel<EPI><<<ceil_div(p.total, 8) * 8, 256, kDGemmLds, s>>>(p);
+    distill_gemm_kernel<EPI><<<ceil_div(p.total, 8) * 8, 256, dgemm_lds(EPI), s>>>(p);
     return hipGetLastError();
 }
 
@@ -418,8 +464,9 @@ hipError_t init_distill_kernels()
                        reinterpret_cast<const void*>(distill_gemm_kernel<kResidual>),
                        reinterpret_cast<const void*>(distill_gemm_kernel<kBackward>),
                        reinterpret_cast<const void*>(distill_gemm_kernel<kAdam>)};
-    for (const void* f : k) {
-        const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, kDGemmLds);
+    static_assert(kSwiglu == 0 && kResidual == 1 && kBackward == 2 && kAdam == 3, "the order above");
+    for (int i = 0; i < 4; ++i) {
+        const hipError_t e = hipFuncSetAttribute(k[i], hipFuncAttributeMaxDynamicSharedMemorySize, dgemm_lds(i));
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
