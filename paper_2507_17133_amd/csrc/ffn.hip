@@ -6,7 +6,7 @@
 //
 // Both operands of both GEMMs are K-contiguous (x [T][d], W1/W3 [F][d], H [R][F], W2 [d][F]), which is
 // the natural operand order of the bf16 MFMAs: a lane supplies 8 consecutive k of one row.  A block owns a
-// BM x 256 output tile; k tiles of 64 (whole 128-byte lines per row) are staged in LDS in 16-byte chunks,
+// BM x 256 output tile (128 or 64 columns where those would leave CUs without one); k tiles of 64 (whole 128-byte lines per row) are staged in LDS in 16-byte chunks,
 // XOR-swizzled so that the ds_read_b128 fragment loads are conflict free.  In GEMM1 a block's 256 B rows
 // are 128 columns of W1 and the same 128 columns of W3, interleaved tile by tile, so that the gate and up
 // values of one (row, f) land in the same lane and SwiGLU is applied in registers.
@@ -24,6 +24,7 @@
 //   128 rows  ffn_gemm_ws_kernel   four waves that load and four that multiply, persistent
 //   64, 32    ffn_gemm_kernel      four waves, plain multi-stage ring (decode: weight streaming bound);
 //             ffn_gemm_narrow_kernel  a quarter of the columns per block, where that kernel would have too few blocks
+//             ffn_gemm_pair_kernel  the bodies of these two for two problems side by side (routed units, shared experts)
 #include "internal.h"
 #include "tiles.h"
 
