@@ -713,7 +713,7 @@ __device__ __forceinline__ void ws_block(const GemmArgs& p, const int n_mt, cons
                 next += slots;
                 set_up(t);
             }
-                char* dst = smem + stage * STAGE + lw * 1024;
+            char* dst = smem + stage * STAGE + lw * 1024;
 #pragma unroll
             for (int i = 0; i < LB; ++i)
                 __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(gb[i] + kt * BK),
