@@ -73,6 +73,26 @@ struct GateArgs {
     int t_base;            // token of the batch that token 0 of this launch is (a multiple of 16 with bits)
 };
 
+// What a block of 16 tokens leaves of its winners besides the lists: a map of its tokens per expert (p.bits: a quarter of a
+// segment's word), or counts for the launches behind it.
+__device__ __forceinline__ void note_winner(const GateArgs& p, int* hist, int tl, int e)
+{
+    if (p.bits != nullptr) atomicOr(&hist[e], 1 << tl);
+    else atomicAdd(&hist[e], 1);
+}
+template <int THREADS>
+__device__ __forceinline__ void flush_winners(const GateArgs& p, const int* hist, int tid)
+{
+    if (p.bits != nullptr) {
+        const int t16 = p.t_base / 16 + (int)blockIdx.x;
+        unsigned short* out = reinterpret_cast<unsigned short*>(p.bits) + (size_t)(t16 >> 2) * p.m * 4 + (t16 & 3);
+        for (int i = tid; i < p.m; i += THREADS) out[4 * i] = (unsigned short)hist[i];
+    } else if (p.expert_cnt != nullptr) {
+        for (int i = tid; i < p.m; i += THREADS)
+            if (hist[i] > 0) atomicAdd(&p.expert_cnt[i], hist[i]);
+    }
+}
+
 // TopK(.,K) of one token by one wavefront: lane holds experts lane, lane+64, ...; K (+1 for the best
 // loser) rounds of "best of my candidates, then best across lanes" (higher score, equal scores: lower
 // id); lane j keeps the j-th winner, weights are normalised over lanes 0..K-1.
@@ -354,10 +374,10 @@ __global__ void __launch_bounds__(512) gate_few_kernel(GateArgs p)
         const int tl = wave * 4 + (lane >> 4);
         const bool valid = t0 + tl < p.T;
         float v[1] = {(lane & 15) < p.m ? logit[tl * 16 + (lane & 15)] : -__builtin_inff()};
-        topk_rows<1>(p, v, t0 + tl, valid, lane, [&](int, int e, float) { atomicAdd(&hist[e], 1); });
+        topk_rows<1>(p, v, t0 + tl, valid, lane, [&](int, int e, float) { note_winner(p, hist, tl, e); });
     }
     __syncthreads();
-    if (p.expert_cnt != nullptr && tid < p.m && hist[tid] > 0) atomicAdd(&p.expert_cnt[tid], hist[tid]);
+    flush_winners<512>(p, hist, tid);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -641,15 +661,11 @@ __global__ void __launch_bounds__(THREADS) gate_topk_kernel(GateArgs p)
     constexpr int QB = THREADS == 1024 && NC > 0 ? 1 : NC > 8 ? 4 : THREADS == 256 ? 8 : 4;
     __shared__ int hist[kMaxExperts];                      // counts, or 16-bit maps of the block's tokens
     const int tid = threadIdx.x, lane = tid & 63;
-    const bool bits = p.bits != nullptr;
     for (int i = tid; i < p.m; i += THREADS) hist[i] = 0;
     __syncthreads();
     const int per = NC > 0 ? 16 : 64;                      // lanes of a token
     const int tl = tid / per, t = (int)blockIdx.x * (THREADS / per) + tl;
-    auto put = [&](int, int e, float) {
-        if (bits) atomicOr(&hist[e], 1 << tl);
-        else atomicAdd(&hist[e], 1);
-    };
+    auto put = [&](int, int e, float) { note_winner(p, hist, tl, e); };
     if constexpr (NC > 0) {
         float v[NC];
         read_logits<NC, 16, QB>(p, min(t, p.T - 1), lane & 15, -__builtin_inff(), v);
@@ -660,14 +676,7 @@ __global__ void __launch_bounds__(THREADS) gate_topk_kernel(GateArgs p)
         topk_token(p, v, t, lane, put);
     }
     __syncthreads();
-    if (bits) {
-        const int t16 = p.t_base / 16 + (int)blockIdx.x;
-        unsigned short* out = reinterpret_cast<unsigned short*>(p.bits) + (size_t)(t16 >> 2) * p.m * 4 + (t16 & 3);
-        for (int i = tid; i < p.m; i += THREADS) out[4 * i] = (unsigned short)hist[i];
-    } else if (p.expert_cnt != nullptr) {
-        for (int i = tid; i < p.m; i += THREADS)
-            if (hist[i] > 0) atomicAdd(&p.expert_cnt[i], hist[i]);
-    }
+    flush_winners<THREADS>(p, hist, tid);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -1056,8 +1065,12 @@ __device__ __forceinline__ void decide_rows(const int* cnt_s, int* unit_s, int* 
 // writes what the whole batch has one of (counts, unit maps and offsets, tile tables).  Nothing passes between blocks: each
 // counts the whole batch from the bitmaps of its TopK entries (token t of segment g names expert i: bit t mod 64 of word
 // [g][i]), takes Algorithm 1's decision and the unit offsets from that and scatters its own segment.
-//   kBits  the bitmaps come from the TopK launch
-//   kLists every block makes them from the TopK lists (at most 16 experts: a ballot per expert; more: LDS atomics)
+//   kBits  the bitmaps come from the launch that takes TopK 16 tokens to a block (more than 16 experts; at most 16 beyond
+//          kFewExpertsTokens tokens)
+//   kLists every block makes them from the TopK lists (at most 16 experts: a mask per token, then a ballot per expert; more: LDS
+//          atomics).  A ballot per entry and expert made few experts with long lists slow: routing of 2048 tokens x 16 of 16
+//          experts 68 us, now 50; 300 x 8 of 16 19.8, 15.4; beyond, lists read by every block instead of bitmaps: 8192 x 8 of 16
+//          81, now 17.4, x 16 of 16 146, 19.6
 //   kTopK  one segment: the block takes TopK of the logits itself and is the only one (NC: 1 topk_few, more topk_rows, 0
 //          topk_token)
 // Bound by latency: some ten barriers, two trips to the L2 and what a block reads of the bitmaps (8 m bytes per segment).  TopK
@@ -1215,15 +1228,22 @@ __global__ void __launch_bounds__(1024) route_rows_kernel(RowArgs p, GateArgs g)
             if (p.m <= 16) {
                 for (int sgm = wave; sgm < p.n_seg; sgm += 16) {
                     const int t = sgm * kSegTokens + lane;
+                    const int32_t* list = p.topk_idx + (size_t)min(t, p.T - 1) * p.K;
+                    unsigned named = 0u;                   // the token's experts, eight entries on their way at a time
+                    for (int j = 0; j < p.K; j += 8) {
+                        int e[8];
+#pragma unroll
+                        for (int q = 0; q < 8; ++q)
+                            if (j + q < p.K) e[q] = list[j + q];
+#pragma unroll
+                        for (int q = 0; q < 8; ++q)
+                            if (j + q < p.K) named |= 1u << e[q];
+                    }
+                    if (t >= p.T) named = 0u;
                     unsigned long long mine = 0ull;
-                    int next = t < p.T ? p.topk_idx[(size_t)t * p.K] : -1;
-                    for (int j = 0; j < p.K; ++j) {
-                        const int e = next;
-                        if (j + 1 < p.K) next = t < p.T ? p.topk_idx[(size_t)t * p.K + j + 1] : -1;
-                        for (int i = 0; i < p.m; ++i) {
-                            const unsigned long long b = __ballot(e == i);
-                            if (lane == i) mine |= b;
-                        }
+                    for (int i = 0; i < p.m; ++i) {
+                        const unsigned long long b = __ballot((named >> i) & 1u);
+                        if (lane == i) mine = b;
                     }
                     if (lane < p.m) local[sgm * bp + bit_slot(lane)] = mine;
                 }
@@ -1506,8 +1526,8 @@ hipError_t launch_route(const Dims& D, const bf16_t* x, const void* gate, const 
     const bool whole = plan.chunk >= D.T;
     enum { kOneBlock, kFromBits, kFromLists, kThreeLaunches } how = kThreeLaunches;
     if (D.n_seg == 1 && whole) how = kOneBlock;
-    else if (!few_fmt && rows_fit(D.n_seg, D.m) && (whole || plan.chunk % 16 == 0)) how = kFromBits;
-    else if (rows_fit(D.n_seg, D.m) && (few_fmt || D.n_seg == 1)) how = kFromLists;
+    else if (!few && rows_fit(D.n_seg, D.m) && (whole || plan.chunk % 16 == 0)) how = kFromBits;
+    else if (rows_fit(D.n_seg, D.m) && (few || D.n_seg == 1)) how = kFromLists;
     int32_t* counters = how == kThreeLaunches ? R.expert_cnt : nullptr;
     // Preparation: cut an fp32 gate matrix into its pieces (only the MFMA gates need them) and clear the expert
     // counters, if used (the logit kernel of the many-expert gate clears them itself).
