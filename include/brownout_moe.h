@@ -181,7 +181,10 @@ moe_status moe_distill_united(const moe_config *cfg, const moe_ffn_weights *expe
  * Gate + TopK + Algorithm 1 + row lists for T tokens x [T][d] bf16.
  *   gate_w [m][d] fp32 (row i = centroid e_i) or, with cfg->gate_format ==
  *   MOE_GATE_PACKED, the buffer moe_pack_gate wrote; gate_bias [m] fp32 or NULL:
- *   s_{i,t} = x_t . e_i (+ bias_i), accumulated to fp32 accuracy.
+ *   s_{i,t} = x_t . e_i (+ bias_i), accumulated to fp32 accuracy.  A NaN logit
+ *   ranks and weighs as -infinity.  A token with fewer than K logits above that has
+ *   its list filled up with entries of weight 0, which may name an expert again;
+ *   with none at all its weights are NaN.
  *   threshold in [0,1]: share of token->expert assignments that stays on
  *   original experts (1 = zero-brownout).  Algorithm 1 is read so that it
  *   reproduces the paper's worked examples: experts sorted by count descending
