@@ -7,7 +7,7 @@
 //            slice of K) and TopK                                    (Architecture of BrownoutMoE)
 //   rows     up to 8192 tokens, one launch: expert counts, Algorithm 1's S1/S2 split and unit map (Brownout Approach,
 //            Algorithm 1), the row lists row_token, row_weight, token_rows (stable: ascending token inside a unit) and the
-//            GEMM tile tables; up to 64 tokens it takes TopK as well
+//            GEMM tile tables; for few tokens it takes TopK as well
 //   count, scan, scatter   the same for larger batches: the rows each 64-token segment gives each unit, offsets of segments
 //            inside units and unit totals, row lists and tile tables
 // No floating-point atomics anywhere; integer atomics only where the result does not depend on order.
@@ -443,7 +443,7 @@ __global__ void __launch_bounds__(256) gate_small_kernel(GateArgs p, const float
             else if (t0 + q < p.T) static_cast<float*>(p.logits)[(size_t)(t0 + q) * p.m_pad + e] = (float)s;
         }
     }
-    if (p.logits != nullptr) return;                      // TopK is the routing block's (batches of one segment)
+    if (p.logits != nullptr) return;                      // TopK is the routing block's
     __syncthreads();
     if (wave < TPB && t0 + wave < p.T) {
         topk_few(p, (lane & 15) < p.m ? logit[wave][lane & 15] : 0.0f, t0 + wave, lane < 16, lane,
@@ -1473,6 +1473,18 @@ static hipError_t launch_gate(GateArgs g, const GatePlan& plan, bool topk, hipSt
     return hipSuccess;
 }
 
+// Whether one block takes TopK and routes the batch: a segment of at most 16 experts, or of at most 64 and 15 entries; of more, as
+// long as one CU has the logits ranked before a launch over several would have started.  moe_route with that launch / without, us: 24
+// tokens x 15 of 256 experts 24.8 / 24.8, x 16 of 128 20.7 / 20.8, 32 tokens 24.8 / 27.0, 20.9 / 24.6; 32 tokens x 8 of 128 16.9 / 17.1, x 2
+// of 128 15.9 / 14.4; 64 tokens x 8 of 128 17.1 / 22.7, x 15 of 256 25.5 / 39.4, x 32 of 128 31 / 60; 64 x 4 of 60 15.8 / 15.6, x 8 of 32
+// 15.9 / 14.1.
+static bool one_block_routes(const Dims& D)
+{
+    if (D.n_seg > 1) return false;
+    if (D.m_pad == 16 || (D.m_pad <= 64 && D.K <= 15)) return true;
+    return D.T <= (D.m_pad <= 128 && D.K <= 15 ? 32 : 24);
+}
+
 // The block that takes TopK of a batch of one segment and routes it.
 static hipError_t launch_route_topk(const GateArgs& g, const RowArgs& p, hipStream_t s)
 {
@@ -1497,13 +1509,13 @@ hipError_t launch_route(const Dims& D, const bf16_t* x, const void* gate, const 
     // plain fp64 gate reads them as they are (larger batches: cut here on every call, 6 us, then the MFMA gate).
     const bool few_fmt = D.m_pad == 16;
     const bool few = few_fmt && D.T <= kFewExpertsTokens;
-    // Who makes the row lists: one block that takes TopK of one segment's logits as well, a block per segment on the whole
+    // Who makes the row lists: one block that takes TopK of a small batch's logits as well, a block per segment on the whole
     // batch's bitmaps, or beyond kRowSegs segments the count, scan and scatter launches.
     GatePlan plan{1, D.T};
     if (!few_fmt) plan = plan_gate(D.T, D.m_pad, D.d, logit_bytes);
     const bool whole = plan.chunk >= D.T;
     enum { kOneBlock, kFromBits, kFromLists, kThreeLaunches } how = kThreeLaunches;
-    if (D.n_seg == 1 && whole) how = kOneBlock;
+    if (whole && one_block_routes(D)) how = kOneBlock;
     else if (!few && rows_fit(D.n_seg, D.m) && (whole || plan.chunk % 16 == 0)) how = kFromBits;
     else if (rows_fit(D.n_seg, D.m) && (few || D.n_seg == 1)) how = kFromLists;
     int32_t* counters = how == kThreeLaunches ? R.expert_cnt : nullptr;

@@ -1,6 +1,6 @@
 """Where the row kernel takes the tokens of an expert from: bitmaps of the launch that takes TopK wherever its blocks have 16 tokens,
-the TopK lists of at most 16 experts up to 2048 tokens, the routing block's own TopK; with long lists of few experts, which
-need no more time than the three launches of larger batches."""
+the TopK lists of at most 16 experts up to 2048 tokens, the routing block's own TopK of a segment of up to 64 experts or of 24 or
+32 tokens; with long lists of few experts, which need no more time than the three launches of larger batches."""
 import re
 
 import pytest
@@ -13,7 +13,9 @@ from tests._util import check_route, oracle_route
 BITS, LISTS, TOPK, THREE = "0", "1", "2", None
 # T, m, K and the source
 CASES = [(64, 16, 16, TOPK), (65, 16, 16, LISTS), (100, 1, 1, LISTS), (703, 16, 9, LISTS), (2048, 13, 13, LISTS), (2049, 16, 16, BITS),
-         (2065, 3, 2, BITS), (3007, 9, 8, BITS), (8192, 12, 12, BITS), (8193, 16, 8, THREE), (65, 17, 8, BITS), (8192, 40, 17, BITS)]
+         (2065, 3, 2, BITS), (3007, 9, 8, BITS), (8192, 12, 12, BITS), (8193, 16, 8, THREE), (65, 17, 8, BITS), (8192, 40, 17, BITS),
+         (64, 64, 15, TOPK), (65, 64, 15, BITS), (64, 65, 1, BITS), (32, 128, 8, TOPK), (33, 65, 15, BITS), (24, 256, 32, TOPK),
+         (24, 129, 15, TOPK), (25, 256, 15, BITS), (24, 17, 16, TOPK), (25, 17, 16, BITS), (49, 200, 31, BITS)]
 
 
 def _source(launches):
