@@ -1440,7 +1440,7 @@ static GatePlan plan_gate(int T, int m_pad, int d, size_t bytes)
     P.n_slice = ceil_div(ksteps, ceil_div(ksteps, sl));                  // no empty slice
     const int64_t most = (int64_t)(bytes / ((size_t)m_pad * (P.n_slice == 1 ? 4 : 8 * P.n_slice)));
     const int64_t unit = most >= 64 ? 64 : most >= 16 ? 16 : 1;
-    P.chunk = (int)std::min<int64_t>(T, std::max<int64_t>(most / unit * unit, 1));
+    P.chunk = most >= T ? T : (int)std::max<int64_t>(most / unit * unit, 1);
     return P;
 }
 

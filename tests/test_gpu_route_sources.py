@@ -31,6 +31,13 @@ def test_sources_of_the_cases(tmp_path):
         assert r["status"] == 0 and _source(r["launches"]) == w, (c, w)
 
 
+def test_logits_that_fit_the_scratch_go_through_it_at_once(tmp_path):
+    """Room for 26 and for 100 tokens or a few more: more than a multiple of 16 or 64, and all there are."""
+    calls = [dict(entry=e, cfg=[1024, 64, 256, 2, 8, 0, 0, 0, 0, 1], T=T) for T in (24, 25, 100) for e in ("route", "forward")]
+    for c, r in zip(calls, trace(calls, tmp_path)):
+        assert r["status"] == 0 and [l["T"] for l in r["launches"] if l["name"] == "gate_logits_kernel"] == [c["T"]], c
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("T,m,K", [c[:3] for c in CASES])
 @pytest.mark.parametrize("threshold,full", [(1.0, False), (0.4, False), (0.0, True)])
