@@ -108,26 +108,39 @@ TilePlan make_tile_plan(int64_t rows, bool even)
     return p;
 }
 
-// Tile height of the routed units.  Where all experts together have fewer 256-column blocks than the chip has CUs, weights are
+// Tile heights of the routed units.  Where all experts together have fewer 256-column blocks than the chip has CUs, weights are
 // few and the narrow kernel's time is its own latency: no taller tiles then (64 tokens over 8 experts of 256 x 512: 23.8 us
-// at 32 rows, 25.3 at 64).  With many experts whose weights take some k tiles to stream, padding costs nothing (the MFMAs hide
-// behind the weights) and the fuller units want it: the next height from a third of the rows on.  Layer forward at 32 / 64 / 128
-// rows of a tile: Qwen3 shape at 0.5 brownout, 8 rows per expert 97 / 70 / 75 us; without brownout 8 rows 204 / 207 / 209, 16 rows
-// - / 242 / 226, 28 rows - / 263 / 254, 44 rows - / 294 / 278 (at 0.4 brownout 156 / 137); DeepSeek-V3 shape 4 rows 1684 / 1582 /
-// 1613 (at 0.5 752 / 653 / 714), 12 rows 2401 / 2411 / 2311, 32 rows - / 3446 / 3329.  Few experts hold near the mean: Mixtral
-// shape at 0.5, 30 rows - / 354 / 392.  Shared experts of a width of their own go out with tiles of up to 64 rows only: 250 tokens
-// of the 60-expert shape, 17 rows, 270 at 64 and 296 at 128.
+// at 32 rows, 25.3 at 64).  With many experts whose weights take some k tiles to stream, a GEMM takes as long as its rounds of blocks,
+// and those follow from how the gate and brownout fill the units: from 4 rows per expert on the table kernel chooses between 32
+// and 64 rows, from 12 on between 64 and 128 (tiles.h; one launch takes either).  Layer forward in us at the lower height, the taller and
+// as chosen, skewed gate, then even gate; 2048 x 768, 128 experts: 8 rows per expert without brownout 200 / 207 / 200, 16 rows 230 / 228 /
+// 222, 28 rows 250 / 275 / 250; at 0.5 brownout 85 / 69 / 69, 97 / 79 / 79, 106 / 98 / 98; even, at 0.5, 11 rows 149 / 155 / 149, 16 rows 154 /
+// 166 / 154, 28 rows 183 / 176 / 175; 2048 x 1408, 60 experts at 0.6: 8 rows 68 / 60 / 61, even 119 / 129 / 119, 17 rows 131 / 147 / 131; DeepSeek-V3
+// shape, 8 rows 2084 / 1962 / 1964, 12 rows 2447 / 2388 / 2388, even, at 0.4, 40 rows 3115 / 2967 / 2969.
+// With up to 16 experts or less than 1024 columns the mean decides.  There too the other height can be the better one (4096 x 2048, 16
+// experts, 8 rows 176 us at 32 rows and 164 at 64; 960 x 2048, 128 experts, 8 rows at 0.5 107 and 92), now and then by as much.
+// Shared experts of a width of their own go out with tiles of up to 64 rows only: 250 tokens of the 60-expert shape, 17 rows, 270 at
+// 64 and 296 at 128.
 constexpr int kBesideTokens = 256;
-static int routed_tile_rows(const Dims& D, int n_cu)
+static TilePlan routed_tile_plan(const Dims& D, int n_cu)
 {
     const int64_t entries = (int64_t)D.T * D.K, rows = entries / D.m;
     const bool few = std::min<int64_t>(entries, D.m) * ceil_div(D.F, 128) < n_cu;
-    const int bm = pick_tile_rows(rows, few);
-    if (few || tuning().force_bm || D.m <= 16 || D.d < 1024) return bm;
+    TilePlan p;
+    p.bm = pick_tile_rows(rows, few);
+    if (few || tuning().force_bm || D.m <= 16 || D.d < 1024) return p;
     const bool beside = D.Ns > 0 && D.Fs != D.F && D.T <= kBesideTokens;
-    if (bm == 64 && rows >= 12 && !beside) return 128;
-    if (bm == 32 && rows >= 4) return 64;
-    return bm;
+    if (p.bm == 64 && !beside) {
+        p.bm = 128;
+        p.lo = 64;
+    } else if (p.bm == 32 && rows >= 4) {
+        p.bm = 64;
+        p.lo = 32;
+    }
+    p.cols1 = ceil_div(D.F, 128); p.k1 = D.d / 64;
+    p.cols2 = ceil_div(D.d, 256) * D.ksplit; p.k2 = ceil_div(D.F / 64, D.ksplit);
+    p.n_cu = n_cu; p.inv_cu = (unsigned)((((uint64_t)1 << 32) + n_cu - 1) / n_cu);
+    return p;
 }
 
 // A launch of shared experts alone.  Up to kBesideTokens tokens of few enough 64-row blocks go to the narrow kernel, in one launch
@@ -555,7 +568,7 @@ moe_status moe_forward(const moe_config* cfg, const void* x, int32_t T, const vo
     jobs.n = split_shared ? 2 : 1;
     jobs.cap = D.tile_cap;
     jobs.job[0].u_lo = 0; jobs.job[0].u_hi = split_shared ? D.m + D.G : D.U;
-    jobs.job[0].plan.bm = routed_tile_rows(D, dev.n_cu);
+    jobs.job[0].plan = routed_tile_plan(D, dev.n_cu);
     jobs.job[0].table = at<int32_t>(workspace, W.tiles0);
     // a threshold of 1 browns nothing out (a route of the caller's may, whatever threshold comes with it)
     jobs.job[0].bm_hi = route || threshold < 1.0 ? taller_tile_rows(D, jobs.job[0].plan.bm, dev.n_cu) : 0;

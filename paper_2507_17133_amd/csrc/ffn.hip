@@ -21,8 +21,9 @@
 //                                  further blocks of the same launch take the tiles left over after the last
 //                                  full round: cut along K (fp32 partial tiles, summed by
 //                                  gemm_tail_sum_kernel) or in two along N
-//   128 rows  ffn_gemm_ws_kernel   four waves that load and four that multiply, persistent
+//   128 rows  ffn_gemm_ws_kernel   four waves that load and four that multiply, persistent; 64 where the table holds those
 //   64, 32    ffn_gemm_kernel      four waves, plain multi-stage ring (decode: weight streaming bound);
+//             ffn_gemm_either_kernel  the same for the one of the two heights that the table holds;
 //             ffn_gemm_narrow_kernel  a quarter of the columns per block, where that kernel would have too few blocks
 //             ffn_gemm_pair_kernel  the bodies of these two for two problems side by side (routed units, shared experts)
 #include "internal.h"
@@ -77,6 +78,7 @@ __global__ void __launch_bounds__(64) tile_table_kernel(const int32_t* __restric
 struct GemmArgs {
     const bf16_t* A; long lda; const int32_t* gather;
     const int32_t* table;
+    int lower;                                  // rows of the lower tiles that the launch takes as well (TilePlan::lo; 0: none)
     const bf16_t *wa0, *wa1, *wa2;              // per weight source (experts, united, shared); GEMM1: W1, GEMM2: W2
     const bf16_t *wb0, *wb1, *wb2;              // GEMM1: W3; GEMM2: unused
     int m, G;
@@ -112,7 +114,7 @@ struct Tile {
     const bf16_t *Wa, *Wb;
 };
 
-// M tiles of a launch with tiles of BM rows: none if the table was cut for the job's other height.
+// M tiles of a launch with tiles of BM rows: none if the table was cut for another height of the job.
 template <int BM>
 __device__ __forceinline__ int m_tiles(const GemmArgs& p)
 {
@@ -595,6 +597,30 @@ constexpr int small_stages() { return BM == 32 ? 4 : 3; }
 template <int BM>
 constexpr int narrow_stages() { return BM == 32 ? 6 : 5; }
 
+// The routed and united units' block: tiles of BM rows, or (k32or64) of the height that the table holds.
+constexpr int k32or64 = 96;
+template <int BM, bool NARROW, bool SWIGLU>
+__device__ __forceinline__ void routed_block(const GemmArgs& p, const int block)
+{
+    if constexpr (BM == k32or64) {
+        if (__builtin_amdgcn_readfirstlane(p.table[1]) == 64) routed_block<64, NARROW, SWIGLU>(p, block);
+        else routed_block<32, NARROW, SWIGLU>(p, block);
+    } else if constexpr (NARROW) {
+        narrow_block<BM, narrow_stages<BM>(), SWIGLU>(p, block);
+    } else {
+        small_block<BM, 256, 1, 4, 64, small_stages<BM>(), SWIGLU>(p, block);
+    }
+}
+
+// Tiles of BM or BM / 2 rows, as the table says: a launch for each height would cost a browned-out decode batch of 70 us two empty
+// ones of 4 us.
+template <int BM, bool NARROW, bool SWIGLU>
+__global__ void __launch_bounds__(256) ffn_gemm_either_kernel(GemmArgs p)
+{
+    static_assert(BM == 64, "32 or 64 rows");
+    routed_block<k32or64, NARROW, SWIGLU>(p, blockIdx.x);
+}
+
 // Shared experts of a width of their own (ps: the first n_s blocks) beside the routed and united units (pr) in one launch.  A launch
 // each left most CUs idle at the ends of both: the shared GEMM2 of 37 tokens of the 60-expert shape (K = 5632) is 64 blocks of 44 k
 // tiles, 15.7 us, the routed one 13.5 us of 256-column blocks with 11.  Layer forward of that shape in two launches per GEMM and in
@@ -604,8 +630,7 @@ __global__ void __launch_bounds__(256) ffn_gemm_pair_kernel(GemmArgs ps, GemmArg
 {
     const int b = blockIdx.x;
     if (b < n_s) narrow_block<BMS, narrow_stages<BMS>(), SWIGLU>(ps, b);
-    else if constexpr (NARROW) narrow_block<BMR, narrow_stages<BMR>(), SWIGLU>(pr, b - n_s);
-    else small_block<BMR, 256, 1, 4, 64, small_stages<BMR>(), SWIGLU>(pr, b - n_s);
+    else routed_block<BMR, NARROW, SWIGLU>(pr, b - n_s);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -805,16 +830,26 @@ __device__ __forceinline__ void ws_block(const GemmArgs& p, const int n_mt, cons
 
 // Tiles of 128 x 256 or, where those would leave CUs idle in fewer rounds, of 128 x 128: a round of the narrow ones pulls two
 // thirds of the bytes.  Only the table says how many rows there are, so the choice is the kernel's (one unit of 256 rows, K 14336
-// in four slices: 128 tiles 59 us, 256 narrow ones 44; 28672 x 4096: 224 tiles 70 us, 448 narrow ones 87).
+// in four slices: 128 tiles 59 us, 256 narrow ones 44; 28672 x 4096: 224 tiles 70 us, 448 narrow ones 87).  So is that of tiles of 64
+// rows, where the job offers them.
 template <bool SWIGLU>
 __global__ void __launch_bounds__(512) ffn_gemm_ws_kernel(GemmArgs p)
 {
-    const int n_mt = m_tiles<128>(p);
     const int wide = (p.N + (SWIGLU ? 127 : 255)) / (SWIGLU ? 128 : 256), narrow = (p.N + (SWIGLU ? 63 : 127)) / (SWIGLU ? 64 : 128);
-    const int G = gridDim.x, tw = n_mt * wide * p.ksplit, tn = n_mt * narrow * p.ksplit;
-    if (3 * ((tw + G - 1) / G) <= 2 * ((tn + G - 1) / G)) ws_block<128, 256, 2, 2, 3, SWIGLU>(p, n_mt, wide);
-    else if constexpr (SWIGLU) ws_block<128, 128, 4, 1, 4, SWIGLU>(p, n_mt, narrow);
-    else ws_block<128, 128, 2, 2, 4, SWIGLU>(p, n_mt, narrow);
+    // rounds of wide and of narrow tiles, weighed by the rows of A and of weights that a k tile of theirs brings in
+    auto wide_wins = [&](int n_mt, int bm) {
+        const int G = gridDim.x, tw = n_mt * wide * p.ksplit, tn = n_mt * narrow * p.ksplit;
+        return (bm + 256) * ((tw + G - 1) / G) <= (bm + 128) * ((tn + G - 1) / G);
+    };
+    if (const int n_mt = m_tiles<128>(p)) {
+        if (wide_wins(n_mt, 128)) ws_block<128, 256, 2, 2, 3, SWIGLU>(p, n_mt, wide);
+        else if constexpr (SWIGLU) ws_block<128, 128, 4, 1, 4, SWIGLU>(p, n_mt, narrow);
+        else ws_block<128, 128, 2, 2, 4, SWIGLU>(p, n_mt, narrow);
+    } else if (p.lower == 64) {
+        const int n_lo = m_tiles<64>(p);
+        if (SWIGLU || wide_wins(n_lo, 64)) ws_block<64, 256, 2, 2, 3, SWIGLU>(p, n_lo, wide);
+        else if constexpr (!SWIGLU) ws_block<64, 128, 2, 2, 5, SWIGLU>(p, n_lo, narrow);
+    }
 }
 
 // Tells the compiler that a pointer is the same in every lane (keeps it in scalar registers).
@@ -1421,8 +1456,28 @@ template <int BM, bool SWIGLU>
 constexpr auto small_kernel() { return ffn_gemm_kernel<BM, 256, 1, 4, 64, small_stages<BM>(), SWIGLU>; }
 template <int BM, bool SWIGLU>
 constexpr auto narrow_kernel() { return ffn_gemm_narrow_kernel<BM, narrow_stages<BM>(), SWIGLU>; }
+template <int BM, bool NARROW>
+constexpr int routed_lds()
+{
+    if constexpr (BM == k32or64) return std::max(routed_lds<32, NARROW>(), routed_lds<64, NARROW>());
+    else return NARROW ? narrow_lds<BM>() : small_lds<BM>();
+}
 template <int BMR, bool NARROW, int BMS>
-constexpr int pair_lds() { return std::max(NARROW ? narrow_lds<BMR>() : small_lds<BMR>(), narrow_lds<BMS>()); }
+constexpr int pair_lds() { return std::max(routed_lds<BMR, NARROW>(), narrow_lds<BMS>()); }
+
+// The pair kernel for (BMR, NARROW, BMS): its LDS attribute, or a launch.
+template <int BMR, bool NARROW, int BMS, bool SWIGLU>
+static hipError_t init_pair() { return set_lds(ffn_gemm_pair_kernel<BMR, NARROW, BMS, SWIGLU>, pair_lds<BMR, NARROW, BMS>()); }
+template <int BMR, bool NARROW, bool SWIGLU>
+static void launch_pair(const GemmArgs& a, const GemmArgs& r, bool s32, int n_s, int n, hipStream_t s)
+{
+    if constexpr (BMR != 64)
+        if (s32) {
+            ffn_gemm_pair_kernel<BMR, NARROW, 32, SWIGLU><<<n, 256, pair_lds<BMR, NARROW, 32>(), s>>>(a, r, n_s);
+            return;
+        }
+    ffn_gemm_pair_kernel<BMR, NARROW, 64, SWIGLU><<<n, 256, pair_lds<BMR, NARROW, 64>(), s>>>(a, r, n_s);
+}
 
 template <bool SWIGLU>
 static hipError_t init_gemms()
@@ -1432,12 +1487,13 @@ static hipError_t init_gemms()
     if ((e = set_lds(small_kernel<32, SWIGLU>(), small_lds<32>())) != hipSuccess) return e;
     if ((e = set_lds(narrow_kernel<64, SWIGLU>(), narrow_lds<64>())) != hipSuccess) return e;
     if ((e = set_lds(narrow_kernel<32, SWIGLU>(), narrow_lds<32>())) != hipSuccess) return e;
-    if ((e = set_lds(ffn_gemm_pair_kernel<32, false, 32, SWIGLU>, pair_lds<32, false, 32>())) != hipSuccess) return e;
-    if ((e = set_lds(ffn_gemm_pair_kernel<32, false, 64, SWIGLU>, pair_lds<32, false, 64>())) != hipSuccess) return e;
-    if ((e = set_lds(ffn_gemm_pair_kernel<64, false, 64, SWIGLU>, pair_lds<64, false, 64>())) != hipSuccess) return e;
-    if ((e = set_lds(ffn_gemm_pair_kernel<32, true, 32, SWIGLU>, pair_lds<32, true, 32>())) != hipSuccess) return e;
-    if ((e = set_lds(ffn_gemm_pair_kernel<32, true, 64, SWIGLU>, pair_lds<32, true, 64>())) != hipSuccess) return e;
-    if ((e = set_lds(ffn_gemm_pair_kernel<64, true, 64, SWIGLU>, pair_lds<64, true, 64>())) != hipSuccess) return e;
+    if ((e = set_lds(ffn_gemm_either_kernel<64, false, SWIGLU>, routed_lds<k32or64, false>())) != hipSuccess) return e;
+    if ((e = set_lds(ffn_gemm_either_kernel<64, true, SWIGLU>, routed_lds<k32or64, true>())) != hipSuccess) return e;
+    if ((e = init_pair<32, false, 32, SWIGLU>()) != hipSuccess || (e = init_pair<32, true, 32, SWIGLU>()) != hipSuccess) return e;
+    if ((e = init_pair<32, false, 64, SWIGLU>()) != hipSuccess || (e = init_pair<32, true, 64, SWIGLU>()) != hipSuccess) return e;
+    if ((e = init_pair<64, false, 64, SWIGLU>()) != hipSuccess || (e = init_pair<64, true, 64, SWIGLU>()) != hipSuccess) return e;
+    if ((e = init_pair<k32or64, false, 32, SWIGLU>()) != hipSuccess || (e = init_pair<k32or64, true, 32, SWIGLU>()) != hipSuccess) return e;
+    if ((e = init_pair<k32or64, false, 64, SWIGLU>()) != hipSuccess || (e = init_pair<k32or64, true, 64, SWIGLU>()) != hipSuccess) return e;
     if ((e = set_lds(ffn_gemm_ws_kernel<SWIGLU>, kWsLds)) != hipSuccess) return e;
     return set_lds(ffn_gemm_w4_kernel<SWIGLU>, kW4Lds);
 }
@@ -1449,7 +1505,7 @@ hipError_t init_ffn_kernels()
 }
 
 // One GEMM of one group of units: the kernel its tile height and its expected number of blocks ask for.
-enum GemmKind { kSmall32, kSmall64, kNarrow32, kNarrow64, kWs, kW4 };
+enum GemmKind { kSmall32, kSmall64, kSmallEither, kNarrow32, kNarrow64, kNarrowEither, kWs, kW4 };
 struct GemmLaunch {
     GemmArgs a;
     int max_mtiles;                              // M tiles there can be at most
@@ -1457,7 +1513,7 @@ struct GemmLaunch {
 };
 
 template <bool SWIGLU>
-constexpr int tile_columns(GemmKind k) { return (k == kNarrow32 || k == kNarrow64 ? 64 : 256) / (SWIGLU ? 2 : 1); }
+constexpr int tile_columns(GemmKind k) { return (k >= kNarrow32 && k <= kNarrowEither ? 64 : 256) / (SWIGLU ? 2 : 1); }
 
 // Blocks of the kernels that take a tile per block.
 static int tile_grid(const GemmArgs& a, int max_mtiles)
@@ -1476,6 +1532,8 @@ static hipError_t launch_gemm(const GemmLaunch& l, int n_cu, hipStream_t s)
         case kNarrow64: narrow_kernel<64, SWIGLU>()<<<grid, 256, narrow_lds<64>(), s>>>(a); break;
         case kSmall32: small_kernel<32, SWIGLU>()<<<grid, 256, small_lds<32>(), s>>>(a); break;
         case kSmall64: small_kernel<64, SWIGLU>()<<<grid, 256, small_lds<64>(), s>>>(a); break;
+        case kSmallEither: ffn_gemm_either_kernel<64, false, SWIGLU><<<grid, 256, routed_lds<k32or64, false>(), s>>>(a); break;
+        case kNarrowEither: ffn_gemm_either_kernel<64, true, SWIGLU><<<grid, 256, routed_lds<k32or64, true>(), s>>>(a); break;
         case kWs: {
             // persistent, one block per CU, a multiple of 8; its tiles are 128 columns (GEMM1: 64) at the narrowest
             const long total = (long)l.max_mtiles * ceil_div(a.N, SWIGLU ? 64 : 128) * a.ksplit;
@@ -1506,7 +1564,7 @@ static hipError_t launch_gemm(const GemmLaunch& l, int n_cu, hipStream_t s)
 // 256-row problems in one launch gain nothing: power sets their time).
 static bool pairable(GemmKind shared, GemmKind routed)
 {
-    return (shared == kNarrow64 && routed < kWs) || (shared == kNarrow32 && (routed == kSmall32 || routed == kNarrow32));
+    return routed < kWs && (shared == kNarrow64 || (shared == kNarrow32 && routed != kSmall64 && routed != kNarrow64));
 }
 
 template <bool SWIGLU>
@@ -1518,16 +1576,12 @@ static hipError_t launch_gemm_pair(const GemmLaunch& sh, const GemmLaunch& ro, h
     const int n_s = tile_grid(a, sh.max_mtiles), n = n_s + tile_grid(r, ro.max_mtiles);
     const bool s32 = sh.kind == kNarrow32;
     switch (ro.kind) {
-        case kSmall32:
-            if (s32) ffn_gemm_pair_kernel<32, false, 32, SWIGLU><<<n, 256, pair_lds<32, false, 32>(), s>>>(a, r, n_s);
-            else ffn_gemm_pair_kernel<32, false, 64, SWIGLU><<<n, 256, pair_lds<32, false, 64>(), s>>>(a, r, n_s);
-            break;
-        case kNarrow32:
-            if (s32) ffn_gemm_pair_kernel<32, true, 32, SWIGLU><<<n, 256, pair_lds<32, true, 32>(), s>>>(a, r, n_s);
-            else ffn_gemm_pair_kernel<32, true, 64, SWIGLU><<<n, 256, pair_lds<32, true, 64>(), s>>>(a, r, n_s);
-            break;
-        case kSmall64: ffn_gemm_pair_kernel<64, false, 64, SWIGLU><<<n, 256, pair_lds<64, false, 64>(), s>>>(a, r, n_s); break;
-        default: ffn_gemm_pair_kernel<64, true, 64, SWIGLU><<<n, 256, pair_lds<64, true, 64>(), s>>>(a, r, n_s); break;
+        case kSmall32: launch_pair<32, false, SWIGLU>(a, r, s32, n_s, n, s); break;
+        case kNarrow32: launch_pair<32, true, SWIGLU>(a, r, s32, n_s, n, s); break;
+        case kSmall64: launch_pair<64, false, SWIGLU>(a, r, s32, n_s, n, s); break;
+        case kNarrow64: launch_pair<64, true, SWIGLU>(a, r, s32, n_s, n, s); break;
+        case kSmallEither: launch_pair<k32or64, false, SWIGLU>(a, r, s32, n_s, n, s); break;
+        default: launch_pair<k32or64, true, SWIGLU>(a, r, s32, n_s, n, s); break;
     }
     return hipGetLastError();
 }
@@ -1546,11 +1600,11 @@ hipError_t launch_ffn(const Dims& D, const FfnProblem* problems, int n_problems,
     DeviceInfo dev;
     hipError_t e = ensure_device_init(&dev);
     if (e != hipSuccess) return e;
-    auto plan = [&](auto swiglu, const FfnProblem& P, int bm) {
+    auto plan = [&](auto swiglu, const FfnProblem& P, int bm, int lo) {
         constexpr bool SWIGLU = decltype(swiglu)::value;
         GemmLaunch l;
         GemmArgs& g = l.a;
-        g.table = P.table;
+        g.table = P.table; g.lower = lo;
         g.m = D.m; g.G = D.G;
         if (SWIGLU) {
             g.A = x; g.lda = D.d; g.gather = gather;
@@ -1572,25 +1626,28 @@ hipError_t launch_ffn(const Dims& D, const FfnProblem* problems, int n_problems,
         g.partial = partial; g.partial_cap = D.tail_blocks;
         // M tiles there can be at most: a unit that holds rows has one for every bm of them and a ragged one, and no more
         // units hold rows than there are rows
-        l.max_mtiles = (int)std::min<int64_t>(D.row_cap / bm + std::min<int64_t>(P.units.n, D.row_cap), D.tile_cap);
+        l.max_mtiles = (int)std::min<int64_t>(D.row_cap / (lo ? lo : bm) + std::min<int64_t>(P.units.n, D.row_cap), D.tile_cap);
         // M tiles to expect when no unit is browned out (united units take rows from the experts).  Chooses the kernel, the grid
         // is sized for max_mtiles: tiles of 64 or 32 rows whose 256-column blocks would not give every CU one go to the narrow
         // kernel.
         const long likely = (long)(P.units.entries / P.plan.bm + std::min<int64_t>(P.units.entries, D.m) +
                                    (int64_t)P.units.even * ceil_div(D.T, P.plan.bm));
         const bool narrow = likely * ceil_div(g.N, SWIGLU ? 128 : 256) * g.ksplit < dev.n_cu;
-        l.kind = bm == 256 ? kW4 : bm == 128 ? kWs : bm == 64 ? (narrow ? kNarrow64 : kSmall64) : narrow ? kNarrow32 : kSmall32;
+        if (bm >= 128) l.kind = bm == 256 ? kW4 : kWs;
+        else if (lo) l.kind = narrow ? kNarrowEither : kSmallEither;
+        else if (bm == 64) l.kind = narrow ? kNarrow64 : kSmall64;
+        else l.kind = narrow ? kNarrow32 : kSmall32;
         return l;
     };
-    // Both heights where the table kernel chooses between two: the launch of the height it did not take returns at once.
+    // A launch for bm_hi as well where the table may hold tiles of that height: the one that has none returns at once.
     auto gemm = [&](auto swiglu) -> hipError_t {
         constexpr bool SWIGLU = decltype(swiglu)::value;
         ProfScope ps(SWIGLU ? MOE_STAGE_GEMM1 : MOE_STAGE_GEMM2, s);
         GemmLaunch todo[4];
         int n = 0;
         for (int j = 0; j < n_problems; ++j) {
-            todo[n++] = plan(swiglu, problems[j], problems[j].plan.bm);
-            if (problems[j].bm_hi > 0) todo[n++] = plan(swiglu, problems[j], problems[j].bm_hi);
+            todo[n++] = plan(swiglu, problems[j], problems[j].plan.bm, problems[j].plan.lo);
+            if (problems[j].bm_hi > 0) todo[n++] = plan(swiglu, problems[j], problems[j].bm_hi, 0);
         }
         int paired = -1;                          // the routed launch that takes the shared experts (the last one) along
         if (n_problems == 2)

@@ -39,10 +39,14 @@ hipError_t ensure_device_init(DeviceInfo* info);
 hipError_t init_ffn_kernels();      // ffn.hip
 hipError_t init_route_kernels();    // route.hip
 
-// How the rows of the units are cut into GEMM M tiles: one tile height for every unit of a launch, decided on
-// the host from the expected rows per unit (the real counts stay on the device).
+// How the rows of the units are cut into GEMM M tiles: one tile height for every unit of a launch, from the expected rows per
+// unit on the host, or one of two from the real counts on the device (tiles.h), both taken by the same launch.
 struct TilePlan {
-    int bm;      // 256, 128, 64 or 32
+    int bm;          // 256, 128, 64 or 32
+    int lo = 0;      // 64 (with bm 128) or 32 (64): the height that the table takes unless the taller one saves rounds; 0: none
+    int cols1 = 0, cols2 = 0, k1 = 0, k2 = 0;     // with lo: blocks per M tile and k tiles per block of the two GEMMs
+    int n_cu = 0;                                 // and the CUs, with 2^32 / n_cu rounded up
+    unsigned inv_cu = 0;
 };
 TilePlan make_tile_plan(int64_t rows_per_unit, bool even);     // even: exactly that many in every unit, else their mean
 
@@ -109,7 +113,7 @@ struct FfnWeights { const bf16_t *w1, *w3, *w2; };
 // all T tokens each (shared experts; units on calibration tokens).
 struct FfnUnits { int n; int64_t entries; int even; };
 // Units of one width: how their rows are cut into M tiles, and the tile table, which the routing kernels or
-// launch_tile_tables have written; bm_hi: the other height of a job that leaves the choice to them (0: none).
+// launch_tile_tables have written; bm_hi: a height that has a launch of its own (TileJob::bm_hi).
 struct FfnProblem { FfnUnits units; int F; TilePlan plan; int bm_hi; int32_t* table; };
 // Runs W2(silu(W1 x)*(W3 x)) for the rows of the tiles in the tables of one problem, or of the routed and united units and then the
 // shared experts; writes Y[row][d] = FFN(x[gather ? gather[row] : row]) (the row weights are applied by the combine).  Weight

@@ -961,19 +961,6 @@ __device__ __forceinline__ void lds_sync()
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
-// Inclusive sum over the lanes of a wavefront: four shifts inside the rows of 16 lanes, then the rows' last lanes passed on (cross-lane
-// reads through the LDS crossbar take some 100 cycles a step).
-__device__ __forceinline__ int wave_scan(int v)
-{
-    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false);       // row_shr:1
-    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false);       // row_shr:2
-    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false);       // row_shr:4
-    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false);       // row_shr:8
-    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false);       // row_bcast:15 into rows 1 and 3
-    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false);       // row_bcast:31 into rows 2 and 3
-    return v;
-}
-
 // Algorithm 1 as in brownout_decide, in 1024 threads, four neighbouring lanes per expert.  What bounds it is the issue of m^2
 // comparisons on one CU: a wave's 16 experts lie in step `wave` of its walk over the counts, so in all other steps the order
 // "count descending, id ascending" is one comparison with c or c - 1.  grp_s: zero; *any_s is set where a unit is united.
