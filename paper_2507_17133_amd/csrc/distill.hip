@@ -391,11 +391,13 @@ __global__ void __launch_bounds__(256, 2) distill_gemm_kernel(DGemm p)
             fetch(0, have);
 #pragma unroll
             for (int rg = 0; rg < 2; ++rg) {
+                if (rg > 0) wave_lds_order();
 #pragma unroll
                 for (int i = 0; i < 2; ++i)
 #pragma unroll
                     for (int j = 0; j < 4; ++j)
                         *reinterpret_cast<f32x4*>(own + (i * 16 + (lane & 15)) * kAdamRow + (j * 16 + c4) * 4) = acc[rg * 2 + i][j];
+                wave_lds_order();
 #pragma unroll
                 for (int ps = 0; ps < 2; ++ps) {
                     if (rg * 32 + ps * 16 + 16 < 64) fetch(rg * 32 + ps * 16 + 16, next);
@@ -434,6 +436,7 @@ __global__ void __launch_bounds__(256, 2) distill_gemm_kernel(DGemm p)
             if (p.first) update(std::true_type{});
             else update(std::false_type{});
             if (J.r[4].p) {
+                wave_lds_order();
                 unsigned short* out = J.r[4].at<unsigned short>(g) + (size_t)(n0 + wn * 64) * J.M + m0 + wm * 64;
 #pragma unroll
                 for (int q = 0; q < 8; ++q) {

@@ -223,6 +223,7 @@ __device__ __forceinline__ void store_tile_lines(const GemmArgs& p, const Tile& 
                                    pack_f16(acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]));
         }
     }
+    wave_lds_order();
     constexpr int LPR = ROWB / 16;                              // lanes per row on the way out: 8 or 4
     constexpr int RPI = 64 / LPR;                               // rows per store instruction: 8 or 16
     const int k = lane % LPR, rr = lane / LPR;

@@ -96,6 +96,16 @@ struct ProfScope {
     ~ProfScope() { prof_end(stage, s); }
 };
 
+// Between what the lanes of a wave write to LDS and what others of its lanes read there: an order for the compiler, which knows one
+// lane's accesses only and may move a load above stores of another type.  The hardware carries out a wave's LDS operations in
+// order, so no instruction comes of it.
+__device__ __forceinline__ void wave_lds_order()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // ---- routing (route.hip) ----
 struct TileJobs;
 // gate: fp32 [m][d] (D.gate_format MOE_GATE_FP32; split into gate_split on the way) or the packed pieces
