@@ -122,6 +122,29 @@ __device__ __forceinline__ int m_tiles(const GemmArgs& p)
     return head.y == BM ? head.x : 0;
 }
 
+// Tile L of the launch's tile order -> its row tile and column tile.  Super-tiles of group_m M tiles x all N tiles, M fastest: the
+// ~32 blocks an XCD runs at a time cover group_m x (32/group_m) tiles and share their A and B panels in that XCD's L2.
+__device__ __forceinline__ void tile_coords(const GemmArgs& p, int n_mt, int n_ntiles, int L, int& mt, int& nt)
+{
+    const int gspan = p.group_m * n_ntiles;
+    const int gi = L / gspan, rem = L - gi * gspan;
+    const int mt_first = gi * p.group_m;
+    const int gsz = min(p.group_m, n_mt - mt_first);
+    nt = rem / gsz;
+    mt = mt_first + (rem - nt * gsz);
+}
+
+// Weights of the tile's unit.
+template <bool SWIGLU>
+__device__ __forceinline__ void set_weights(const GemmArgs& p, Tile& t)
+{
+    const int src = t.unit < p.m ? 0 : (t.unit < p.m + p.G ? 1 : 2);
+    const int widx = t.unit - (src == 0 ? 0 : (src == 1 ? p.m : p.m + p.G));
+    const size_t wsz = (size_t)p.N * p.K;
+    t.Wa = (src == 0 ? p.wa0 : (src == 1 ? p.wa1 : p.wa2)) + (size_t)widx * wsz;
+    t.Wb = SWIGLU ? (src == 0 ? p.wb0 : (src == 1 ? p.wb1 : p.wb2)) + (size_t)widx * wsz : nullptr;
+}
+
 template <int BM, int BNC, bool SWIGLU>
 __device__ __forceinline__ bool decode_tile(const GemmArgs& p, int block, Tile& t)
 {
@@ -137,22 +160,11 @@ __device__ __forceinline__ bool decode_tile(const GemmArgs& p, int block, Tile& 
     t.ks = p.ksplit;
     t.part = -1;
     t.half = 0;
-    const int L = Lfull - t.kslice * tiles;
-    // Super-tiles of group_m M tiles x all N tiles, M fastest: the ~32 blocks an XCD runs at a time
-    // cover group_m x (32/group_m) tiles and share their A and B panels in that XCD's L2.
-    const int gspan = p.group_m * p.n_ntiles;
-    const int gi = L / gspan, rem = L - gi * gspan;
-    const int mt_first = gi * p.group_m;
-    const int gsz = min(p.group_m, n_mt - mt_first);
-    t.nt = rem / gsz;
-    const int mt = mt_first + (rem - t.nt * gsz);
+    int mt;
+    tile_coords(p, n_mt, p.n_ntiles, Lfull - t.kslice * tiles, mt, t.nt);
     const int4 te = reinterpret_cast<const int4*>(p.table + 4)[mt];
     t.unit = te.x; t.row0 = te.y; t.nrows = te.z;
-    const int src = t.unit < p.m ? 0 : (t.unit < p.m + p.G ? 1 : 2);
-    const int widx = t.unit - (src == 0 ? 0 : (src == 1 ? p.m : p.m + p.G));
-    const size_t wsz = (size_t)p.N * p.K;
-    t.Wa = (src == 0 ? p.wa0 : (src == 1 ? p.wa1 : p.wa2)) + (size_t)widx * wsz;
-    t.Wb = SWIGLU ? (src == 0 ? p.wb0 : (src == 1 ? p.wb1 : p.wb2)) + (size_t)widx * wsz : nullptr;
+    set_weights<SWIGLU>(p, t);
     t.n0 = t.nt * BNC;
     return true;
 }
@@ -658,21 +670,12 @@ __device__ __forceinline__ void tile_at(const GemmArgs& p, int n_mt, int n_ntile
     t.ks = p.ksplit;
     t.part = -1;
     t.half = 0;
-    L -= t.kslice * tiles;
-    const int gspan = p.group_m * n_ntiles;
-    const int gi = L / gspan, rem = L - gi * gspan;
-    const int mt_first = gi * p.group_m;
-    const int gsz = min(p.group_m, n_mt - mt_first);
-    t.nt = rem / gsz;
-    const int mt = __builtin_amdgcn_readfirstlane(mt_first + (rem - t.nt * gsz));
+    int mt;
+    tile_coords(p, n_mt, n_ntiles, L - t.kslice * tiles, mt, t.nt);
     typedef const __attribute__((address_space(4))) int* scalar_ptr;
-    const scalar_ptr te = (scalar_ptr)(unsigned long)(p.table + 4 + 4 * mt);
+    const scalar_ptr te = (scalar_ptr)(unsigned long)(p.table + 4 + 4 * __builtin_amdgcn_readfirstlane(mt));
     t.unit = te[0]; t.row0 = te[1]; t.nrows = te[2];
-    const int src = t.unit < p.m ? 0 : (t.unit < p.m + p.G ? 1 : 2);
-    const int widx = t.unit - (src == 0 ? 0 : (src == 1 ? p.m : p.m + p.G));
-    const size_t wsz = (size_t)p.N * p.K;
-    t.Wa = (src == 0 ? p.wa0 : (src == 1 ? p.wa1 : p.wa2)) + (size_t)widx * wsz;
-    t.Wb = SWIGLU ? (src == 0 ? p.wb0 : (src == 1 ? p.wb1 : p.wb2)) + (size_t)widx * wsz : nullptr;
+    set_weights<SWIGLU>(p, t);
     t.n0 = t.nt * bnc;
 }
 
@@ -897,18 +900,6 @@ __host__ __device__ inline int tail_split(int G, int rem, int nk_all)
     return (nk_all + 5) * (sl - 1) > sl * (rem * sl / 8 + 7) ? sl : 1;
 }
 
-// Tile L of the launch's tile order -> its row tile and column tile: super-tiles of group_m M tiles x all N
-// tiles, M fastest.
-__device__ __forceinline__ void tile_coords(const GemmArgs& p, int n_mt, int L, int& mt, int& nt)
-{
-    const int gspan = p.group_m * p.n_ntiles;
-    const int gi = L / gspan, rem = L - gi * gspan;
-    const int mt_first = gi * p.group_m;
-    const int gsz = min(p.group_m, n_mt - mt_first);
-    nt = rem / gsz;
-    mt = mt_first + (rem - nt * gsz);
-}
-
 // Left-over tiles that are not cut along K: when there are at most G/2 of them, each is cut in two along N
 // instead (two blocks, 256 rows x half the columns each: no partial sums, half a tile time).
 __host__ __device__ inline bool tail_halves(int G, int rem, int nk_all)
@@ -994,7 +985,7 @@ __device__ __forceinline__ bool decode_tile_at(const GemmArgs& p, const Sched& s
         }
     }
     int mt;
-    tile_coords(p, n_mt, L, mt, t.nt);
+    tile_coords(p, n_mt, p.n_ntiles, L, mt, t.nt);
     const int4 te = reinterpret_cast<const int4*>(p.table + 4)[mt];
     t.unit = te.x; t.row0 = te.y; t.nrows = te.z;
     const int src = t.unit < p.m ? 0 : (t.unit < p.m + p.G ? 1 : 2);
@@ -1038,7 +1029,7 @@ __global__ void __launch_bounds__(256) gemm_tail_sum_kernel(GemmArgs p, int G)
     for (int item = blockIdx.x; item < rem * 64; item += gridDim.x) {
         const int j = item >> 6, strip = item & 63;
         int mt, nt;
-        tile_coords(p, n_mt, t_full + j, mt, nt);
+        tile_coords(p, n_mt, p.n_ntiles, t_full + j, mt, nt);
         const int4 te = reinterpret_cast<const int4*>(p.table + 4)[mt];
         const int row0 = te.y, nrows = te.z;
         const int r = strip * 4 + (threadIdx.x >> 6);

@@ -63,8 +63,8 @@ struct GateArgs {
     const bf16_t* x; const unsigned short* split; const float* bias;
     int T, d, m, m_pad, K, score_fn;
     int32_t* topk_idx; float* topk_w; uint8_t* near_tie;
-    int32_t* expert_cnt;   // the batch's expert counts (atomics on cleared counters); null for small batches, whose
-                           // routing block counts the experts itself
+    int32_t* expert_cnt;   // the batch's expert counts (atomics on cleared counters); null where the row kernel counts the
+                           // experts itself
     int n_slice;           // 17 experts and more: slices of K, each leaving fp64 partial logits
     void* logits;          // one slice: [T][m_pad] fp32, bias added; else [n_slice][T][m_pad] fp64
     int32_t* clear_cnt;    // expert counters the logit kernel clears for the TopK launch behind it (or null)
@@ -161,20 +161,26 @@ __device__ __forceinline__ void topk_token(const GateArgs& p, const float (&v)[4
     if (lane == 0 && p.near_tie != nullptr) p.near_tie[t] = any_close != 0ull ? 1 : 0;
 }
 
-// Weights and outputs of four tokens, a row of 16 lanes each: lane j of a row holds the key and the id of the j-th winner.
-template <typename Put>
+// Weights and outputs of four tokens, a row of 16 lanes each: lane j of a row holds the key and the id of the j-th winner.  LIKE_TOKEN:
+// the weights are added up in topk_token's order.
+template <bool LIKE_TOKEN, typename Put>
 __device__ __forceinline__ void weights_rows(const GateArgs& p, int my_k, int my_i, int t, bool valid, int lane, Put put)
 {
     const int K = p.K, r = lane & 15, n_pick = K < p.m ? K + 1 : K;
     const float my_v = key_value(my_k);
-    const float top = __shfl(my_v, lane & ~15);
+    const float top = dpp_f<0x150>(my_v);                   // row_newbcast: lane 0 of the row
     float num = 0.0f;
     if (r < K) num = p.score_fn == 0 ? expf(my_v - top) : 1.0f / (1.0f + expf(-my_v));
     float den = num;
-    den += dpp_f<0x121>(den);
-    den += dpp_f<0x122>(den);
-    den += dpp_f<0x124>(den);
-    den += dpp_f<0x128>(den);
+    if constexpr (LIKE_TOKEN) {
+#pragma unroll
+        for (int off = 8; off >= 1; off >>= 1) den += __shfl_xor(den, off);
+    } else {
+        den += dpp_f<0x121>(den);
+        den += dpp_f<0x122>(den);
+        den += dpp_f<0x124>(den);
+        den += dpp_f<0x128>(den);
+    }
     const float nxt = __shfl(my_v, (lane & ~15) | ((r + 1) & 15));
     const bool close = r + 1 < n_pick && (my_v - nxt) < 1e-6f;
     const unsigned long long any_close = __ballot(close);
@@ -221,7 +227,7 @@ __device__ __forceinline__ void topk_rows(const GateArgs& p, const float (&v)[NC
         for (int c = 0; c < NC; ++c) k[c] = c == wc ? kNone : k[c];
         if (r == j) { my_k = mx; my_i = id; }
     }
-    weights_rows(p, my_k, my_i, t, valid, lane, put);
+    weights_rows<false>(p, my_k, my_i, t, valid, lane, put);
 }
 
 // The same for at most 16 experts, lane r of the row holding expert r, with topk_token's winners and weights: an expert already
@@ -242,25 +248,7 @@ __device__ __forceinline__ void topk_few(const GateArgs& p, float v, int t, bool
         if (id == r) k = kTaken;
         if (r == j) { my_k = mx; my_i = id; }
     }
-    const float my_v = key_value(my_k);
-    const float top = dpp_f<0x150>(my_v);                   // row_newbcast: lane 0 of the row
-    float num = 0.0f;
-    if (r < K) num = p.score_fn == 0 ? expf(my_v - top) : 1.0f / (1.0f + expf(-my_v));
-    float den = num;
-#pragma unroll
-    for (int off = 8; off >= 1; off >>= 1) den += __shfl_xor(den, off);
-    const float nxt = __shfl(my_v, (lane & ~15) | ((r + 1) & 15));
-    const bool close = r + 1 < n_pick && (my_v - nxt) < 1e-6f;
-    const unsigned long long any_close = __ballot(close);
-    if (valid) {
-        if (r < K) {
-            const float w = num / den;
-            p.topk_idx[(size_t)t * K + r] = my_i;
-            p.topk_w[(size_t)t * K + r] = w;
-            put(r, my_i, w);
-        }
-        if (r == 0 && p.near_tie != nullptr) p.near_tie[t] = ((any_close >> (lane & 48)) & 0xFFFFull) != 0ull ? 1 : 0;
-    }
+    weights_rows<true>(p, my_k, my_i, t, valid, lane, put);
 }
 
 // gate for at most 16 experts in batches beyond kFewExpertsTokens tokens: one block = 16 tokens x the one tile of
@@ -375,10 +363,8 @@ __global__ void __launch_bounds__(256) gate_small_kernel(GateArgs p, const float
     constexpr int NP = TPB * M;                           // (token, expert) pairs of the block
     __shared__ double part[NP][33];
     __shared__ float logit[TPB][16];
-    __shared__ int hist[16];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int t0 = blockIdx.x * TPB;
-    if (tid < 16) hist[tid] = 0;
     double acc[TPB][M];
 #pragma unroll
     for (int q = 0; q < TPB; ++q)
@@ -445,14 +431,8 @@ __global__ void __launch_bounds__(256) gate_small_kernel(GateArgs p, const float
     }
     if (p.logits != nullptr) return;                      // TopK is the routing block's
     __syncthreads();
-    if (wave < TPB && t0 + wave < p.T) {
-        topk_few(p, (lane & 15) < p.m ? logit[wave][lane & 15] : 0.0f, t0 + wave, lane < 16, lane,
-                 [&](int, int e, float) { atomicAdd(&hist[e], 1); });
-    }
-    if (p.expert_cnt != nullptr) {                        // large batches: the launch's counts (cleared beforehand)
-        __syncthreads();
-        if (tid < p.m && hist[tid] > 0) atomicAdd(&p.expert_cnt[tid], hist[tid]);
-    }
+    if (wave < TPB && t0 + wave < p.T)                    // the row kernel counts the experts, from the lists
+        topk_few(p, (lane & 15) < p.m ? logit[wave][lane & 15] : 0.0f, t0 + wave, lane < 16, lane, [](int, int, float) {});
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -657,64 +637,6 @@ __global__ void __launch_bounds__(THREADS) gate_topk_kernel(GateArgs p)
     flush_winners<THREADS>(p, hist, tid);
 }
 
-// ------------------------------------------------------------------------------------------------
-// Algorithm 1 on the expert counts, PARTS threads per expert (m <= 256); the sum of the counts into *sum_s, if given.  Sorting is implicit: expert j
-// precedes expert i in the order "count descending, id ascending" iff cnt_j > cnt_i or (equal and
-// j < i); P_i = tokens covered before i is the sum of the counts of those j.
-// ------------------------------------------------------------------------------------------------
-template <int PARTS>
-__device__ __forceinline__ void brownout_decide(const int* cnt_s, unsigned char* s2_s, int* unit_s, int* sum_s, int m, int way,
-                                                double threshold, int full, int tid, bool write,
-                                                int32_t* expert_unit, uint8_t* expert_in_s1)
-{
-    // cnt_s: 16-byte aligned, zero from m up to kMaxExperts (a count of 0 adds nothing to P or S).  Four counts per
-    // LDS read, and sums in 32 bits (the counts add up to T K <= 2^30): the loop is bound by the latency of its
-    // reads, so a block of 1024 threads gives each expert four neighbouring lanes that read a quarter each.
-    const int ex = tid / PARTS, part = tid % PARTS;
-    bool in_s1 = false;
-    if (ex < m) {
-        const int c = cnt_s[ex];
-        int P = 0, S = 0;
-        const int4* c4 = reinterpret_cast<const int4*>(cnt_s);
-        const int n4 = ((m + 3) >> 2) + PARTS - 1;
-#pragma unroll 8
-        for (int q = part; q < n4 / PARTS * PARTS; q += PARTS) {
-            const int4 v = c4[q];
-            const int j = 4 * q;
-            S += (v.x + v.y) + (v.z + v.w);
-            P += (v.x > c || (v.x == c && j < ex)) ? v.x : 0;
-            P += (v.y > c || (v.y == c && j + 1 < ex)) ? v.y : 0;
-            P += (v.z > c || (v.z == c && j + 2 < ex)) ? v.z : 0;
-            P += (v.w > c || (v.w == c && j + 3 < ex)) ? v.w : 0;
-        }
-#pragma unroll
-        for (int o = 1; o < PARTS; o <<= 1) {       // lanes of one expert are all here (PARTS divides 64)
-            S += __shfl_xor(S, o);
-            P += __shfl_xor(P, o);
-        }
-        in_s1 = (double)P < (double)S * threshold;
-        if (part == 0) s2_s[ex] = (!in_s1 && c > 0) ? 1 : 0;
-        if (sum_s != nullptr && tid == 0) *sum_s = S;
-    }
-    __syncthreads();
-    if (ex < m && part == 0) {
-        const int g = ex / way, lo = g * way, hi = min(m, lo + way);
-        int members = 0;
-        for (int i = lo; i < hi; ++i) members += s2_s[i];
-        int unit = ex;
-        if (s2_s[ex]) {
-            if (full) unit = -1;
-            else if (members >= 2) unit = m + g;
-        }
-        unit_s[ex] = unit;
-        if (write) {
-            if (expert_unit) expert_unit[ex] = unit;
-            if (expert_in_s1) expert_in_s1[ex] = in_s1 ? 1 : 0;
-        }
-    }
-    __syncthreads();
-}
-
 struct RowArgs {
     const int32_t* topk_idx; const float* topk_w; const int32_t* expert_cnt;
     int32_t* expert_unit; uint8_t* expert_in_s1;
@@ -816,12 +738,85 @@ __device__ __forceinline__ void scatter_shared(const RowArgs& p, const int* off_
     }
 }
 
+// Workgroup barrier for what goes through LDS: the stores and loads of a wave to memory stay in flight across it (waiting for
+// the outputs of every step cost the rows kernel about 1 us a barrier).
+__device__ __forceinline__ void lds_sync()
+{
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+}
+
+// Algorithm 1 on the expert counts, in 1024 threads, four neighbouring lanes per expert (m <= 256).  Sorting is implicit: expert j precedes
+// expert i in the order "count descending, id ascending" iff cnt_j > cnt_i or (equal and j < i); P_i = tokens covered before i is the
+// sum of the counts of those j.  Sums in 32 bits (the counts add up to T K <= 2^30); cnt_s is 16-byte aligned and zero from m up to
+// kMaxExperts.  What bounds it is the issue of m^2 comparisons on one CU: a wave's 16 experts lie in step `wave` of its walk over the counts, so in all other steps the order
+// "count descending, id ascending" is one comparison with c or c - 1.  grp_s: zero; *any_s is set where a unit is united.
+__device__ __forceinline__ void decide_rows(const int* cnt_s, int* unit_s, int* grp_s, int* sum_s, int* any_s, const RowArgs& p,
+                                            int tid, bool write)
+{
+    const int ex = tid >> 2, part = tid & 3;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    bool in_s1 = false, s2 = false;
+    int gr = 0;
+    if (p.threshold == 1.0) {
+        // P < S but for experts without tokens: nobody is browned out.  The sum of the counts, for the caller
+        if (ex < p.m) in_s1 = cnt_s[ex] > 0;
+        if (wave == 15) {
+            const int4 v = reinterpret_cast<const int4*>(cnt_s)[tid & 63];
+            const int S = wave_scan((v.x + v.y) + (v.z + v.w));
+            if ((tid & 63) == 63) *sum_s = S;
+        }
+    } else if (ex < p.m) {
+        const int c = cnt_s[ex];
+        int P = 0, S = 0;
+        const int4* c4 = reinterpret_cast<const int4*>(cnt_s) + part;
+        const int steps = (p.m + 15) >> 4;                  // (counts past m are zero)
+        gr = ex / p.way;
+        auto add = [&](int it, int th) {
+            const int4 v = c4[4 * it];
+            S += (v.x + v.y) + (v.z + v.w);
+            P += (v.x > th ? v.x : 0) + (v.y > th ? v.y : 0);
+            P += (v.z > th ? v.z : 0) + (v.w > th ? v.w : 0);
+        };
+#pragma unroll 4
+        for (int it = 0; it < wave; ++it) add(it, c - 1);
+        {
+            const int4 v = c4[4 * wave];
+            const int j = 16 * wave + 4 * part;
+            S += (v.x + v.y) + (v.z + v.w);
+            P += v.x > c - (j < ex) ? v.x : 0;
+            P += v.y > c - (j + 1 < ex) ? v.y : 0;
+            P += v.z > c - (j + 2 < ex) ? v.z : 0;
+            P += v.w > c - (j + 3 < ex) ? v.w : 0;
+        }
+#pragma unroll 4
+        for (int it = wave + 1; it < steps; ++it) add(it, c);
+        S += dpp_i<0xB1>(S);                                // quad_perm: lanes l ^ 1, then l ^ 2
+        P += dpp_i<0xB1>(P);
+        S += dpp_i<0x4E>(S);
+        P += dpp_i<0x4E>(P);
+        in_s1 = (double)P < (double)S * p.threshold;
+        s2 = !in_s1 && c > 0;
+        if (part == 0 && s2) atomicAdd(&grp_s[gr], 1);
+        if (tid == 0) *sum_s = S;
+    }
+    lds_sync();
+    if (ex < p.m && part == 0) {
+        const int unit = !s2 ? ex : p.full ? -1 : grp_s[gr] >= 2 ? p.m + gr : ex;
+        unit_s[ex] = unit;
+        if (unit >= p.m) *any_s = 1;
+        if (write) {
+            if (p.expert_unit) p.expert_unit[ex] = unit;
+            if (p.expert_in_s1) p.expert_in_s1[ex] = in_s1 ? 1 : 0;
+        }
+    }
+    lds_sync();
+}
+
 // One segment (64 tokens) per block: which tokens have a row in unit u, as one bit per token, and how many.
 __global__ void __launch_bounds__(1024) route_count_kernel(RowArgs p)
 {
     __shared__ __attribute__((aligned(16))) int cnt_s[kMaxExperts];
-    __shared__ int unit_s[kMaxExperts];
-    __shared__ unsigned char s2_s[kMaxExperts];
+    __shared__ int unit_s[kMaxExperts], grp_s[kMaxExperts], sum_s, any_s;
     __shared__ unsigned long long bm[kMaxUnits];
     const int tid = threadIdx.x, seg = blockIdx.x;
     const int t0 = seg * kSegTokens, t1 = min(p.T, t0 + kSegTokens);
@@ -829,11 +824,13 @@ __global__ void __launch_bounds__(1024) route_count_kernel(RowArgs p)
     int ex[NE];
     float w[NE];
     load_entries<1024, false>(p, t0, t1, tid, ex, w);       // on their way while Algorithm 1 runs
-    if (tid < kMaxExperts) cnt_s[tid] = tid < p.m ? p.expert_cnt[tid] : 0;
+    if (tid < kMaxExperts) {
+        cnt_s[tid] = tid < p.m ? p.expert_cnt[tid] : 0;
+        grp_s[tid] = 0;
+    }
     for (int i = tid; i < p.U; i += 1024) bm[i] = 0ull;
     __syncthreads();
-    brownout_decide<4>(cnt_s, s2_s, unit_s, nullptr, p.m, p.way, p.threshold, p.full, tid, seg == 0, p.expert_unit,
-                       p.expert_in_s1);
+    decide_rows(cnt_s, unit_s, grp_s, &sum_s, &any_s, p, tid, seg == 0);
 #pragma unroll
     for (int q = 0; q < NE; ++q) {
         const int u = ex[q] >= 0 ? unit_s[ex[q]] : -1;
@@ -952,78 +949,6 @@ __global__ void __launch_bounds__(256) route_scatter_kernel(RowArgs p)
     if (repeated) repeated_s = 1;
     __syncthreads();
     if (repeated_s) rewrite_repeated<256>(p, unit_s, t0, t1, tid);
-}
-
-// Workgroup barrier for what goes through LDS: the stores and loads of a wave to memory stay in flight across it (waiting for
-// the outputs of every step cost the rows kernel about 1 us a barrier).
-__device__ __forceinline__ void lds_sync()
-{
-    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-}
-
-// Algorithm 1 as in brownout_decide, in 1024 threads, four neighbouring lanes per expert.  What bounds it is the issue of m^2
-// comparisons on one CU: a wave's 16 experts lie in step `wave` of its walk over the counts, so in all other steps the order
-// "count descending, id ascending" is one comparison with c or c - 1.  grp_s: zero; *any_s is set where a unit is united.
-__device__ __forceinline__ void decide_rows(const int* cnt_s, int* unit_s, int* grp_s, int* sum_s, int* any_s, const RowArgs& p,
-                                            int tid, bool write)
-{
-    const int ex = tid >> 2, part = tid & 3;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    bool in_s1 = false, s2 = false;
-    int gr = 0;
-    if (p.threshold == 1.0) {
-        // P < S but for experts without tokens: nobody is browned out.  The sum of the counts, for the caller
-        if (ex < p.m) in_s1 = cnt_s[ex] > 0;
-        if (wave == 15) {
-            const int4 v = reinterpret_cast<const int4*>(cnt_s)[tid & 63];
-            const int S = wave_scan((v.x + v.y) + (v.z + v.w));
-            if ((tid & 63) == 63) *sum_s = S;
-        }
-    } else if (ex < p.m) {
-        const int c = cnt_s[ex];
-        int P = 0, S = 0;
-        const int4* c4 = reinterpret_cast<const int4*>(cnt_s) + part;
-        const int steps = (p.m + 15) >> 4;                  // (counts past m are zero)
-        gr = ex / p.way;
-        auto add = [&](int it, int th) {
-            const int4 v = c4[4 * it];
-            S += (v.x + v.y) + (v.z + v.w);
-            P += (v.x > th ? v.x : 0) + (v.y > th ? v.y : 0);
-            P += (v.z > th ? v.z : 0) + (v.w > th ? v.w : 0);
-        };
-#pragma unroll 4
-        for (int it = 0; it < wave; ++it) add(it, c - 1);
-        {
-            const int4 v = c4[4 * wave];
-            const int j = 16 * wave + 4 * part;
-            S += (v.x + v.y) + (v.z + v.w);
-            P += v.x > c - (j < ex) ? v.x : 0;
-            P += v.y > c - (j + 1 < ex) ? v.y : 0;
-            P += v.z > c - (j + 2 < ex) ? v.z : 0;
-            P += v.w > c - (j + 3 < ex) ? v.w : 0;
-        }
-#pragma unroll 4
-        for (int it = wave + 1; it < steps; ++it) add(it, c);
-        S += dpp_i<0xB1>(S);                                // quad_perm: lanes l ^ 1, then l ^ 2
-        P += dpp_i<0xB1>(P);
-        S += dpp_i<0x4E>(S);
-        P += dpp_i<0x4E>(P);
-        in_s1 = (double)P < (double)S * p.threshold;
-        s2 = !in_s1 && c > 0;
-        if (part == 0 && s2) atomicAdd(&grp_s[gr], 1);
-        if (tid == 0) *sum_s = S;
-    }
-    lds_sync();
-    if (ex < p.m && part == 0) {
-        const int unit = !s2 ? ex : p.full ? -1 : grp_s[gr] >= 2 ? p.m + gr : ex;
-        unit_s[ex] = unit;
-        if (unit >= p.m) *any_s = 1;
-        if (write) {
-            if (p.expert_unit) p.expert_unit[ex] = unit;
-            if (p.expert_in_s1) p.expert_in_s1[ex] = in_s1 ? 1 : 0;
-        }
-    }
-    lds_sync();
 }
 
 // Batches whose bitmaps fit a block's LDS: everything behind the TopK lists in one launch, a block per segment and one more that
@@ -1165,7 +1090,7 @@ __global__ void __launch_bounds__(1024) route_rows_kernel(RowArgs p, GateArgs g)
             };
             if (ranked) {
                 const int at = min(t, p.T - 1) * kMaxTopK + (lane & 15);
-                weights_rows(g, __float_as_int(w_s[at]), ex_s[at], t, t < p.T, lane, put);
+                weights_rows<false>(g, __float_as_int(w_s[at]), ex_s[at], t, t < p.T, lane, put);
                 continue;
             }
             const int r = lane & (per - 1), tt = min(t, p.T - 1);
