@@ -248,10 +248,12 @@ moe_status moe_forward(const moe_config *cfg, const void *x, int32_t T, const vo
  */
 enum {
     MOE_STAGE_PREP = 0,   /* clear counters, split gate weights                */
-    MOE_STAGE_GATE = 1,   /* affinities, TopK, weights, expert counts          */
-    MOE_STAGE_COUNT = 2,  /* Algorithm 1 + rows per unit and token block       */
-    MOE_STAGE_SCAN = 3,   /* offsets                                           */
-    MOE_STAGE_SCATTER = 4,/* row lists                                         */
+    MOE_STAGE_GATE = 1,   /* affinities, TopK, weights (of few tokens the affinities only) */
+    MOE_STAGE_COUNT = 2,  /* Algorithm 1, row lists and tile table; for few tokens TopK too; */
+                          /* beyond 8192 tokens (fewer with more than 128 experts)     */
+                          /* Algorithm 1 + rows per unit and token block only          */
+    MOE_STAGE_SCAN = 3,   /* those batches: offsets (else not recorded)        */
+    MOE_STAGE_SCATTER = 4,/* those batches: row lists (else not recorded)      */
     MOE_STAGE_TILES = 5,  /* GEMM tile table                                   */
     MOE_STAGE_GEMM1 = 6,  /* rows x [W1|W3] + SwiGLU                           */
     MOE_STAGE_GEMM2 = 7,  /* H x W2                                            */

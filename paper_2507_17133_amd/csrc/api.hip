@@ -91,8 +91,9 @@ static moe_status hip_fail(hipError_t e, const char* where)
 // GEMM tile height from the rows per unit: `even`, every unit holds that many (calibration tokens, a shared expert), else
 // their mean over the experts.  A gate's popular experts hold several times the mean, and every further tile of a
 // unit stages its weights again, so a tile is at least one to four times the mean.  Layer forward in us at tiles of 32 / 64
-// / 128 rows, Zipf gates: DeepSeek-V3 shape, 16 rows per expert 2929 / 2627 / 2628, 32 rows 4457 / 3609 / 3508; Qwen3 shape,
-// 8 rows 210 / 218 / 231, 16 rows 251 / 234 / 248, 64 rows - / 333 / 326; uniform gate, Mixtral shape, 16 rows 525 / 507 / 563.
+// / 128 rows, Zipf gates: DeepSeek-V3 shape, 16 rows per expert 2919 / 2635 / 2622, 32 rows 4231 / 3497 / 3334; Qwen3 shape,
+// 8 rows 222 / 229 / 229, 16 rows 259 / 246 / 247, 64 rows 398 / 339 / 311; uniform gate, Mixtral shape, 16 rows 512 / 531 / 542, 100 rows
+// 1073 / 647 / 573.
 static int pick_tile_rows(int64_t rows, bool even)
 {
     if (tuning().force_bm) return tuning().force_bm;
@@ -159,12 +160,11 @@ static TilePlan make_shared_plan(const Dims& D, int n_cu)
 // The taller tile that the table kernel may choose instead in a browned-out batch (0: none).  Offered where its blocks fill
 // the CUs once if no entry is dropped: the launch that gets no tiles costs 3 to 10 us, which shorter forwards would feel.
 // Layer forward in us at 40 / 80 % brownout, tiles of 64, 128 and 256 rows: DeepSeek-V3 shape, 16 rows per expert
-// 1127 / 1041, 920 / 839, 993 / 865; 32 rows 1809 / 1701, 1354 / 1290, 1223 / 1073; 94 rows (128 and 256) 3083 / 2950, 2368 / 2258;
-// Qwen3 shape, 250 rows 450 / 409, 382 / 334; with a uniform gate and 30 %, 32 rows 3355, 3360, 4077.
+// 1079 / 932, 901 / 812, 950 / 821; 32 rows 1613 / 1452, 1216 / 1058, 1144 / 999; 94 rows (128 and 256) 2431 / 2312, 2131 / 1954;
+// Qwen3 shape, 250 rows 360 / 331, 354 / 308; with a uniform gate and 30 %, 32 rows 3275, 3372, 3845.
 // GEMM2 keeps its planes at either height (the 256-row kernel then does not cut its tail, nor has it scratch for that below 384
-// tokens).  Still the better height there, at 30 / 80 % with 128 rows and with the choice of 256: 8 experts of 4096 x 14336, 400
-// tokens 522 / 392, 508 / 319, 1021 tokens 988 / 738, 775 / 530; at 30 / 60 % 16 experts of 2048 x 4096, 300 tokens 227 / 201, 218 /
-// 200, 64 experts of 4096 x 4096, 300 tokens 537 / 401, 567 / 367.
+// tokens).  Still the better height there: 8 experts of 4096 x 14336 at 30 / 80 % with 128 rows and with the choice of 256, 400
+// tokens 530 / 357, 540 / 351, 1021 tokens 1012 / 654, 903 / 570.
 static int taller_tile_rows(const Dims& D, int bm, int n_cu)
 {
     if (tuning().force_bm) return 0;

@@ -651,12 +651,12 @@ __global__ void __launch_bounds__(256) ffn_gemm_pair_kernel(GemmArgs ps, GemmArg
 // 32 KiB of loads that miss its L2 in flight (46 GB/s, whatever is queued behind them), and a wave that issues more waits in the
 // issue, its MFMAs with it.  Here the MFMAs do not show in the time where weights stream (8 units of 64 rows, 28672 x 4096: 354 us
 // with and without them), and the loaders run up to NST - 1 k tiles ahead, on into the next output tile while the others store
-// the last.  Against eight waves that load and multiply in turns (two groups out of phase, a block per tile): one unit of 256
-// rows 79 -> 69.6 us (28672 x 4096) and 62.8 -> 44.0 (4096 x 14336), 8 units of 64 rows 360 -> 338 and 177 -> 170; layer
-// forward of 1400 Mixtral-shaped tokens 1383 -> 1272, 4000 of the Qwen3 shape 558 -> 497, 2000 of the DeepSeek-V3 shape 4670
-// -> 4490.  (A wave that has both roles but reads its fragments a step ahead, as in the 256-row kernel: 94.5 and 76.8 us for
-// the one unit.  Starts of the k walk spread over the blocks, so that rows a power of two apart are not read at the same k:
-// 338 -> 354 us.)
+// the last.  Against eight waves that load and multiply in turns (two groups out of phase, a block per tile), in the layer, by rocprofv3:
+// one unit of 256 rows 77 -> 72 us (28672 x 4096) and 61 -> 45 (4096 x 14336), 8 units of 64 rows 355 -> 349 and 180 -> 179; layer
+// forward of 1400 Mixtral-shaped tokens 1305 -> 1193, 4000 of the Qwen3 shape 556 -> 489, 2000 of the DeepSeek-V3 shape 4684
+// -> 4630.  (A wave that has both roles but reads its fragments a step ahead, as in the 256-row kernel: 94.5 and 76.8 us for
+// the one unit.  Starts of the k walk spread over the blocks, so that rows a power of two apart are not read at the same k: 8 units
+// 338 -> 354 us, the kernel by itself.)
 // One barrier per k tile, in the middle of the step before: tile c has landed, and everyone has read tile c-1, whose stage takes
 // tile c+NST-1.  What a loader needs of the next tile comes through the scalar cache: a vector load's wait would be one for every
 // load in flight.

@@ -22,8 +22,10 @@ struct TileJobs {
     int cap;                 // entries a table holds
 };
 
-// Time of one GEMM tile of bm rows, in twentieths of a 32-row one (DeepSeek-V3 shape, tiles full: 20.6 and 14.7 ms for all
-// of 16384 tokens at 64 and 128 rows, 10.4 at 256; 1021 tokens at 32 and 64 rows: 2.68 and 1.81).
+// What a GEMM tile of bm rows counts for in the choice of bm_hi, in twentieths of a 32-row one.  Full tiles alone (DeepSeek-V3 shape, even
+// gate, 16384 tokens: 33.9, 20.6, 14.0 and 11.9 ms at 32, 64, 128 and 256 rows) would say 20, 24, 33 and 56, but the batches
+// that choose hold ragged ones, and 256 rows win there from fewer saved tiles on: 88 tiles of 128 rows against 57 of 256 (1021 tokens at
+// 0.4 brownout) 1216 and 1144 us, 57 against 46 (512 tokens) 901 and 950.  The line, 54 / 38 = 1.42, lies between those two.
 __device__ __forceinline__ int tile_cost(int bm) { return bm == 256 ? 54 : bm == 128 ? 38 : bm == 64 ? 27 : 20; }
 
 // Inclusive sum over the lanes of a wavefront: four shifts inside the rows of 16 lanes, then the rows' last lanes passed on (cross-lane

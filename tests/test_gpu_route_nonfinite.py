@@ -13,7 +13,7 @@ from tests._util import npf
 pytestmark = pytest.mark.gpu
 
 
-# one block routes up to 1024 tokens (held in registers up to T 2^k = 8192 entries, read again beyond), more do not
+# 3 tokens: the block that takes TopK routes them; more: a block per 64 tokens counts entries again where tokens name an expert twice
 @pytest.mark.parametrize("T,m,K", [(3, 20, 4), (300, 130, 8), (700, 40, 13), (1024, 60, 5), (1100, 60, 5)])
 @pytest.mark.parametrize("what", ["nan", "bias"])
 @pytest.mark.parametrize("threshold", [1.0, 0.5])
