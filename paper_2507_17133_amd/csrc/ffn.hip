@@ -876,6 +876,11 @@ __device__ __forceinline__ const bf16_t* uniform_ptr(const bf16_t* ptr)
 // when a wave has read its last fragments of tile kt and its loads of tile kt+1 have landed; from there
 // on one load is issued every eight MFMAs: first the A rows of tile kt+2 into the buffer just left, then
 // the B rows of tile kt+3.  Requests past the end of K are clamped to the last k tile (never read).
+// The MFMAs of a step go down strips of two A fragments: each B fragment is used twice in a row, the two A fragments by turns.  Under
+// the power limit the order of the operands shows: a loop of nothing but these MFMAs on random bits sustains 2016 TFLOP/s row by
+// row (a B fragment changes with every MFMA), 2043 row by row there and back, 2075 in strips of two, 2070 in strips of four, 1947
+// with both operands new each time.  Layer forward row by row and in strips: 16384 tokens of the DeepSeek-V3 shape 10580 -> 10440 us, 4096
+// Mixtral-shaped ones 2242 -> 2217, 8192 of the Qwen3 shape 644 -> 638, 5003 of the 60-expert shape 507 -> 499.
 // Between output tiles: the gather indices of the next tile are fetched during the main loop, its first
 // k tiles are requested before the epilogue of the current tile, so they land while that runs.
 // Blocks b, b+8, ... share an XCD; block b takes the tiles xcd*chunk + slot, + slots, ... of its XCD's
@@ -1243,42 +1248,40 @@ __device__ __forceinline__ void w4_block(const GemmArgs& p, const int block, con
                     const int a_rd = st == 0 ? a_cur : a_cur ^ 1;
                     const int b_rd = st == 0 ? b_cur : b_nxt;
 #pragma unroll
-                    for (int i = 0; i < FM; ++i)
-#pragma unroll
-                        for (int j = 0; j < FN; ++j) {
-                            const int mi = i * FN + j;
-                            if (st == 0 && mi == BAR) {
-                                // my reads of tile kt are done (both its buffers may be refilled) and my loads
-                                // of tile kt+1 have landed: everything but the HLB youngest requests
-                                __builtin_amdgcn_sched_barrier(0);
-                                __builtin_amdgcn_s_waitcnt(vmcnt_lgkm0_imm(HLB));
-                                lds_barrier();
-                                __builtin_amdgcn_sched_barrier(0);
-                            }
-                            acc[i][j] =
-                                __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[st][j], fa[st][i], acc[i][j], 0, 0, 0);
-                            if (mi < NRD && (mi & 1) == 0) {      // fragment reads, one per two MFMAs
-                                const int r = mi >> 1;
-                                __builtin_amdgcn_sched_barrier(0);
-                                if (r < FN) read_frag_b(b_rd, st ^ 1, r, st ^ 1);
-                                else read_frag_a(a_rd, st ^ 1, r - FN, st ^ 1);
-                                __builtin_amdgcn_sched_barrier(0);
-                            }
-                            // One direct load per slot of EV MFMAs (eight for the full tile: closer together they
-                            // queue up in the texture path and hold the wave).  After the barrier: the A rows of
-                            // tile kt+2 into the A buffer just left, then the B rows of tile kt+3 into tile kt's
-                            // B buffer, all but the first two of them during the first three quarters of the
-                            // next tile's first step.
-                            if (mi % EV == 0) {
-                                const int slot = mi / EV;
-                                __builtin_amdgcn_sched_barrier(0);
-                                if (st == 0 && slot < HLB - 2) load_b(slot + 2, t2, b_nn);
-                                if (st == 0 && slot >= 6) load_a(slot - 6, t2, a_cur);
-                                if (st == 1 && slot < 6) load_a(slot + 2, t2, a_cur);
-                                if (st == 1 && slot >= 6) load_b(slot - 6, t3, b_cur);
-                                __builtin_amdgcn_sched_barrier(0);
-                            }
+                    for (int mi = 0; mi < NM; ++mi) {
+                        const int i = mi / (2 * FN) * 2 + (mi & 1), j = mi % (2 * FN) >> 1;
+                        if (st == 0 && mi == BAR) {
+                            // my reads of tile kt are done (both its buffers may be refilled) and my loads
+                            // of tile kt+1 have landed: everything but the HLB youngest requests
+                            __builtin_amdgcn_sched_barrier(0);
+                            __builtin_amdgcn_s_waitcnt(vmcnt_lgkm0_imm(HLB));
+                            lds_barrier();
+                            __builtin_amdgcn_sched_barrier(0);
                         }
+                        acc[i][j] =
+                            __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[st][j], fa[st][i], acc[i][j], 0, 0, 0);
+                        if (mi < NRD && (mi & 1) == 0) {      // fragment reads, one per two MFMAs
+                            const int r = mi >> 1;
+                            __builtin_amdgcn_sched_barrier(0);
+                            if (r < FN) read_frag_b(b_rd, st ^ 1, r, st ^ 1);
+                            else read_frag_a(a_rd, st ^ 1, r - FN, st ^ 1);
+                            __builtin_amdgcn_sched_barrier(0);
+                        }
+                        // One direct load per slot of EV MFMAs (eight for the full tile: closer together they
+                        // queue up in the texture path and hold the wave).  After the barrier: the A rows of
+                        // tile kt+2 into the A buffer just left, then the B rows of tile kt+3 into tile kt's
+                        // B buffer, all but the first two of them during the first three quarters of the
+                        // next tile's first step.
+                        if (mi % EV == 0) {
+                            const int slot = mi / EV;
+                            __builtin_amdgcn_sched_barrier(0);
+                            if (st == 0 && slot < HLB - 2) load_b(slot + 2, t2, b_nn);
+                            if (st == 0 && slot >= 6) load_a(slot - 6, t2, a_cur);
+                            if (st == 1 && slot < 6) load_a(slot + 2, t2, a_cur);
+                            if (st == 1 && slot >= 6) load_b(slot - 6, t3, b_cur);
+                            __builtin_amdgcn_sched_barrier(0);
+                        }
+                    }
                     __builtin_amdgcn_sched_barrier(0);
                     __builtin_amdgcn_s_waitcnt(0xC07F);   // next step's fragments are in registers
                     __builtin_amdgcn_sched_barrier(0);
