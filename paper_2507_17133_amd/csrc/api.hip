@@ -174,6 +174,21 @@ static int taller_tile_rows(const Dims& D, int bm, int n_cu)
     return hi;
 }
 
+// Weights of the units that hold rows, and of the shared experts, beyond which they are streamed past the caches: what the 256 MiB memory-side
+// cache could still hold when the layer is called again.  Layer forward without and with it, three layers in turn: 256 tokens of
+// the Mixtral shape 538 -> 510 us, its united unit alone (352 MB) 134 -> 125, 37 tokens of the 60-expert shape (277 MB) 89 -> 83, 232 of the
+// Qwen3 shape 220 -> 200, 40 of the DeepSeek-V3 shape 1010 -> 943.  Below the line there is less to gain (60 of the 60-expert shape, 242 MB,
+// 91.6 -> 88.4; 232 of the Qwen3 shape, 179 MB, 87.7 -> 85.9), and one layer called over and over would lose what it finds there
+// (83 -> 89 and 68 -> 85; between 256 and 320 MB up to 4 %).  With weights streamed that further tiles read later: 7113 tokens of the
+// DeepSeek-V3 shape 8510 -> 10130; in the 256-row kernel, where eight M tiles in a row read the same ones: 8192 of the Qwen3 shape 618 ->
+// 649.
+constexpr int64_t kKeptBytes = (int64_t)256 << 20;
+static int units_to_stream(const Dims& D)
+{
+    const int64_t left = kKeptBytes - (int64_t)D.Ns * 6 * D.d * D.Fs, unit = (int64_t)6 * D.d * D.F;
+    return (int)std::max<int64_t>(0, left / unit + 1);
+}
+
 Dims make_dims(const moe_config& c, int T)
 {
     Dims D;
@@ -236,7 +251,8 @@ static void carve_route_pieces(const Dims& D, Workspace& W, size_t& o)
     W.row_token = take((size_t)D.row_cap * 4);
     W.row_weight = take((size_t)D.row_cap * 4);
     W.token_rows = take((size_t)D.row_cap * 4);
-    W.n_rows = take(4);
+    W.n_rows = take(8);
+    W.streamed = W.n_rows + 4;
     W.near_tie = take((size_t)D.T);
     // the pieces of an fp32 gate matrix.  A packed gate of more than 16 experts brings them; with at most 16
     // experts the gate is fp32 rows in either format, cut on the way only beyond kFewExpertsTokens tokens
@@ -478,7 +494,7 @@ moe_status moe_route(const moe_config* cfg, const void* x, int32_t T, const void
     const RouteBufs R = resolve_route(out, workspace, W);
     hipStream_t s = static_cast<hipStream_t>(stream);
     TileJobs none;
-    none.n = 0; none.cap = 0;
+    none.n = none.cap = none.count_units = none.stream_units = 0; none.streamed = nullptr;
     hipError_t e = launch_route(D, static_cast<const bf16_t*>(x), gate_w, gate_bias, threshold,
                                 use_full_brownout ? 1 : 0, R, at<bf16_t>(workspace, W.gate_split),
                                 at<int32_t>(workspace, W.seg_cnt), at<int32_t>(workspace, W.seg_off),
@@ -505,7 +521,7 @@ moe_status moe_route_static(const moe_config* cfg, const void* x, int32_t T, con
     const RouteBufs R = resolve_route(out, sp, W);
     hipStream_t s = static_cast<hipStream_t>(stream);
     TileJobs none;
-    none.n = 0; none.cap = 0;
+    none.n = none.cap = none.count_units = none.stream_units = 0; none.streamed = nullptr;
     // everything the kernels read from the scratch they write first in the same call (counters are cleared by
     // the first kernel), so what an earlier call left there does not matter
     e = launch_route(D, static_cast<const bf16_t*>(x), gate_w, gate_bias, threshold, use_full_brownout ? 1 : 0, R,
@@ -567,6 +583,9 @@ moe_status moe_forward(const moe_config* cfg, const void* x, int32_t T, const vo
     TileJobs jobs;
     jobs.n = split_shared ? 2 : 1;
     jobs.cap = D.tile_cap;
+    jobs.count_units = D.m + D.G;
+    jobs.stream_units = units_to_stream(D);
+    jobs.streamed = at<int32_t>(workspace, W.streamed);
     jobs.job[0].u_lo = 0; jobs.job[0].u_hi = split_shared ? D.m + D.G : D.U;
     jobs.job[0].plan = routed_tile_plan(D, dev.n_cu);
     jobs.job[0].table = at<int32_t>(workspace, W.tiles0);
@@ -597,7 +616,7 @@ moe_status moe_forward(const moe_config* cfg, const void* x, int32_t T, const vo
         if (j == 1 || !split_shared) units.even = D.Ns;
         problems[j] = FfnProblem{units, j == 0 ? D.F : D.Fs, J.plan, J.bm_hi, J.table};
     }
-    e = launch_ffn(D, problems, jobs.n, xb, R.row_token, fe, fu, fs, H, Y, partial, s);
+    e = launch_ffn(D, problems, jobs.n, xb, R.row_token, fe, fu, fs, H, Y, partial, jobs.streamed, s);
     if (e != hipSuccess) return hip_fail(e, "moe_forward/ffn");
     e = launch_combine(D, xb, Y, R.token_rows, R.row_weight, static_cast<bf16_t*>(out), s);
     if (e != hipSuccess) return hip_fail(e, "moe_forward/combine");
@@ -663,7 +682,7 @@ moe_status moe_build_united(const moe_config* cfg, const moe_ffn_weights* expert
         hipError_t err = launch_uniform_units(u0, n0, u1, n1, first_slot, n_calib, plan.bm, tiles, s);
         if (err != hipSuccess) return err;
         const FfnProblem units{FfnUnits{n0 + n1, 0, n0 + n1}, D.F, plan, 0, tiles};
-        return launch_ffn(D, &units, 1, xb, row_token, fe, fu, fs, H, Y, partial, s);
+        return launch_ffn(D, &units, 1, xb, row_token, fe, fu, fs, H, Y, partial, nullptr, s);
     };
     for (int g = 0; g < G; ++g) {
         const int lo = g * way, hi = lo + way < m ? lo + way : m, k = hi - lo;
@@ -760,7 +779,7 @@ moe_status moe_distill_united(const moe_config* cfg, const moe_ffn_weights* expe
                 const int i0 = lo + (int)((int64_t)k * q / batches), i1 = lo + (int)((int64_t)k * (q + 1) / batches);
                 const FfnProblem units{FfnUnits{i1 - i0, 0, i1 - i0}, D.F, plan, 0, tiles};
                 if ((e = launch_uniform_units(i0, i1 - i0, 0, 0, 0, n_calib, plan.bm, tiles, s)) != hipSuccess ||
-                    (e = launch_ffn(D, &units, 1, xb, row_token, fe, fu, fs, H, Yo, partial, s)) != hipSuccess)
+                    (e = launch_ffn(D, &units, 1, xb, row_token, fe, fu, fs, H, Yo, partial, nullptr, s)) != hipSuccess)
                     return hip_fail(e, "moe_distill_united/teacher");
                 e = launch_teacher_stats(Yo, i1 - i0, q == 0, q == batches - 1, k, n_calib, D.d, D.F, g - g0, buf, s);
                 if (e != hipSuccess) return hip_fail(e, "moe_distill_united/mean");

@@ -65,19 +65,19 @@ __device__ __forceinline__ float swiglu(float g, float u)
 
 // ------------------------------------------------------------------------------------------------
 // Tile tables from the unit counts, when the routing kernels have not already built them (row lists brought
-// by the caller): one wavefront per job.
+// by the caller): one wavefront per job, and one for whether weights are streamed.
 // ------------------------------------------------------------------------------------------------
 __global__ void __launch_bounds__(64) tile_table_kernel(const int32_t* __restrict__ unit_cnt,
                                                         const int32_t* __restrict__ unit_off, TileJobs jobs)
 {
-    if ((int)blockIdx.x < jobs.n)
-        build_tile_table(unit_cnt, unit_off, jobs.job[blockIdx.x], jobs.cap, threadIdx.x);
+    build_tables(unit_cnt, unit_off, jobs, blockIdx.x, threadIdx.x);
 }
 
 // ------------------------------------------------------------------------------------------------
 struct GemmArgs {
     const bf16_t* A; long lda; const int32_t* gather;
     const int32_t* table;
+    const int32_t* streamed;                    // load_weights: nonzero if the layer's weights are
     int lower;                                  // rows of the lower tiles that the launch takes as well (TilePlan::lo; 0: none)
     const bf16_t *wa0, *wa1, *wa2;              // per weight source (experts, united, shared); GEMM1: W1, GEMM2: W2
     const bf16_t *wb0, *wb1, *wb2;              // GEMM1: W3; GEMM2: unused
@@ -101,6 +101,30 @@ __device__ __forceinline__ void lds_barrier()
     asm volatile("" ::: "memory");
 }
 
+// One direct load: 16 bytes per lane, 1 KiB of LDS from dst on.
+template <int POLICY = 0>
+__device__ __forceinline__ void load_lds(const void* src, char* dst)
+{
+    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src, (__attribute__((address_space(3))) void*)dst, 16,
+                                     0, POLICY);
+}
+
+// A k tile's loads of weights, `step` bytes of LDS apart.  `streamed`: with the non-temporal hint, where the layer's weights do not
+// outlast a call in the memory-side cache anyway and one tile, or tiles side by side, read these: without it their lines push everything
+// else out of the caches on the way (with sc0 or sc1 besides: no change).
+constexpr int kNonTemporal = 2;
+template <int N>
+__device__ __forceinline__ void load_weights(bool streamed, const bf16_t* const* src, int k, char* dst, int step)
+{
+    if (streamed) {
+#pragma unroll
+        for (int i = 0; i < N; ++i) load_lds<kNonTemporal>(src[i] + k, dst + i * step);
+    } else {
+#pragma unroll
+        for (int i = 0; i < N; ++i) load_lds(src[i] + k, dst + i * step);
+    }
+}
+
 // s_waitcnt immediates (gfx9 encoding: vmcnt in bits 3:0 and 15:14, expcnt 6:4, lgkmcnt 11:8).
 __host__ __device__ constexpr int vmcnt_imm(int n) { return (n & 0xF) | ((n >> 4) << 14) | 0x0F70; }       // vmcnt <= n
 __host__ __device__ constexpr int vmcnt_lgkm0_imm(int n) { return vmcnt_imm(n) & 0xF0FF; }                 // and lgkmcnt 0
@@ -111,6 +135,7 @@ struct Tile {
     int kslice, ks;                             // this block multiplies slice kslice of ks slices of K
     int part;                                   // slot in GemmArgs::partial the result goes to, or -1: to the output
     int half;                                   // column-half tail of the four-wave kernel: which half of the tile
+    bool streamed;                              // load_weights
     const bf16_t *Wa, *Wb;
 };
 
@@ -120,6 +145,14 @@ __device__ __forceinline__ int m_tiles(const GemmArgs& p)
 {
     const int2 head = *reinterpret_cast<const int2*>(p.table);      // one load, not two in a row
     return head.y == BM ? head.x : 0;
+}
+
+// Whether row tile mt is its unit's only one: no neighbour has the unit.  (All loads at once, none behind a comparison.)
+template <typename Table>
+__device__ __forceinline__ bool only_tile(Table table, int n_mt, int mt, int unit)
+{
+    const int before = table[4 * max(mt, 1)], after = table[4 * min(mt + 2, n_mt)];
+    return (mt == 0 | before != unit) & (mt + 1 == n_mt | after != unit);
 }
 
 // Tile L of the launch's tile order -> its row tile and column tile.  Super-tiles of group_m M tiles x all N tiles, M fastest: the
@@ -148,6 +181,7 @@ __device__ __forceinline__ void set_weights(const GemmArgs& p, Tile& t)
 template <int BM, int BNC, bool SWIGLU>
 __device__ __forceinline__ bool decode_tile(const GemmArgs& p, int block, Tile& t)
 {
+    const int stream = *p.streamed;
     const int n_mt = m_tiles<BM>(p);
     const int tiles = n_mt * p.n_ntiles;
     const int total = tiles * p.ksplit;
@@ -164,6 +198,7 @@ __device__ __forceinline__ bool decode_tile(const GemmArgs& p, int block, Tile& 
     tile_coords(p, n_mt, p.n_ntiles, Lfull - t.kslice * tiles, mt, t.nt);
     const int4 te = reinterpret_cast<const int4*>(p.table + 4)[mt];
     t.unit = te.x; t.row0 = te.y; t.nrows = te.z;
+    t.streamed = only_tile(p.table, n_mt, mt, t.unit) & (stream != 0);
     set_weights<SWIGLU>(p, t);
     t.n0 = t.nt * BNC;
     return true;
@@ -444,8 +479,8 @@ __device__ __forceinline__ void small_block(const GemmArgs& p, const int block)
         char* dst = smem + (kt % NSTAGE) * STAGE + wave * 1024;
 #pragma unroll
         for (int i = 0; i < LD_PER_WAVE; ++i)
-            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(gptr[i] + kt * BK),
-                                             (__attribute__((address_space(3))) void*)(dst + i * NW * 1024), 16, 0, 0);
+            if (i * NW * RPG < BM) load_lds(gptr[i] + kt * BK, dst + i * NW * 1024);
+        load_weights<LD_PER_WAVE - BM / RPG / NW>(t.streamed, gptr + BM / RPG / NW, kt * BK, dst + BM / RPG * 1024, NW * 1024);
     };
 
     f32x16 acc[FM][FN];
@@ -535,8 +570,8 @@ __device__ __forceinline__ void narrow_block(const GemmArgs& p, const int block)
         char* dst = smem + stage * STAGE + wave * 1024;
 #pragma unroll
         for (int i = 0; i < LD_PER_WAVE; ++i)
-            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(gptr[i] + kt * BK),
-                                             (__attribute__((address_space(3))) void*)(dst + i * NW * 1024), 16, 0, 0);
+            if (i * NW * RPG < BM) load_lds(gptr[i] + kt * BK, dst + i * NW * 1024);
+        load_weights<LD_PER_WAVE - BM / RPG / NW>(t.streamed, gptr + BM / RPG / NW, kt * BK, dst + BM / RPG * 1024, NW * 1024);
     };
 
     f32x4 acc[FM][FN];
@@ -675,6 +710,7 @@ __device__ __forceinline__ void tile_at(const GemmArgs& p, int n_mt, int n_ntile
     typedef const __attribute__((address_space(4))) int* scalar_ptr;
     const scalar_ptr te = (scalar_ptr)(unsigned long)(p.table + 4 + 4 * __builtin_amdgcn_readfirstlane(mt));
     t.unit = te[0]; t.row0 = te[1]; t.nrows = te[2];
+    t.streamed = only_tile((scalar_ptr)(unsigned long)p.table, n_mt, __builtin_amdgcn_readfirstlane(mt), t.unit);
     set_weights<SWIGLU>(p, t);
     t.n0 = t.nt * bnc;
 }
@@ -705,10 +741,14 @@ __device__ __forceinline__ void ws_block(const GemmArgs& p, const int n_mt, cons
         const int lw = wave - NW;
         const bf16_t *ga[LA], *gb[LB];
         int next = first, kt = 0, nk = 0, stage = 0;
+        // in a launch of one round the M tiles of a unit read its weights side by side
+        const bool stream = *(scalar_ptr)(unsigned long)p.streamed != 0, one_round = total <= (int)gridDim.x;
+        bool streamed = false;
         auto set_up = [&](const Tile& t) {
             int k_first;
             k_range<BK>(p, t, k_first, nk);
             kt = 0;
+            streamed = stream && (t.streamed || one_round);
             if (nk <= 0) return;
             const int r8 = lane >> 3;
 #pragma unroll
@@ -743,14 +783,9 @@ __device__ __forceinline__ void ws_block(const GemmArgs& p, const int n_mt, cons
                 set_up(t);
             }
             char* dst = smem + stage * STAGE + lw * 1024;
+            load_weights<LB>(streamed, gb, kt * BK, dst + BM * RB, NW * 1024);
 #pragma unroll
-            for (int i = 0; i < LB; ++i)
-                __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(gb[i] + kt * BK),
-                                                 (__attribute__((address_space(3))) void*)(dst + BM * RB + i * NW * 1024), 16, 0, 0);
-#pragma unroll
-            for (int i = 0; i < LA; ++i)
-                __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(ga[i] + kt * BK),
-                                                 (__attribute__((address_space(3))) void*)(dst + i * NW * 1024), 16, 0, 0);
+            for (int i = 0; i < LA; ++i) load_lds(ga[i] + kt * BK, dst + i * NW * 1024);
             stage = stage == NST - 1 ? 0 : stage + 1;
             ++kt;
             return true;
@@ -1584,13 +1619,13 @@ static hipError_t launch_gemm_pair(const GemmLaunch& sh, const GemmLaunch& ro, h
 hipError_t launch_tile_tables(const int32_t* unit_cnt, const int32_t* unit_off, const TileJobs& jobs, hipStream_t s)
 {
     ProfScope ps(MOE_STAGE_TILES, s);
-    tile_table_kernel<<<jobs.n, 64, 0, s>>>(unit_cnt, unit_off, jobs);
+    tile_table_kernel<<<jobs.n + 1, 64, 0, s>>>(unit_cnt, unit_off, jobs);
     return hipGetLastError();
 }
 
 hipError_t launch_ffn(const Dims& D, const FfnProblem* problems, int n_problems, const bf16_t* x, const int32_t* gather,
                       const FfnWeights& experts, const FfnWeights& united, const FfnWeights& shared, bf16_t* H, bf16_t* Y,
-                      float* partial, hipStream_t s)
+                      float* partial, const int32_t* streamed, hipStream_t s)
 {
     DeviceInfo dev;
     hipError_t e = ensure_device_init(&dev);
@@ -1599,7 +1634,7 @@ hipError_t launch_ffn(const Dims& D, const FfnProblem* problems, int n_problems,
         constexpr bool SWIGLU = decltype(swiglu)::value;
         GemmLaunch l;
         GemmArgs& g = l.a;
-        g.table = P.table; g.lower = lo;
+        g.table = P.table; g.streamed = streamed ? streamed : P.table + 2; g.lower = lo;       // word 2 of a table is 0
         g.m = D.m; g.G = D.G;
         if (SWIGLU) {
             g.A = x; g.lda = D.d; g.gather = gather;

@@ -926,7 +926,7 @@ __global__ void __launch_bounds__(256) route_scatter_kernel(RowArgs p)
     if (seg == p.n_seg) {
         for (int u = tid; u <= p.U; u += 256) p.unit_off[u] = off_s[u];
         if (tid == 0 && p.n_rows) p.n_rows[0] = off_s[p.U];
-        if (wave < p.jobs.n) build_tile_table(ucnt_s, off_s, p.jobs.job[wave], p.jobs.cap, lane);
+        build_tables(ucnt_s, off_s, p.jobs, wave, lane);
         return;
     }
 #pragma unroll
@@ -1259,7 +1259,7 @@ __global__ void __launch_bounds__(1024) route_rows_kernel(RowArgs p, GateArgs g)
         lds_sync();
     }
     // the GEMM tile tables, by the last wavefronts (with kTopK the first ones hold the tokens of a short batch)
-    if (writer && 15 - wave < p.jobs.n) build_tile_table(ucnt_s, off_s, p.jobs.job[15 - wave], p.jobs.cap, lane);
+    if (writer) build_tables(ucnt_s, off_s, p.jobs, 15 - wave, lane);
     if (SRC != kTopK && writer) return;
 
     const int j = tid & ((1 << p.lk) - 1);

@@ -20,6 +20,9 @@ struct TileJobs {
     int n;                   // 0, 1 or 2 jobs (routed + united units; shared units of another width)
     TileJob job[2];
     int cap;                 // entries a table holds
+    int count_units;         // *streamed (ffn.hip, load_weights) is whether at least stream_units of the units
+    int stream_units;        // [0, count_units) hold rows
+    int32_t* streamed;
 };
 
 // What a GEMM tile of bm rows counts for in the choice of bm_hi, in twentieths of a 32-row one.  Full tiles alone (DeepSeek-V3 shape, even
@@ -108,6 +111,19 @@ __device__ __forceinline__ void build_tile_table(const int* cnt, const int* off,
             if (at < cap) entries[at] = make_int4(u, o + r, min(bm, c - r), 0);
             ++at;
         }
+    }
+}
+
+// Wavefront w of a kernel that has the counts: table w, and behind the tables whether the weights are streamed.
+__device__ __forceinline__ void build_tables(const int* cnt, const int* off, const TileJobs& jobs, int w, int lane)
+{
+    if (w < jobs.n) {
+        build_tile_table(cnt, off, jobs.job[w], jobs.cap, lane);
+    } else if (w == jobs.n && w > 0) {
+        int active = 0;
+        for (int u = lane; u < jobs.count_units; u += 64) active += cnt[u] > 0;
+        active = __builtin_amdgcn_readlane(wave_scan(active), 63);
+        if (lane == 0) *jobs.streamed = active >= jobs.stream_units;
     }
 }
 
