@@ -16,9 +16,7 @@
 // summed by one block) a pass over two groups of 8 and 4 teachers at n = d = 2048, F = 1408 with 8 steps took 56.9 ms,
 // 50 of them in the one-block sums and 3.4 in the GEMMs; now 3.4 ms.  Of those a step's four launches take 0.36 ms
 // (kSwiglu 80 us, kResidual 47, kBackward 59, kAdam 170 of which 484 MB of masters and moments are 94 us at the rate
-// of a large copy; 197 while its epilogue read and wrote them in pieces of 64 bytes).  The k loop pulls 40 to 50 GB/s per CU
-// whatever the lead of its loads (two more k tiles in registers: no change), for the blocks of an XCD reach each slab of
-// their panels together.
+// of a large copy; 197 while its epilogue read and wrote them in pieces of 64 bytes).
 #include "internal.h"
 
 #include <algorithm>
@@ -160,18 +158,25 @@ struct DGemm {
 constexpr int kImgPitch = 272;                             // bytes per row of a 128 x 128 bf16 image in LDS
 // kAdam: per wave 32 rows x 64 columns of products (272 bytes a row) and a transposed bf16 image of its 64 x 64 (144 a column)
 constexpr int kAdamRow = 272, kAdamCol = 144, kAdamWave = 32 * kAdamRow + 64 * kAdamCol;
-constexpr int dgemm_lds(int epi) { return epi == kAdam ? 4 * kAdamWave : 2 * 128 * kImgPitch; }    // else two images; the k loop: 64 KiB
+constexpr int kSlab = 128 * 128;                           // 128 rows of a k tile: two buffers of A rows and three of B rows in the k loop
+constexpr int kDgemmLds = 5 * kSlab;                       // two blocks share a CU's 160 KiB; the last 32 bytes: block_sum's
+static_assert(2 * 128 * kImgPitch <= kDgemmLds - 32 && 4 * kAdamWave <= kDgemmLds, "an epilogue's images take the place of the buffers");
 
-// 128 x 128 x 64 tiles, four waves (64 x 64 each, 16x16x32 MFMA), two LDS stages filled by direct global->LDS
-// loads, two blocks per CU: the second block's waves cover the barrier and the load latency of the first.
-// A wave's 64 x 64 tile is either inside the matrix or outside (M and N are multiples of 64).
+// 128 x 128 x 64 tiles, four waves (64 x 64 each, 16x16x32 MFMA), two blocks per CU.  A wave's 64 x 64 tile is either inside the matrix
+// or outside (M and N are multiples of 64).
+// What bounds the k loop: 128 KiB of fragments and 64 KiB of tiles pass through the LDS per k tile of two blocks, 1536 cycles against 1024
+// of MFMAs, if nothing in a wave waits for anything else in it.  So the fragments of the next step of 16 MFMAs are read between the MFMAs of
+// this one, and direct global->LDS loads are issued one by one between them (all eight of a k tile in a row, then fragments, then MFMAs,
+// over two stages of 64 KiB: 2085 cycles, as long with one block on a CU as with two; now 1780 and 1530).  The
+// 80 KiB of a block are two buffers of A rows and three of B rows, so that loads lead by one and two k tiles.  One barrier per k tile, three
+// quarters into its first step, when a wave has read its last fragments of tile kt and its loads of tile kt+1 have landed; behind it come
+// the A rows of tile kt+2 into the buffer just left, then the B rows of tile kt+3.  Loads past the end of K are clamped to the last
+// k tile and never used.  Two groups at n = d = 2048, F = 1408: kSwiglu 77 -> 65 us, the call with 8 steps 3.37 -> 3.20 ms.
 template <int EPI>
 __global__ void __launch_bounds__(256, 2) distill_gemm_kernel(DGemm p)
 {
-    constexpr int STAGE = 256 * 128;
     constexpr int BNC = EPI == kSwiglu ? 64 : 128;         // output columns of a tile
     extern __shared__ __attribute__((aligned(16))) char smem[];
-    __shared__ double red[4];
     // block id mod 8 is the XCD: a contiguous range of tiles each, super-tiles of 8 M tiles x all N tiles inside
     const int chunk = (p.total + 7) >> 3;
     const int L = (blockIdx.x & 7) * chunk + (blockIdx.x >> 3);
@@ -187,64 +192,99 @@ __global__ void __launch_bounds__(256, 2) distill_gemm_kernel(DGemm p)
     const int wm = wave >> 1, wn = wave & 1;
     const int K = J.K;
 
-    // wave w moves the 8-row groups w, w+4, ... of a stage (A rows first, then B rows); 16-byte chunk c of row r
-    // sits in slot c ^ ((r/2)&7) (conflict-free ds_read_b128)
-    const bf16_t* src[8];
+    // Wave w moves the 8-row groups w, w+4, ... of A and of B; 16-byte chunk c of row r sits in slot c ^ ((r/2)&7) (conflict-free
+    // ds_read_b128), a term that is the same for all loads of a lane.  An address is a wave-uniform base and a lane offset.
+    const int wave_s = __builtin_amdgcn_readfirstlane(wave);
+    const int r8 = lane >> 3, csw = (lane & 7) ^ ((((wave & 1) << 2) + (r8 >> 1)) & 7);
+    const unsigned off = (unsigned)(r8 * K * 2 + csw * 16);
+    const bf16_t *base_a[4], *base_b[4];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        const int row = (wave + i * 4) * 8 + (lane >> 3);
-        const bf16_t* base;
-        if (i < 4) {
-            base = J.A.at<const bf16_t>(g) + (size_t)min(m0 + row, J.M - 1) * K;
-        } else if (EPI == kSwiglu) {
-            // the wave tile's 16-column MFMA tiles alternate W1 / W3 of the same 16 columns
-            const int n = row - 128, w_n = n >> 6, j = (n >> 4) & 3;
-            const int col = n0 + w_n * 32 + (j >> 1) * 16 + (n & 15);
-            base = ((j & 1) ? J.B1 : J.B).at<const bf16_t>(g) + (size_t)min(col, J.N - 1) * K;
-        } else {
-            base = J.B.at<const bf16_t>(g) + (size_t)min(n0 + row - 128, J.N - 1) * K;
-        }
-        src[i] = base + (((lane & 7) ^ ((row >> 1) & 7)) << 3);
+    for (int i = 0; i < 4; ++i) {
+        const int grp = wave_s + i * 4;                   // of 16
+        base_a[i] = uniform_ptr(J.A.at<const bf16_t>(g) + (size_t)min(m0 + grp * 8, J.M - 8) * K);
+        // kSwiglu: the wave tile's 16-column MFMA tiles alternate W1 / W3 of the same 16 columns
+        const bool third = EPI == kSwiglu && ((grp >> 1) & 1);
+        const int col = EPI == kSwiglu ? n0 + (grp >> 3) * 32 + ((grp >> 2) & 1) * 16 + (grp & 1) * 8 : n0 + grp * 8;
+        base_b[i] = uniform_ptr((third ? J.B1 : J.B).at<const bf16_t>(g) + (size_t)min(col, J.N - 8) * K);
     }
-    auto issue = [&](int kt) {
-        char* dst = smem + (kt & 1) * STAGE + wave * 1024;
-#pragma unroll
-        for (int i = 0; i < 8; ++i)
-            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src[i] + kt * 64),
-                                             (__attribute__((address_space(3))) void*)(dst + i * 4096), 16, 0, 0);
+    const int nk = K >> 6, last = nk - 1;
+    auto load_a = [&](int i, int kt) {
+        load_lds(reinterpret_cast<const char*>(base_a[i] + (size_t)min(kt, last) * 64) + off,
+                 smem + (kt & 1) * kSlab + (wave_s + i * 4) * 1024);
+    };
+    auto load_b = [&](int i, int kt, int buf) {
+        load_lds(reinterpret_cast<const char*>(base_b[i] + (size_t)min(kt, last) * 64) + off,
+                 smem + (2 + buf) * kSlab + (wave_s + i * 4) * 1024);
+    };
+    const int a_off = (wm * 64 + (lane & 15)) * 128, b_off = 2 * kSlab + (wn * 64 + (lane & 15)) * 128;
+    const int swz = ((lane & 15) >> 1) & 7;
+    bf16x8 fa[2][4], fb[2][4];
+    auto read_a = [&](int buf, int half, int i) {
+        fa[half][i] = *reinterpret_cast<const bf16x8*>(smem + buf * kSlab + a_off + i * 2048 + (((half * 4 + (lane >> 4)) ^ swz) << 4));
+    };
+    auto read_b = [&](int buf, int half, int j) {
+        fb[half][j] = *reinterpret_cast<const bf16x8*>(smem + buf * kSlab + b_off + j * 2048 + (((half * 4 + (lane >> 4)) ^ swz) << 4));
     };
     f32x4 acc[4][4];
 #pragma unroll
     for (int i = 0; i < 4; ++i)
 #pragma unroll
         for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-    const int a_off = (wm * 64 + (lane & 15)) * 128, b_off = (128 + wn * 64 + (lane & 15)) * 128;
-    const int swz = ((lane & 15) >> 1) & 7;
-    const int nk = K >> 6;
-    issue(0);
-    for (int kt = 0; kt < nk; ++kt) {
-        __builtin_amdgcn_s_waitcnt(0x0F70);               // vmcnt(0): this wave's part of tile kt has landed
-        asm volatile("" ::: "memory");
-        __builtin_amdgcn_s_barrier();                     // everyone's part has; nobody still reads the other stage
-        asm volatile("" ::: "memory");
-        if (kt + 1 < nk) issue(kt + 1);
-        const char* St = smem + (kt & 1) * STAGE;
 #pragma unroll
-        for (int kk = 0; kk < 2; ++kk) {
-            const int sw = ((kk * 4 + (lane >> 4)) ^ swz) << 4;
-            bf16x8 fa[4], fb[4];
+    for (int i = 0; i < 4; ++i) load_a(i, 0);
 #pragma unroll
-            for (int i = 0; i < 4; ++i) fa[i] = *reinterpret_cast<const bf16x8*>(St + a_off + i * 2048 + sw);
+    for (int i = 0; i < 4; ++i) load_b(i, 0, 0);
 #pragma unroll
-            for (int j = 0; j < 4; ++j) fb[j] = *reinterpret_cast<const bf16x8*>(St + b_off + j * 2048 + sw);
+    for (int i = 0; i < 4; ++i) load_a(i, 1);
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < 4; ++i) load_b(i, 1, 1);
+    load_b(0, 2, 2);
+    __builtin_amdgcn_s_waitcnt(vmcnt_imm(9));             // tile 0 has landed, the nine younger loads are in flight
+    lds_barrier();
 #pragma unroll
-                for (int j = 0; j < 4; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[j], fa[i], acc[i][j], 0, 0, 0);
-        }
+    for (int i = 0; i < 4; ++i) {
+        read_a(0, 0, i);
+        read_b(0, 0, i);
     }
-    __syncthreads();                                      // every wave has left the stages: images go there
+    __builtin_amdgcn_s_waitcnt(0xC07F);
+    int b_cur = 0;                                        // B buffer of tile kt (kt mod 3)
+    for (int kt = 0; kt < nk; ++kt) {
+        const int a_cur = kt & 1, b_nxt = b_cur == 2 ? 0 : b_cur + 1, b_nn = b_nxt == 2 ? 0 : b_nxt + 1;
+#pragma unroll
+        for (int st = 0; st < 2; ++st) {
+#pragma unroll
+            for (int mi = 0; mi < 16; ++mi) {
+                if (st == 0 && mi == 12) {
+                    // my reads of tile kt are done (its buffers may be refilled) and my loads of tile kt+1 have landed:
+                    // all but the four youngest, B rows of tile kt+2
+                    __builtin_amdgcn_sched_barrier(0);
+                    __builtin_amdgcn_s_waitcnt(vmcnt_lgkm0_imm(4));
+                    lds_barrier();
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                const int i = (mi >> 3) * 2 + (mi & 1), j = (mi & 7) >> 1;
+                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[st][j], fa[st][i], acc[i][j], 0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
+                if (mi < 8) {                             // fragments of the next step
+                    if (mi < 4) read_b(st == 0 ? b_cur : b_nxt, st ^ 1, mi);
+                    else read_a(st == 0 ? a_cur : a_cur ^ 1, st ^ 1, mi - 4);
+                }
+                if ((mi & 3) == 0) {
+                    if (st == 0 && mi < 12) load_b(1 + (mi >> 2), kt + 2, b_nn);
+                    if (st == 0 && mi == 12) load_a(0, kt + 2);
+                    if (st == 1 && mi < 12) load_a(1 + (mi >> 2), kt + 2);
+                    if (st == 1 && mi == 12) load_b(0, kt + 3, b_cur);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            __builtin_amdgcn_s_waitcnt(0xC07F);           // lgkmcnt(0): the next step's fragments are in registers
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        b_cur = b_nxt;
+    }
+    __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));             // clamped loads still target this block's LDS
+    lds_barrier();                                        // every wave has left the buffers: images go there
+    double* red = reinterpret_cast<double*>(smem + kDgemmLds - 32);
 
     // A lane holds, for row wm*64 + 16 i + (lane & 15) of the tile, the columns wn*64 + 16 j + 4 (lane >> 4) + 0..3.
     const int r_l = wm * 64 + (lane & 15), c4 = 4 * (lane >> 4);
@@ -457,7 +497,7 @@ static hipError_t launch_dgemm(DGemm& p, int groups, hipStream_t s)
     }
     p.tiles = p.job[0].mt * p.job[0].nt;
     p.total = groups * p.n_jobs * p.tiles;
-    distill_gemm_kernel<EPI><<<ceil_div(p.total, 8) * 8, 256, dgemm_lds(EPI), s>>>(p);
+    distill_gemm_kernel<EPI><<<ceil_div(p.total, 8) * 8, 256, kDgemmLds, s>>>(p);
     return hipGetLastError();
 }
 
@@ -469,7 +509,7 @@ hipError_t init_distill_kernels()
                        reinterpret_cast<const void*>(distill_gemm_kernel<kAdam>)};
     static_assert(kSwiglu == 0 && kResidual == 1 && kBackward == 2 && kAdam == 3, "the order above");
     for (int i = 0; i < 4; ++i) {
-        const hipError_t e = hipFuncSetAttribute(k[i], hipFuncAttributeMaxDynamicSharedMemorySize, dgemm_lds(i));
+        const hipError_t e = hipFuncSetAttribute(k[i], hipFuncAttributeMaxDynamicSharedMemorySize, kDgemmLds);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;

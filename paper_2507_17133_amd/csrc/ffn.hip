@@ -91,24 +91,6 @@ struct GemmArgs {
     int partial_cap;                            // fp32 tiles it holds
 };
 
-// Workgroup barrier that orders LDS traffic for the compiler without the vmcnt(0) wait __syncthreads()
-// implies: tiles still in flight to LDS (tracked by vmcnt) must stay in flight across it.  Every wave
-// waits for the loads it needs (s_waitcnt vmcnt) itself before arriving.
-__device__ __forceinline__ void lds_barrier()
-{
-    asm volatile("" ::: "memory");
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
-}
-
-// One direct load: 16 bytes per lane, 1 KiB of LDS from dst on.
-template <int POLICY = 0>
-__device__ __forceinline__ void load_lds(const void* src, char* dst)
-{
-    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src, (__attribute__((address_space(3))) void*)dst, 16,
-                                     0, POLICY);
-}
-
 // A k tile's loads of weights, `step` bytes of LDS apart.  `streamed`: with the non-temporal hint, where the layer's weights do not
 // outlast a call in the memory-side cache anyway and one tile, or tiles side by side, read these: without it their lines push everything
 // else out of the caches on the way (with sc0 or sc1 besides: no change).
@@ -124,10 +106,6 @@ __device__ __forceinline__ void load_weights(bool streamed, const bf16_t* const*
         for (int i = 0; i < N; ++i) load_lds(src[i] + k, dst + i * step);
     }
 }
-
-// s_waitcnt immediates (gfx9 encoding: vmcnt in bits 3:0 and 15:14, expcnt 6:4, lgkmcnt 11:8).
-__host__ __device__ constexpr int vmcnt_imm(int n) { return (n & 0xF) | ((n >> 4) << 14) | 0x0F70; }       // vmcnt <= n
-__host__ __device__ constexpr int vmcnt_lgkm0_imm(int n) { return vmcnt_imm(n) & 0xF0FF; }                 // and lgkmcnt 0
 
 // Which tile a block works on.
 struct Tile {
@@ -889,15 +867,6 @@ __global__ void __launch_bounds__(512) ffn_gemm_ws_kernel(GemmArgs p)
         if (SWIGLU || wide_wins(n_lo, 64)) ws_block<64, 256, 2, 2, 3, SWIGLU>(p, n_lo, wide);
         else if constexpr (!SWIGLU) ws_block<64, 128, 2, 2, 5, SWIGLU>(p, n_lo, narrow);
     }
-}
-
-// Tells the compiler that a pointer is the same in every lane (keeps it in scalar registers).
-__device__ __forceinline__ const bf16_t* uniform_ptr(const bf16_t* ptr)
-{
-    const unsigned long long v = reinterpret_cast<unsigned long long>(ptr);
-    const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)v);
-    const unsigned hi = __builtin_amdgcn_readfirstlane((unsigned)(v >> 32));
-    return reinterpret_cast<const bf16_t*>(((unsigned long long)hi << 32) | lo);
 }
 
 // ------------------------------------------------------------------------------------------------
