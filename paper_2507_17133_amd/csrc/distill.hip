@@ -289,6 +289,14 @@ __global__ void __launch_bounds__(256, 2) distill_gemm_kernel(DGemm p)
     // A lane holds, for row wm*64 + 16 i + (lane & 15) of the tile, the columns wn*64 + 16 j + 4 (lane >> 4) + 0..3.
     const int r_l = wm * 64 + (lane & 15), c4 = 4 * (lane >> 4);
     const bool w_in = m0 + wm * 64 < J.M && (EPI == kSwiglu || n0 + wn * 64 < J.N);
+    // what kResidual and kBackward read, all of it in flight together; a tile outside the matrix reads the first one
+    const size_t at0 = w_in ? (size_t)(m0 + r_l) * J.N + n0 + wn * 64 + c4 : (size_t)(lane & 15) * J.N + c4;
+    auto fetch = [&](const float* from, f32x4 (&to)[4][4]) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) to[i][j] = *reinterpret_cast<const f32x4*>(from + at0 + (size_t)(i * 16) * J.N + j * 16);
+    };
     // bf16 results go through LDS: `rows` holds [tile row][tile column], `cols` [tile column][tile row]
     auto put_row = [&](char* img, int r, int c, const unsigned short (&v)[4]) {
         *reinterpret_cast<uint2*>(img + r * kImgPitch + c * 2) = pack4(v);
@@ -338,18 +346,18 @@ __global__ void __launch_bounds__(256, 2) distill_gemm_kernel(DGemm p)
         // r: mean teacher output (fp32 [n][d]), dY [n][d], dY^T [d][n] (null: loss only), loss partials [tiles]
         const float* tb = J.r[0].at<const float>(g);
         const bool store = J.r[1].p != nullptr;
+        f32x4 ts[4][4];
+        fetch(tb, ts);
         double s = 0.0;
 #pragma unroll
         for (int i = 0; i < 4; ++i)
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 const int r = r_l + i * 16, c = wn * 64 + j * 16 + c4;
-                f32x4 t = {0.f, 0.f, 0.f, 0.f};
-                if (w_in) t = *reinterpret_cast<const f32x4*>(tb + (size_t)(m0 + r) * J.N + n0 + c);
                 unsigned short v[4];
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
-                    const float df = acc[i][j][e] - t[e];
+                    const float df = acc[i][j][e] - ts[i][j][e];
                     v[e] = f_to_bf(df);
                     if (w_in) s += (double)df * (double)df;
                 }
@@ -368,17 +376,15 @@ __global__ void __launch_bounds__(256, 2) distill_gemm_kernel(DGemm p)
         // r: G, U (fp32 [n][F]), dG^T, dU^T [F][n].  dG = dA U sig(G) (1 + G (1 - sig(G))), dU = dA silu(G)
         const float* G = J.r[0].at<const float>(g);
         const float* U = J.r[1].at<const float>(g);
+        f32x4 gvs[4][4], uvs[4][4];
+        fetch(G, gvs);
+        fetch(U, uvs);
 #pragma unroll
         for (int i = 0; i < 4; ++i)
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 const int r = r_l + i * 16, c = wn * 64 + j * 16 + c4;
-                f32x4 gv = {0.f, 0.f, 0.f, 0.f}, uv = gv;
-                if (w_in) {
-                    const size_t at = (size_t)(m0 + r) * J.N + n0 + c;
-                    gv = *reinterpret_cast<const f32x4*>(G + at);
-                    uv = *reinterpret_cast<const f32x4*>(U + at);
-                }
+                const f32x4 gv = gvs[i][j], uv = uvs[i][j];
                 unsigned short dg[4], du[4];
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
