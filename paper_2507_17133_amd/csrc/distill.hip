@@ -139,25 +139,27 @@ struct Ref {                                              // a buffer of every g
     char* p; size_t stride;
     template <typename T> __device__ __forceinline__ T* at(int g) const { return reinterpret_cast<T*>(p + g * stride); }
 };
-enum { kSwiglu, kResidual, kBackward, kAdam };
+enum { kSwiglu, kResidual, kUpdate };                      // the kernels
+enum { kBackward, kAdam, kTranspose };                     // what a job of kUpdate is; kTranspose: r[0] = A transposed, no product
 struct DJob {
+    int kind;                                              // kUpdate only
     Ref A, B, B1;                                          // B1: kSwiglu only (B = W1, B1 = W3)
     int M, N, K;
-    int mt, nt;                                            // tiles
-    Ref r[5];                                              // see the epilogues
+    int mt, nt;                                            // tiles of a group
+    int chunk;                                             // an XCD's share of the tiles of all groups
+    Ref r[4];                                              // see the epilogues
 };
 struct DGemm {
-    DJob job[3];
-    int n_jobs, tiles;                                     // every job has the same number of tiles per group
-    int total;                                             // groups * jobs * tiles
+    DJob job[3];                                           // in the order in which their tiles are handed out
+    int n_jobs, groups;
     float gscale, lr, c1, c2;                              // kAdam
     int first;                                             // kAdam: no masters or moments yet
     Ref part, floor_; int n_part; double lscale; float* hist; size_t hist_stride;   // kBackward: the loss of this step
 };
 
 constexpr int kImgPitch = 272;                             // bytes per row of a 128 x 128 bf16 image in LDS
-// kAdam: per wave 32 rows x 64 columns of products (272 bytes a row) and a transposed bf16 image of its 64 x 64 (144 a column)
-constexpr int kAdamRow = 272, kAdamCol = 144, kAdamWave = 32 * kAdamRow + 64 * kAdamCol;
+// kAdam: per wave 32 rows x 64 columns of products
+constexpr int kAdamRow = 272, kAdamWave = 32 * kAdamRow;
 constexpr int kSlab = 128 * 128;                           // 128 rows of a k tile: two buffers of A rows and three of B rows in the k loop
 constexpr int kDgemmLds = 5 * kSlab;                       // two blocks share a CU's 160 KiB; the last 32 bytes: block_sum's
 static_assert(2 * 128 * kImgPitch <= kDgemmLds - 32 && 4 * kAdamWave <= kDgemmLds, "an epilogue's images take the place of the buffers");
@@ -177,13 +179,13 @@ __global__ void __launch_bounds__(256, 2) distill_gemm_kernel(DGemm p)
 {
     constexpr int BNC = EPI == kSwiglu ? 64 : 128;         // output columns of a tile
     extern __shared__ __attribute__((aligned(16))) char smem[];
-    // block id mod 8 is the XCD: a contiguous range of tiles each, super-tiles of 8 M tiles x all N tiles inside
-    const int chunk = (p.total + 7) >> 3;
-    const int L = (blockIdx.x & 7) * chunk + (blockIdx.x >> 3);
-    if ((int)(blockIdx.x >> 3) >= chunk || L >= p.total) return;
-    const int gj = L / p.tiles, tile = L - gj * p.tiles;
-    const int g = gj / p.n_jobs;
-    const DJob& J = p.job[gj - g * p.n_jobs];
+    // block id mod 8 is the XCD: of every job a contiguous range of tiles each, super-tiles of 8 M tiles x all N tiles inside
+    int at = blockIdx.x >> 3, jn = 0;
+    while (jn + 1 < p.n_jobs && at >= p.job[jn].chunk) at -= p.job[jn++].chunk;
+    const DJob& J = p.job[jn];
+    const int tiles = J.mt * J.nt, L = (blockIdx.x & 7) * J.chunk + at;
+    if (at >= J.chunk || L >= p.groups * tiles) return;
+    const int g = L / tiles, tile = L - g * tiles;
     const int gspan = 8 * J.nt, gi = tile / gspan, rem = tile - gi * gspan;
     const int gsz = min(8, J.mt - gi * 8);
     const int nt = rem / gsz, mt = gi * 8 + (rem - nt * gsz);
@@ -191,6 +193,34 @@ __global__ void __launch_bounds__(256, 2) distill_gemm_kernel(DGemm p)
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave >> 1, wn = wave & 1;
     const int K = J.K;
+
+    // image of R rows x C columns -> out[(row0 + r) * ld + col0 + c], 16 bytes per thread, rows < row_end, columns < col_end
+    auto flush = [&](const char* img, int R, int C, unsigned short* out, int ld, int row0, int row_end, int col0, int col_end) {
+        const int cpr = C >> 3;
+        for (int i = tid; i < R * cpr; i += 256) {
+            const int r = i / cpr, c = (i - r * cpr) * 8;
+            if (row0 + r < row_end && col0 + c < col_end)
+                *reinterpret_cast<uint4*>(out + (size_t)(row0 + r) * ld + col0 + c) =
+                    *reinterpret_cast<const uint4*>(img + r * kImgPitch + c * 2);
+        }
+    };
+    if (EPI == kUpdate && J.kind == kTranspose) {
+        const unsigned short* in = J.A.at<const unsigned short>(g);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const int r = wave * 32 + (i & 3) * 8 + (lane >> 3), c = (i >> 2) * 64 + (lane & 7) * 8;
+            if (m0 + r < J.M && n0 + c < J.N) {
+                const uint4 v = *reinterpret_cast<const uint4*>(in + (size_t)(m0 + r) * J.N + n0 + c);
+                const unsigned w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+                for (int e = 0; e < 8; ++e)
+                    *reinterpret_cast<unsigned short*>(smem + (c + e) * kImgPitch + r * 2) = (unsigned short)(w[e >> 1] >> (16 * (e & 1)));
+            }
+        }
+        __syncthreads();
+        flush(smem, 128, 128, J.r[0].at<unsigned short>(g), J.M, n0, J.N, m0, J.M);
+        return;
+    }
 
     // Wave w moves the 8-row groups w, w+4, ... of A and of B; 16-byte chunk c of row r sits in slot c ^ ((r/2)&7) (conflict-free
     // ds_read_b128), a term that is the same for all loads of a lane.  An address is a wave-uniform base and a lane offset.
@@ -305,16 +335,6 @@ __global__ void __launch_bounds__(256, 2) distill_gemm_kernel(DGemm p)
 #pragma unroll
         for (int e = 0; e < 4; ++e) *reinterpret_cast<unsigned short*>(img + (c + e) * kImgPitch + r * 2) = v[e];
     };
-    // image of R rows x C columns -> out[(row0 + r) * ld + col0 + c], 16 bytes per thread, rows < row_end, columns < col_end
-    auto flush = [&](const char* img, int R, int C, unsigned short* out, int ld, int row0, int row_end, int col0, int col_end) {
-        const int cpr = C >> 3;
-        for (int i = tid; i < R * cpr; i += 256) {
-            const int r = i / cpr, c = (i - r * cpr) * 8;
-            if (row0 + r < row_end && col0 + c < col_end)
-                *reinterpret_cast<uint4*>(out + (size_t)(row0 + r) * ld + col0 + c) =
-                    *reinterpret_cast<const uint4*>(img + r * kImgPitch + c * 2);
-        }
-    };
     char* rows = smem;
     char* cols = smem + 128 * kImgPitch;
 
@@ -372,7 +392,7 @@ __global__ void __launch_bounds__(256, 2) distill_gemm_kernel(DGemm p)
             flush(rows, 128, 128, J.r[1].at<unsigned short>(g), J.N, m0, J.M, n0, J.N);
             flush(cols, 128, 128, J.r[2].at<unsigned short>(g), J.M, n0, J.N, m0, J.M);
         }
-    } else if constexpr (EPI == kBackward) {
+    } else if (J.kind == kBackward) {
         // r: G, U (fp32 [n][F]), dG^T, dU^T [F][n].  dG = dA U sig(G) (1 + G (1 - sig(G))), dU = dA silu(G)
         const float* G = J.r[0].at<const float>(g);
         const float* U = J.r[1].at<const float>(g);
@@ -403,7 +423,7 @@ __global__ void __launch_bounds__(256, 2) distill_gemm_kernel(DGemm p)
             if (tid == 0) p.hist[g * p.hist_stride] = l;
         }
     } else {
-        // r: master, first and second moment (fp32 [M][N]), the bf16 copy [M][N], its transpose [N][M] or null.
+        // r: master, first and second moment (fp32 [M][N]), the bf16 copy [M][N].
         // Adam with bias correction; the first step starts from the bf16 copy and zero moments.  32 rows x 64 columns of products
         // at a time go through LDS of the wave's own, and a lane works on rows 4 q + (lane >> 4), columns 4 (lane & 15) + 0..3: 256
         // bytes of a row at a time, and the state of the next 16 rows is on its way meanwhile.
@@ -413,7 +433,6 @@ __global__ void __launch_bounds__(256, 2) distill_gemm_kernel(DGemm p)
         unsigned short* wb = J.r[3].at<unsigned short>(g);
         const float beta1 = 0.9f, beta2 = 0.999f, eps = 1e-8f;
         char* own = smem + wave * kAdamWave;
-        char* img = own + 32 * kAdamRow;
         const int cr = lane >> 4, cc = 4 * (lane & 15);
         const size_t at0 = (size_t)(m0 + wm * 64 + cr) * J.N + n0 + wn * 64 + cc;
         // (the first step by itself, so that the loads in flight can be counted)
@@ -466,10 +485,6 @@ __global__ void __launch_bounds__(256, 2) distill_gemm_kernel(DGemm p)
                         *reinterpret_cast<f32x4*>(Mo + at) = m;
                         *reinterpret_cast<f32x4*>(V + at) = v;
                         *reinterpret_cast<uint2*>(wb + at) = pack4(o);
-                        if (J.r[4].p)
-#pragma unroll
-                            for (int e = 0; e < 4; ++e)
-                                *reinterpret_cast<unsigned short*>(img + (cc + e) * kAdamCol + (rg * 32 + rl) * 2) = o[e];
                     }
 #pragma unroll
                     for (int q = 0; q < 4; ++q)
@@ -481,15 +496,6 @@ __global__ void __launch_bounds__(256, 2) distill_gemm_kernel(DGemm p)
         if (w_in) {
             if (p.first) update(std::true_type{});
             else update(std::false_type{});
-            if (J.r[4].p) {
-                wave_lds_order();
-                unsigned short* out = J.r[4].at<unsigned short>(g) + (size_t)(n0 + wn * 64) * J.M + m0 + wm * 64;
-#pragma unroll
-                for (int q = 0; q < 8; ++q) {
-                    const int c = q * 8 + (lane >> 3), r = 8 * (lane & 7);
-                    *reinterpret_cast<uint4*>(out + (size_t)c * J.M + r) = *reinterpret_cast<const uint4*>(img + c * kAdamCol + r * 2);
-                }
-            }
         }
     }
 }
@@ -497,13 +503,16 @@ __global__ void __launch_bounds__(256, 2) distill_gemm_kernel(DGemm p)
 template <int EPI>
 static hipError_t launch_dgemm(DGemm& p, int groups, hipStream_t s)
 {
+    int slots = 0;
     for (int j = 0; j < p.n_jobs; ++j) {
-        p.job[j].mt = ceil_div(p.job[j].M, 128);
-        p.job[j].nt = ceil_div(p.job[j].N, EPI == kSwiglu ? 64 : 128);
+        DJob& J = p.job[j];
+        J.mt = ceil_div(J.M, 128);
+        J.nt = ceil_div(J.N, EPI == kSwiglu ? 64 : 128);
+        J.chunk = ceil_div(groups * J.mt * J.nt, 8);
+        slots += J.chunk;
     }
-    p.tiles = p.job[0].mt * p.job[0].nt;
-    p.total = groups * p.n_jobs * p.tiles;
-    distill_gemm_kernel<EPI><<<ceil_div(p.total, 8) * 8, 256, kDgemmLds, s>>>(p);
+    p.groups = groups;
+    distill_gemm_kernel<EPI><<<slots * 8, 256, kDgemmLds, s>>>(p);
     return hipGetLastError();
 }
 
@@ -511,11 +520,9 @@ hipError_t init_distill_kernels()
 {
     const void* k[] = {reinterpret_cast<const void*>(distill_gemm_kernel<kSwiglu>),
                        reinterpret_cast<const void*>(distill_gemm_kernel<kResidual>),
-                       reinterpret_cast<const void*>(distill_gemm_kernel<kBackward>),
-                       reinterpret_cast<const void*>(distill_gemm_kernel<kAdam>)};
-    static_assert(kSwiglu == 0 && kResidual == 1 && kBackward == 2 && kAdam == 3, "the order above");
-    for (int i = 0; i < 4; ++i) {
-        const hipError_t e = hipFuncSetAttribute(k[i], hipFuncAttributeMaxDynamicSharedMemorySize, kDgemmLds);
+                       reinterpret_cast<const void*>(distill_gemm_kernel<kUpdate>)};
+    for (const void* f : k) {
+        const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, kDgemmLds);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
@@ -615,10 +622,10 @@ hipError_t distill_groups(const bf16_t* x, int n, int d, int F, int groups, bf16
     auto weight = [&](const bf16_t* w) { return Ref{reinterpret_cast<char*>(const_cast<bf16_t*>(w)), dF * 2}; };
     const Ref none{nullptr, 0}, X{reinterpret_cast<char*>(const_cast<bf16_t*>(x)), 0}, Xt{base + B.xt, 0};
     auto us = [](const void* p) { return static_cast<const unsigned short*>(p); };
-    auto job = [&](Ref a, Ref b, Ref b1, int M, int N, int K, Ref r0, Ref r1, Ref r2, Ref r3, Ref r4) {
+    auto job = [&](int kind, Ref a, Ref b, Ref b1, int M, int N, int K, Ref r0, Ref r1, Ref r2, Ref r3) {
         DJob j;
-        j.A = a; j.B = b; j.B1 = b1; j.M = M; j.N = N; j.K = K; j.mt = j.nt = 0;
-        j.r[0] = r0; j.r[1] = r1; j.r[2] = r2; j.r[3] = r3; j.r[4] = r4;
+        j.kind = kind; j.A = a; j.B = b; j.B1 = b1; j.M = M; j.N = N; j.K = K; j.mt = j.nt = j.chunk = 0;
+        j.r[0] = r0; j.r[1] = r1; j.r[2] = r2; j.r[3] = r3;
         return j;
     };
     transpose16_kernel<<<dim3(d / 64, n / 64, 1), 256, 0, s>>>(us(x), 0, reinterpret_cast<unsigned short*>(base + B.xt), 0, n, d);
@@ -638,27 +645,33 @@ hipError_t distill_groups(const bf16_t* x, int n, int d, int F, int groups, bf16
         p.hist = hist ? hist + t : nullptr; p.hist_stride = steps + 1;
         p.n_jobs = 1;
         p.job[0] = p.job[1] = p.job[2] =
-            job(X, weight(w1u), weight(w3u), n, F, d, ref(B.G), ref(B.U), ref(B.A), ref(B.At), none);
+            job(0, X, weight(w1u), weight(w3u), n, F, d, ref(B.G), ref(B.U), ref(B.A), ref(B.At));
         if ((e = launch_dgemm<kSwiglu>(p, groups, s)) != hipSuccess) return e;
-        p.job[0] = job(ref(B.A), weight(w2u), none, n, d, F, ref(B.tbar), train ? ref(B.dY) : none,
-                       train ? ref(B.dYt) : none, ref(B.part), none);
+        p.job[0] = job(0, ref(B.A), weight(w2u), none, n, d, F, ref(B.tbar), train ? ref(B.dY) : none,
+                       train ? ref(B.dYt) : none, ref(B.part));
         if ((e = launch_dgemm<kResidual>(p, groups, s)) != hipSuccess) return e;
         if (!train) {
             sum_partials_kernel<<<groups, 256, 0, s>>>(base + B.part, B.group, loss_tiles, base + B.floor_, B.group, p.lscale,
                                                        p.hist, p.hist_stride);
             return hipGetLastError();
         }
-        p.job[0] = job(ref(B.dY), ref(B.w2t), none, n, F, d, ref(B.G), ref(B.U), ref(B.dGt), ref(B.dUt), none);
-        if ((e = launch_dgemm<kBackward>(p, groups, s)) != hipSuccess) return e;
         b1t *= 0.9f;
         b2t *= 0.999f;
         p.c1 = (float)(1.0 / (1.0 - b1t));
         p.c2 = (float)(1.0 / (1.0 - b2t));
-        p.n_jobs = 3;
-        p.job[0] = job(ref(B.dGt), Xt, none, F, d, n, ref(B.W[0]), ref(B.M[0]), ref(B.V[0]), weight(w1u), none);
-        p.job[1] = job(ref(B.dUt), Xt, none, F, d, n, ref(B.W[1]), ref(B.M[1]), ref(B.V[1]), weight(w3u), none);
-        p.job[2] = job(ref(B.dYt), ref(B.At), none, d, F, n, ref(B.W[2]), ref(B.M[2]), ref(B.V[2]), weight(w2u), ref(B.w2t));
-        if ((e = launch_dgemm<kAdam>(p, groups, s)) != hipSuccess) return e;
+        auto adam = [&](int q, Ref a, Ref b, int M, int N, bf16_t* w) {
+            return job(kAdam, a, b, none, M, N, n, ref(B.W[q]), ref(B.M[q]), ref(B.V[q]), weight(w));
+        };
+        // W2 is updated beside the backward pass, which reads W2^T; that follows beside the update of W1 and W3
+        p.n_jobs = 2;
+        p.job[0] = adam(2, ref(B.dYt), ref(B.At), d, F, w2u);
+        p.job[1] = job(kBackward, ref(B.dY), ref(B.w2t), none, n, F, d, ref(B.G), ref(B.U), ref(B.dGt), ref(B.dUt));
+        if ((e = launch_dgemm<kUpdate>(p, groups, s)) != hipSuccess) return e;
+        p.n_jobs = t + 1 < steps ? 3 : 2;
+        p.job[0] = adam(0, ref(B.dGt), Xt, F, d, w1u);
+        p.job[1] = adam(1, ref(B.dUt), Xt, F, d, w3u);
+        p.job[2] = job(kTranspose, weight(w2u), none, none, d, F, 64, ref(B.w2t), none, none, none);
+        if ((e = launch_dgemm<kUpdate>(p, groups, s)) != hipSuccess) return e;
     }
     return hipSuccess;
 }
