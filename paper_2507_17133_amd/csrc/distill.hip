@@ -29,16 +29,9 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 
 __device__ __forceinline__ float bf_to_f(unsigned short b) { return __uint_as_float(((unsigned)b) << 16); }
-__device__ __forceinline__ unsigned short f_to_bf(float f)
-{
-    unsigned u = __float_as_uint(f);
-    u += 0x7FFFu + ((u >> 16) & 1u);
-    return (unsigned short)(u >> 16);
-}
-__device__ __forceinline__ uint2 pack4(const unsigned short (&v)[4])
-{
-    return make_uint2((unsigned)v[0] | ((unsigned)v[1] << 16), (unsigned)v[2] | ((unsigned)v[3] << 16));
-}
+__device__ __forceinline__ uint2 pack4(const float (&v)[4]) { return make_uint2(pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3])); }
+// 1 / (1 + e^-g) with the hardware reciprocal (1 ulp, less than __expf adds), one instruction for the ten of a division
+__device__ __forceinline__ float sigmoid(float g) { return __builtin_amdgcn_rcpf(1.0f + __expf(-g)); }
 
 // out[c][r] = in[r][c] (16-bit elements), R and C multiples of 64; blockIdx.z: group
 __global__ void __launch_bounds__(256) transpose16_kernel(const unsigned short* __restrict__ in, size_t in_stride,
@@ -328,12 +321,12 @@ __global__ void __launch_bounds__(256, 2) distill_gemm_kernel(DGemm p)
             for (int j = 0; j < 4; ++j) to[i][j] = *reinterpret_cast<const f32x4*>(from + at0 + (size_t)(i * 16) * J.N + j * 16);
     };
     // bf16 results go through LDS: `rows` holds [tile row][tile column], `cols` [tile column][tile row]
-    auto put_row = [&](char* img, int r, int c, const unsigned short (&v)[4]) {
-        *reinterpret_cast<uint2*>(img + r * kImgPitch + c * 2) = pack4(v);
-    };
-    auto put_col = [&](char* img, int r, int c, const unsigned short (&v)[4]) {
+    auto put_row = [&](char* img, int r, int c, uint2 v) { *reinterpret_cast<uint2*>(img + r * kImgPitch + c * 2) = v; };
+    auto put_col = [&](char* img, int r, int c, uint2 v) {
+        const unsigned w[2] = {v.x, v.y};
 #pragma unroll
-        for (int e = 0; e < 4; ++e) *reinterpret_cast<unsigned short*>(img + (c + e) * kImgPitch + r * 2) = v[e];
+        for (int e = 0; e < 4; ++e)
+            *reinterpret_cast<unsigned short*>(img + (c + e) * kImgPitch + r * 2) = (unsigned short)(w[e >> 1] >> (16 * (e & 1)));
     };
     char* rows = smem;
     char* cols = smem + 128 * kImgPitch;
@@ -348,11 +341,11 @@ __global__ void __launch_bounds__(256, 2) distill_gemm_kernel(DGemm p)
             for (int jp = 0; jp < 2; ++jp) {
                 const f32x4 gv = acc[i][2 * jp], uv = acc[i][2 * jp + 1];
                 const int r = r_l + i * 16, c = wn * 32 + jp * 16 + c4;
-                unsigned short a[4];
+                float a[4];
 #pragma unroll
-                for (int e = 0; e < 4; ++e) a[e] = f_to_bf(gv[e] / (1.0f + __expf(-gv[e])) * uv[e]);
-                put_row(rows, r, c, a);
-                put_col(cols, r, c, a);
+                for (int e = 0; e < 4; ++e) a[e] = gv[e] * sigmoid(gv[e]) * uv[e];
+                put_row(rows, r, c, pack4(a));
+                put_col(cols, r, c, pack4(a));
                 if (w_in) {
                     const size_t at = (size_t)(m0 + r) * J.N + n0 + c;
                     *reinterpret_cast<f32x4*>(G + at) = gv;
@@ -374,16 +367,16 @@ __global__ void __launch_bounds__(256, 2) distill_gemm_kernel(DGemm p)
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 const int r = r_l + i * 16, c = wn * 64 + j * 16 + c4;
-                unsigned short v[4];
+                float v[4];
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
                     const float df = acc[i][j][e] - ts[i][j][e];
-                    v[e] = f_to_bf(df);
+                    v[e] = df;
                     if (w_in) s += (double)df * (double)df;
                 }
                 if (store) {
-                    put_row(rows, r, c, v);
-                    put_col(cols, r, c, v);
+                    put_row(rows, r, c, pack4(v));
+                    put_col(cols, r, c, pack4(v));
                 }
             }
         const double t = block_sum(s, red);               // (its barrier also completes the images)
@@ -405,15 +398,15 @@ __global__ void __launch_bounds__(256, 2) distill_gemm_kernel(DGemm p)
             for (int j = 0; j < 4; ++j) {
                 const int r = r_l + i * 16, c = wn * 64 + j * 16 + c4;
                 const f32x4 gv = gvs[i][j], uv = uvs[i][j];
-                unsigned short dg[4], du[4];
+                float dg[4], du[4];
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
-                    const float da = acc[i][j][e], sg = 1.0f / (1.0f + __expf(-gv[e]));
-                    dg[e] = f_to_bf(da * uv[e] * sg * (1.0f + gv[e] * (1.0f - sg)));
-                    du[e] = f_to_bf(da * gv[e] * sg);
+                    const float da = acc[i][j][e], sg = sigmoid(gv[e]);
+                    dg[e] = da * uv[e] * sg * (1.0f + gv[e] * (1.0f - sg));
+                    du[e] = da * gv[e] * sg;
                 }
-                put_col(rows, r, c, dg);
-                put_col(cols, r, c, du);
+                put_col(rows, r, c, pack4(dg));
+                put_col(cols, r, c, pack4(du));
             }
         __syncthreads();
         flush(rows, 128, 128, J.r[2].at<unsigned short>(g), J.M, n0, J.N, m0, J.M);
@@ -472,14 +465,16 @@ __global__ void __launch_bounds__(256, 2) distill_gemm_kernel(DGemm p)
                         const size_t at = at0 + (size_t)(rg * 32 + ps * 16 + 4 * q) * J.N;
                         const f32x4 prod = *reinterpret_cast<const f32x4*>(own + rl * kAdamRow + cc * 4);
                         f32x4 &w = have[q][0], &m = have[q][1], &v = have[q][2];
-                        unsigned short o[4];
+                        float o[4];
 #pragma unroll
                         for (int e = 0; e < 4; ++e) {
                             const float gr = prod[e] * p.gscale;
                             m[e] = fmaf(beta1, m[e], (1.0f - beta1) * gr);
                             v[e] = fmaf(beta2, v[e], (1.0f - beta2) * gr * gr);
-                            w[e] = w[e] - p.lr * (m[e] * p.c1) / (sqrtf(v[e] * p.c2) + eps);
-                            o[e] = f_to_bf(w[e]);
+                            // hardware square root and reciprocal, 1 ulp each and 2 of the 25 instructions of the exact ones: the
+                            // rounding of the difference is the error of w (a denormal v counts as 0 beside eps)
+                            w[e] = w[e] - p.lr * (m[e] * p.c1) * __builtin_amdgcn_rcpf(__builtin_amdgcn_sqrtf(v[e] * p.c2) + eps);
+                            o[e] = w[e];
                         }
                         *reinterpret_cast<f32x4*>(W + at) = w;
                         *reinterpret_cast<f32x4*>(Mo + at) = m;

@@ -40,15 +40,6 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
-// two floats -> two bf16 (round to nearest even) in one 32-bit word, first value in the low half
-__device__ __forceinline__ unsigned pack_bf16(float lo, float hi)
-{
-    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-    typedef float f32x2 __attribute__((ext_vector_type(2)));
-    const f32x2 v = {lo, hi};
-    const bf16x2 b = __builtin_convertvector(v, bf16x2);
-    return __builtin_bit_cast(unsigned, b);
-}
 // Two floats -> two IEEE half values in one 32-bit word (round toward zero, so an overflow saturates at
 // the largest finite half instead of becoming infinite).  Y, the FFN output rows between GEMM2 and the
 // combine, is stored this way: the combine adds up rows of different experts that partly cancel, and with

@@ -138,6 +138,16 @@ __device__ __forceinline__ const bf16_t* uniform_ptr(const bf16_t* ptr)
     return reinterpret_cast<const bf16_t*>(((unsigned long long)hi << 32) | lo);
 }
 
+// two floats -> two bf16 (round to nearest even) in one 32-bit word, first value in the low half
+__device__ __forceinline__ unsigned pack_bf16(float lo, float hi)
+{
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    typedef float f32x2 __attribute__((ext_vector_type(2)));
+    const f32x2 v = {lo, hi};
+    const bf16x2 b = __builtin_convertvector(v, bf16x2);
+    return __builtin_bit_cast(unsigned, b);
+}
+
 // ---- routing (route.hip) ----
 struct TileJobs;
 // gate: fp32 [m][d] (D.gate_format MOE_GATE_FP32; split into gate_split on the way) or the packed pieces
