@@ -153,12 +153,13 @@ struct DGemm {
 constexpr int kImgPitch = 272;                             // bytes per row of a 128 x 128 bf16 image in LDS
 // kAdam: per wave 32 rows x 64 columns of products
 constexpr int kAdamRow = 272, kAdamWave = 32 * kAdamRow;
-constexpr int kSlab = 128 * 128;                           // 128 rows of a k tile: two buffers of A rows and three of B rows in the k loop
-constexpr int kDgemmLds = 5 * kSlab;                       // two blocks share a CU's 160 KiB; the last 32 bytes: block_sum's
-static_assert(2 * 128 * kImgPitch <= kDgemmLds - 32 && 4 * kAdamWave <= kDgemmLds, "an epilogue's images take the place of the buffers");
+// LDS bytes of a block with tiles of 32 FM rows of A by 32 FN rows of B: two buffers of A rows and three of B rows in the k loop; an
+// epilogue's images take their place, and the last 32 bytes are block_sum's.  Two blocks of the smaller tiles share a CU's 160 KiB.
+constexpr int dgemm_lds(int fm, int fn) { return (2 * fm + 3 * fn) * 32 * 128; }
+static_assert(2 * 128 * kImgPitch <= dgemm_lds(4, 4) - 32 && 4 * kAdamWave <= dgemm_lds(4, 4) && dgemm_lds(4, 4) <= 80 * 1024, "4 x 4");
 
-// 128 x 128 x 64 tiles, four waves (64 x 64 each, 16x16x32 MFMA), two blocks per CU.  A wave's 64 x 64 tile is either inside the matrix
-// or outside (M and N are multiples of 64).
+// Four waves, 16x16x32 MFMA, k tiles of 64: 128 x 128 tiles (64 x 64 a wave), two blocks per CU, or for kSwiglu 256 x 192 (128 x 96 a wave, the
+// accumulators in the accumulation registers), one block.  M and N are multiples of 64, so a 64 x 64 wave tile is inside the matrix or outside.
 // What bounds the k loop: 128 KiB of fragments and 64 KiB of tiles pass through the LDS per k tile of two blocks, 1536 cycles against 1024
 // of MFMAs, if nothing in a wave waits for anything else in it.  So the fragments of the next step of 16 MFMAs are read between the MFMAs of
 // this one, and direct global->LDS loads are issued one by one between them (all eight of a k tile in a row, then fragments, then MFMAs,
@@ -167,10 +168,12 @@ static_assert(2 * 128 * kImgPitch <= kDgemmLds - 32 && 4 * kAdamWave <= kDgemmLd
 // quarters into its first step, when a wave has read its last fragments of tile kt and its loads of tile kt+1 have landed; behind it come
 // the A rows of tile kt+2 into the buffer just left, then the B rows of tile kt+3.  Loads past the end of K are clamped to the last
 // k tile and never used.  Two groups at n = d = 2048, F = 1408: kSwiglu 77 -> 65 us, the call with 8 steps 3.37 -> 3.20 ms.
-template <int EPI>
-__global__ void __launch_bounds__(256, 2) distill_gemm_kernel(DGemm p)
+template <int EPI, int FM, int FN>
+__global__ void __launch_bounds__(256, FM * FN == 16 ? 2 : 1) distill_gemm_kernel(DGemm p)
 {
-    constexpr int BNC = EPI == kSwiglu ? 64 : 128;         // output columns of a tile
+    static_assert(EPI == kSwiglu || (FM == 4 && FN == 4), "the other epilogues are written for 128 x 128 tiles");
+    // rows of A and of B of a tile, its output columns, bytes of the two in a k tile
+    constexpr int BM = 32 * FM, BN = 32 * FN, BNC = EPI == kSwiglu ? BN / 2 : BN, kSlabA = BM * 128, kSlabB = BN * 128;
     extern __shared__ __attribute__((aligned(16))) char smem[];
     // block id mod 8 is the XCD: of every job a contiguous range of tiles each, super-tiles of 8 M tiles x all N tiles inside
     int at = blockIdx.x >> 3, jn = 0;
@@ -182,19 +185,19 @@ __global__ void __launch_bounds__(256, 2) distill_gemm_kernel(DGemm p)
     const int gspan = 8 * J.nt, gi = tile / gspan, rem = tile - gi * gspan;
     const int gsz = min(8, J.mt - gi * 8);
     const int nt = rem / gsz, mt = gi * 8 + (rem - nt * gsz);
-    const int m0 = mt * 128, n0 = nt * BNC;
+    const int m0 = mt * BM, n0 = nt * BNC;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave >> 1, wn = wave & 1;
     const int K = J.K;
 
     // image of R rows x C columns -> out[(row0 + r) * ld + col0 + c], 16 bytes per thread, rows < row_end, columns < col_end
-    auto flush = [&](const char* img, int R, int C, unsigned short* out, int ld, int row0, int row_end, int col0, int col_end) {
+    auto flush = [&](const char* img, int pitch, int R, int C, unsigned short* out, int ld, int row0, int row_end, int col0, int col_end) {
         const int cpr = C >> 3;
         for (int i = tid; i < R * cpr; i += 256) {
             const int r = i / cpr, c = (i - r * cpr) * 8;
             if (row0 + r < row_end && col0 + c < col_end)
                 *reinterpret_cast<uint4*>(out + (size_t)(row0 + r) * ld + col0 + c) =
-                    *reinterpret_cast<const uint4*>(img + r * kImgPitch + c * 2);
+                    *reinterpret_cast<const uint4*>(img + r * pitch + c * 2);
         }
     };
     if (EPI == kUpdate && J.kind == kTranspose) {
@@ -211,7 +214,7 @@ __global__ void __launch_bounds__(256, 2) distill_gemm_kernel(DGemm p)
             }
         }
         __syncthreads();
-        flush(smem, 128, 128, J.r[0].at<unsigned short>(g), J.M, n0, J.N, m0, J.M);
+        flush(smem, kImgPitch, 128, 128, J.r[0].at<unsigned short>(g), J.M, n0, J.N, m0, J.M);
         return;
     }
 
@@ -220,55 +223,72 @@ __global__ void __launch_bounds__(256, 2) distill_gemm_kernel(DGemm p)
     const int wave_s = __builtin_amdgcn_readfirstlane(wave);
     const int r8 = lane >> 3, csw = (lane & 7) ^ ((((wave & 1) << 2) + (r8 >> 1)) & 7);
     const unsigned off = (unsigned)(r8 * K * 2 + csw * 16);
-    const bf16_t *base_a[4], *base_b[4];
+    const bf16_t *base_a[FM], *base_b[FN];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int grp = wave_s + i * 4;                   // of 16
-        base_a[i] = uniform_ptr(J.A.at<const bf16_t>(g) + (size_t)min(m0 + grp * 8, J.M - 8) * K);
+    for (int i = 0; i < FM; ++i)
+        base_a[i] = uniform_ptr(J.A.at<const bf16_t>(g) + (size_t)min(m0 + (wave_s + i * 4) * 8, J.M - 8) * K);
+#pragma unroll
+    for (int i = 0; i < FN; ++i) {
+        const int grp = wave_s + i * 4;                   // of 4 FN
         // kSwiglu: the wave tile's 16-column MFMA tiles alternate W1 / W3 of the same 16 columns
-        const bool third = EPI == kSwiglu && ((grp >> 1) & 1);
-        const int col = EPI == kSwiglu ? n0 + (grp >> 3) * 32 + ((grp >> 2) & 1) * 16 + (grp & 1) * 8 : n0 + grp * 8;
+        const int half = grp / (2 * FN), j = (grp - half * 2 * FN) >> 1;
+        const bool third = EPI == kSwiglu && (j & 1);
+        const int col = EPI == kSwiglu ? n0 + half * (BN / 4) + (j >> 1) * 16 + (grp & 1) * 8 : n0 + grp * 8;
         base_b[i] = uniform_ptr((third ? J.B1 : J.B).at<const bf16_t>(g) + (size_t)min(col, J.N - 8) * K);
     }
     const int nk = K >> 6, last = nk - 1;
     auto load_a = [&](int i, int kt) {
         load_lds(reinterpret_cast<const char*>(base_a[i] + (size_t)min(kt, last) * 64) + off,
-                 smem + (kt & 1) * kSlab + (wave_s + i * 4) * 1024);
+                 smem + (kt & 1) * kSlabA + (wave_s + i * 4) * 1024);
     };
     auto load_b = [&](int i, int kt, int buf) {
         load_lds(reinterpret_cast<const char*>(base_b[i] + (size_t)min(kt, last) * 64) + off,
-                 smem + (2 + buf) * kSlab + (wave_s + i * 4) * 1024);
+                 smem + 2 * kSlabA + buf * kSlabB + (wave_s + i * 4) * 1024);
     };
-    const int a_off = (wm * 64 + (lane & 15)) * 128, b_off = 2 * kSlab + (wn * 64 + (lane & 15)) * 128;
+    const int a_off = (wm * (BM / 2) + (lane & 15)) * 128, b_off = 2 * kSlabA + (wn * (BN / 2) + (lane & 15)) * 128;
     const int swz = ((lane & 15) >> 1) & 7;
-    bf16x8 fa[2][4], fb[2][4];
+    bf16x8 fa[2][FM], fb[2][FN];
     auto read_a = [&](int buf, int half, int i) {
-        fa[half][i] = *reinterpret_cast<const bf16x8*>(smem + buf * kSlab + a_off + i * 2048 + (((half * 4 + (lane >> 4)) ^ swz) << 4));
+        fa[half][i] = *reinterpret_cast<const bf16x8*>(smem + buf * kSlabA + a_off + i * 2048 + (((half * 4 + (lane >> 4)) ^ swz) << 4));
     };
     auto read_b = [&](int buf, int half, int j) {
-        fb[half][j] = *reinterpret_cast<const bf16x8*>(smem + buf * kSlab + b_off + j * 2048 + (((half * 4 + (lane >> 4)) ^ swz) << 4));
+        fb[half][j] = *reinterpret_cast<const bf16x8*>(smem + buf * kSlabB + b_off + j * 2048 + (((half * 4 + (lane >> 4)) ^ swz) << 4));
     };
-    f32x4 acc[4][4];
+    f32x4 acc[FM][FN];
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < FM; ++i)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int j = 0; j < FN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    // large tiles: the accumulators stay in the accumulation registers
+    auto pin = [&]() {
+        if constexpr (FM * FN > 16) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) load_a(i, 0);
+            for (int i = 0; i < FM; ++i)
 #pragma unroll
-    for (int i = 0; i < 4; ++i) load_b(i, 0, 0);
+                for (int j = 0; j < FN; ++j) asm volatile("" : "+a"(acc[i][j]));
+        }
+    };
+    pin();
+    constexpr int NM = FM * FN, BAR = NM * 3 / 4;         // MFMAs of a step, and the barrier's place in the first step
+    // loads of a k tile (A rows of the next but one, then B rows of the one after that), MFMAs from one to the next (from the barrier on), and
+    // how many come before the next k tile
+    constexpr int LD = FM + FN, GAP = 2 * NM / LD, SL = (2 * NM - BAR + GAP - 1) / GAP;
+    static_assert((LD - 1) * GAP < 2 * NM && SL >= FM && SL <= LD && LD <= BAR, "loads end before the next ones begin, reads before the barrier");
 #pragma unroll
-    for (int i = 0; i < 4; ++i) load_a(i, 1);
+    for (int kt = 0; kt < 2; ++kt) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) load_b(i, 1, 1);
-    load_b(0, 2, 2);
-    __builtin_amdgcn_s_waitcnt(vmcnt_imm(9));             // tile 0 has landed, the nine younger loads are in flight
+        for (int i = 0; i < FM; ++i) load_a(i, kt);
+#pragma unroll
+        for (int i = 0; i < FN; ++i) load_b(i, kt, kt);
+    }
+#pragma unroll
+    for (int i = 0; i < SL - FM; ++i) load_b(i, 2, 2);
+    __builtin_amdgcn_s_waitcnt(vmcnt_imm(FN + SL));       // tile 0 has landed, the younger loads are in flight
     lds_barrier();
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        read_a(0, 0, i);
-        read_b(0, 0, i);
-    }
+    for (int j = 0; j < FN; ++j) read_b(0, 0, j);
+#pragma unroll
+    for (int i = 0; i < FM; ++i) read_a(0, 0, i);
     __builtin_amdgcn_s_waitcnt(0xC07F);
     int b_cur = 0;                                        // B buffer of tile kt (kt mod 3)
     for (int kt = 0; kt < nk; ++kt) {
@@ -276,27 +296,29 @@ __global__ void __launch_bounds__(256, 2) distill_gemm_kernel(DGemm p)
 #pragma unroll
         for (int st = 0; st < 2; ++st) {
 #pragma unroll
-            for (int mi = 0; mi < 16; ++mi) {
-                if (st == 0 && mi == 12) {
+            for (int mi = 0; mi < NM; ++mi) {
+                if (st == 0 && mi == BAR) {
                     // my reads of tile kt are done (its buffers may be refilled) and my loads of tile kt+1 have landed:
-                    // all but the four youngest, B rows of tile kt+2
+                    // all but the youngest, B rows of tile kt+2
                     __builtin_amdgcn_sched_barrier(0);
-                    __builtin_amdgcn_s_waitcnt(vmcnt_lgkm0_imm(4));
+                    __builtin_amdgcn_s_waitcnt(vmcnt_lgkm0_imm(FN));
                     lds_barrier();
                     __builtin_amdgcn_sched_barrier(0);
                 }
-                const int i = (mi >> 3) * 2 + (mi & 1), j = (mi & 7) >> 1;
+                const int i = mi / (2 * FN) * 2 + (mi & 1), j = mi % (2 * FN) >> 1;
                 acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[st][j], fa[st][i], acc[i][j], 0, 0, 0);
                 __builtin_amdgcn_sched_barrier(0);
-                if (mi < 8) {                             // fragments of the next step
-                    if (mi < 4) read_b(st == 0 ? b_cur : b_nxt, st ^ 1, mi);
-                    else read_a(st == 0 ? a_cur : a_cur ^ 1, st ^ 1, mi - 4);
+                constexpr int RG = FM * FN > 16 ? 2 : 1;  // fragments of the next step
+                if (mi % RG == 0 && mi / RG < LD) {
+                    const int r = mi / RG;
+                    if (r < FN) read_b(st == 0 ? b_cur : b_nxt, st ^ 1, r);
+                    else read_a(st == 0 ? a_cur : a_cur ^ 1, st ^ 1, r - FN);
                 }
-                if ((mi & 3) == 0) {
-                    if (st == 0 && mi < 12) load_b(1 + (mi >> 2), kt + 2, b_nn);
-                    if (st == 0 && mi == 12) load_a(0, kt + 2);
-                    if (st == 1 && mi < 12) load_a(1 + (mi >> 2), kt + 2);
-                    if (st == 1 && mi == 12) load_b(0, kt + 3, b_cur);
+                const int l = st == 0 ? mi < BAR ? mi + 2 * NM - BAR : mi - BAR : mi + NM - BAR;       // MFMAs since the barrier
+                if (l % GAP == 0 && l / GAP < LD) {
+                    if (st == 0 && mi < BAR) load_b(l / GAP - FM, kt + 2, b_nn);
+                    else if (l / GAP < FM) load_a(l / GAP, kt + 2);
+                    else load_b(l / GAP - FM, kt + 3, b_cur);
                 }
                 __builtin_amdgcn_sched_barrier(0);
             }
@@ -307,59 +329,62 @@ __global__ void __launch_bounds__(256, 2) distill_gemm_kernel(DGemm p)
     }
     __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));             // clamped loads still target this block's LDS
     lds_barrier();                                        // every wave has left the buffers: images go there
-    double* red = reinterpret_cast<double*>(smem + kDgemmLds - 32);
+    pin();
+    double* red = reinterpret_cast<double*>(smem + dgemm_lds(FM, FN) - 32);
 
-    // A lane holds, for row wm*64 + 16 i + (lane & 15) of the tile, the columns wn*64 + 16 j + 4 (lane >> 4) + 0..3.
-    const int r_l = wm * 64 + (lane & 15), c4 = 4 * (lane >> 4);
-    const bool w_in = m0 + wm * 64 < J.M && (EPI == kSwiglu || n0 + wn * 64 < J.N);
+    // A lane holds, for row wm*BM/2 + 16 i + (lane & 15) of the tile, the B rows wn*BN/2 + 16 j + 4 (lane >> 4) + 0..3.
+    const int r_l = wm * (BM / 2) + (lane & 15), c4 = 4 * (lane >> 4);
+    const bool w_in = m0 + wm * 64 < J.M && n0 + wn * 64 < J.N;            // (not kSwiglu)
     // what kResidual and kBackward read, all of it in flight together; a tile outside the matrix reads the first one
     const size_t at0 = w_in ? (size_t)(m0 + r_l) * J.N + n0 + wn * 64 + c4 : (size_t)(lane & 15) * J.N + c4;
-    auto fetch = [&](const float* from, f32x4 (&to)[4][4]) {
+    auto fetch = [&](const float* from, f32x4 (&to)[FM][FN]) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
+        for (int i = 0; i < FM; ++i)
 #pragma unroll
-            for (int j = 0; j < 4; ++j) to[i][j] = *reinterpret_cast<const f32x4*>(from + at0 + (size_t)(i * 16) * J.N + j * 16);
+            for (int j = 0; j < FN; ++j) to[i][j] = *reinterpret_cast<const f32x4*>(from + at0 + (size_t)(i * 16) * J.N + j * 16);
     };
     // bf16 results go through LDS: `rows` holds [tile row][tile column], `cols` [tile column][tile row]
-    auto put_row = [&](char* img, int r, int c, uint2 v) { *reinterpret_cast<uint2*>(img + r * kImgPitch + c * 2) = v; };
+    constexpr int kRowPitch = BNC * 2 + 16, kColPitch = BM * 2 + 16;
+    auto put_row = [&](char* img, int r, int c, uint2 v) { *reinterpret_cast<uint2*>(img + r * kRowPitch + c * 2) = v; };
     auto put_col = [&](char* img, int r, int c, uint2 v) {
         const unsigned w[2] = {v.x, v.y};
 #pragma unroll
         for (int e = 0; e < 4; ++e)
-            *reinterpret_cast<unsigned short*>(img + (c + e) * kImgPitch + r * 2) = (unsigned short)(w[e >> 1] >> (16 * (e & 1)));
+            *reinterpret_cast<unsigned short*>(img + (c + e) * kColPitch + r * 2) = (unsigned short)(w[e >> 1] >> (16 * (e & 1)));
     };
     char* rows = smem;
-    char* cols = smem + 128 * kImgPitch;
+    char* cols = smem + (EPI == kSwiglu ? BM * kRowPitch : 128 * kImgPitch);
+    static_assert(EPI != kSwiglu || BM * kRowPitch + BNC * kColPitch <= dgemm_lds(FM, FN), "both images");
 
     if constexpr (EPI == kSwiglu) {
         // r: G, U (fp32 [n][F]), A [n][F], A^T [F][n]
         float* G = J.r[0].at<float>(g);
         float* U = J.r[1].at<float>(g);
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
+        for (int i = 0; i < FM; ++i)
 #pragma unroll
-            for (int jp = 0; jp < 2; ++jp) {
+            for (int jp = 0; jp < FN / 2; ++jp) {
                 const f32x4 gv = acc[i][2 * jp], uv = acc[i][2 * jp + 1];
-                const int r = r_l + i * 16, c = wn * 32 + jp * 16 + c4;
+                const int r = r_l + i * 16, c = wn * (BNC / 2) + jp * 16 + c4;
                 float a[4];
 #pragma unroll
                 for (int e = 0; e < 4; ++e) a[e] = gv[e] * sigmoid(gv[e]) * uv[e];
                 put_row(rows, r, c, pack4(a));
                 put_col(cols, r, c, pack4(a));
-                if (w_in) {
+                if (m0 + wm * (BM / 2) + i * 16 < J.M && n0 + wn * (BNC / 2) + jp * 16 < J.N) {
                     const size_t at = (size_t)(m0 + r) * J.N + n0 + c;
                     *reinterpret_cast<f32x4*>(G + at) = gv;
                     *reinterpret_cast<f32x4*>(U + at) = uv;
                 }
             }
         __syncthreads();
-        flush(rows, 128, 64, J.r[2].at<unsigned short>(g), J.N, m0, J.M, n0, J.N);
-        flush(cols, 64, 128, J.r[3].at<unsigned short>(g), J.M, n0, J.N, m0, J.M);
+        flush(rows, kRowPitch, BM, BNC, J.r[2].at<unsigned short>(g), J.N, m0, J.M, n0, J.N);
+        flush(cols, kColPitch, BNC, BM, J.r[3].at<unsigned short>(g), J.M, n0, J.N, m0, J.M);
     } else if constexpr (EPI == kResidual) {
         // r: mean teacher output (fp32 [n][d]), dY [n][d], dY^T [d][n] (null: loss only), loss partials [tiles]
         const float* tb = J.r[0].at<const float>(g);
         const bool store = J.r[1].p != nullptr;
-        f32x4 ts[4][4];
+        f32x4 ts[FM][FN];
         fetch(tb, ts);
         double s = 0.0;
 #pragma unroll
@@ -382,14 +407,14 @@ __global__ void __launch_bounds__(256, 2) distill_gemm_kernel(DGemm p)
         const double t = block_sum(s, red);               // (its barrier also completes the images)
         if (tid == 0) J.r[3].at<double>(g)[tile] = t;
         if (store) {
-            flush(rows, 128, 128, J.r[1].at<unsigned short>(g), J.N, m0, J.M, n0, J.N);
-            flush(cols, 128, 128, J.r[2].at<unsigned short>(g), J.M, n0, J.N, m0, J.M);
+            flush(rows, kImgPitch, 128, 128, J.r[1].at<unsigned short>(g), J.N, m0, J.M, n0, J.N);
+            flush(cols, kImgPitch, 128, 128, J.r[2].at<unsigned short>(g), J.M, n0, J.N, m0, J.M);
         }
     } else if (J.kind == kBackward) {
         // r: G, U (fp32 [n][F]), dG^T, dU^T [F][n].  dG = dA U sig(G) (1 + G (1 - sig(G))), dU = dA silu(G)
         const float* G = J.r[0].at<const float>(g);
         const float* U = J.r[1].at<const float>(g);
-        f32x4 gvs[4][4], uvs[4][4];
+        f32x4 gvs[FM][FN], uvs[FM][FN];
         fetch(G, gvs);
         fetch(U, uvs);
 #pragma unroll
@@ -409,8 +434,8 @@ __global__ void __launch_bounds__(256, 2) distill_gemm_kernel(DGemm p)
                 put_col(cols, r, c, pack4(du));
             }
         __syncthreads();
-        flush(rows, 128, 128, J.r[2].at<unsigned short>(g), J.M, n0, J.N, m0, J.M);
-        flush(cols, 128, 128, J.r[3].at<unsigned short>(g), J.M, n0, J.N, m0, J.M);
+        flush(rows, kImgPitch, 128, 128, J.r[2].at<unsigned short>(g), J.M, n0, J.N, m0, J.M);
+        flush(cols, kImgPitch, 128, 128, J.r[3].at<unsigned short>(g), J.M, n0, J.N, m0, J.M);
         if (tile == 0 && p.hist != nullptr) {
             const float l = sum_partials(p.part.at<const double>(g), p.n_part, *p.floor_.at<const float>(g), p.lscale, red);
             if (tid == 0) p.hist[g * p.hist_stride] = l;
@@ -495,31 +520,46 @@ __global__ void __launch_bounds__(256, 2) distill_gemm_kernel(DGemm p)
     }
 }
 
-template <int EPI>
+template <int EPI, int FM = 4, int FN = 4>
 static hipError_t launch_dgemm(DGemm& p, int groups, hipStream_t s)
 {
     int slots = 0;
     for (int j = 0; j < p.n_jobs; ++j) {
         DJob& J = p.job[j];
-        J.mt = ceil_div(J.M, 128);
-        J.nt = ceil_div(J.N, EPI == kSwiglu ? 64 : 128);
+        J.mt = ceil_div(J.M, FM * 32);
+        J.nt = ceil_div(J.N, FN * (EPI == kSwiglu ? 16 : 32));
         J.chunk = ceil_div(groups * J.mt * J.nt, 8);
         slots += J.chunk;
     }
     p.groups = groups;
-    distill_gemm_kernel<EPI><<<slots * 8, 256, kDgemmLds, s>>>(p);
+    distill_gemm_kernel<EPI, FM, FN><<<slots * 8, 256, dgemm_lds(FM, FN), s>>>(p);
     return hipGetLastError();
+}
+
+// kSwiglu in tiles of 256 x 192 or of 128 x 128: what takes less time by rounds of one or two blocks on 256 CUs (a last round of at most one of the
+// small tiles is shorter).  In us at K = 2048, epilogue included, a round of the large ones takes 48, of two small ones 37 and of one 27: two
+// groups of 2048 tokens at F = 1408 are 240 large tiles in 49 us or 704 small ones in 63.  Per MFMA a large tile passes 3/4 of the bytes through
+// the LDS and 7/12 through the L1.  (The other three epilogues lose more as one block on a CU than their loop gains: kResidual at 256 x 128 37 -> 39
+// us, the launch with kBackward at 256 x 192 87 -> 116.)
+static bool large_swiglu(int M, int N, int groups)
+{
+    const int64_t small = (int64_t)groups * ceil_div(M, 128) * ceil_div(N, 64), large = (int64_t)groups * ceil_div(M, 256) * ceil_div(N, 96);
+    const int64_t rest = small % 512;
+    return (large + 255) / 256 * 48 < small / 512 * 37 + (rest > 256 ? 37 : rest > 0 ? 27 : 0);
+}
+
+template <int EPI, int FM = 4, int FN = 4>
+static hipError_t init_dgemm()
+{
+    return hipFuncSetAttribute(reinterpret_cast<const void*>(distill_gemm_kernel<EPI, FM, FN>), hipFuncAttributeMaxDynamicSharedMemorySize,
+                               dgemm_lds(FM, FN));
 }
 
 hipError_t init_distill_kernels()
 {
-    const void* k[] = {reinterpret_cast<const void*>(distill_gemm_kernel<kSwiglu>),
-                       reinterpret_cast<const void*>(distill_gemm_kernel<kResidual>),
-                       reinterpret_cast<const void*>(distill_gemm_kernel<kUpdate>)};
-    for (const void* f : k) {
-        const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, kDgemmLds);
-        if (e != hipSuccess) return e;
-    }
+    const hipError_t e[] = {init_dgemm<kSwiglu>(), init_dgemm<kSwiglu, 8, 6>(), init_dgemm<kResidual>(), init_dgemm<kUpdate>()};
+    for (hipError_t x : e)
+        if (x != hipSuccess) return x;
     return hipSuccess;
 }
 
@@ -641,7 +681,8 @@ hipError_t distill_groups(const bf16_t* x, int n, int d, int F, int groups, bf16
         p.n_jobs = 1;
         p.job[0] = p.job[1] = p.job[2] =
             job(0, X, weight(w1u), weight(w3u), n, F, d, ref(B.G), ref(B.U), ref(B.A), ref(B.At));
-        if ((e = launch_dgemm<kSwiglu>(p, groups, s)) != hipSuccess) return e;
+        e = large_swiglu(n, F, groups) ? launch_dgemm<kSwiglu, 8, 6>(p, groups, s) : launch_dgemm<kSwiglu>(p, groups, s);
+        if (e != hipSuccess) return e;
         p.job[0] = job(0, ref(B.A), weight(w2u), none, n, d, F, ref(B.tbar), train ? ref(B.dY) : none,
                        train ? ref(B.dYt) : none, ref(B.part));
         if ((e = launch_dgemm<kResidual>(p, groups, s)) != hipSuccess) return e;
