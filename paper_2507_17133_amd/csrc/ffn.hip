@@ -80,6 +80,7 @@ struct GemmArgs {
     int ksplit; long plane;                     // GEMM2 only: K split into ksplit slices, slice s writes out + s*plane
     float* partial;                             // four-wave kernel, ksplit 1: scratch of the K-split tail (or null)
     int partial_cap;                            // fp32 tiles it holds
+    int split;                                  // its left-over tiles may be cut along K (the sum of the slices is launched behind it)
 };
 
 // A k tile's loads of weights, `step` bytes of LDS apart.  `streamed`: with the non-temporal hint, where the layer's weights do not
@@ -902,9 +903,9 @@ __host__ __device__ inline int tail_split(int G, int rem, int nk_all)
 
 // Left-over tiles that are not cut along K: when there are at most G/2 of them, each is cut in two along N
 // instead (two blocks, 256 rows x half the columns each: no partial sums, half a tile time).
-__host__ __device__ inline bool tail_halves(int G, int rem, int nk_all)
+__host__ __device__ inline bool tail_halves(int G, int rem, int nk_all, int sl)
 {
-    return rem > 0 && 2 * rem <= G && nk_all >= 8 && tail_split(G, rem, nk_all) == 1;
+    return rem > 0 && 2 * rem <= G && nk_all >= 8 && sl == 1;
 }
 
 // What a block of the persistent kernel needs to know about the launch as a whole: computed once per block
@@ -931,8 +932,8 @@ __device__ __forceinline__ Sched make_sched(const GemmArgs& p, int slots)
         sc.t_full = sc.tiles / G * G;
         sc.chunk = sc.t_full >> 3;
         sc.rem = sc.tiles - sc.t_full;
-        sc.sl = tail_split(G, sc.rem, p.K / 64);
-        sc.halves = tail_halves(G, sc.rem, p.K / 64) ? 1 : 0;
+        sc.sl = p.split ? tail_split(G, sc.rem, p.K / 64) : 1;
+        sc.halves = tail_halves(G, sc.rem, p.K / 64, sc.sl) ? 1 : 0;
     }
     return sc;
 }
@@ -1321,14 +1322,14 @@ __device__ __forceinline__ void w4_block(const GemmArgs& p, const int block, con
 }
 
 // One launch: G blocks (one per CU) for the whole tiles and, where the left-over tiles may be cut (p.partial
-// set), 2 G more behind them: G for column halves, G for K slices.  They are independent work, so a CU
+// set), G more behind them for column halves and, where they may be cut along K, G for K slices.  They are independent work, so a CU
 // picks one up as soon as its block of whole tiles is done; a launch uses at most one of the two kinds
 // (only the device knows which), the blocks of the other return at once.  Block id mod 8 is the XCD in all
-// three ranges (G is a multiple of 8).
+// all ranges (G is a multiple of 8).
 template <bool SWIGLU>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) ffn_gemm_w4_kernel(GemmArgs p)
 {
-    const int g = p.partial != nullptr ? (int)gridDim.x / 3 : (int)gridDim.x;
+    const int g = p.partial == nullptr ? (int)gridDim.x : (int)gridDim.x / (p.split ? 3 : 2);
     const int b = blockIdx.x;
     if (b < g) w4_block<SWIGLU, 0>(p, b, g);
     else if (b < 2 * g) w4_block<SWIGLU, 2>(p, b - g, g);
@@ -1499,6 +1500,7 @@ enum GemmKind { kSmall32, kSmall64, kSmallEither, kNarrow32, kNarrow64, kNarrowE
 struct GemmLaunch {
     GemmArgs a;
     int max_mtiles;                              // M tiles there can be at most
+    int known_mtiles;                            // M tiles where every unit holds all tokens, else -1
     GemmKind kind;
 };
 
@@ -1539,8 +1541,15 @@ static hipError_t launch_gemm(const GemmLaunch& l, int n_cu, hipStream_t s)
             const int blocks = (int)std::min<long>((total + 7) / 8 * 8, std::max(8, n_cu / 8 * 8));
             const int max_tail = (int)std::min<long>(total, blocks - 1);
             if (a.ksplit != 1 || blocks > a.partial_cap || max_tail <= 0) a.partial = nullptr;
-            ffn_gemm_w4_kernel<SWIGLU><<<a.partial ? 3 * blocks : blocks, 256, kW4Lds, s>>>(a);
-            if (a.partial == nullptr) break;
+            // Blocks and a sum (4.8 us) for K slices only where some number of left-over tiles, or the one there is going to be, would be
+            // cut: never with K < 1024, and not in 4 of 5 launches of calibration batches and shared experts.  Layer forward, 8192 tokens
+            // of the Qwen3 shape (GEMM2: K 768) 615 -> 612 us, 5003 of the 60-expert shape (the shared expert's two) 488 -> 480.
+            const int rem = l.known_mtiles >= 0 ? (int)((long)l.known_mtiles * a.n_ntiles % blocks) : 0;
+            a.split = 0;
+            for (int r = rem ? rem : 1; a.partial && a.K >= 1024 && !a.split && r <= (l.known_mtiles >= 0 ? rem : max_tail); ++r)
+                a.split = tail_split(blocks, r, a.K / 64) > 1;
+            ffn_gemm_w4_kernel<SWIGLU><<<a.partial ? (a.split ? 3 : 2) * blocks : blocks, 256, kW4Lds, s>>>(a);
+            if (!a.split) break;
             const hipError_t e = hipGetLastError();
             if (e != hipSuccess) return e;
             gemm_tail_sum_kernel<SWIGLU><<<std::min(max_tail * 64, 2048), 256, 0, s>>>(a, blocks);
@@ -1613,10 +1622,11 @@ hipError_t launch_ffn(const Dims& D, const FfnProblem* problems, int n_problems,
         }
         g.n_ntiles = 0;                           // set at the launch from the kernel's tile width
         g.group_m = tuning().group_m ? tuning().group_m : (bm == 256 ? 8 : 4);
-        g.partial = partial; g.partial_cap = D.tail_blocks;
+        g.partial = partial; g.partial_cap = D.tail_blocks; g.split = 0;
         // M tiles there can be at most: a unit that holds rows has one for every bm of them and a ragged one, and no more
         // units hold rows than there are rows
         l.max_mtiles = (int)std::min<int64_t>(D.row_cap / (lo ? lo : bm) + std::min<int64_t>(P.units.n, D.row_cap), D.tile_cap);
+        l.known_mtiles = P.units.entries == 0 ? P.units.even * ceil_div(D.T, bm) : -1;
         // M tiles to expect when no unit is browned out (united units take rows from the experts).  Chooses the kernel, the grid
         // is sized for max_mtiles: tiles of 64 or 32 rows whose 256-column blocks would not give every CU one go to the narrow
         // kernel.
