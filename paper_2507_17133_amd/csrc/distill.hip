@@ -146,7 +146,7 @@ struct DGemm {
     DJob job[3];                                           // in the order in which their tiles are handed out
     int n_jobs, groups;
     float gscale, lr, c1, c2;                              // kAdam
-    int first;                                             // kAdam: no masters or moments yet
+    int first, last;                                       // kAdam: no masters or moments yet; none are read again
     Ref part, floor_; int n_part; double lscale; float* hist; size_t hist_stride;   // kBackward: the loss of this step
 };
 
@@ -453,8 +453,8 @@ __global__ void __launch_bounds__(256, FM * FN == 16 ? 2 : 1) distill_gemm_kerne
         char* own = smem + wave * kAdamWave;
         const int cr = lane >> 4, cc = 4 * (lane & 15);
         const size_t at0 = (size_t)(m0 + wm * 64 + cr) * J.N + n0 + wn * 64 + cc;
-        // (the first step by itself, so that the loads in flight can be counted)
-        auto update = [&](auto first) {
+        // (the first and the last step by themselves, so that the loads in flight can be counted; behind the last one nothing reads the state)
+        auto update = [&](auto first, auto last_step) {
             f32x4 have[4][3], next[4][3];
             auto fetch = [&](int row, f32x4 (&to)[4][3]) {
 #pragma unroll
@@ -501,9 +501,11 @@ __global__ void __launch_bounds__(256, FM * FN == 16 ? 2 : 1) distill_gemm_kerne
                             w[e] = w[e] - p.lr * (m[e] * p.c1) * __builtin_amdgcn_rcpf(__builtin_amdgcn_sqrtf(v[e] * p.c2) + eps);
                             o[e] = w[e];
                         }
-                        *reinterpret_cast<f32x4*>(W + at) = w;
-                        *reinterpret_cast<f32x4*>(Mo + at) = m;
-                        *reinterpret_cast<f32x4*>(V + at) = v;
+                        if constexpr (!decltype(last_step)::value) {
+                            *reinterpret_cast<f32x4*>(W + at) = w;
+                            *reinterpret_cast<f32x4*>(Mo + at) = m;
+                            *reinterpret_cast<f32x4*>(V + at) = v;
+                        }
                         *reinterpret_cast<uint2*>(wb + at) = pack4(o);
                     }
 #pragma unroll
@@ -514,8 +516,9 @@ __global__ void __launch_bounds__(256, FM * FN == 16 ? 2 : 1) distill_gemm_kerne
             }
         };
         if (w_in) {
-            if (p.first) update(std::true_type{});
-            else update(std::false_type{});
+            if (p.first) update(std::true_type{}, std::false_type{});
+            else if (p.last) update(std::false_type{}, std::true_type{});
+            else update(std::false_type{}, std::false_type{});
         }
     }
 }
@@ -675,7 +678,7 @@ hipError_t distill_groups(const bf16_t* x, int n, int d, int F, int groups, bf16
         const bool train = t < steps;
         if (!train && hist == nullptr) break;
         DGemm p;
-        p.gscale = 2.0f / (float)n; p.lr = lr; p.c1 = p.c2 = 1.0f; p.first = t == 0 ? 1 : 0;
+        p.gscale = 2.0f / (float)n; p.lr = lr; p.c1 = p.c2 = 1.0f; p.first = t == 0 ? 1 : 0; p.last = t + 1 == steps ? 1 : 0;
         p.part = ref(B.part); p.floor_ = ref(B.floor_); p.n_part = loss_tiles; p.lscale = (double)(1.0f / (float)n);
         p.hist = hist ? hist + t : nullptr; p.hist_stride = steps + 1;
         p.n_jobs = 1;
