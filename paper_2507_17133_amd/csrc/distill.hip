@@ -6,17 +6,19 @@
 //   forward   G = X W1^T, U = X W3^T, A = silu(G) U, Y = A W2^T
 //   backward  dY = Y - mean_i Y_i  (the factor 2/n goes into the update), dW2 = dY^T A, dA = dY W2,
 //             dG = dA U silu'(G), dU = dA silu(G), dW1 = dG^T X, dW3 = dU^T X
-// A step is four launches of one GEMM kernel with four epilogues, over several groups at a time (the groups are
-// independent and one of a small model does not fill the chip):
-//   kSwiglu  G, U, A and A^T            kResidual  dY, dY^T and the loss        (Y is not stored)
-//   kBackward  dG^T, dU^T (dA is not stored; the loss of the step is summed up on the way)
-//   kAdam  the three gradients stay in registers: masters, moments, the bf16 copies and W2^T are updated there
+// A step is four launches of one GEMM kernel, over several groups at a time (the groups are independent and one of a small model
+// does not fill the chip):
+//   kSwiglu    G, U, A and A^T          kResidual  dY, dY^T and the loss        (Y is not stored)
+//   kUpdate    kAdam of W2 beside kBackward: dG^T, dU^T (dA is not stored; the loss of the step is summed up on the way)
+//   kUpdate    kAdam of W1 and W3, and the new W2 transposed, which the backward pass beside W2's update may not see yet
+// kAdam: the gradients stay in registers, masters, moments and the bf16 copies are updated there.
 // The contractions over tokens read K-contiguous operands that the earlier epilogues have written transposed.
 // Why: with each of these as a pass of its own (64-row GEMM tiles with fp32 results, transposes, SwiGLU, Adam, the loss
 // summed by one block) a pass over two groups of 8 and 4 teachers at n = d = 2048, F = 1408 with 8 steps took 56.9 ms,
-// 50 of them in the one-block sums and 3.4 in the GEMMs; now 3.4 ms.  Of those a step's four launches take 0.36 ms
-// (kSwiglu 80 us, kResidual 47, kBackward 59, kAdam 170 of which 484 MB of masters and moments are 94 us at the rate
-// of a large copy; 197 while its epilogue read and wrote them in pieces of 64 bytes).
+// 50 of them in the one-block sums and 3.4 in the GEMMs; now 2.8 ms.  Of those a step's four launches take 0.27 ms
+// (kSwiglu 49 us, kResidual 36, kBackward with W2 88, W1 and W3 94; the 484 MB of masters and moments alone are 94 us at the rate of a large
+// copy).  With the loads, fragment reads and MFMAs of a k tile one after the other, and W2 updated with W1 and W3, they took 0.35
+// (77, 43, 57 and 160).
 #include "internal.h"
 
 #include <algorithm>
