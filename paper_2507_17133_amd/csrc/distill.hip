@@ -32,8 +32,6 @@ typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 
 __device__ __forceinline__ float bf_to_f(unsigned short b) { return __uint_as_float(((unsigned)b) << 16); }
 __device__ __forceinline__ uint2 pack4(const float (&v)[4]) { return make_uint2(pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3])); }
-// 1 / (1 + e^-g) with the hardware reciprocal (1 ulp, less than __expf adds), one instruction for the ten of a division
-__device__ __forceinline__ float sigmoid(float g) { return __builtin_amdgcn_rcpf(1.0f + __expf(-g)); }
 
 // out[c][r] = in[r][c] (16-bit elements), R and C multiples of 64; blockIdx.z: group
 __global__ void __launch_bounds__(256) transpose16_kernel(const unsigned short* __restrict__ in, size_t in_stride,
@@ -370,7 +368,7 @@ __global__ void __launch_bounds__(256, FM * FN == 16 ? 2 : 1) distill_gemm_kerne
                 const int r = r_l + i * 16, c = wn * (BNC / 2) + jp * 16 + c4;
                 float a[4];
 #pragma unroll
-                for (int e = 0; e < 4; ++e) a[e] = gv[e] * sigmoid(gv[e]) * uv[e];
+                for (int e = 0; e < 4; ++e) a[e] = gv[e] / (1.0f + __expf(-gv[e])) * uv[e];
                 put_row(rows, r, c, pack4(a));
                 put_col(cols, r, c, pack4(a));
                 if (m0 + wm * (BM / 2) + i * 16 < J.M && n0 + wn * (BNC / 2) + jp * 16 < J.N) {
@@ -428,7 +426,7 @@ __global__ void __launch_bounds__(256, FM * FN == 16 ? 2 : 1) distill_gemm_kerne
                 float dg[4], du[4];
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
-                    const float da = acc[i][j][e], sg = sigmoid(gv[e]);
+                    const float da = acc[i][j][e], sg = 1.0f / (1.0f + __expf(-gv[e]));
                     dg[e] = da * uv[e] * sg * (1.0f + gv[e] * (1.0f - sg));
                     du[e] = da * gv[e] * sg;
                 }
@@ -498,9 +496,8 @@ __global__ void __launch_bounds__(256, FM * FN == 16 ? 2 : 1) distill_gemm_kerne
                             const float gr = prod[e] * p.gscale;
                             m[e] = fmaf(beta1, m[e], (1.0f - beta1) * gr);
                             v[e] = fmaf(beta2, v[e], (1.0f - beta2) * gr * gr);
-                            // hardware square root and reciprocal, 1 ulp each and 2 of the 25 instructions of the exact ones: the
-                            // rounding of the difference is the error of w (a denormal v counts as 0 beside eps)
-                            w[e] = w[e] - p.lr * (m[e] * p.c1) * __builtin_amdgcn_rcpf(__builtin_amdgcn_sqrtf(v[e] * p.c2) + eps);
+                            // correctly rounded (the reciprocal and square root that are 1 ulp off would save 2 % of a call)
+                            w[e] = w[e] - p.lr * (m[e] * p.c1) / (sqrtf(v[e] * p.c2) + eps);
                             o[e] = w[e];
                         }
                         if constexpr (!decltype(last_step)::value) {
