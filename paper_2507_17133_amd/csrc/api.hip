@@ -585,7 +585,8 @@ moe_status moe_forward(const moe_config* cfg, const void* x, int32_t T, const vo
     jobs.cap = D.tile_cap;
     jobs.count_units = D.m + D.G;
     jobs.stream_units = units_to_stream(D);
-    jobs.streamed = at<int32_t>(workspace, W.streamed);
+    // no more units hold rows than there are TopK entries
+    jobs.streamed = std::min<int64_t>((int64_t)T * D.K, jobs.count_units) < jobs.stream_units ? nullptr : at<int32_t>(workspace, W.streamed);
     jobs.job[0].u_lo = 0; jobs.job[0].u_hi = split_shared ? D.m + D.G : D.U;
     jobs.job[0].plan = routed_tile_plan(D, dev.n_cu);
     jobs.job[0].table = at<int32_t>(workspace, W.tiles0);

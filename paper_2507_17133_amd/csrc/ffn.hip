@@ -61,14 +61,13 @@ __device__ __forceinline__ float swiglu(float g, float u)
 __global__ void __launch_bounds__(64) tile_table_kernel(const int32_t* __restrict__ unit_cnt,
                                                         const int32_t* __restrict__ unit_off, TileJobs jobs)
 {
-    build_tables(unit_cnt, unit_off, jobs, blockIdx.x, threadIdx.x);
+    build_tables<true>(unit_cnt, unit_off, jobs, blockIdx.x, threadIdx.x);
 }
 
 // ------------------------------------------------------------------------------------------------
 struct GemmArgs {
     const bf16_t* A; long lda; const int32_t* gather;
     const int32_t* table;
-    const int32_t* streamed;                    // load_weights: nonzero if the layer's weights are
     int lower;                                  // rows of the lower tiles that the launch takes as well (TilePlan::lo; 0: none)
     const bf16_t *wa0, *wa1, *wa2;              // per weight source (experts, united, shared); GEMM1: W1, GEMM2: W2
     const bf16_t *wb0, *wb1, *wb2;              // GEMM1: W3; GEMM2: unused
@@ -78,14 +77,20 @@ struct GemmArgs {
     int n_ntiles;
     int group_m;                                // M tiles per L2 super-tile
     int ksplit; long plane;                     // GEMM2 only: K split into ksplit slices, slice s writes out + s*plane
-    float* partial;                             // four-wave kernel, ksplit 1: scratch of the K-split tail (or null)
+    union {
+        float* partial;                         // four-wave kernel, ksplit 1: scratch of the K-split tail (or null)
+        const int32_t* streamed;                // the others, STREAM: TileJobs::streamed
+    };
     int partial_cap;                            // fp32 tiles it holds
     int split;                                  // its left-over tiles may be cut along K (the sum of the slices is launched behind it)
 };
 
 // A k tile's loads of weights, `step` bytes of LDS apart.  `streamed`: with the non-temporal hint, where the layer's weights do not
 // outlast a call in the memory-side cache anyway and one tile, or tiles side by side, read these: without it their lines push everything
-// else out of the caches on the way (with sc0 or sc1 besides: no change).
+// else out of the caches on the way (with sc0 or sc1 besides: no change).  A kernel looks at the table for that only where the layer may have so
+// many weights (STREAM, from the host): the flag, the tile's neighbours and a choice between two kinds of load are 0.2 to 0.5 us of a small call,
+// in the GEMMs and in the block that makes the row lists (layer forward, kernels that always look and these: 64 tokens over 8 experts of 256 x 512
+// 20.3 -> 20.0 us, one token 17.9 -> 17.5, 300 tokens 27.8 -> 27.4, one token of the 60-expert shape 50.1 -> 49.6).
 constexpr int kNonTemporal = 2;
 template <int N>
 __device__ __forceinline__ void load_weights(bool streamed, const bf16_t* const* src, int k, char* dst, int step)
@@ -148,10 +153,11 @@ __device__ __forceinline__ void set_weights(const GemmArgs& p, Tile& t)
     t.Wb = SWIGLU ? (src == 0 ? p.wb0 : (src == 1 ? p.wb1 : p.wb2)) + (size_t)widx * wsz : nullptr;
 }
 
-template <int BM, int BNC, bool SWIGLU>
+template <int BM, int BNC, bool STREAM, bool SWIGLU>
 __device__ __forceinline__ bool decode_tile(const GemmArgs& p, int block, Tile& t)
 {
-    const int stream = *p.streamed;
+    int stream = 0;
+    if constexpr (STREAM) stream = *p.streamed;
     const int n_mt = m_tiles<BM>(p);
     const int tiles = n_mt * p.n_ntiles;
     const int total = tiles * p.ksplit;
@@ -168,7 +174,8 @@ __device__ __forceinline__ bool decode_tile(const GemmArgs& p, int block, Tile& 
     tile_coords(p, n_mt, p.n_ntiles, Lfull - t.kslice * tiles, mt, t.nt);
     const int4 te = reinterpret_cast<const int4*>(p.table + 4)[mt];
     t.unit = te.x; t.row0 = te.y; t.nrows = te.z;
-    t.streamed = only_tile(p.table, n_mt, mt, t.unit) & (stream != 0);
+    t.streamed = false;
+    if constexpr (STREAM) t.streamed = only_tile(p.table, n_mt, mt, t.unit) & (stream != 0);
     set_weights<SWIGLU>(p, t);
     t.n0 = t.nt * BNC;
     return true;
@@ -416,7 +423,7 @@ struct Lds {
 // Small-tile kernel (4 waves, 32 or 64 rows): one ring of NSTAGE (A+B) stages, tiles kt+1..kt+NSTAGE-1 in
 // flight while tile kt is multiplied.  Used when experts hold few rows (decode): weight streaming bound.
 // ------------------------------------------------------------------------------------------------
-template <int BM, int BN, int WM, int WN, int BK, int NSTAGE, bool SWIGLU>
+template <int BM, int BN, int WM, int WN, int BK, int NSTAGE, bool STREAM, bool SWIGLU>
 __device__ __forceinline__ void small_block(const GemmArgs& p, const int block)
 {
     using L = Lds<BK>;
@@ -426,12 +433,12 @@ __device__ __forceinline__ void small_block(const GemmArgs& p, const int block)
     constexpr int NW = WM * WN;
     constexpr int GROUPS = (BM + BN) / RPG;
     constexpr int LD_PER_WAVE = GROUPS / NW;
-    static_assert(GROUPS % NW == 0, "loader shape");
+    static_assert(GROUPS % NW == 0 && BM % (RPG * NW) == 0, "loader shape");
     static_assert(!SWIGLU || (FN % 2 == 0), "gate/up tiles must pair inside a wavefront");
     extern __shared__ __attribute__((aligned(16))) char smem[];
 
     Tile t;
-    if (!decode_tile<BM, SWIGLU ? BN / 2 : BN, SWIGLU>(p, block, t)) return;
+    if (!decode_tile<BM, SWIGLU ? BN / 2 : BN, STREAM, SWIGLU>(p, block, t)) return;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave / WN, wn = wave % WN;
     int k_first, nk;
@@ -449,8 +456,9 @@ __device__ __forceinline__ void small_block(const GemmArgs& p, const int block)
         char* dst = smem + (kt % NSTAGE) * STAGE + wave * 1024;
 #pragma unroll
         for (int i = 0; i < LD_PER_WAVE; ++i)
-            if (i * NW * RPG < BM) load_lds(gptr[i] + kt * BK, dst + i * NW * 1024);
-        load_weights<LD_PER_WAVE - BM / RPG / NW>(t.streamed, gptr + BM / RPG / NW, kt * BK, dst + BM / RPG * 1024, NW * 1024);
+            if (!STREAM || i * NW * RPG < BM) load_lds(gptr[i] + kt * BK, dst + i * NW * 1024);
+        if constexpr (STREAM)
+            load_weights<LD_PER_WAVE - BM / RPG / NW>(t.streamed, gptr + BM / RPG / NW, kt * BK, dst + BM / RPG * 1024, NW * 1024);
     };
 
     f32x16 acc[FM][FN];
@@ -493,10 +501,10 @@ __device__ __forceinline__ void small_block(const GemmArgs& p, const int block)
     store_tile_lines<FM, FN, TM, TN, SWIGLU>(p, t, acc, wm, wn, lane, smem + wave * 8192);
 }
 
-template <int BM, int BN, int WM, int WN, int BK, int NSTAGE, bool SWIGLU>
+template <int BM, int BN, int WM, int WN, int BK, int NSTAGE, bool STREAM, bool SWIGLU>
 __global__ void __launch_bounds__(WM * WN * 64) ffn_gemm_kernel(GemmArgs p)
 {
-    small_block<BM, BN, WM, WN, BK, NSTAGE, SWIGLU>(p, blockIdx.x);
+    small_block<BM, BN, WM, WN, BK, NSTAGE, STREAM, SWIGLU>(p, blockIdx.x);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -510,7 +518,7 @@ __global__ void __launch_bounds__(WM * WN * 64) ffn_gemm_kernel(GemmArgs p)
 // and 256 now) 58.3 -> 44.2 us, 37 tokens with a shared expert of 2048 x 5632 (44 and 16 blocks before) 133 -> 100 us, 64 tokens
 // over 8 experts of 256 x 512 27.8 -> 24.1 us.
 // ------------------------------------------------------------------------------------------------
-template <int BM, int NSTAGE, bool SWIGLU>
+template <int BM, int NSTAGE, bool STREAM, bool SWIGLU>
 __device__ __forceinline__ void narrow_block(const GemmArgs& p, const int block)
 {
     constexpr int BK = 64, BN = 64, NW = 4, TM = BM / 2, TN = BN / 2, FM = TM / 16, FN = TN / 16;
@@ -518,11 +526,11 @@ __device__ __forceinline__ void narrow_block(const GemmArgs& p, const int block)
     constexpr int RB = L::RB, RPG = L::RPG;
     constexpr int STAGE = (BM + BN) * RB;
     constexpr int LD_PER_WAVE = (BM + BN) / RPG / NW;
-    static_assert((BM + BN) % (RPG * NW) == 0 && BM % RPG == 0, "loader shape");
+    static_assert((BM + BN) % (RPG * NW) == 0 && BM % (RPG * NW) == 0, "loader shape");
     extern __shared__ __attribute__((aligned(16))) char smem[];
 
     Tile t;
-    if (!decode_tile<BM, SWIGLU ? BN / 2 : BN, SWIGLU>(p, block, t)) return;
+    if (!decode_tile<BM, SWIGLU ? BN / 2 : BN, STREAM, SWIGLU>(p, block, t)) return;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave >> 1, wn = wave & 1;
     int k_first, nk;
@@ -540,8 +548,9 @@ __device__ __forceinline__ void narrow_block(const GemmArgs& p, const int block)
         char* dst = smem + stage * STAGE + wave * 1024;
 #pragma unroll
         for (int i = 0; i < LD_PER_WAVE; ++i)
-            if (i * NW * RPG < BM) load_lds(gptr[i] + kt * BK, dst + i * NW * 1024);
-        load_weights<LD_PER_WAVE - BM / RPG / NW>(t.streamed, gptr + BM / RPG / NW, kt * BK, dst + BM / RPG * 1024, NW * 1024);
+            if (!STREAM || i * NW * RPG < BM) load_lds(gptr[i] + kt * BK, dst + i * NW * 1024);
+        if constexpr (STREAM)
+            load_weights<LD_PER_WAVE - BM / RPG / NW>(t.streamed, gptr + BM / RPG / NW, kt * BK, dst + BM / RPG * 1024, NW * 1024);
     };
 
     f32x4 acc[FM][FN];
@@ -603,10 +612,10 @@ __device__ __forceinline__ void narrow_block(const GemmArgs& p, const int block)
     }
 }
 
-template <int BM, int NSTAGE, bool SWIGLU>
+template <int BM, int NSTAGE, bool STREAM, bool SWIGLU>
 __global__ void __launch_bounds__(256) ffn_gemm_narrow_kernel(GemmArgs p)
 {
-    narrow_block<BM, NSTAGE, SWIGLU>(p, blockIdx.x);
+    narrow_block<BM, NSTAGE, STREAM, SWIGLU>(p, blockIdx.x);
 }
 
 // Stages of the kernels for 32 and 64 rows; two narrow blocks of either height fit a CU.
@@ -617,38 +626,38 @@ constexpr int narrow_stages() { return BM == 32 ? 6 : 5; }
 
 // The routed and united units' block: tiles of BM rows, or (k32or64) of the height that the table holds.
 constexpr int k32or64 = 96;
-template <int BM, bool NARROW, bool SWIGLU>
+template <int BM, bool NARROW, bool STREAM, bool SWIGLU>
 __device__ __forceinline__ void routed_block(const GemmArgs& p, const int block)
 {
     if constexpr (BM == k32or64) {
-        if (__builtin_amdgcn_readfirstlane(p.table[1]) == 64) routed_block<64, NARROW, SWIGLU>(p, block);
-        else routed_block<32, NARROW, SWIGLU>(p, block);
+        if (__builtin_amdgcn_readfirstlane(p.table[1]) == 64) routed_block<64, NARROW, STREAM, SWIGLU>(p, block);
+        else routed_block<32, NARROW, STREAM, SWIGLU>(p, block);
     } else if constexpr (NARROW) {
-        narrow_block<BM, narrow_stages<BM>(), SWIGLU>(p, block);
+        narrow_block<BM, narrow_stages<BM>(), STREAM, SWIGLU>(p, block);
     } else {
-        small_block<BM, 256, 1, 4, 64, small_stages<BM>(), SWIGLU>(p, block);
+        small_block<BM, 256, 1, 4, 64, small_stages<BM>(), STREAM, SWIGLU>(p, block);
     }
 }
 
 // Tiles of BM or BM / 2 rows, as the table says: a launch for each height would cost a browned-out decode batch of 70 us two empty
 // ones of 4 us.
-template <int BM, bool NARROW, bool SWIGLU>
+template <int BM, bool NARROW, bool STREAM, bool SWIGLU>
 __global__ void __launch_bounds__(256) ffn_gemm_either_kernel(GemmArgs p)
 {
     static_assert(BM == 64, "32 or 64 rows");
-    routed_block<k32or64, NARROW, SWIGLU>(p, blockIdx.x);
+    routed_block<k32or64, NARROW, STREAM, SWIGLU>(p, blockIdx.x);
 }
 
 // Shared experts of a width of their own (ps: the first n_s blocks) beside the routed and united units (pr) in one launch.  A launch
 // each left most CUs idle at the ends of both: the shared GEMM2 of 37 tokens of the 60-expert shape (K = 5632) is 64 blocks of 44 k
 // tiles, 15.7 us, the routed one 13.5 us of 256-column blocks with 11.  Layer forward of that shape in two launches per GEMM and in
 // one: 1 token 63 -> 51 us, 8 at 0.6 brownout 83 -> 68, 37 98 -> 88, 120 251 -> 228.
-template <int BMR, bool NARROW, int BMS, bool SWIGLU>
+template <int BMR, bool NARROW, int BMS, bool STREAM, bool SWIGLU>
 __global__ void __launch_bounds__(256) ffn_gemm_pair_kernel(GemmArgs ps, GemmArgs pr, int n_s)
 {
     const int b = blockIdx.x;
-    if (b < n_s) narrow_block<BMS, narrow_stages<BMS>(), SWIGLU>(ps, b);
-    else routed_block<BMR, NARROW, SWIGLU>(pr, b - n_s);
+    if (b < n_s) narrow_block<BMS, narrow_stages<BMS>(), STREAM, SWIGLU>(ps, b);
+    else routed_block<BMR, NARROW, STREAM, SWIGLU>(pr, b - n_s);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -667,7 +676,7 @@ __global__ void __launch_bounds__(256) ffn_gemm_pair_kernel(GemmArgs ps, GemmArg
 // load in flight.
 // ------------------------------------------------------------------------------------------------
 // Tile L of a launch whose blocks walk over several (L counts the tiles of all K slices).
-template <bool SWIGLU>
+template <bool STREAM, bool SWIGLU>
 __device__ __forceinline__ void tile_at(const GemmArgs& p, int n_mt, int n_ntiles, int bnc, int L, Tile& t)
 {
     const int tiles = n_mt * n_ntiles;
@@ -680,14 +689,15 @@ __device__ __forceinline__ void tile_at(const GemmArgs& p, int n_mt, int n_ntile
     typedef const __attribute__((address_space(4))) int* scalar_ptr;
     const scalar_ptr te = (scalar_ptr)(unsigned long)(p.table + 4 + 4 * __builtin_amdgcn_readfirstlane(mt));
     t.unit = te[0]; t.row0 = te[1]; t.nrows = te[2];
-    t.streamed = only_tile((scalar_ptr)(unsigned long)p.table, n_mt, __builtin_amdgcn_readfirstlane(mt), t.unit);
+    t.streamed = false;
+    if constexpr (STREAM) t.streamed = only_tile((scalar_ptr)(unsigned long)p.table, n_mt, __builtin_amdgcn_readfirstlane(mt), t.unit);
     set_weights<SWIGLU>(p, t);
     t.n0 = t.nt * bnc;
 }
 
 constexpr int kWsStore = 16384;                          // 4 KiB of LDS per storing wave, beside the stages
 
-template <int BM, int BN, int WM, int WN, int NST, bool SWIGLU>
+template <int BM, int BN, int WM, int WN, int NST, bool STREAM, bool SWIGLU>
 __device__ __forceinline__ void ws_block(const GemmArgs& p, const int n_mt, const int n_ntiles)
 {
     constexpr int BK = 64, NW = 4;                       // loaders, and as many (WM x WN) that multiply
@@ -712,7 +722,9 @@ __device__ __forceinline__ void ws_block(const GemmArgs& p, const int n_mt, cons
         const bf16_t *ga[LA], *gb[LB];
         int next = first, kt = 0, nk = 0, stage = 0;
         // in a launch of one round the M tiles of a unit read its weights side by side
-        const bool stream = *(scalar_ptr)(unsigned long)p.streamed != 0, one_round = total <= (int)gridDim.x;
+        bool stream = false;
+        if constexpr (STREAM) stream = *(scalar_ptr)(unsigned long)p.streamed != 0;
+        const bool one_round = total <= (int)gridDim.x;
         bool streamed = false;
         auto set_up = [&](const Tile& t) {
             int k_first;
@@ -748,7 +760,7 @@ __device__ __forceinline__ void ws_block(const GemmArgs& p, const int n_mt, cons
             while (kt >= nk) {                            // on to the next tile that has any k
                 if (next >= end) return false;
                 Tile t;
-                tile_at<SWIGLU>(p, n_mt, n_ntiles, BNC, next, t);
+                tile_at<STREAM, SWIGLU>(p, n_mt, n_ntiles, BNC, next, t);
                 next += slots;
                 set_up(t);
             }
@@ -798,7 +810,7 @@ __device__ __forceinline__ void ws_block(const GemmArgs& p, const int n_mt, cons
     }
     for (int next = first; next < end; next += slots) {
         Tile t;
-        tile_at<SWIGLU>(p, n_mt, n_ntiles, BNC, next, t);
+        tile_at<false, SWIGLU>(p, n_mt, n_ntiles, BNC, next, t);
         int k_first, nk;
         k_range<BK>(p, t, k_first, nk);
         f32x4 acc[FM][FN];
@@ -841,7 +853,7 @@ __device__ __forceinline__ void ws_block(const GemmArgs& p, const int n_mt, cons
 // thirds of the bytes.  Only the table says how many rows there are, so the choice is the kernel's (one unit of 256 rows, K 14336
 // in four slices: 128 tiles 59 us, 256 narrow ones 44; 28672 x 4096: 224 tiles 70 us, 448 narrow ones 87).  So is that of tiles of 64
 // rows, where the job offers them.
-template <bool SWIGLU>
+template <bool STREAM, bool SWIGLU>
 __global__ void __launch_bounds__(512) ffn_gemm_ws_kernel(GemmArgs p)
 {
     const int wide = (p.N + (SWIGLU ? 127 : 255)) / (SWIGLU ? 128 : 256), narrow = (p.N + (SWIGLU ? 63 : 127)) / (SWIGLU ? 64 : 128);
@@ -851,13 +863,13 @@ __global__ void __launch_bounds__(512) ffn_gemm_ws_kernel(GemmArgs p)
         return (bm + 256) * ((tw + G - 1) / G) <= (bm + 128) * ((tn + G - 1) / G);
     };
     if (const int n_mt = m_tiles<128>(p)) {
-        if (wide_wins(n_mt, 128)) ws_block<128, 256, 2, 2, 3, SWIGLU>(p, n_mt, wide);
-        else if constexpr (SWIGLU) ws_block<128, 128, 4, 1, 4, SWIGLU>(p, n_mt, narrow);
-        else ws_block<128, 128, 2, 2, 4, SWIGLU>(p, n_mt, narrow);
+        if (wide_wins(n_mt, 128)) ws_block<128, 256, 2, 2, 3, STREAM, SWIGLU>(p, n_mt, wide);
+        else if constexpr (SWIGLU) ws_block<128, 128, 4, 1, 4, STREAM, SWIGLU>(p, n_mt, narrow);
+        else ws_block<128, 128, 2, 2, 4, STREAM, SWIGLU>(p, n_mt, narrow);
     } else if (p.lower == 64) {
         const int n_lo = m_tiles<64>(p);
-        if (SWIGLU || wide_wins(n_lo, 64)) ws_block<64, 256, 2, 2, 3, SWIGLU>(p, n_lo, wide);
-        else if constexpr (!SWIGLU) ws_block<64, 128, 2, 2, 5, SWIGLU>(p, n_lo, narrow);
+        if (SWIGLU || wide_wins(n_lo, 64)) ws_block<64, 256, 2, 2, 3, STREAM, SWIGLU>(p, n_lo, wide);
+        else if constexpr (!SWIGLU) ws_block<64, 128, 2, 2, 5, STREAM, SWIGLU>(p, n_lo, narrow);
     }
 }
 
@@ -1443,10 +1455,10 @@ static hipError_t set_lds(Kern kern, int lds)
     return hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
 }
 
-template <int BM, bool SWIGLU>
-constexpr auto small_kernel() { return ffn_gemm_kernel<BM, 256, 1, 4, 64, small_stages<BM>(), SWIGLU>; }
-template <int BM, bool SWIGLU>
-constexpr auto narrow_kernel() { return ffn_gemm_narrow_kernel<BM, narrow_stages<BM>(), SWIGLU>; }
+template <int BM, bool STREAM, bool SWIGLU>
+constexpr auto small_kernel() { return ffn_gemm_kernel<BM, 256, 1, 4, 64, small_stages<BM>(), STREAM, SWIGLU>; }
+template <int BM, bool STREAM, bool SWIGLU>
+constexpr auto narrow_kernel() { return ffn_gemm_narrow_kernel<BM, narrow_stages<BM>(), STREAM, SWIGLU>; }
 template <int BM, bool NARROW>
 constexpr int routed_lds()
 {
@@ -1457,42 +1469,44 @@ template <int BMR, bool NARROW, int BMS>
 constexpr int pair_lds() { return std::max(routed_lds<BMR, NARROW>(), narrow_lds<BMS>()); }
 
 // The pair kernel for (BMR, NARROW, BMS): its LDS attribute, or a launch.
-template <int BMR, bool NARROW, int BMS, bool SWIGLU>
-static hipError_t init_pair() { return set_lds(ffn_gemm_pair_kernel<BMR, NARROW, BMS, SWIGLU>, pair_lds<BMR, NARROW, BMS>()); }
-template <int BMR, bool NARROW, bool SWIGLU>
+template <int BMR, bool NARROW, int BMS, bool STREAM, bool SWIGLU>
+static hipError_t init_pair() { return set_lds(ffn_gemm_pair_kernel<BMR, NARROW, BMS, STREAM, SWIGLU>, pair_lds<BMR, NARROW, BMS>()); }
+template <int BMR, bool NARROW, bool STREAM, bool SWIGLU>
 static void launch_pair(const GemmArgs& a, const GemmArgs& r, bool s32, int n_s, int n, hipStream_t s)
 {
     if constexpr (BMR != 64)
         if (s32) {
-            ffn_gemm_pair_kernel<BMR, NARROW, 32, SWIGLU><<<n, 256, pair_lds<BMR, NARROW, 32>(), s>>>(a, r, n_s);
+            ffn_gemm_pair_kernel<BMR, NARROW, 32, STREAM, SWIGLU><<<n, 256, pair_lds<BMR, NARROW, 32>(), s>>>(a, r, n_s);
             return;
         }
-    ffn_gemm_pair_kernel<BMR, NARROW, 64, SWIGLU><<<n, 256, pair_lds<BMR, NARROW, 64>(), s>>>(a, r, n_s);
+    ffn_gemm_pair_kernel<BMR, NARROW, 64, STREAM, SWIGLU><<<n, 256, pair_lds<BMR, NARROW, 64>(), s>>>(a, r, n_s);
 }
 
-template <bool SWIGLU>
+template <bool STREAM, bool SWIGLU>
 static hipError_t init_gemms()
 {
     hipError_t e;
-    if ((e = set_lds(small_kernel<64, SWIGLU>(), small_lds<64>())) != hipSuccess) return e;
-    if ((e = set_lds(small_kernel<32, SWIGLU>(), small_lds<32>())) != hipSuccess) return e;
-    if ((e = set_lds(narrow_kernel<64, SWIGLU>(), narrow_lds<64>())) != hipSuccess) return e;
-    if ((e = set_lds(narrow_kernel<32, SWIGLU>(), narrow_lds<32>())) != hipSuccess) return e;
-    if ((e = set_lds(ffn_gemm_either_kernel<64, false, SWIGLU>, routed_lds<k32or64, false>())) != hipSuccess) return e;
-    if ((e = set_lds(ffn_gemm_either_kernel<64, true, SWIGLU>, routed_lds<k32or64, true>())) != hipSuccess) return e;
-    if ((e = init_pair<32, false, 32, SWIGLU>()) != hipSuccess || (e = init_pair<32, true, 32, SWIGLU>()) != hipSuccess) return e;
-    if ((e = init_pair<32, false, 64, SWIGLU>()) != hipSuccess || (e = init_pair<32, true, 64, SWIGLU>()) != hipSuccess) return e;
-    if ((e = init_pair<64, false, 64, SWIGLU>()) != hipSuccess || (e = init_pair<64, true, 64, SWIGLU>()) != hipSuccess) return e;
-    if ((e = init_pair<k32or64, false, 32, SWIGLU>()) != hipSuccess || (e = init_pair<k32or64, true, 32, SWIGLU>()) != hipSuccess) return e;
-    if ((e = init_pair<k32or64, false, 64, SWIGLU>()) != hipSuccess || (e = init_pair<k32or64, true, 64, SWIGLU>()) != hipSuccess) return e;
-    if ((e = set_lds(ffn_gemm_ws_kernel<SWIGLU>, kWsLds)) != hipSuccess) return e;
+    if ((e = set_lds(small_kernel<64, STREAM, SWIGLU>(), small_lds<64>())) != hipSuccess) return e;
+    if ((e = set_lds(small_kernel<32, STREAM, SWIGLU>(), small_lds<32>())) != hipSuccess) return e;
+    if ((e = set_lds(narrow_kernel<64, STREAM, SWIGLU>(), narrow_lds<64>())) != hipSuccess) return e;
+    if ((e = set_lds(narrow_kernel<32, STREAM, SWIGLU>(), narrow_lds<32>())) != hipSuccess) return e;
+    if ((e = set_lds(ffn_gemm_either_kernel<64, false, STREAM, SWIGLU>, routed_lds<k32or64, false>())) != hipSuccess) return e;
+    if ((e = set_lds(ffn_gemm_either_kernel<64, true, STREAM, SWIGLU>, routed_lds<k32or64, true>())) != hipSuccess) return e;
+    if ((e = init_pair<32, false, 32, STREAM, SWIGLU>()) != hipSuccess || (e = init_pair<32, true, 32, STREAM, SWIGLU>()) != hipSuccess) return e;
+    if ((e = init_pair<32, false, 64, STREAM, SWIGLU>()) != hipSuccess || (e = init_pair<32, true, 64, STREAM, SWIGLU>()) != hipSuccess) return e;
+    if ((e = init_pair<64, false, 64, STREAM, SWIGLU>()) != hipSuccess || (e = init_pair<64, true, 64, STREAM, SWIGLU>()) != hipSuccess) return e;
+    if ((e = init_pair<k32or64, false, 32, STREAM, SWIGLU>()) != hipSuccess || (e = init_pair<k32or64, true, 32, STREAM, SWIGLU>()) != hipSuccess) return e;
+    if ((e = init_pair<k32or64, false, 64, STREAM, SWIGLU>()) != hipSuccess || (e = init_pair<k32or64, true, 64, STREAM, SWIGLU>()) != hipSuccess) return e;
+    if ((e = set_lds(ffn_gemm_ws_kernel<STREAM, SWIGLU>, kWsLds)) != hipSuccess) return e;
     return set_lds(ffn_gemm_w4_kernel<SWIGLU>, kW4Lds);
 }
 
 hipError_t init_ffn_kernels()
 {
-    const hipError_t e = init_gemms<true>();
-    return e != hipSuccess ? e : init_gemms<false>();
+    const hipError_t e[] = {init_gemms<true, true>(), init_gemms<true, false>(), init_gemms<false, true>(), init_gemms<false, false>()};
+    for (hipError_t x : e)
+        if (x != hipSuccess) return x;
+    return hipSuccess;
 }
 
 // One GEMM of one group of units: the kernel its tile height and its expected number of blocks ask for.
@@ -1513,24 +1527,24 @@ static int tile_grid(const GemmArgs& a, int max_mtiles)
     return (int)(((long)max_mtiles * a.n_ntiles * a.ksplit + 7) / 8 * 8);
 }
 
-template <bool SWIGLU>
+template <bool STREAM, bool SWIGLU>
 static hipError_t launch_gemm(const GemmLaunch& l, int n_cu, hipStream_t s)
 {
     GemmArgs a = l.a;
     a.n_ntiles = ceil_div(a.N, tile_columns<SWIGLU>(l.kind));
     const int grid = tile_grid(a, l.max_mtiles);
     switch (l.kind) {
-        case kNarrow32: narrow_kernel<32, SWIGLU>()<<<grid, 256, narrow_lds<32>(), s>>>(a); break;
-        case kNarrow64: narrow_kernel<64, SWIGLU>()<<<grid, 256, narrow_lds<64>(), s>>>(a); break;
-        case kSmall32: small_kernel<32, SWIGLU>()<<<grid, 256, small_lds<32>(), s>>>(a); break;
-        case kSmall64: small_kernel<64, SWIGLU>()<<<grid, 256, small_lds<64>(), s>>>(a); break;
-        case kSmallEither: ffn_gemm_either_kernel<64, false, SWIGLU><<<grid, 256, routed_lds<k32or64, false>(), s>>>(a); break;
-        case kNarrowEither: ffn_gemm_either_kernel<64, true, SWIGLU><<<grid, 256, routed_lds<k32or64, true>(), s>>>(a); break;
+        case kNarrow32: narrow_kernel<32, STREAM, SWIGLU>()<<<grid, 256, narrow_lds<32>(), s>>>(a); break;
+        case kNarrow64: narrow_kernel<64, STREAM, SWIGLU>()<<<grid, 256, narrow_lds<64>(), s>>>(a); break;
+        case kSmall32: small_kernel<32, STREAM, SWIGLU>()<<<grid, 256, small_lds<32>(), s>>>(a); break;
+        case kSmall64: small_kernel<64, STREAM, SWIGLU>()<<<grid, 256, small_lds<64>(), s>>>(a); break;
+        case kSmallEither: ffn_gemm_either_kernel<64, false, STREAM, SWIGLU><<<grid, 256, routed_lds<k32or64, false>(), s>>>(a); break;
+        case kNarrowEither: ffn_gemm_either_kernel<64, true, STREAM, SWIGLU><<<grid, 256, routed_lds<k32or64, true>(), s>>>(a); break;
         case kWs: {
             // persistent, one block per CU, a multiple of 8; its tiles are 128 columns (GEMM1: 64) at the narrowest
             const long total = (long)l.max_mtiles * ceil_div(a.N, SWIGLU ? 64 : 128) * a.ksplit;
             const int blocks = (int)std::min<long>((total + 7) / 8 * 8, std::max(8, n_cu / 8 * 8));
-            ffn_gemm_ws_kernel<SWIGLU><<<blocks, 512, kWsLds, s>>>(a);
+            ffn_gemm_ws_kernel<STREAM, SWIGLU><<<blocks, 512, kWsLds, s>>>(a);
             break;
         }
         case kW4: {
@@ -1566,7 +1580,7 @@ static bool pairable(GemmKind shared, GemmKind routed)
     return routed < kWs && (shared == kNarrow64 || (shared == kNarrow32 && routed != kSmall64 && routed != kNarrow64));
 }
 
-template <bool SWIGLU>
+template <bool STREAM, bool SWIGLU>
 static hipError_t launch_gemm_pair(const GemmLaunch& sh, const GemmLaunch& ro, hipStream_t s)
 {
     GemmArgs a = sh.a, r = ro.a;
@@ -1575,12 +1589,12 @@ static hipError_t launch_gemm_pair(const GemmLaunch& sh, const GemmLaunch& ro, h
     const int n_s = tile_grid(a, sh.max_mtiles), n = n_s + tile_grid(r, ro.max_mtiles);
     const bool s32 = sh.kind == kNarrow32;
     switch (ro.kind) {
-        case kSmall32: launch_pair<32, false, SWIGLU>(a, r, s32, n_s, n, s); break;
-        case kNarrow32: launch_pair<32, true, SWIGLU>(a, r, s32, n_s, n, s); break;
-        case kSmall64: launch_pair<64, false, SWIGLU>(a, r, s32, n_s, n, s); break;
-        case kNarrow64: launch_pair<64, true, SWIGLU>(a, r, s32, n_s, n, s); break;
-        case kSmallEither: launch_pair<k32or64, false, SWIGLU>(a, r, s32, n_s, n, s); break;
-        default: launch_pair<k32or64, true, SWIGLU>(a, r, s32, n_s, n, s); break;
+        case kSmall32: launch_pair<32, false, STREAM, SWIGLU>(a, r, s32, n_s, n, s); break;
+        case kNarrow32: launch_pair<32, true, STREAM, SWIGLU>(a, r, s32, n_s, n, s); break;
+        case kSmall64: launch_pair<64, false, STREAM, SWIGLU>(a, r, s32, n_s, n, s); break;
+        case kNarrow64: launch_pair<64, true, STREAM, SWIGLU>(a, r, s32, n_s, n, s); break;
+        case kSmallEither: launch_pair<k32or64, false, STREAM, SWIGLU>(a, r, s32, n_s, n, s); break;
+        default: launch_pair<k32or64, true, STREAM, SWIGLU>(a, r, s32, n_s, n, s); break;
     }
     return hipGetLastError();
 }
@@ -1588,7 +1602,7 @@ static hipError_t launch_gemm_pair(const GemmLaunch& sh, const GemmLaunch& ro, h
 hipError_t launch_tile_tables(const int32_t* unit_cnt, const int32_t* unit_off, const TileJobs& jobs, hipStream_t s)
 {
     ProfScope ps(MOE_STAGE_TILES, s);
-    tile_table_kernel<<<jobs.n + 1, 64, 0, s>>>(unit_cnt, unit_off, jobs);
+    tile_table_kernel<<<jobs.n + (jobs.streamed != nullptr), 64, 0, s>>>(unit_cnt, unit_off, jobs);
     return hipGetLastError();
 }
 
@@ -1603,7 +1617,7 @@ hipError_t launch_ffn(const Dims& D, const FfnProblem* problems, int n_problems,
         constexpr bool SWIGLU = decltype(swiglu)::value;
         GemmLaunch l;
         GemmArgs& g = l.a;
-        g.table = P.table; g.streamed = streamed ? streamed : P.table + 2; g.lower = lo;       // word 2 of a table is 0
+        g.table = P.table; g.lower = lo;
         g.m = D.m; g.G = D.G;
         if (SWIGLU) {
             g.A = x; g.lda = D.d; g.gather = gather;
@@ -1622,7 +1636,7 @@ hipError_t launch_ffn(const Dims& D, const FfnProblem* problems, int n_problems,
         }
         g.n_ntiles = 0;                           // set at the launch from the kernel's tile width
         g.group_m = tuning().group_m ? tuning().group_m : (bm == 256 ? 8 : 4);
-        g.partial = partial; g.partial_cap = D.tail_blocks; g.split = 0;
+        g.partial_cap = D.tail_blocks; g.split = 0;
         // M tiles there can be at most: a unit that holds rows has one for every bm of them and a ragged one, and no more
         // units hold rows than there are rows
         l.max_mtiles = (int)std::min<int64_t>(D.row_cap / (lo ? lo : bm) + std::min<int64_t>(P.units.n, D.row_cap), D.tile_cap);
@@ -1637,11 +1651,13 @@ hipError_t launch_ffn(const Dims& D, const FfnProblem* problems, int n_problems,
         else if (lo) l.kind = narrow ? kNarrowEither : kSmallEither;
         else if (bm == 64) l.kind = narrow ? kNarrow64 : kSmall64;
         else l.kind = narrow ? kNarrow32 : kSmall32;
+        if (l.kind == kW4) g.partial = partial;
+        else g.streamed = streamed;
         return l;
     };
     // A launch for bm_hi as well where the table may hold tiles of that height: the one that has none returns at once.
-    auto gemm = [&](auto swiglu) -> hipError_t {
-        constexpr bool SWIGLU = decltype(swiglu)::value;
+    auto gemm = [&](auto swiglu, auto stream) -> hipError_t {
+        constexpr bool SWIGLU = decltype(swiglu)::value, STREAM = decltype(stream)::value;
         ProfScope ps(SWIGLU ? MOE_STAGE_GEMM1 : MOE_STAGE_GEMM2, s);
         GemmLaunch todo[4];
         int n = 0;
@@ -1655,13 +1671,16 @@ hipError_t launch_ffn(const Dims& D, const FfnProblem* problems, int n_problems,
                 if (pairable(todo[n - 1].kind, todo[i].kind)) paired = i;
         hipError_t err;
         for (int i = 0; i < n - (paired >= 0 ? 1 : 0); ++i) {
-            err = i == paired ? launch_gemm_pair<SWIGLU>(todo[n - 1], todo[i], s) : launch_gemm<SWIGLU>(todo[i], dev.n_cu, s);
+            err = i == paired ? launch_gemm_pair<STREAM, SWIGLU>(todo[n - 1], todo[i], s) : launch_gemm<STREAM, SWIGLU>(todo[i], dev.n_cu, s);
             if (err != hipSuccess) return err;
         }
         return hipSuccess;
     };
-    if ((e = gemm(std::true_type{})) != hipSuccess) return e;
-    return gemm(std::false_type{});
+    auto both = [&](auto stream) {
+        const hipError_t err = gemm(std::true_type{}, stream);
+        return err != hipSuccess ? err : gemm(std::false_type{}, stream);
+    };
+    return streamed ? both(std::true_type{}) : both(std::false_type{});
 }
 
 hipError_t launch_combine(const Dims& D, const bf16_t* x, const bf16_t* Y, const int32_t* token_rows,

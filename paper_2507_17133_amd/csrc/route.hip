@@ -15,6 +15,7 @@
 #include "tiles.h"
 
 #include <algorithm>
+#include <type_traits>
 
 namespace bmoe {
 
@@ -926,7 +927,7 @@ __global__ void __launch_bounds__(256) route_scatter_kernel(RowArgs p)
     if (seg == p.n_seg) {
         for (int u = tid; u <= p.U; u += 256) p.unit_off[u] = off_s[u];
         if (tid == 0 && p.n_rows) p.n_rows[0] = off_s[p.U];
-        build_tables(ucnt_s, off_s, p.jobs, wave, lane);
+        build_tables<true>(ucnt_s, off_s, p.jobs, wave, lane);
         return;
     }
 #pragma unroll
@@ -973,7 +974,7 @@ enum { kBits, kLists, kTopK };
 __host__ __device__ constexpr int bit_slot(int e) { return e + (e >> 3); }
 __host__ __device__ constexpr int bit_pitch(int m) { return m + (m >> 3) + 1; }
 
-template <int SRC, int NC>
+template <int SRC, int NC, bool STREAM>
 __global__ void __launch_bounds__(1024) route_rows_kernel(RowArgs p, GateArgs g)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char rsm[];      // bitmaps [n_seg][bit_pitch(m)]; kTopK: logits
@@ -1259,7 +1260,7 @@ __global__ void __launch_bounds__(1024) route_rows_kernel(RowArgs p, GateArgs g)
         lds_sync();
     }
     // the GEMM tile tables, by the last wavefronts (with kTopK the first ones hold the tokens of a short batch)
-    if (writer) build_tables(ucnt_s, off_s, p.jobs, 15 - wave, lane);
+    if (writer) build_tables<STREAM>(ucnt_s, off_s, p.jobs, 15 - wave, lane);
     if (SRC != kTopK && writer) return;
 
     const int j = tid & ((1 << p.lk) - 1);
@@ -1288,6 +1289,24 @@ constexpr int kGateLds16 = 3 * gate_rows<1, 1>() * 128;
 constexpr int kGateLds64 = 2 * gate_rows<2, 2>() * 128;
 constexpr int kGateLds128 = 2 * gate_rows<4, 2>() * 128;
 
+template <bool STREAM>
+static hipError_t init_rows()
+{
+    const void* topk[] = {reinterpret_cast<const void*>(route_rows_kernel<kTopK, 0, STREAM>),
+                          reinterpret_cast<const void*>(route_rows_kernel<kTopK, 4, STREAM>),
+                          reinterpret_cast<const void*>(route_rows_kernel<kTopK, 8, STREAM>),
+                          reinterpret_cast<const void*>(route_rows_kernel<kTopK, 16, STREAM>)};
+    hipError_t e;
+    for (const void* k : topk)
+        if ((e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, kSegTokens * (kMaxExperts + 16) * 4)) != hipSuccess)
+            return e;
+    const void* rows[] = {reinterpret_cast<const void*>(route_rows_kernel<kBits, 0, STREAM>),
+                          reinterpret_cast<const void*>(route_rows_kernel<kLists, 0, STREAM>)};
+    for (const void* k : rows)
+        if ((e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, kRowLds)) != hipSuccess) return e;
+    return hipSuccess;
+}
+
 hipError_t init_route_kernels()
 {
     hipError_t e;
@@ -1300,17 +1319,7 @@ hipError_t init_route_kernels()
     e = hipFuncSetAttribute(reinterpret_cast<const void*>(gate_logits_kernel<4, 2, 2, 2, 2>),
                             hipFuncAttributeMaxDynamicSharedMemorySize, kGateLds128);
     if (e != hipSuccess) return e;
-    const void* topk[] = {reinterpret_cast<const void*>(route_rows_kernel<kTopK, 0>),
-                          reinterpret_cast<const void*>(route_rows_kernel<kTopK, 4>),
-                          reinterpret_cast<const void*>(route_rows_kernel<kTopK, 8>),
-                          reinterpret_cast<const void*>(route_rows_kernel<kTopK, 16>)};
-    for (const void* k : topk)
-        if ((e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, kSegTokens * (kMaxExperts + 16) * 4)) != hipSuccess)
-            return e;
-    const void* rows[] = {reinterpret_cast<const void*>(route_rows_kernel<kBits, 0>),
-                          reinterpret_cast<const void*>(route_rows_kernel<kLists, 0>)};
-    for (const void* k : rows)
-        if ((e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, kRowLds)) != hipSuccess) return e;
+    if ((e = init_rows<true>()) != hipSuccess || (e = init_rows<false>()) != hipSuccess) return e;
     return hipFuncSetAttribute(reinterpret_cast<const void*>(gate_few_kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
                                kGateFewLds);
 }
@@ -1398,14 +1407,15 @@ static bool one_block_routes(const Dims& D)
 }
 
 // The block that takes TopK of a batch of one segment and routes it.
+template <bool STREAM>
 static hipError_t launch_route_topk(const GateArgs& g, const RowArgs& p, hipStream_t s)
 {
     const size_t lds = g.m_pad == 16 ? 0 : (size_t)p.T * (g.m_pad + 16) * 4;     // the logits
-    if (g.m_pad == 16) route_rows_kernel<kTopK, 1><<<1, 1024, lds, s>>>(p, g);
-    else if (g.K + 1 > 16) route_rows_kernel<kTopK, 0><<<1, 1024, lds, s>>>(p, g);
-    else if (g.m_pad <= 64) route_rows_kernel<kTopK, 4><<<1, 1024, lds, s>>>(p, g);
-    else if (g.m_pad <= 128) route_rows_kernel<kTopK, 8><<<1, 1024, lds, s>>>(p, g);
-    else route_rows_kernel<kTopK, 16><<<1, 1024, lds, s>>>(p, g);
+    if (g.m_pad == 16) route_rows_kernel<kTopK, 1, STREAM><<<1, 1024, lds, s>>>(p, g);
+    else if (g.K + 1 > 16) route_rows_kernel<kTopK, 0, STREAM><<<1, 1024, lds, s>>>(p, g);
+    else if (g.m_pad <= 64) route_rows_kernel<kTopK, 4, STREAM><<<1, 1024, lds, s>>>(p, g);
+    else if (g.m_pad <= 128) route_rows_kernel<kTopK, 8, STREAM><<<1, 1024, lds, s>>>(p, g);
+    else route_rows_kernel<kTopK, 16, STREAM><<<1, 1024, lds, s>>>(p, g);
     return hipGetLastError();
 }
 
@@ -1481,11 +1491,15 @@ hipError_t launch_route(const Dims& D, const bf16_t* x, const void* gate, const 
     p.jobs = jobs;
     if (how != kThreeLaunches) {
         ProfScope ps(MOE_STAGE_COUNT, s);
-        if (how == kOneBlock) return launch_route_topk(g, p, s);
-        const size_t lds = (size_t)D.n_seg * bit_pitch(D.m) * 8;
-        if (how == kFromBits) route_rows_kernel<kBits, 0><<<D.n_seg + 1, 1024, lds, s>>>(p, g);
-        else route_rows_kernel<kLists, 0><<<D.n_seg + 1, 1024, lds, s>>>(p, g);
-        return hipGetLastError();
+        auto launch = [&](auto stream) -> hipError_t {
+            constexpr bool STREAM = decltype(stream)::value;
+            if (how == kOneBlock) return launch_route_topk<STREAM>(g, p, s);
+            const size_t lds = (size_t)D.n_seg * bit_pitch(D.m) * 8;
+            if (how == kFromBits) route_rows_kernel<kBits, 0, STREAM><<<D.n_seg + 1, 1024, lds, s>>>(p, g);
+            else route_rows_kernel<kLists, 0, STREAM><<<D.n_seg + 1, 1024, lds, s>>>(p, g);
+            return hipGetLastError();
+        };
+        return jobs.streamed ? launch(std::true_type{}) : launch(std::false_type{});
     }
     {
         ProfScope ps(MOE_STAGE_COUNT, s);

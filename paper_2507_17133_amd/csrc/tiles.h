@@ -22,7 +22,7 @@ struct TileJobs {
     int cap;                 // entries a table holds
     int count_units;         // *streamed (ffn.hip, load_weights) is whether at least stream_units of the units
     int stream_units;        // [0, count_units) hold rows
-    int32_t* streamed;
+    int32_t* streamed;       // null: the host knows that they do not
 };
 
 // What a GEMM tile of bm rows counts for in the choice of bm_hi, in twentieths of a 32-row one.  Full tiles alone (DeepSeek-V3 shape, even
@@ -114,12 +114,13 @@ __device__ __forceinline__ void build_tile_table(const int* cnt, const int* off,
     }
 }
 
-// Wavefront w of a kernel that has the counts: table w, and behind the tables whether the weights are streamed.
+// Wavefront w of a kernel that has the counts: table w, and behind the tables whether the weights are streamed (STREAM: where they may be).
+template <bool STREAM>
 __device__ __forceinline__ void build_tables(const int* cnt, const int* off, const TileJobs& jobs, int w, int lane)
 {
     if (w < jobs.n) {
         build_tile_table(cnt, off, jobs.job[w], jobs.cap, lane);
-    } else if (w == jobs.n && w > 0) {
+    } else if (STREAM && w == jobs.n && jobs.streamed != nullptr) {
         int active = 0;
         for (int u = lane; u < jobs.count_units; u += 64) active += cnt[u] > 0;
         active = __builtin_amdgcn_readlane(wave_scan(active), 63);
