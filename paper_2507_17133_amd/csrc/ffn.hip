@@ -122,17 +122,19 @@ __device__ __forceinline__ int m_tiles(const GemmArgs& p)
     return head.y == BM ? head.x : 0;
 }
 
-// Whether row tile mt is its unit's only one: no neighbour has the unit.  (All loads at once, none behind a comparison.)
+// Whether all row tiles of a unit that has one in [lo, hi) are there: neither neighbour has the unit.  (Both loads at once, none behind a
+// comparison.)
 template <typename Table>
-__device__ __forceinline__ bool only_tile(Table table, int n_mt, int mt, int unit)
+__device__ __forceinline__ bool holds_unit(Table table, int n_mt, int lo, int hi, int unit)
 {
-    const int before = table[4 * max(mt, 1)], after = table[4 * min(mt + 2, n_mt)];
-    return (mt == 0 | before != unit) & (mt + 1 == n_mt | after != unit);
+    const int before = table[4 * max(lo, 1)], after = table[4 * min(hi + 1, n_mt)];
+    return (lo == 0 | before != unit) & (hi >= n_mt | after != unit);
 }
 
 // Tile L of the launch's tile order -> its row tile and column tile.  Super-tiles of group_m M tiles x all N tiles, M fastest: the
-// ~32 blocks an XCD runs at a time cover group_m x (32/group_m) tiles and share their A and B panels in that XCD's L2.
-__device__ __forceinline__ void tile_coords(const GemmArgs& p, int n_mt, int n_ntiles, int L, int& mt, int& nt)
+// ~32 blocks an XCD runs at a time cover group_m x (32/group_m) tiles and share their A and B panels in that XCD's L2.  Returns the
+// super-tile's first M tile.
+__device__ __forceinline__ int tile_coords(const GemmArgs& p, int n_mt, int n_ntiles, int L, int& mt, int& nt)
 {
     const int gspan = p.group_m * n_ntiles;
     const int gi = L / gspan, rem = L - gi * gspan;
@@ -140,6 +142,7 @@ __device__ __forceinline__ void tile_coords(const GemmArgs& p, int n_mt, int n_n
     const int gsz = min(p.group_m, n_mt - mt_first);
     nt = rem / gsz;
     mt = mt_first + (rem - nt * gsz);
+    return mt_first;
 }
 
 // Weights of the tile's unit.
@@ -175,7 +178,7 @@ __device__ __forceinline__ bool decode_tile(const GemmArgs& p, int block, Tile& 
     const int4 te = reinterpret_cast<const int4*>(p.table + 4)[mt];
     t.unit = te.x; t.row0 = te.y; t.nrows = te.z;
     t.streamed = false;
-    if constexpr (STREAM) t.streamed = only_tile(p.table, n_mt, mt, t.unit) & (stream != 0);
+    if constexpr (STREAM) t.streamed = holds_unit(p.table, n_mt, mt, mt + 1, t.unit) & (stream != 0);
     set_weights<SWIGLU>(p, t);
     t.n0 = t.nt * BNC;
     return true;
@@ -675,9 +678,12 @@ __global__ void __launch_bounds__(256) ffn_gemm_pair_kernel(GemmArgs ps, GemmArg
 // tile c+NST-1.  What a loader needs of the next tile comes through the scalar cache: a vector load's wait would be one for every
 // load in flight.
 // ------------------------------------------------------------------------------------------------
-// Tile L of a launch whose blocks walk over several (L counts the tiles of all K slices).
+// Tile L of a launch whose blocks walk over several (L counts the tiles of all K slices).  In a launch of one round the M tiles of a super-tile
+// read their weights side by side; further M tiles of a unit belong to other blocks, often of another XCD, which then find
+// nothing in the caches: streamed all the same, 513 tokens of the 60-expert shape take 295 us and not 282, 513 over 24 experts of 4096 x 1024 with
+// a shared one of 2048 199 and not 185, 800 of those 233 (227 with nothing streamed) and not 223.
 template <bool STREAM, bool SWIGLU>
-__device__ __forceinline__ void tile_at(const GemmArgs& p, int n_mt, int n_ntiles, int bnc, int L, Tile& t)
+__device__ __forceinline__ void tile_at(const GemmArgs& p, int n_mt, int n_ntiles, int bnc, int L, bool one_round, Tile& t)
 {
     const int tiles = n_mt * n_ntiles;
     t.kslice = p.ksplit > 1 ? L / tiles : 0;
@@ -685,12 +691,15 @@ __device__ __forceinline__ void tile_at(const GemmArgs& p, int n_mt, int n_ntile
     t.part = -1;
     t.half = 0;
     int mt;
-    tile_coords(p, n_mt, n_ntiles, L - t.kslice * tiles, mt, t.nt);
+    [[maybe_unused]] const int group = tile_coords(p, n_mt, n_ntiles, L - t.kslice * tiles, mt, t.nt);
     typedef const __attribute__((address_space(4))) int* scalar_ptr;
     const scalar_ptr te = (scalar_ptr)(unsigned long)(p.table + 4 + 4 * __builtin_amdgcn_readfirstlane(mt));
     t.unit = te[0]; t.row0 = te[1]; t.nrows = te[2];
     t.streamed = false;
-    if constexpr (STREAM) t.streamed = only_tile((scalar_ptr)(unsigned long)p.table, n_mt, __builtin_amdgcn_readfirstlane(mt), t.unit);
+    if constexpr (STREAM) {
+        const int lo = __builtin_amdgcn_readfirstlane(one_round ? group : mt);
+        t.streamed = holds_unit((scalar_ptr)(unsigned long)p.table, n_mt, lo, lo + (one_round ? p.group_m : 1), t.unit);
+    }
     set_weights<SWIGLU>(p, t);
     t.n0 = t.nt * bnc;
 }
@@ -721,7 +730,6 @@ __device__ __forceinline__ void ws_block(const GemmArgs& p, const int n_mt, cons
         const int lw = wave - NW;
         const bf16_t *ga[LA], *gb[LB];
         int next = first, kt = 0, nk = 0, stage = 0;
-        // in a launch of one round the M tiles of a unit read its weights side by side
         bool stream = false;
         if constexpr (STREAM) stream = *(scalar_ptr)(unsigned long)p.streamed != 0;
         const bool one_round = total <= (int)gridDim.x;
@@ -730,7 +738,7 @@ __device__ __forceinline__ void ws_block(const GemmArgs& p, const int n_mt, cons
             int k_first;
             k_range<BK>(p, t, k_first, nk);
             kt = 0;
-            streamed = stream && (t.streamed || one_round);
+            streamed = stream && t.streamed;
             if (nk <= 0) return;
             const int r8 = lane >> 3;
 #pragma unroll
@@ -760,7 +768,7 @@ __device__ __forceinline__ void ws_block(const GemmArgs& p, const int n_mt, cons
             while (kt >= nk) {                            // on to the next tile that has any k
                 if (next >= end) return false;
                 Tile t;
-                tile_at<STREAM, SWIGLU>(p, n_mt, n_ntiles, BNC, next, t);
+                tile_at<STREAM, SWIGLU>(p, n_mt, n_ntiles, BNC, next, one_round, t);
                 next += slots;
                 set_up(t);
             }
@@ -810,7 +818,7 @@ __device__ __forceinline__ void ws_block(const GemmArgs& p, const int n_mt, cons
     }
     for (int next = first; next < end; next += slots) {
         Tile t;
-        tile_at<false, SWIGLU>(p, n_mt, n_ntiles, BNC, next, t);
+        tile_at<false, SWIGLU>(p, n_mt, n_ntiles, BNC, next, false, t);
         int k_first, nk;
         k_range<BK>(p, t, k_first, nk);
         f32x4 acc[FM][FN];
