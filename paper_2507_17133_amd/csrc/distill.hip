@@ -538,16 +538,23 @@ static hipError_t launch_dgemm(DGemm& p, int groups, hipStream_t s)
     return hipGetLastError();
 }
 
-// kSwiglu in tiles of 256 x 192 or of 128 x 128: what takes less time by rounds of one or two blocks on 256 CUs (a last round of at most one of the
-// small tiles is shorter).  In us at K = 2048, epilogue included, a round of the large ones takes 48, of two small ones 37 and of one 27: two
-// groups of 2048 tokens at F = 1408 are 240 large tiles in 49 us or 704 small ones in 63.  Per MFMA a large tile passes 3/4 of the bytes through
-// the LDS and 7/12 through the L1.  (The other three epilogues lose more as one block on a CU than their loop gains: kResidual at 256 x 128 37 -> 39
-// us, the launch with kBackward at 256 x 192 87 -> 116.)
-static bool large_swiglu(int M, int N, int groups)
+// kSwiglu in tiles of 256 x 192 or of 128 x 128: what takes less time by rounds of one or two blocks on a CU.  Epilogue included, a round
+// takes so many us (n = 2048, one group, F = 3072 and 2048):
+//   K                  64    128    256    512   1024   2048   4096
+//   one large tile   18.4   19.0   20.5   24.5   33.5     51     87      17.5 + 1.03 per k tile
+//   two small ones   13.8   14.5   15.8   18.8   24.2     40     71      12.5 + 0.87 per k tile
+// A last round of small tiles that is not full takes half to all of that: its blocks start before the round in front of it has ended.  Over 350 shapes
+// of 128 to 4096 x 128 to 3072, 256 to 4096 tokens, 1 to 8 groups (fitted to 150 of them), a step takes 0.08 % longer than with the better tile each time,
+// 3.4 % at most (small ones always 0.52 %; with 48, 37 and, for a last round of up to 256, 27 us at every K, 0.27 %: 3008 tokens, 512 x 1600, 3 groups
+// lost 2.3 %).  Two groups of 2048 tokens at 2048 x 1408 are 240 large tiles in 49 us or 704 small ones in 63.  Per MFMA a large tile
+// passes 3/4 of the bytes through the LDS and 7/12 through the L1.  (The other three epilogues lose more as one block on a CU than their loop gains: kResidual
+// at 256 x 128 37 -> 39 us, the launch with kBackward at 256 x 192 87 -> 116.)
+static bool large_swiglu(int M, int N, int K, int groups, int n_cu)
 {
     const int64_t small = (int64_t)groups * ceil_div(M, 128) * ceil_div(N, 64), large = (int64_t)groups * ceil_div(M, 256) * ceil_div(N, 96);
-    const int64_t rest = small % 512;
-    return (large + 255) / 256 * 48 < small / 512 * 37 + (rest > 256 ? 37 : rest > 0 ? 27 : 0);
+    const int64_t slots = 2 * n_cu, rest = small % slots, kt = K / 64;
+    const int64_t rounds = small / slots * 1024 + (rest > 0 ? 512 + 512 * rest / slots : 0);               // in 1/1024, times in 1/100 us
+    return (large + n_cu - 1) / n_cu * 1024 * (1750 + 103 * kt) < rounds * (1250 + 87 * kt);
 }
 
 template <int EPI, int FM = 4, int FN = 4>
@@ -652,6 +659,9 @@ hipError_t launch_teacher_stats(const bf16_t* y_half, int b, bool first, bool la
 hipError_t distill_groups(const bf16_t* x, int n, int d, int F, int groups, bf16_t* w1u, bf16_t* w3u, bf16_t* w2u, int steps,
                           float lr, float* hist, void* buf, hipStream_t s)
 {
+    DeviceInfo dev;
+    hipError_t e = ensure_device_init(&dev);
+    if (e != hipSuccess) return e;
     const DistillLayout B = distill_layout(n, d, F, groups);
     char* base = static_cast<char*>(buf);
     const size_t dF = (size_t)d * F;
@@ -669,8 +679,7 @@ hipError_t distill_groups(const bf16_t* x, int n, int d, int F, int groups, bf16
     if (steps > 0)
         transpose16_kernel<<<dim3(F / 64, d / 64, groups), 256, 0, s>>>(
             us(w2u), dF, reinterpret_cast<unsigned short*>(base + B.w2t), B.group / 2, d, F);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
+    if ((e = hipGetLastError()) != hipSuccess) return e;
     double b1t = 1.0, b2t = 1.0;
     const int loss_tiles = ceil_div(n, 128) * ceil_div(d, 128);
     for (int t = 0; t <= steps; ++t) {
@@ -683,7 +692,7 @@ hipError_t distill_groups(const bf16_t* x, int n, int d, int F, int groups, bf16
         p.n_jobs = 1;
         p.job[0] = p.job[1] = p.job[2] =
             job(0, X, weight(w1u), weight(w3u), n, F, d, ref(B.G), ref(B.U), ref(B.A), ref(B.At));
-        e = large_swiglu(n, F, groups) ? launch_dgemm<kSwiglu, 8, 6>(p, groups, s) : launch_dgemm<kSwiglu>(p, groups, s);
+        e = large_swiglu(n, F, d, groups, dev.n_cu) ? launch_dgemm<kSwiglu, 8, 6>(p, groups, s) : launch_dgemm<kSwiglu>(p, groups, s);
         if (e != hipSuccess) return e;
         p.job[0] = job(0, ref(B.A), weight(w2u), none, n, d, F, ref(B.tbar), train ? ref(B.dY) : none,
                        train ? ref(B.dYt) : none, ref(B.part));
