@@ -174,15 +174,20 @@ static int taller_tile_rows(const Dims& D, int bm, int n_cu)
     return hi;
 }
 
-// Weights of the units that hold rows, and of the shared experts, beyond which they are streamed past the caches: what the 256 MiB memory-side
-// cache could still hold when the layer is called again.  Layer forward without and with it, three layers in turn: 256 tokens of
-// the Mixtral shape 538 -> 510 us, its united unit alone (352 MB) 134 -> 125, 37 tokens of the 60-expert shape (277 MB) 89 -> 83, 232 of the
-// Qwen3 shape 220 -> 200, 40 of the DeepSeek-V3 shape 1010 -> 943.  Below the line there is less to gain (60 of the 60-expert shape, 242 MB,
-// 91.6 -> 88.4; 232 of the Qwen3 shape, 179 MB, 87.7 -> 85.9), and one layer called over and over would lose what it finds there
-// (83 -> 89 and 68 -> 85; between 256 and 320 MB up to 4 %).  With weights streamed that further tiles read later: 7113 tokens of the
-// DeepSeek-V3 shape 8510 -> 10130; in the 256-row kernel, where eight M tiles in a row read the same ones: 8192 of the Qwen3 shape 618 ->
-// 649.
-constexpr int64_t kKeptBytes = (int64_t)256 << 20;
+// Weights of the units that hold rows, and of the shared experts, beyond which they are streamed past the caches.  Below it one layer called over and
+// over would lose what it still finds in the 256 MiB memory-side cache; above it the lines push each other out before they are read again.
+// Layer forward in us without and with streaming, one layer over and over, then as many in turn as hold 1.6 GB:
+//   37 tokens, 60-expert shape    231 MiB  67.5  77.2   80.3  76.7     4096 x 4096, 128 tokens  192 MiB  61.7  81.0   82.8  80.5
+//                                 264 MiB  73.1  78.0   83.7  79.6                              288 MiB  92.9  88.0   93.8  88.1
+//                                 280 MiB  82.7  80.4   92.1  85.9     4096 x 4096, 20 tokens   288 MiB  78.6  73.5   82.9  74.5
+//                                 297 MiB  92.1  86.3   94.3  87.1     one of 4096 x 14336, 256 tokens (336 MiB) 132.3 124.7 131.6 124.0
+//   232 tokens, Qwen3 experts     270 MiB  83.8  89.2   94.4  89.1                              64 tokens        108.9 102.1 106.3 101.1
+//                                 288 MiB  95.8  92.1   97.8  92.4     7168 x 2048, 40 tokens   252 MiB  76.4  75.8   79.3  76.4
+//                                 306 MiB 111.3 106.0  108.3 102.5                              336 MiB  86.7  78.2   87.0  79.0
+// So layers in turn would gain some 5 % below the line too, and one layer alone lose up to 30.  With weights streamed that further tiles read later:
+// 7113 tokens of the DeepSeek-V3 shape 8510 -> 10130; in the 256-row kernel, where eight M tiles in a row read the same ones: 8192 of the
+// Qwen3 shape 618 -> 649.
+constexpr int64_t kKeptBytes = (int64_t)288 << 20;
 static int units_to_stream(const Dims& D)
 {
     const int64_t left = kKeptBytes - (int64_t)D.Ns * 6 * D.d * D.Fs, unit = (int64_t)6 * D.d * D.F;
