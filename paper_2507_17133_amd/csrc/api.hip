@@ -256,8 +256,6 @@ static void carve_route_pieces(const Dims& D, Workspace& W, size_t& o)
     W.row_token = take((size_t)D.row_cap * 4);
     W.row_weight = take((size_t)D.row_cap * 4);
     W.token_rows = take((size_t)D.row_cap * 4);
-    W.n_rows = take(8);
-    W.streamed = W.n_rows + 4;
     W.near_tie = take((size_t)D.T);
     // the pieces of an fp32 gate matrix.  A packed gate of more than 16 experts brings them; with at most 16
     // experts the gate is fp32 rows in either format, cut on the way only beyond kFewExpertsTokens tokens
@@ -265,6 +263,7 @@ static void carve_route_pieces(const Dims& D, Workspace& W, size_t& o)
     W.gate_split = take(no_pieces ? 0 : (size_t)3 * D.m_pad * D.d * 2);
     W.seg_cnt = take((size_t)D.n_seg * D.U * 4);
     W.seg_off = take((size_t)D.n_seg * D.U * 4);
+    W.n_rows = take(4);
 }
 
 Workspace carve_workspace(const Dims& D)
@@ -274,7 +273,9 @@ Workspace carve_workspace(const Dims& D)
     carve_route_pieces(D, W, o);
     W.route_total = o;
     auto take = [&](size_t bytes) { size_t at = o; o = align_up(o + bytes, 256); return at; };
-    W.tiles0 = take(16 + (size_t)D.tile_cap * 16);
+    // the first table follows n_rows in its 256 bytes, 16 of them for the flag before the table (TileJobs::may_stream)
+    W.tiles0 = W.n_rows + 32;
+    o = align_up(W.tiles0 + 16 + (size_t)D.tile_cap * 16, 256);
     W.tiles1 = take(16 + (size_t)D.tile_cap * 16);
     W.h_rows = D.row_cap;
     W.y_rows = y_rows_bound(D);
@@ -499,7 +500,7 @@ moe_status moe_route(const moe_config* cfg, const void* x, int32_t T, const void
     const RouteBufs R = resolve_route(out, workspace, W);
     hipStream_t s = static_cast<hipStream_t>(stream);
     TileJobs none;
-    none.n = none.cap = none.count_units = none.stream_units = 0; none.streamed = nullptr;
+    none.n = none.cap = none.count_units = none.stream_units = 0; none.may_stream = false;
     hipError_t e = launch_route(D, static_cast<const bf16_t*>(x), gate_w, gate_bias, threshold,
                                 use_full_brownout ? 1 : 0, R, at<bf16_t>(workspace, W.gate_split),
                                 at<int32_t>(workspace, W.seg_cnt), at<int32_t>(workspace, W.seg_off),
@@ -526,7 +527,7 @@ moe_status moe_route_static(const moe_config* cfg, const void* x, int32_t T, con
     const RouteBufs R = resolve_route(out, sp, W);
     hipStream_t s = static_cast<hipStream_t>(stream);
     TileJobs none;
-    none.n = none.cap = none.count_units = none.stream_units = 0; none.streamed = nullptr;
+    none.n = none.cap = none.count_units = none.stream_units = 0; none.may_stream = false;
     // everything the kernels read from the scratch they write first in the same call (counters are cleared by
     // the first kernel), so what an earlier call left there does not matter
     e = launch_route(D, static_cast<const bf16_t*>(x), gate_w, gate_bias, threshold, use_full_brownout ? 1 : 0, R,
@@ -591,7 +592,7 @@ moe_status moe_forward(const moe_config* cfg, const void* x, int32_t T, const vo
     jobs.count_units = D.m + D.G;
     jobs.stream_units = units_to_stream(D);
     // no more units hold rows than there are TopK entries
-    jobs.streamed = std::min<int64_t>((int64_t)T * D.K, jobs.count_units) < jobs.stream_units ? nullptr : at<int32_t>(workspace, W.streamed);
+    jobs.may_stream = std::min<int64_t>((int64_t)T * D.K, jobs.count_units) >= jobs.stream_units;
     jobs.job[0].u_lo = 0; jobs.job[0].u_hi = split_shared ? D.m + D.G : D.U;
     jobs.job[0].plan = routed_tile_plan(D, dev.n_cu);
     jobs.job[0].table = at<int32_t>(workspace, W.tiles0);
@@ -622,7 +623,7 @@ moe_status moe_forward(const moe_config* cfg, const void* x, int32_t T, const vo
         if (j == 1 || !split_shared) units.even = D.Ns;
         problems[j] = FfnProblem{units, j == 0 ? D.F : D.Fs, J.plan, J.bm_hi, J.table};
     }
-    e = launch_ffn(D, problems, jobs.n, xb, R.row_token, fe, fu, fs, H, Y, partial, jobs.streamed, s);
+    e = launch_ffn(D, problems, jobs.n, xb, R.row_token, fe, fu, fs, H, Y, partial, jobs.may_stream, s);
     if (e != hipSuccess) return hip_fail(e, "moe_forward/ffn");
     e = launch_combine(D, xb, Y, R.token_rows, R.row_weight, static_cast<bf16_t*>(out), s);
     if (e != hipSuccess) return hip_fail(e, "moe_forward/combine");
@@ -688,7 +689,7 @@ moe_status moe_build_united(const moe_config* cfg, const moe_ffn_weights* expert
         hipError_t err = launch_uniform_units(u0, n0, u1, n1, first_slot, n_calib, plan.bm, tiles, s);
         if (err != hipSuccess) return err;
         const FfnProblem units{FfnUnits{n0 + n1, 0, n0 + n1}, D.F, plan, 0, tiles};
-        return launch_ffn(D, &units, 1, xb, row_token, fe, fu, fs, H, Y, partial, nullptr, s);
+        return launch_ffn(D, &units, 1, xb, row_token, fe, fu, fs, H, Y, partial, false, s);
     };
     for (int g = 0; g < G; ++g) {
         const int lo = g * way, hi = lo + way < m ? lo + way : m, k = hi - lo;
@@ -785,7 +786,7 @@ moe_status moe_distill_united(const moe_config* cfg, const moe_ffn_weights* expe
                 const int i0 = lo + (int)((int64_t)k * q / batches), i1 = lo + (int)((int64_t)k * (q + 1) / batches);
                 const FfnProblem units{FfnUnits{i1 - i0, 0, i1 - i0}, D.F, plan, 0, tiles};
                 if ((e = launch_uniform_units(i0, i1 - i0, 0, 0, 0, n_calib, plan.bm, tiles, s)) != hipSuccess ||
-                    (e = launch_ffn(D, &units, 1, xb, row_token, fe, fu, fs, H, Yo, partial, nullptr, s)) != hipSuccess)
+                    (e = launch_ffn(D, &units, 1, xb, row_token, fe, fu, fs, H, Yo, partial, false, s)) != hipSuccess)
                     return hip_fail(e, "moe_distill_united/teacher");
                 e = launch_teacher_stats(Yo, i1 - i0, q == 0, q == batches - 1, k, n_calib, D.d, D.F, g - g0, buf, s);
                 if (e != hipSuccess) return hip_fail(e, "moe_distill_united/mean");

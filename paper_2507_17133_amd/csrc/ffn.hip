@@ -77,20 +77,18 @@ struct GemmArgs {
     int n_ntiles;
     int group_m;                                // M tiles per L2 super-tile
     int ksplit; long plane;                     // GEMM2 only: K split into ksplit slices, slice s writes out + s*plane
-    union {
-        float* partial;                         // four-wave kernel, ksplit 1: scratch of the K-split tail (or null)
-        const int32_t* streamed;                // the others, STREAM: TileJobs::streamed
-    };
+    float* partial;                             // four-wave kernel, ksplit 1: scratch of the K-split tail (or null)
     int partial_cap;                            // fp32 tiles it holds
     int split;                                  // its left-over tiles may be cut along K (the sum of the slices is launched behind it)
 };
 
 // A k tile's loads of weights, `step` bytes of LDS apart.  `streamed`: with the non-temporal hint, where the layer's weights do not
 // outlast a call in the memory-side cache anyway and one tile, or tiles side by side, read these: without it their lines push everything
-// else out of the caches on the way (with sc0 or sc1 besides: no change).  A kernel looks at the table for that only where the layer may have so
+// else out of the caches on the way (with sc0 or sc1 besides: no change).  A kernel asks the device for that only where the layer may have so
 // many weights (STREAM, from the host): the flag, the tile's neighbours and a choice between two kinds of load are 0.2 to 0.5 us of a small call,
 // in the GEMMs and in the block that makes the row lists (layer forward, kernels that always look and these: 64 tokens over 8 experts of 256 x 512
-// 20.3 -> 20.0 us, one token 17.9 -> 17.5, 300 tokens 27.8 -> 27.4, one token of the 60-expert shape 50.1 -> 49.6).
+// 20.3 -> 20.0 us, one token 17.9 -> 17.5, 300 tokens 27.8 -> 27.4, one token of the 60-expert shape 50.1 -> 49.6).  Shared experts of a width of
+// their own are never streamed (beside routed units: 37 tokens of the 60-expert shape 140.4 us with it, 139.3 without).
 constexpr int kNonTemporal = 2;
 template <int N>
 __device__ __forceinline__ void load_weights(bool streamed, const bf16_t* const* src, int k, char* dst, int step)
@@ -114,12 +112,27 @@ struct Tile {
     const bf16_t *Wa, *Wb;
 };
 
+__device__ __forceinline__ int2 table_head(const GemmArgs& p) { return *reinterpret_cast<const int2*>(p.table); }      // one load, not two in a row
+
 // M tiles of a launch with tiles of BM rows: none if the table was cut for another height of the job.
 template <int BM>
-__device__ __forceinline__ int m_tiles(const GemmArgs& p)
+__device__ __forceinline__ int m_tiles(const int2 head) { return head.y == BM ? head.x : 0; }
+
+// body(whether its tiles may be streamed, head of the table).  The flag comes with the head, from the same line, and the whole body is there
+// twice, so that weights which may be streamed (STREAM) but are not take hardly longer than those that cannot be.  Layer forward of 100
+// tokens of the Qwen3 shape at 0.8 brownout: one body with a branch in its loop 62.3 us, here 61.0, kernels without streaming 60.4; 25 of the
+// 60-expert shape at 0.6, full: 46.3, 45.7 and 45.1.
+template <bool STREAM, typename Body>
+__device__ __forceinline__ void by_flag(const GemmArgs& p, Body body)
 {
-    const int2 head = *reinterpret_cast<const int2*>(p.table);      // one load, not two in a row
-    return head.y == BM ? head.x : 0;
+    const int2 head = table_head(p);
+    if constexpr (STREAM) {
+        if (p.table[-1] != 0) {
+            body(std::true_type{}, head);
+            return;
+        }
+    }
+    body(std::false_type{}, head);
 }
 
 // Whether all row tiles of a unit that has one in [lo, hi) are there: neither neighbour has the unit.  (Both loads at once, none behind a
@@ -156,12 +169,10 @@ __device__ __forceinline__ void set_weights(const GemmArgs& p, Tile& t)
     t.Wb = SWIGLU ? (src == 0 ? p.wb0 : (src == 1 ? p.wb1 : p.wb2)) + (size_t)widx * wsz : nullptr;
 }
 
-template <int BM, int BNC, bool STREAM, bool SWIGLU>
-__device__ __forceinline__ bool decode_tile(const GemmArgs& p, int block, Tile& t)
+template <int BM, int BNC, bool STREAMED, bool SWIGLU>
+__device__ __forceinline__ bool decode_tile(const GemmArgs& p, const int2 head, int block, Tile& t)
 {
-    int stream = 0;
-    if constexpr (STREAM) stream = *p.streamed;
-    const int n_mt = m_tiles<BM>(p);
+    const int n_mt = m_tiles<BM>(head);
     const int tiles = n_mt * p.n_ntiles;
     const int total = tiles * p.ksplit;
     const int chunk = (total + 7) >> 3;
@@ -177,8 +188,7 @@ __device__ __forceinline__ bool decode_tile(const GemmArgs& p, int block, Tile& 
     tile_coords(p, n_mt, p.n_ntiles, Lfull - t.kslice * tiles, mt, t.nt);
     const int4 te = reinterpret_cast<const int4*>(p.table + 4)[mt];
     t.unit = te.x; t.row0 = te.y; t.nrows = te.z;
-    t.streamed = false;
-    if constexpr (STREAM) t.streamed = holds_unit(p.table, n_mt, mt, mt + 1, t.unit) & (stream != 0);
+    t.streamed = STREAMED && holds_unit(p.table, n_mt, mt, mt + 1, t.unit);
     set_weights<SWIGLU>(p, t);
     t.n0 = t.nt * BNC;
     return true;
@@ -426,8 +436,8 @@ struct Lds {
 // Small-tile kernel (4 waves, 32 or 64 rows): one ring of NSTAGE (A+B) stages, tiles kt+1..kt+NSTAGE-1 in
 // flight while tile kt is multiplied.  Used when experts hold few rows (decode): weight streaming bound.
 // ------------------------------------------------------------------------------------------------
-template <int BM, int BN, int WM, int WN, int BK, int NSTAGE, bool STREAM, bool SWIGLU>
-__device__ __forceinline__ void small_block(const GemmArgs& p, const int block)
+template <int BM, int BN, int WM, int WN, int BK, int NSTAGE, bool STREAMED, bool SWIGLU>
+__device__ __forceinline__ void small_block(const GemmArgs& p, const int2 head, const int block)
 {
     using L = Lds<BK>;
     constexpr int TM = BM / WM, TN = BN / WN, FM = TM / 32, FN = TN / 32;
@@ -441,7 +451,7 @@ __device__ __forceinline__ void small_block(const GemmArgs& p, const int block)
     extern __shared__ __attribute__((aligned(16))) char smem[];
 
     Tile t;
-    if (!decode_tile<BM, SWIGLU ? BN / 2 : BN, STREAM, SWIGLU>(p, block, t)) return;
+    if (!decode_tile<BM, SWIGLU ? BN / 2 : BN, STREAMED, SWIGLU>(p, head, block, t)) return;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave / WN, wn = wave % WN;
     int k_first, nk;
@@ -459,8 +469,8 @@ __device__ __forceinline__ void small_block(const GemmArgs& p, const int block)
         char* dst = smem + (kt % NSTAGE) * STAGE + wave * 1024;
 #pragma unroll
         for (int i = 0; i < LD_PER_WAVE; ++i)
-            if (!STREAM || i * NW * RPG < BM) load_lds(gptr[i] + kt * BK, dst + i * NW * 1024);
-        if constexpr (STREAM)
+            if (!STREAMED || i * NW * RPG < BM) load_lds(gptr[i] + kt * BK, dst + i * NW * 1024);
+        if constexpr (STREAMED)
             load_weights<LD_PER_WAVE - BM / RPG / NW>(t.streamed, gptr + BM / RPG / NW, kt * BK, dst + BM / RPG * 1024, NW * 1024);
     };
 
@@ -507,7 +517,9 @@ __device__ __forceinline__ void small_block(const GemmArgs& p, const int block)
 template <int BM, int BN, int WM, int WN, int BK, int NSTAGE, bool STREAM, bool SWIGLU>
 __global__ void __launch_bounds__(WM * WN * 64) ffn_gemm_kernel(GemmArgs p)
 {
-    small_block<BM, BN, WM, WN, BK, NSTAGE, STREAM, SWIGLU>(p, blockIdx.x);
+    by_flag<STREAM>(p, [&](auto streamed, int2 head) {
+        small_block<BM, BN, WM, WN, BK, NSTAGE, decltype(streamed)::value, SWIGLU>(p, head, blockIdx.x);
+    });
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -521,8 +533,8 @@ __global__ void __launch_bounds__(WM * WN * 64) ffn_gemm_kernel(GemmArgs p)
 // and 256 now) 58.3 -> 44.2 us, 37 tokens with a shared expert of 2048 x 5632 (44 and 16 blocks before) 133 -> 100 us, 64 tokens
 // over 8 experts of 256 x 512 27.8 -> 24.1 us.
 // ------------------------------------------------------------------------------------------------
-template <int BM, int NSTAGE, bool STREAM, bool SWIGLU>
-__device__ __forceinline__ void narrow_block(const GemmArgs& p, const int block)
+template <int BM, int NSTAGE, bool STREAMED, bool SWIGLU>
+__device__ __forceinline__ void narrow_block(const GemmArgs& p, const int2 head, const int block)
 {
     constexpr int BK = 64, BN = 64, NW = 4, TM = BM / 2, TN = BN / 2, FM = TM / 16, FN = TN / 16;
     using L = Lds<BK>;
@@ -533,7 +545,7 @@ __device__ __forceinline__ void narrow_block(const GemmArgs& p, const int block)
     extern __shared__ __attribute__((aligned(16))) char smem[];
 
     Tile t;
-    if (!decode_tile<BM, SWIGLU ? BN / 2 : BN, STREAM, SWIGLU>(p, block, t)) return;
+    if (!decode_tile<BM, SWIGLU ? BN / 2 : BN, STREAMED, SWIGLU>(p, head, block, t)) return;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave >> 1, wn = wave & 1;
     int k_first, nk;
@@ -551,8 +563,8 @@ __device__ __forceinline__ void narrow_block(const GemmArgs& p, const int block)
         char* dst = smem + stage * STAGE + wave * 1024;
 #pragma unroll
         for (int i = 0; i < LD_PER_WAVE; ++i)
-            if (!STREAM || i * NW * RPG < BM) load_lds(gptr[i] + kt * BK, dst + i * NW * 1024);
-        if constexpr (STREAM)
+            if (!STREAMED || i * NW * RPG < BM) load_lds(gptr[i] + kt * BK, dst + i * NW * 1024);
+        if constexpr (STREAMED)
             load_weights<LD_PER_WAVE - BM / RPG / NW>(t.streamed, gptr + BM / RPG / NW, kt * BK, dst + BM / RPG * 1024, NW * 1024);
     };
 
@@ -618,7 +630,7 @@ __device__ __forceinline__ void narrow_block(const GemmArgs& p, const int block)
 template <int BM, int NSTAGE, bool STREAM, bool SWIGLU>
 __global__ void __launch_bounds__(256) ffn_gemm_narrow_kernel(GemmArgs p)
 {
-    narrow_block<BM, NSTAGE, STREAM, SWIGLU>(p, blockIdx.x);
+    by_flag<STREAM>(p, [&](auto streamed, int2 head) { narrow_block<BM, NSTAGE, decltype(streamed)::value, SWIGLU>(p, head, blockIdx.x); });
 }
 
 // Stages of the kernels for 32 and 64 rows; two narrow blocks of either height fit a CU.
@@ -629,16 +641,16 @@ constexpr int narrow_stages() { return BM == 32 ? 6 : 5; }
 
 // The routed and united units' block: tiles of BM rows, or (k32or64) of the height that the table holds.
 constexpr int k32or64 = 96;
-template <int BM, bool NARROW, bool STREAM, bool SWIGLU>
-__device__ __forceinline__ void routed_block(const GemmArgs& p, const int block)
+template <int BM, bool NARROW, bool STREAMED, bool SWIGLU>
+__device__ __forceinline__ void routed_block(const GemmArgs& p, const int2 head, const int block)
 {
     if constexpr (BM == k32or64) {
-        if (__builtin_amdgcn_readfirstlane(p.table[1]) == 64) routed_block<64, NARROW, STREAM, SWIGLU>(p, block);
-        else routed_block<32, NARROW, STREAM, SWIGLU>(p, block);
+        if (__builtin_amdgcn_readfirstlane(head.y) == 64) routed_block<64, NARROW, STREAMED, SWIGLU>(p, head, block);
+        else routed_block<32, NARROW, STREAMED, SWIGLU>(p, head, block);
     } else if constexpr (NARROW) {
-        narrow_block<BM, narrow_stages<BM>(), STREAM, SWIGLU>(p, block);
+        narrow_block<BM, narrow_stages<BM>(), STREAMED, SWIGLU>(p, head, block);
     } else {
-        small_block<BM, 256, 1, 4, 64, small_stages<BM>(), STREAM, SWIGLU>(p, block);
+        small_block<BM, 256, 1, 4, 64, small_stages<BM>(), STREAMED, SWIGLU>(p, head, block);
     }
 }
 
@@ -648,7 +660,7 @@ template <int BM, bool NARROW, bool STREAM, bool SWIGLU>
 __global__ void __launch_bounds__(256) ffn_gemm_either_kernel(GemmArgs p)
 {
     static_assert(BM == 64, "32 or 64 rows");
-    routed_block<k32or64, NARROW, STREAM, SWIGLU>(p, blockIdx.x);
+    by_flag<STREAM>(p, [&](auto streamed, int2 head) { routed_block<k32or64, NARROW, decltype(streamed)::value, SWIGLU>(p, head, blockIdx.x); });
 }
 
 // Shared experts of a width of their own (ps: the first n_s blocks) beside the routed and united units (pr) in one launch.  A launch
@@ -659,8 +671,8 @@ template <int BMR, bool NARROW, int BMS, bool STREAM, bool SWIGLU>
 __global__ void __launch_bounds__(256) ffn_gemm_pair_kernel(GemmArgs ps, GemmArgs pr, int n_s)
 {
     const int b = blockIdx.x;
-    if (b < n_s) narrow_block<BMS, narrow_stages<BMS>(), STREAM, SWIGLU>(ps, b);
-    else routed_block<BMR, NARROW, STREAM, SWIGLU>(pr, b - n_s);
+    if (b < n_s) narrow_block<BMS, narrow_stages<BMS>(), false, SWIGLU>(ps, table_head(ps), b);
+    else by_flag<STREAM>(pr, [&](auto streamed, int2 head) { routed_block<BMR, NARROW, decltype(streamed)::value, SWIGLU>(pr, head, b - n_s); });
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -730,9 +742,7 @@ __device__ __forceinline__ void ws_block(const GemmArgs& p, const int n_mt, cons
         const int lw = wave - NW;
         const bf16_t *ga[LA], *gb[LB];
         int next = first, kt = 0, nk = 0, stage = 0;
-        bool stream = false;
-        if constexpr (STREAM) stream = *(scalar_ptr)(unsigned long)p.streamed != 0;
-        const bool one_round = total <= (int)gridDim.x;
+        const bool stream = STREAM && ((scalar_ptr)(unsigned long)p.table)[-1] != 0, one_round = total <= (int)gridDim.x;
         bool streamed = false;
         auto set_up = [&](const Tile& t) {
             int k_first;
@@ -870,12 +880,13 @@ __global__ void __launch_bounds__(512) ffn_gemm_ws_kernel(GemmArgs p)
         const int G = gridDim.x, tw = n_mt * wide * p.ksplit, tn = n_mt * narrow * p.ksplit;
         return (bm + 256) * ((tw + G - 1) / G) <= (bm + 128) * ((tn + G - 1) / G);
     };
-    if (const int n_mt = m_tiles<128>(p)) {
+    const int2 head = table_head(p);
+    if (const int n_mt = m_tiles<128>(head)) {
         if (wide_wins(n_mt, 128)) ws_block<128, 256, 2, 2, 3, STREAM, SWIGLU>(p, n_mt, wide);
         else if constexpr (SWIGLU) ws_block<128, 128, 4, 1, 4, STREAM, SWIGLU>(p, n_mt, narrow);
         else ws_block<128, 128, 2, 2, 4, STREAM, SWIGLU>(p, n_mt, narrow);
     } else if (p.lower == 64) {
-        const int n_lo = m_tiles<64>(p);
+        const int n_lo = m_tiles<64>(head);
         if (SWIGLU || wide_wins(n_lo, 64)) ws_block<64, 256, 2, 2, 3, STREAM, SWIGLU>(p, n_lo, wide);
         else if constexpr (!SWIGLU) ws_block<64, 128, 2, 2, 5, STREAM, SWIGLU>(p, n_lo, narrow);
     }
@@ -942,7 +953,7 @@ template <int MODE>
 __device__ __forceinline__ Sched make_sched(const GemmArgs& p, int slots)
 {
     Sched sc;
-    sc.n_mt = m_tiles<256>(p);
+    sc.n_mt = m_tiles<256>(table_head(p));
     sc.tiles = sc.n_mt * p.n_ntiles;
     if (MODE == 0 && p.partial == nullptr) {
         sc.chunk = (sc.tiles * p.ksplit + 7) >> 3;
@@ -1039,7 +1050,7 @@ __device__ __forceinline__ void store_partial16(float* __restrict__ dst, const f
 template <bool SWIGLU>
 __global__ void __launch_bounds__(256) gemm_tail_sum_kernel(GemmArgs p, int G)
 {
-    const int n_mt = m_tiles<256>(p);
+    const int n_mt = m_tiles<256>(table_head(p));
     const int tiles = n_mt * p.n_ntiles;
     const int t_full = tiles / G * G, rem = tiles - t_full;
     const int sl = tail_split(G, rem, p.K / 64);
@@ -1344,7 +1355,7 @@ __device__ __forceinline__ void w4_block(const GemmArgs& p, const int block, con
 // One launch: G blocks (one per CU) for the whole tiles and, where the left-over tiles may be cut (p.partial
 // set), G more behind them for column halves and, where they may be cut along K, G for K slices.  They are independent work, so a CU
 // picks one up as soon as its block of whole tiles is done; a launch uses at most one of the two kinds
-// (only the device knows which), the blocks of the other return at once.  Block id mod 8 is the XCD in all
+// (only the device knows which), the blocks of the other return at once.  Block id mod 8 is the XCD in
 // all ranges (G is a multiple of 8).
 template <bool SWIGLU>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) ffn_gemm_w4_kernel(GemmArgs p)
@@ -1610,13 +1621,13 @@ static hipError_t launch_gemm_pair(const GemmLaunch& sh, const GemmLaunch& ro, h
 hipError_t launch_tile_tables(const int32_t* unit_cnt, const int32_t* unit_off, const TileJobs& jobs, hipStream_t s)
 {
     ProfScope ps(MOE_STAGE_TILES, s);
-    tile_table_kernel<<<jobs.n + (jobs.streamed != nullptr), 64, 0, s>>>(unit_cnt, unit_off, jobs);
+    tile_table_kernel<<<jobs.n + jobs.may_stream, 64, 0, s>>>(unit_cnt, unit_off, jobs);
     return hipGetLastError();
 }
 
 hipError_t launch_ffn(const Dims& D, const FfnProblem* problems, int n_problems, const bf16_t* x, const int32_t* gather,
                       const FfnWeights& experts, const FfnWeights& united, const FfnWeights& shared, bf16_t* H, bf16_t* Y,
-                      float* partial, const int32_t* streamed, hipStream_t s)
+                      float* partial, bool may_stream, hipStream_t s)
 {
     DeviceInfo dev;
     hipError_t e = ensure_device_init(&dev);
@@ -1644,7 +1655,7 @@ hipError_t launch_ffn(const Dims& D, const FfnProblem* problems, int n_problems,
         }
         g.n_ntiles = 0;                           // set at the launch from the kernel's tile width
         g.group_m = tuning().group_m ? tuning().group_m : (bm == 256 ? 8 : 4);
-        g.partial_cap = D.tail_blocks; g.split = 0;
+        g.partial = partial; g.partial_cap = D.tail_blocks; g.split = 0;
         // M tiles there can be at most: a unit that holds rows has one for every bm of them and a ragged one, and no more
         // units hold rows than there are rows
         l.max_mtiles = (int)std::min<int64_t>(D.row_cap / (lo ? lo : bm) + std::min<int64_t>(P.units.n, D.row_cap), D.tile_cap);
@@ -1659,8 +1670,6 @@ hipError_t launch_ffn(const Dims& D, const FfnProblem* problems, int n_problems,
         else if (lo) l.kind = narrow ? kNarrowEither : kSmallEither;
         else if (bm == 64) l.kind = narrow ? kNarrow64 : kSmall64;
         else l.kind = narrow ? kNarrow32 : kSmall32;
-        if (l.kind == kW4) g.partial = partial;
-        else g.streamed = streamed;
         return l;
     };
     // A launch for bm_hi as well where the table may hold tiles of that height: the one that has none returns at once.
@@ -1668,10 +1677,11 @@ hipError_t launch_ffn(const Dims& D, const FfnProblem* problems, int n_problems,
         constexpr bool SWIGLU = decltype(swiglu)::value, STREAM = decltype(stream)::value;
         ProfScope ps(SWIGLU ? MOE_STAGE_GEMM1 : MOE_STAGE_GEMM2, s);
         GemmLaunch todo[4];
-        int n = 0;
+        int n = 0, routed = 0;                    // launches, and those of the first problem
         for (int j = 0; j < n_problems; ++j) {
             todo[n++] = plan(swiglu, problems[j], problems[j].plan.bm, problems[j].plan.lo);
             if (problems[j].bm_hi > 0) todo[n++] = plan(swiglu, problems[j], problems[j].bm_hi, 0);
+            if (j == 0) routed = n;
         }
         int paired = -1;                          // the routed launch that takes the shared experts (the last one) along
         if (n_problems == 2)
@@ -1679,7 +1689,9 @@ hipError_t launch_ffn(const Dims& D, const FfnProblem* problems, int n_problems,
                 if (pairable(todo[n - 1].kind, todo[i].kind)) paired = i;
         hipError_t err;
         for (int i = 0; i < n - (paired >= 0 ? 1 : 0); ++i) {
-            err = i == paired ? launch_gemm_pair<STREAM, SWIGLU>(todo[n - 1], todo[i], s) : launch_gemm<STREAM, SWIGLU>(todo[i], dev.n_cu, s);
+            if (i == paired) err = launch_gemm_pair<STREAM, SWIGLU>(todo[n - 1], todo[i], s);
+            else if (i < routed) err = launch_gemm<STREAM, SWIGLU>(todo[i], dev.n_cu, s);
+            else err = launch_gemm<false, SWIGLU>(todo[i], dev.n_cu, s);
             if (err != hipSuccess) return err;
         }
         return hipSuccess;
@@ -1688,7 +1700,7 @@ hipError_t launch_ffn(const Dims& D, const FfnProblem* problems, int n_problems,
         const hipError_t err = gemm(std::true_type{}, stream);
         return err != hipSuccess ? err : gemm(std::false_type{}, stream);
     };
-    return streamed ? both(std::true_type{}) : both(std::false_type{});
+    return may_stream ? both(std::true_type{}) : both(std::false_type{});
 }
 
 hipError_t launch_combine(const Dims& D, const bf16_t* x, const bf16_t* Y, const int32_t* token_rows,

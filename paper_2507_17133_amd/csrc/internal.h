@@ -67,7 +67,6 @@ Dims make_dims(const moe_config& c, int T);
 struct Workspace {
     size_t topk_idx, topk_w, expert_cnt, expert_unit, expert_in_s1, unit_cnt, unit_off, row_token, row_weight,
         token_rows, n_rows, near_tie;                 // default homes of the moe_route_out fields
-    size_t streamed;                                  // TileJobs::streamed, beside n_rows
     size_t gate_split;                                // [3][m_pad][d] bf16
     size_t seg_cnt, seg_off;                          // [n_seg][U] int32
     size_t route_total;                               // bytes of the pieces above (all that routing alone needs)
@@ -169,10 +168,10 @@ struct FfnUnits { int n; int64_t entries; int even; };
 struct FfnProblem { FfnUnits units; int F; TilePlan plan; int bm_hi; int32_t* table; };
 // Runs W2(silu(W1 x)*(W3 x)) for the rows of the tiles in the tables of one problem, or of the routed and united units and then the
 // shared experts; writes Y[row][d] = FFN(x[gather ? gather[row] : row]) (the row weights are applied by the combine).  Weight
-// source of unit u: u<m experts[u]; u<m+G united[u-m]; else shared[u-m-G].  streamed: TileJobs::streamed.
+// source of unit u: u<m experts[u]; u<m+G united[u-m]; else shared[u-m-G].  may_stream: TileJobs::may_stream.
 hipError_t launch_ffn(const Dims& D, const FfnProblem* problems, int n_problems, const bf16_t* x, const int32_t* gather,
                       const FfnWeights& experts, const FfnWeights& united, const FfnWeights& shared, bf16_t* H, bf16_t* Y,
-                      float* partial, const int32_t* streamed, hipStream_t s);
+                      float* partial, bool may_stream, hipStream_t s);
 // Tile tables from the unit counts of a route that the caller brings.
 hipError_t launch_tile_tables(const int32_t* unit_cnt, const int32_t* unit_off, const TileJobs& jobs, hipStream_t s);
 hipError_t launch_combine(const Dims& D, const bf16_t* x, const bf16_t* Y, const int32_t* token_rows,

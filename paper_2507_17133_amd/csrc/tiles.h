@@ -2,7 +2,7 @@
 // the counts first, and by the stand-alone table kernel used when the caller brings its own row lists).
 //
 // int32 header {n_tiles, rows of a tile, 0, 0}, then one int4 {unit, first row, rows, 0} per M tile, units in ascending
-// order, tiles of a unit consecutive.
+// order, tiles of a unit consecutive.  Where weights may be streamed, the word before the first job's header says whether they are.
 #pragma once
 #include "internal.h"
 
@@ -20,9 +20,8 @@ struct TileJobs {
     int n;                   // 0, 1 or 2 jobs (routed + united units; shared units of another width)
     TileJob job[2];
     int cap;                 // entries a table holds
-    int count_units;         // *streamed (ffn.hip, load_weights) is whether at least stream_units of the units
-    int stream_units;        // [0, count_units) hold rows
-    int32_t* streamed;       // null: the host knows that they do not
+    bool may_stream;         // weights are streamed past the caches (ffn.hip) if at least stream_units of the units [0, count_units)
+    int count_units, stream_units;                         // hold rows (false: the host knows that fewer do)
 };
 
 // What a GEMM tile of bm rows counts for in the choice of bm_hi, in twentieths of a 32-row one.  Full tiles alone (DeepSeek-V3 shape, even
@@ -114,17 +113,17 @@ __device__ __forceinline__ void build_tile_table(const int* cnt, const int* off,
     }
 }
 
-// Wavefront w of a kernel that has the counts: table w, and behind the tables whether the weights are streamed (STREAM: where they may be).
+// Wavefront w of a kernel that has the counts: table w, and behind the tables whether weights are streamed (STREAM: where they may be).
 template <bool STREAM>
 __device__ __forceinline__ void build_tables(const int* cnt, const int* off, const TileJobs& jobs, int w, int lane)
 {
     if (w < jobs.n) {
         build_tile_table(cnt, off, jobs.job[w], jobs.cap, lane);
-    } else if (STREAM && w == jobs.n && jobs.streamed != nullptr) {
+    } else if (STREAM && w == jobs.n && jobs.may_stream) {
         int active = 0;
         for (int u = lane; u < jobs.count_units; u += 64) active += cnt[u] > 0;
         active = __builtin_amdgcn_readlane(wave_scan(active), 63);
-        if (lane == 0) *jobs.streamed = active >= jobs.stream_units;
+        if (lane == 0) jobs.job[0].table[-1] = active >= jobs.stream_units;
     }
 }
 

@@ -10,16 +10,16 @@ from tests._util import npf
 
 pytestmark = pytest.mark.gpu
 
-FILL = 0x5A5A5A5A
 
-
-def _flag(ws, n_rows):
-    """The word behind the number of rows, which has 256 bytes of its own."""
-    w = ws.cpu().numpy().view(np.uint32)
-    w = w[:len(w) // 64 * 64].reshape(-1, 64)
-    mine = w[(w[:, 0] == n_rows) & (w[:, 1] != FILL) & (w[:, 2:] == FILL).all(axis=1)]
-    assert len(mine) == 1
-    return int(mine[0, 1])
+def _flag(ws, cnt, off):
+    """The word before the routed units' tile table in the workspace."""
+    left = ws.cpu().numpy().tobytes()
+    for bm in (32, 64, 128, 256):
+        tiles = [(u, off[u] + r, min(bm, n - r), 0) for u, n in enumerate(cnt) for r in range(0, int(n), bm)]
+        at = left.find(np.asarray([(len(tiles), bm, 0, 0)] + tiles, np.int32).tobytes())
+        if at >= 0:
+            return int(np.frombuffer(left, np.int32, 1, at - 4)[0])
+    raise AssertionError("no table")
 
 
 # units that may hold rows without their weights being streamed: 24 of 12 MiB are 288 MiB; a shared expert of another width brings 3 MiB
@@ -46,6 +46,6 @@ def test_both_sides_of_the_line(T, Fs, below):
             ws.fill_(0x5A)
             outs[n, own is None] = P.moe_forward(c, xs, L.gate_w, L.gate_b, L.experts, None, L.shared, 1.0, route=own, workspace=ws)
             torch.cuda.synchronize()
-            assert _flag(ws, n * (1 + cfg.n_shared) if own is None else FILL) == n - T
+            assert _flag(ws, npf(R.unit_cnt)[:m + cfg.G], npf(R.unit_off)) == n - T
         assert torch.equal(outs[n, True], outs[n, False])
     assert torch.equal(outs[T + 1, True][:T], outs[T, True])

@@ -37,9 +37,17 @@ def test_kernels_that_look(tmp_path):
         assert r["status"] == 0
         seen = [l for l in r["launches"] if l["name"] in LOOKING]
         assert len(seen) >= (1 if c["entry"] == "route" or c["T"] > 2000 else 2) - c.get("own_route", 0), c
+        own_width = c["cfg"][5] and c["cfg"][6] != c["cfg"][1]
+        gemms = {}
         for l in seen:
             flags = re.findall(r"Lb([01])E", l["symbol"])
-            assert (flags[-1:] if "route" in l["name"] else flags[-2:-1]) == [str(int(looks))], (c, l["symbol"])
+            if "route" in l["name"]:
+                assert flags[-1:] == [str(int(looks))], (c, l["symbol"])
+            else:
+                gemms.setdefault(flags[-1], []).append((flags[-2:-1], l))
+        for launches in gemms.values():              # GEMM1, GEMM2: routed units first; shared experts of a width of their own do not look
+            for i, (flag, l) in enumerate(launches):
+                shared = own_width and i == len(launches) - 1 > 0
+                assert flag == [str(int(looks and not shared))], (c, l["symbol"])
         if c.get("own_route"):
-            tables = [l["grid"] for l in r["launches"] if l["name"] == "tile_table_kernel"]
-            assert tables == [(2 if c["cfg"][5] and c["cfg"][6] != c["cfg"][1] else 1) + looks], c
+            assert [l["grid"] for l in r["launches"] if l["name"] == "tile_table_kernel"] == [(2 if own_width else 1) + looks], c
