@@ -1574,13 +1574,12 @@ static hipError_t launch_gemm(const GemmLaunch& l, int n_cu, hipStream_t s)
             const int blocks = (int)std::min<long>((total + 7) / 8 * 8, std::max(8, n_cu / 8 * 8));
             const int max_tail = (int)std::min<long>(total, blocks - 1);
             if (a.ksplit != 1 || blocks > a.partial_cap || max_tail <= 0) a.partial = nullptr;
-            // Blocks and a sum (4.8 us) for K slices only where some number of left-over tiles, or the one there is going to be, would be
-            // cut: never with K < 1024, and not in 4 of 5 launches of calibration batches and shared experts.  Layer forward, 8192 tokens
+            // Blocks and a sum (4.8 us) for K slices only where the number of left-over tiles that there is going to be would be cut (not in 4 of 5
+            // launches of calibration batches and shared experts), or, where it is not known, some number would: from K = 1024 on a
+            // single one always is, below that none.  Layer forward, 8192 tokens
             // of the Qwen3 shape (GEMM2: K 768) 615 -> 612 us, 5003 of the 60-expert shape (the shared expert's two) 488 -> 480.
             const int rem = l.known_mtiles >= 0 ? (int)((long)l.known_mtiles * a.n_ntiles % blocks) : 0;
-            a.split = 0;
-            for (int r = rem ? rem : 1; a.partial && a.K >= 1024 && !a.split && r <= (l.known_mtiles >= 0 ? rem : max_tail); ++r)
-                a.split = tail_split(blocks, r, a.K / 64) > 1;
+            a.split = a.partial != nullptr && (l.known_mtiles < 0 ? a.K >= 1024 : tail_split(blocks, rem, a.K / 64) > 1);
             ffn_gemm_w4_kernel<SWIGLU><<<a.partial ? (a.split ? 3 : 2) * blocks : blocks, 256, kW4Lds, s>>>(a);
             if (!a.split) break;
             const hipError_t e = hipGetLastError();
