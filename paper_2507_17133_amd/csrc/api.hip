@@ -591,11 +591,11 @@ moe_status moe_forward(const moe_config* cfg, const void* x, int32_t T, const vo
     jobs.cap = D.tile_cap;
     jobs.count_units = D.m + D.G;
     jobs.stream_units = units_to_stream(D);
-    // no more units hold rows than there are TopK entries
-    jobs.may_stream = std::min<int64_t>((int64_t)T * D.K, jobs.count_units) >= jobs.stream_units;
     jobs.job[0].u_lo = 0; jobs.job[0].u_hi = split_shared ? D.m + D.G : D.U;
     jobs.job[0].plan = routed_tile_plan(D, dev.n_cu);
     jobs.job[0].table = at<int32_t>(workspace, W.tiles0);
+    // no more units hold rows than there are TopK entries; the 256-row GEMM does not stream
+    jobs.may_stream = std::min<int64_t>((int64_t)T * D.K, jobs.count_units) >= jobs.stream_units && jobs.job[0].plan.bm < 256;
     // a threshold of 1 browns nothing out (a route of the caller's may, whatever threshold comes with it)
     jobs.job[0].bm_hi = route || threshold < 1.0 ? taller_tile_rows(D, jobs.job[0].plan.bm, dev.n_cu) : 0;
     jobs.job[0].m = D.m; jobs.job[0].entries = T * D.K;

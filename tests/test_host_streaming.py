@@ -14,13 +14,14 @@ if not os.path.exists(B.LIB_PATH):
 LOOKING = ("route_rows_kernel", "ffn_gemm_kernel", "ffn_gemm_narrow_kernel", "ffn_gemm_either_kernel", "ffn_gemm_pair_kernel", "ffn_gemm_ws_kernel")
 
 #   d, F, m, K, n_shared, F_s, threshold, tokens that cannot stream, tokens that may.  A unit's weights are 6 d F bytes: 0.8 MB; 9.4 MB, one
-#   token reaches 8 of them; 17.3 MB beside a shared expert of 69 MB; 352 MB; a shared expert of 617 MB
+#   token reaches 8 of them; 17.3 MB beside a shared expert of 69 MB; 352 MB; a shared expert of 617 MB; many rows
 SHAPES = [(256, 512, 8, 2, 0, 0, 0.75, (1, 64, 300, 3000), ()),
           (2048, 768, 128, 8, 0, 0, 0.5, (1, 2), (8, 100, 900)),
           (2048, 1408, 60, 4, 1, 5632, 0.4, (1, 2), (16, 37, 300)),
           (2048, 1408, 60, 4, 1, 5632, 1.0, (1, 2), (16, 37, 300)),
           (4096, 14336, 8, 2, 0, 0, 1.0, (), (1, 256)),
-          (7168, 256, 8, 2, 1, 14336, 1.0, (), (1, 256))]
+          (7168, 256, 8, 2, 1, 14336, 1.0, (), (1, 256)),
+          (2048, 768, 128, 8, 0, 0, 0.5, (6144,), (6143,))]         # 384 rows per expert: 256-row tiles, which are not streamed
 
 
 def test_kernels_that_look(tmp_path):
