@@ -500,7 +500,7 @@ moe_status moe_route(const moe_config* cfg, const void* x, int32_t T, const void
     const RouteBufs R = resolve_route(out, workspace, W);
     hipStream_t s = static_cast<hipStream_t>(stream);
     TileJobs none;
-    none.n = none.cap = none.count_units = none.stream_units = 0; none.may_stream = false;
+    none.n = none.cap = none.count_units = none.stream_units = 0;
     hipError_t e = launch_route(D, static_cast<const bf16_t*>(x), gate_w, gate_bias, threshold,
                                 use_full_brownout ? 1 : 0, R, at<bf16_t>(workspace, W.gate_split),
                                 at<int32_t>(workspace, W.seg_cnt), at<int32_t>(workspace, W.seg_off),
@@ -527,7 +527,7 @@ moe_status moe_route_static(const moe_config* cfg, const void* x, int32_t T, con
     const RouteBufs R = resolve_route(out, sp, W);
     hipStream_t s = static_cast<hipStream_t>(stream);
     TileJobs none;
-    none.n = none.cap = none.count_units = none.stream_units = 0; none.may_stream = false;
+    none.n = none.cap = none.count_units = none.stream_units = 0;
     // everything the kernels read from the scratch they write first in the same call (counters are cleared by
     // the first kernel), so what an earlier call left there does not matter
     e = launch_route(D, static_cast<const bf16_t*>(x), gate_w, gate_bias, threshold, use_full_brownout ? 1 : 0, R,
@@ -589,13 +589,13 @@ moe_status moe_forward(const moe_config* cfg, const void* x, int32_t T, const vo
     TileJobs jobs;
     jobs.n = split_shared ? 2 : 1;
     jobs.cap = D.tile_cap;
-    jobs.count_units = D.m + D.G;
     jobs.stream_units = units_to_stream(D);
     jobs.job[0].u_lo = 0; jobs.job[0].u_hi = split_shared ? D.m + D.G : D.U;
     jobs.job[0].plan = routed_tile_plan(D, dev.n_cu);
     jobs.job[0].table = at<int32_t>(workspace, W.tiles0);
     // no more units hold rows than there are TopK entries; the 256-row GEMM does not stream
-    jobs.may_stream = std::min<int64_t>((int64_t)T * D.K, jobs.count_units) >= jobs.stream_units && jobs.job[0].plan.bm < 256;
+    const bool may_stream = std::min<int64_t>((int64_t)T * D.K, D.m + D.G) >= jobs.stream_units && jobs.job[0].plan.bm < 256;
+    jobs.count_units = may_stream ? D.m + D.G : 0;
     // a threshold of 1 browns nothing out (a route of the caller's may, whatever threshold comes with it)
     jobs.job[0].bm_hi = route || threshold < 1.0 ? taller_tile_rows(D, jobs.job[0].plan.bm, dev.n_cu) : 0;
     jobs.job[0].m = D.m; jobs.job[0].entries = T * D.K;
@@ -623,7 +623,7 @@ moe_status moe_forward(const moe_config* cfg, const void* x, int32_t T, const vo
         if (j == 1 || !split_shared) units.even = D.Ns;
         problems[j] = FfnProblem{units, j == 0 ? D.F : D.Fs, J.plan, J.bm_hi, J.table};
     }
-    e = launch_ffn(D, problems, jobs.n, xb, R.row_token, fe, fu, fs, H, Y, partial, jobs.may_stream, s);
+    e = launch_ffn(D, problems, jobs.n, xb, R.row_token, fe, fu, fs, H, Y, partial, may_stream, s);
     if (e != hipSuccess) return hip_fail(e, "moe_forward/ffn");
     e = launch_combine(D, xb, Y, R.token_rows, R.row_weight, static_cast<bf16_t*>(out), s);
     if (e != hipSuccess) return hip_fail(e, "moe_forward/combine");

@@ -77,7 +77,10 @@ struct GemmArgs {
     int n_ntiles;
     int group_m;                                // M tiles per L2 super-tile
     int ksplit; long plane;                     // GEMM2 only: K split into ksplit slices, slice s writes out + s*plane
-    float* partial;                             // four-wave kernel, ksplit 1: scratch of the K-split tail (or null)
+    union {
+        float* partial;                         // four-wave kernel, ksplit 1: scratch of the K-split tail (or null)
+        const int32_t* streamed;                // 128-row kernel, STREAM: the flag (or null)
+    };
     int partial_cap;                            // fp32 tiles it holds
     int split;                                  // its left-over tiles may be cut along K (the sum of the slices is launched behind it)
 };
@@ -88,7 +91,8 @@ struct GemmArgs {
 // many weights (STREAM, from the host): the flag, the tile's neighbours and a choice between two kinds of load are 0.2 to 0.5 us of a small call,
 // in the GEMMs and in the block that makes the row lists (layer forward, kernels that always look and these: 64 tokens over 8 experts of 256 x 512
 // 20.3 -> 20.0 us, one token 17.9 -> 17.5, 300 tokens 27.8 -> 27.4, one token of the 60-expert shape 50.1 -> 49.6).  Shared experts of a width of
-// their own are never streamed (beside routed units: 37 tokens of the 60-expert shape 140.4 us with it, 139.3 without).
+// their own are not streamed: a layer called over and over finds them in the memory-side cache, past which the routed ones go (257 tokens of the 60-expert
+// shape 257 us with it, 239 without), and beside routed units the branch is saved (37 tokens 140.4, 139.3).
 constexpr int kNonTemporal = 2;
 template <int N>
 __device__ __forceinline__ void load_weights(bool streamed, const bf16_t* const* src, int k, char* dst, int step)
@@ -742,7 +746,7 @@ __device__ __forceinline__ void ws_block(const GemmArgs& p, const int n_mt, cons
         const int lw = wave - NW;
         const bf16_t *ga[LA], *gb[LB];
         int next = first, kt = 0, nk = 0, stage = 0;
-        const bool stream = STREAM && ((scalar_ptr)(unsigned long)p.table)[-1] != 0, one_round = total <= (int)gridDim.x;
+        const bool stream = STREAM && p.streamed != nullptr && *(scalar_ptr)(unsigned long)p.streamed != 0, one_round = total <= (int)gridDim.x;
         bool streamed = false;
         auto set_up = [&](const Tile& t) {
             int k_first;
@@ -1620,7 +1624,7 @@ static hipError_t launch_gemm_pair(const GemmLaunch& sh, const GemmLaunch& ro, h
 hipError_t launch_tile_tables(const int32_t* unit_cnt, const int32_t* unit_off, const TileJobs& jobs, hipStream_t s)
 {
     ProfScope ps(MOE_STAGE_TILES, s);
-    tile_table_kernel<<<jobs.n + jobs.may_stream, 64, 0, s>>>(unit_cnt, unit_off, jobs);
+    tile_table_kernel<<<jobs.n + jobs.may_stream(), 64, 0, s>>>(unit_cnt, unit_off, jobs);
     return hipGetLastError();
 }
 
@@ -1654,7 +1658,7 @@ hipError_t launch_ffn(const Dims& D, const FfnProblem* problems, int n_problems,
         }
         g.n_ntiles = 0;                           // set at the launch from the kernel's tile width
         g.group_m = tuning().group_m ? tuning().group_m : (bm == 256 ? 8 : 4);
-        g.partial = partial; g.partial_cap = D.tail_blocks; g.split = 0;
+        g.partial_cap = D.tail_blocks; g.split = 0;
         // M tiles there can be at most: a unit that holds rows has one for every bm of them and a ragged one, and no more
         // units hold rows than there are rows
         l.max_mtiles = (int)std::min<int64_t>(D.row_cap / (lo ? lo : bm) + std::min<int64_t>(P.units.n, D.row_cap), D.tile_cap);
@@ -1669,6 +1673,8 @@ hipError_t launch_ffn(const Dims& D, const FfnProblem* problems, int n_problems,
         else if (lo) l.kind = narrow ? kNarrowEither : kSmallEither;
         else if (bm == 64) l.kind = narrow ? kNarrow64 : kSmall64;
         else l.kind = narrow ? kNarrow32 : kSmall32;
+        if (l.kind == kWs) g.streamed = &P == problems ? P.table - 1 : nullptr;
+        else g.partial = partial;
         return l;
     };
     // A launch for bm_hi as well where the table may hold tiles of that height: the one that has none returns at once.
@@ -1676,11 +1682,10 @@ hipError_t launch_ffn(const Dims& D, const FfnProblem* problems, int n_problems,
         constexpr bool SWIGLU = decltype(swiglu)::value, STREAM = decltype(stream)::value;
         ProfScope ps(SWIGLU ? MOE_STAGE_GEMM1 : MOE_STAGE_GEMM2, s);
         GemmLaunch todo[4];
-        int n = 0, routed = 0;                    // launches, and those of the first problem
+        int n = 0;
         for (int j = 0; j < n_problems; ++j) {
             todo[n++] = plan(swiglu, problems[j], problems[j].plan.bm, problems[j].plan.lo);
             if (problems[j].bm_hi > 0) todo[n++] = plan(swiglu, problems[j], problems[j].bm_hi, 0);
-            if (j == 0) routed = n;
         }
         int paired = -1;                          // the routed launch that takes the shared experts (the last one) along
         if (n_problems == 2)
@@ -1688,9 +1693,11 @@ hipError_t launch_ffn(const Dims& D, const FfnProblem* problems, int n_problems,
                 if (pairable(todo[n - 1].kind, todo[i].kind)) paired = i;
         hipError_t err;
         for (int i = 0; i < n - (paired >= 0 ? 1 : 0); ++i) {
+            // shared experts that go out alone have no flag, but take the kernel that the routed units take as well where they can: the code of
+            // another instantiation comes from memory (841 tokens of the 60-expert shape at 0.3 brownout 236 -> 240 us)
+            const bool looks = todo[i].kind == kWs || !(n_problems == 2 && i == n - 1);
             if (i == paired) err = launch_gemm_pair<STREAM, SWIGLU>(todo[n - 1], todo[i], s);
-            else if (i < routed) err = launch_gemm<STREAM, SWIGLU>(todo[i], dev.n_cu, s);
-            else err = launch_gemm<false, SWIGLU>(todo[i], dev.n_cu, s);
+            else err = looks ? launch_gemm<STREAM, SWIGLU>(todo[i], dev.n_cu, s) : launch_gemm<false, SWIGLU>(todo[i], dev.n_cu, s);
             if (err != hipSuccess) return err;
         }
         return hipSuccess;

@@ -168,7 +168,7 @@ struct FfnUnits { int n; int64_t entries; int even; };
 struct FfnProblem { FfnUnits units; int F; TilePlan plan; int bm_hi; int32_t* table; };
 // Runs W2(silu(W1 x)*(W3 x)) for the rows of the tiles in the tables of one problem, or of the routed and united units and then the
 // shared experts; writes Y[row][d] = FFN(x[gather ? gather[row] : row]) (the row weights are applied by the combine).  Weight
-// source of unit u: u<m experts[u]; u<m+G united[u-m]; else shared[u-m-G].  may_stream: TileJobs::may_stream.
+// source of unit u: u<m experts[u]; u<m+G united[u-m]; else shared[u-m-G].  may_stream: TileJobs::may_stream().
 hipError_t launch_ffn(const Dims& D, const FfnProblem* problems, int n_problems, const bf16_t* x, const int32_t* gather,
                       const FfnWeights& experts, const FfnWeights& united, const FfnWeights& shared, bf16_t* H, bf16_t* Y,
                       float* partial, bool may_stream, hipStream_t s);

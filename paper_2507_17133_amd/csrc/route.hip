@@ -1499,7 +1499,7 @@ hipError_t launch_route(const Dims& D, const bf16_t* x, const void* gate, const 
             else route_rows_kernel<kLists, 0, STREAM><<<D.n_seg + 1, 1024, lds, s>>>(p, g);
             return hipGetLastError();
         };
-        return jobs.may_stream ? launch(std::true_type{}) : launch(std::false_type{});
+        return jobs.may_stream() ? launch(std::true_type{}) : launch(std::false_type{});
     }
     {
         ProfScope ps(MOE_STAGE_COUNT, s);

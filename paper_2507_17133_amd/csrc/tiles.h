@@ -18,10 +18,11 @@ struct TileJob {
 };
 struct TileJobs {
     int n;                   // 0, 1 or 2 jobs (routed + united units; shared units of another width)
-    TileJob job[2];
+    int count_units;         // weights are streamed past the caches (ffn.hip) if at least stream_units of the units [0, count_units)
+    TileJob job[2];          // hold rows; count_units is 0 where the host knows that fewer do
     int cap;                 // entries a table holds
-    bool may_stream;         // weights are streamed past the caches (ffn.hip) if at least stream_units of the units [0, count_units)
-    int count_units, stream_units;                         // hold rows (false: the host knows that fewer do)
+    int stream_units;
+    __host__ __device__ bool may_stream() const { return count_units > 0; }
 };
 
 // What a GEMM tile of bm rows counts for in the choice of bm_hi, in twentieths of a 32-row one.  Full tiles alone (DeepSeek-V3 shape, even
@@ -119,7 +120,7 @@ __device__ __forceinline__ void build_tables(const int* cnt, const int* off, con
 {
     if (w < jobs.n) {
         build_tile_table(cnt, off, jobs.job[w], jobs.cap, lane);
-    } else if (STREAM && w == jobs.n && jobs.may_stream) {
+    } else if (STREAM && w == jobs.n && jobs.may_stream()) {
         int active = 0;
         for (int u = lane; u < jobs.count_units; u += 64) active += cnt[u] > 0;
         active = __builtin_amdgcn_readlane(wave_scan(active), 63);

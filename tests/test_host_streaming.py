@@ -46,9 +46,9 @@ def test_kernels_that_look(tmp_path):
                 assert flags[-1:] == [str(int(looks))], (c, l["symbol"])
             else:
                 gemms.setdefault(flags[-1], []).append((flags[-2:-1], l))
-        for launches in gemms.values():              # GEMM1, GEMM2: routed units first; shared experts of a width of their own do not look
+        for launches in gemms.values():              # GEMM1, GEMM2: routed units first, then shared experts of a width of their own
             for i, (flag, l) in enumerate(launches):
-                shared = own_width and i == len(launches) - 1 > 0
+                shared = own_width and i == len(launches) - 1 > 0 and l["name"] != "ffn_gemm_ws_kernel"
                 assert flag == [str(int(looks and not shared))], (c, l["symbol"])
         if c.get("own_route"):
             assert [l["grid"] for l in r["launches"] if l["name"] == "tile_table_kernel"] == [(2 if own_width else 1) + looks], c
