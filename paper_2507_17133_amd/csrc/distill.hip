@@ -15,10 +15,10 @@
 // The contractions over tokens read K-contiguous operands that the earlier epilogues have written transposed.
 // Why: with each of these as a pass of its own (64-row GEMM tiles with fp32 results, transposes, SwiGLU, Adam, the loss
 // summed by one block) a pass over two groups of 8 and 4 teachers at n = d = 2048, F = 1408 with 8 steps took 56.9 ms,
-// 50 of them in the one-block sums and 3.4 in the GEMMs; now 2.8 ms.  Of those a step's four launches take 0.27 ms
-// (kSwiglu 49 us, kResidual 36, kBackward with W2 88, W1 and W3 94; the 484 MB of masters and moments alone are 94 us at the rate of a large
-// copy).  With the loads, fragment reads and MFMAs of a k tile one after the other, and W2 updated with W1 and W3, they took 0.35
-// (77, 43, 57 and 160).
+// 50 of them in the one-block sums and 3.4 in the GEMMs; now 2.85 ms.  Of those a step's four launches take 0.30 ms in a kernel trace
+// (kSwiglu 61 us, kResidual 40, kBackward with W2 100, W1 and W3 99; at best 55, 33, 92 and 80; the 484 MB of masters and moments alone are 94 us
+// at the rate of a large copy).  With the loads, fragment reads and MFMAs of a k tile one after the other, and W2 updated with W1 and W3, the
+// call took 3.37 ms.
 #include "internal.h"
 
 #include <algorithm>
@@ -167,7 +167,7 @@ static_assert(2 * 128 * kImgPitch <= dgemm_lds(4, 4) - 32 && 4 * kAdamWave <= dg
 // 80 KiB of a block are two buffers of A rows and three of B rows, so that loads lead by one and two k tiles.  One barrier per k tile, three
 // quarters into its first step, when a wave has read its last fragments of tile kt and its loads of tile kt+1 have landed; behind it come
 // the A rows of tile kt+2 into the buffer just left, then the B rows of tile kt+3.  Loads past the end of K are clamped to the last
-// k tile and never used.  Two groups at n = d = 2048, F = 1408: kSwiglu 77 -> 65 us, the call with 8 steps 3.37 -> 3.20 ms.
+// k tile and never used.  Two groups at n = d = 2048, F = 1408, 128 x 128 tiles in all kernels: kSwiglu 77 -> 65 us, the call with 8 steps 3.37 -> 3.20 ms.
 template <int EPI, int FM, int FN>
 __global__ void __launch_bounds__(256, FM * FN == 16 ? 2 : 1) distill_gemm_kernel(DGemm p)
 {
@@ -453,7 +453,8 @@ __global__ void __launch_bounds__(256, FM * FN == 16 ? 2 : 1) distill_gemm_kerne
         char* own = smem + wave * kAdamWave;
         const int cr = lane >> 4, cc = 4 * (lane & 15);
         const size_t at0 = (size_t)(m0 + wm * 64 + cr) * J.N + n0 + wn * 64 + cc;
-        // (the first and the last step by themselves, so that the loads in flight can be counted; behind the last one nothing reads the state)
+        // (the first and the last step by themselves, so that the loads in flight can be counted; behind the last one nothing reads the
+        // state, which a run of one step writes all the same)
         auto update = [&](auto first, auto last_step) {
             f32x4 have[4][3], next[4][3];
             auto fetch = [&](int row, f32x4 (&to)[4][3]) {
@@ -546,7 +547,7 @@ static hipError_t launch_dgemm(DGemm& p, int groups, hipStream_t s)
 // A last round of small tiles that is not full takes half to all of that: its blocks start before the round in front of it has ended.  Over 350 shapes
 // of 128 to 4096 x 128 to 3072, 256 to 4096 tokens, 1 to 8 groups (fitted to 150 of them), a step takes 0.08 % longer than with the better tile each time,
 // 3.4 % at most (small ones always 0.52 %; with 48, 37 and, for a last round of up to 256, 27 us at every K, 0.27 %: 3008 tokens, 512 x 1600, 3 groups
-// lost 2.3 %).  Two groups of 2048 tokens at 2048 x 1408 are 240 large tiles in 49 us or 704 small ones in 63.  Per MFMA a large tile
+// lost 2.3 %).  Two groups of 2048 tokens at 2048 x 1408 are 240 large tiles in 61 us (kernel trace, 54 at best) or 704 small ones in 70 (60).  Per MFMA a large tile
 // passes 3/4 of the bytes through the LDS and 7/12 through the L1.  (The other three epilogues lose more as one block on a CU than their loop gains: kResidual
 // at 256 x 128 37 -> 39 us, the launch with kBackward at 256 x 192 87 -> 116.)
 static bool large_swiglu(int M, int N, int K, int groups, int n_cu)

@@ -696,8 +696,8 @@ __global__ void __launch_bounds__(256) ffn_gemm_pair_kernel(GemmArgs ps, GemmArg
 // ------------------------------------------------------------------------------------------------
 // Tile L of a launch whose blocks walk over several (L counts the tiles of all K slices).  In a launch of one round the M tiles of a super-tile
 // read their weights side by side; further M tiles of a unit belong to other blocks, often of another XCD, which then find
-// nothing in the caches: streamed all the same, 513 tokens of the 60-expert shape take 295 us and not 282, 513 over 24 experts of 4096 x 1024 with
-// a shared one of 2048 199 and not 185, 800 of those 233 (227 with nothing streamed) and not 223.
+// nothing in the caches: streamed all the same (the M tiles of shared experts, while these were streamed), 513 tokens of the 60-expert shape take
+// 295 us and not 282, 513 over 24 experts of 4096 x 1024 with a shared one of 2048 199 and not 185, 800 of those 233 (227 with nothing streamed) and not 223.
 template <bool STREAM, bool SWIGLU>
 __device__ __forceinline__ void tile_at(const GemmArgs& p, int n_mt, int n_ntiles, int bnc, int L, bool one_round, Tile& t)
 {
